@@ -38,6 +38,31 @@
 
 #include <cstdlib>
 
+// Diagnostics: when a record buffer has been set (moe_debug_set_trace), thread 0 of every block of a tiled launch
+// writes its begin / end time (constant 100 MHz clock), where it ran and what it worked on: the timeline of a launch.
+// Costs one clock read per block and one scalar load of the pointer when unset.
+#define MOE_TRACE_MAX_BLOCKS 65536
+__device__ unsigned long long *g_moe_trace = nullptr;
+extern "C" int moe_debug_set_trace(unsigned long long *records)
+{
+    return hipMemcpyToSymbol(HIP_SYMBOL(g_moe_trace), &records, sizeof(records)) == hipSuccess ? MOE_OK : MOE_ELAUNCH;
+}
+#define MOE_TRACE_BEGIN() const unsigned long long trace_t0_ = wall_clock64()
+#define MOE_TRACE_END(mode_, e_, nrows_, nt_)                                                                   \
+    do {                                                                                                        \
+        unsigned long long *tr_ = g_moe_trace;                                                                  \
+        if (tr_ != nullptr && threadIdx.x == 0 && blockIdx.x < MOE_TRACE_MAX_BLOCKS) {                          \
+            unsigned hw_, xcc_;                                                                                 \
+            asm volatile("s_getreg_b32 %0, hwreg(HW_REG_HW_ID)" : "=s"(hw_));                                   \
+            asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(xcc_));                                 \
+            unsigned long long *r_ = tr_ + 8ull * (blockIdx.x + (mode_) * (unsigned long long)MOE_TRACE_MAX_BLOCKS); \
+            r_[0] = trace_t0_; r_[1] = wall_clock64(); r_[2] = hw_; r_[3] = xcc_;                               \
+            r_[4] = (e_); r_[5] = (nrows_); r_[6] = (nt_); r_[7] = 1;                                           \
+        }                                                                                                       \
+    } while (0)
+
+#include "ffn_wide.h"
+
 #define TM MOE_TILE_M     // token rows per tile
 #define NUM_XCD MOE_NUM_XCD
 #define TILED_THREADS 512
@@ -81,29 +106,32 @@ __device__ __forceinline__ int block_exclusive_scan(int v, int *wave_total /* LD
 
 __global__ __launch_bounds__(MOE_MAX_EXPERTS) void tile_schedule_kernel(int N, const int32_t *__restrict__ counts,
                                                                         const uint8_t *__restrict__ mask, int n_ntc_down,
+                                                                        int wide_steps /* 0: tiled down projection */,
                                                                         int32_t *__restrict__ sched_up,
                                                                         int32_t *__restrict__ sched_down)
 {
-    __shared__ int wsum[3][2], wtot[4][2];
+    __shared__ int wsum[3][2], wtot[4][2], wcost[2];
     const int e = threadIdx.x, w = e >> 6;
     const int c = (e < N && counts[e] > 0 && (mask == nullptr || mask[e] != 0)) ? counts[e] : 0;
     const int n128 = (c + 127) / 128, n112 = (c + 111) / 112, n96 = (c + 95) / 96;
+    const int wide_cost = wave_sum_int(c > 0 ? (c - 1) / WIDE_TM * 16 + wide_cost16((c - 1) % WIDE_TM + 1) : 0);
     const int s128 = wave_sum_int(n128), s112 = wave_sum_int(n112), s96 = wave_sum_int(n96);
     if ((e & 63) == 0) {
         wsum[0][w] = s128;
         wsum[1][w] = s112;
         wsum[2][w] = s96;
+        wcost[w] = wide_cost;
     }
     __syncthreads();
     // every thread takes the same decision from the same totals
     const int t128 = wsum[0][0] + wsum[0][1], t112 = wsum[1][0] + wsum[1][1], t96 = wsum[2][0] + wsum[2][1];
     int tm = 128, best = sched_cost(t128, n_ntc_down, 128);
-    if (t128 * n_ntc_down >= 256) {                         // below that the K range is split instead
+    if (wide_steps == 0 && t128 * n_ntc_down >= 256) {      // below that the K range is split instead
         const int c112 = sched_cost(t112, n_ntc_down, 112), c96 = sched_cost(t96, n_ntc_down, 96);
         if (c112 < best) { best = c112; tm = 112; }
         if (c96 < best) { best = c96; tm = 96; }
     }
-    const int n_dn = tm == 128 ? n128 : tm == 112 ? n112 : n96;
+    const int n_dn = wide_steps > 0 ? (c + WIDE_TM - 1) / WIDE_TM : tm == 128 ? n128 : tm == 112 ? n112 : n96;
     int tot_up, tot_dn;
     const int first_up = block_exclusive_scan(n128, wtot[0], &tot_up);
     const int first_dn = block_exclusive_scan(n_dn, wtot[1], &tot_dn);
@@ -114,6 +142,12 @@ __global__ __launch_bounds__(MOE_MAX_EXPERTS) void tile_schedule_kernel(int N, c
         sched_down[0] = tot_dn;
         sched_down[1] = tm;
         sched_down[2] = sched_down[3] = 0;
+        if (wide_steps > 0) {
+            const int items = tot_dn * n_ntc_down, rest = items % 256;
+            const int pieces = wide_pieces(rest, (wcost[0] + wcost[1]) * n_ntc_down - (items - rest) * 16, wide_steps);
+            sched_down[1] = pieces > 1 ? items - rest : items;
+            sched_down[2] = pieces;
+        }
     }
     int4 *tab = reinterpret_cast<int4 *>(sched_up + 4);
 #ifdef MOE_RAGGED_LAST
@@ -132,29 +166,6 @@ __global__ __launch_bounds__(MOE_MAX_EXPERTS) void tile_schedule_kernel(int N, c
     tab = reinterpret_cast<int4 *>(sched_down + 4);
     for (int j = 0; j < n_dn; ++j) tab[first_dn + j] = make_int4(e, first_dn, n_dn, 0);
 }
-
-// Diagnostics: when a record buffer has been set (moe_debug_set_trace), thread 0 of every block of a tiled launch
-// writes its begin / end time (constant 100 MHz clock), where it ran and what it worked on: the timeline of a launch.
-// Costs one clock read per block and one scalar load of the pointer when unset.
-#define MOE_TRACE_MAX_BLOCKS 65536
-__device__ unsigned long long *g_moe_trace = nullptr;
-extern "C" int moe_debug_set_trace(unsigned long long *records)
-{
-    return hipMemcpyToSymbol(HIP_SYMBOL(g_moe_trace), &records, sizeof(records)) == hipSuccess ? MOE_OK : MOE_ELAUNCH;
-}
-#define MOE_TRACE_BEGIN() const unsigned long long trace_t0_ = wall_clock64()
-#define MOE_TRACE_END(mode_, e_, nrows_, nt_)                                                                   \
-    do {                                                                                                        \
-        unsigned long long *tr_ = g_moe_trace;                                                                  \
-        if (tr_ != nullptr && threadIdx.x == 0 && blockIdx.x < MOE_TRACE_MAX_BLOCKS) {                          \
-            unsigned hw_, xcc_;                                                                                 \
-            asm volatile("s_getreg_b32 %0, hwreg(HW_REG_HW_ID)" : "=s"(hw_));                                   \
-            asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(xcc_));                                 \
-            unsigned long long *r_ = tr_ + 8ull * (blockIdx.x + (mode_) * (unsigned long long)MOE_TRACE_MAX_BLOCKS); \
-            r_[0] = trace_t0_; r_[1] = wall_clock64(); r_[2] = hw_; r_[3] = xcc_;                               \
-            r_[4] = (e_); r_[5] = (nrows_); r_[6] = (nt_); r_[7] = 1;                                           \
-        }                                                                                                       \
-    } while (0)
 
 // MODE 0: up (W1|W3 + SwiGLU -> act); a wave owns NF/2 fragments of W1 and the same NF/2 of W3.
 // MODE 1: down (W2 -> y); a wave owns NF consecutive fragments of W2.
@@ -632,12 +643,13 @@ int moe_ffn_tiled_impl(const moe_shape *s, const void *h, const int32_t *perm, c
     static const int env_dn = getenv("MOE_TILED_WAVES_DOWN") ? atoi(getenv("MOE_TILED_WAVES_DOWN")) : 0;
     const int waves_up = s->T > TM && env_up == 4 ? 4 : 8;
     const int waves_down = s->T > TM && env_dn == 4 && nf == 4 ? 4 : 8;
-    const int n_ntc = (d + 16 * waves_down * nf - 1) / (16 * waves_down * nf);
+    const bool wide = moe_wide_down(s);
+    const int n_ntc = wide ? (d + WIDE_TN - 1) / WIDE_TN : (d + 16 * waves_down * nf - 1) / (16 * waves_down * nf);
     // The tile tables are built at the start of every call, also of one that runs the down stage alone: that call then
     // never reads a table that an earlier call did not build or built from other counts or another mask.
     if (s->T > TM) {
-        hipLaunchKernelGGL(tile_schedule_kernel, dim3(1), dim3(MOE_MAX_EXPERTS), 0, st, N, counts, expert_mask, n_ntc, sched,
-                           sched_down);
+        hipLaunchKernelGGL(tile_schedule_kernel, dim3(1), dim3(MOE_MAX_EXPERTS), 0, st, N, counts, expert_mask, n_ntc,
+                           wide ? s->I / 32 : 0, sched, sched_down);
         MOE_CHECK_LAUNCH();
     }
     if (stages & MOE_FFN_STAGE_UP) {
@@ -645,6 +657,8 @@ int moe_ffn_tiled_impl(const moe_shape *s, const void *h, const int32_t *perm, c
                           (const uint16_t *)w3, sched, expert_mask, act, 1, nullptr, st);
         MOE_CHECK_LAUNCH();
     }
+    if ((stages & MOE_FFN_STAGE_DOWN) && wide)
+        return moe_ffn_wide_down(s, offsets, counts, act, w2, y, sched_down, (float *)((char *)workspace + L.partial), st);
     if (stages & MOE_FFN_STAGE_DOWN) {
         // nf: the widest weight tile that still leaves every compute unit a block (512 columns, then 256 columns), else
         // the narrowest (128 columns); and when even that leaves compute units idle -- few experts with rows, or few of

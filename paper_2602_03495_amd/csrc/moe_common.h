@@ -173,6 +173,10 @@ struct moe_ws_layout {
 #define MOE_SKINNY_MAX_STEPS 32     // 32-wide K steps a wave may hold in registers (K <= 1024 per wave)
 #define MOE_TILE_M 128              // token rows per tile on the tiled path (the down projection may choose 112 or 96 on the device)
 #define MOE_TILE_M_MIN 96
+// down projection over a long inner size (ffn_wide.h)
+#define WIDE_TM 256                 // activation rows per item
+#define WIDE_TN 256                 // output columns per item
+#define WIDE_MAX_PIECES 512         // most pieces of items of a launch (128 MB of fp32 partial sums)
 #define MOE_SKINNY_DOWN_MIN_I 2048  // decode-sized down projections with I up to this run on the tiled kernel
 
 static inline int moe_skinny_nsplit(int K)
@@ -193,6 +197,16 @@ static inline int moe_tiled_down_max_splits(const moe_shape *s)
            (size_t)(2 * nsp) * s->T * s->k * s->d * 4 <= ((size_t)64 << 20))
         nsp *= 2;
     return nsp;
+}
+
+// Whether the down projection runs on the kernel for long inner sizes (ffn_wide.h).  Its items are 256 x 256, so it needs
+// rows to fill them: with 48 MB of activations it is the faster one (d = 4096, I = 14336, 8 experts: 1024 tokens 390 -> 313 us,
+// 2048 tokens 640 -> 439, 8192 tokens 1804 -> 1540), below that the narrower tiles are (800 tokens 285 against 314 us,
+// 700 tokens on two experts 131 against 187).  The tiled kernel's own choice of tile height and K splits serves shorter
+// inner sizes, where an item is too short to be worth cutting (I = 5632: 97 us against 101).
+static inline bool moe_wide_down(const moe_shape *s)
+{
+    return s->T > 128 && s->I >= 8192 && (size_t)s->T * s->k * s->I * 2 >= ((size_t)48 << 20) && (size_t)s->d * s->I * 2 < ((size_t)1 << 32);
 }
 
 // one tile table of the tiled path: int32 hdr[4] + one int4 per token tile, sized for the smallest tile height
@@ -220,6 +234,7 @@ static inline moe_ws_layout moe_ws(const moe_shape *s)
     size_t part = (size_t)moe_skinny_nsplit(s->I) * Rs * s->d * 4;
     const int nsp = moe_tiled_down_max_splits(s);
     if (nsp > 1 && (size_t)nsp * R * s->d * 4 > part) part = (size_t)nsp * R * s->d * 4;
+    if (moe_wide_down(s)) part = (size_t)WIDE_MAX_PIECES * WIDE_TM * WIDE_TN * 4;
     off += moe_align256(part);
     L.sched = off;
     off += 2 * moe_sched_table_bytes(s);              // one table for the up projection, one for the down projection
