@@ -67,6 +67,17 @@ __device__ __forceinline__ float wave_max_dpp(float v)
     return fmaxf(fmaxf(r0, r1), fmaxf(r2, r3));
 }
 
+__device__ __forceinline__ int wave_max_int_dpp(int v)
+{
+    const int lowest = (int)0x80000000u;
+    v = max(v, __builtin_amdgcn_update_dpp(lowest, v, 0x111, 0xF, 0xF, false));
+    v = max(v, __builtin_amdgcn_update_dpp(lowest, v, 0x112, 0xF, 0xF, false));
+    v = max(v, __builtin_amdgcn_update_dpp(lowest, v, 0x114, 0xF, 0xF, false));
+    v = max(v, __builtin_amdgcn_update_dpp(lowest, v, 0x118, 0xF, 0xF, false));
+    return max(max(__builtin_amdgcn_readlane(v, 15), __builtin_amdgcn_readlane(v, 31)),
+               max(__builtin_amdgcn_readlane(v, 47), __builtin_amdgcn_readlane(v, 63)));
+}
+
 __device__ __forceinline__ float wave_sum_dpp(float v)
 {
     v += MOE_DPP_SHR(0.f, v, 1);

@@ -4,7 +4,7 @@
 //   gate_topk_kernel      16 tokens per block; logits by bf16 MFMA 16x16x32 straight from global memory
 //                         (K split over the 8 waves, reduced through LDS), then softmax and top-k per token
 //                         inside one wavefront: k rounds of a DPP max reduction + ballot.
-//   hist_scan_perm_kernel one block per expert: register counts of the selections below / equal to the expert
+//   hist_scan_perm_kernel one block per expert: ballot counts of the selections below / equal to the expert
 //                         (= its offset and workload), then a ballot-based stable compaction of its rows.
 //   Decode-sized batches (T <= 16, T*k <= 128) need no second kernel: the selecting block builds a 16-bit
 //   token mask per expert in LDS, and workload, scan and permutation are popcounts of it.  With more than 16
@@ -13,9 +13,10 @@
 // moe_predict_workload (Section "Residual-Based Prefetching"):
 //   the same kernels on the next layer's gate with bias'[e] = bias[e] + res_vec . W[e], so that
 //   (h + res_vec) . W + bias = h . W + bias'.  Decode-sized: the fold happens inside the gate kernel and the
-//   selecting block emits the workloads and their p largest.  Larger: fold_residual_kernel, gate_topk_kernel,
-//   hist_top_kernel.
-// moe_route_predict: both gates as two "jobs" of the same launches (blockIdx.z) at decode sizes.
+//   selecting block emits the workloads and their p largest.  Larger: the fold runs in blocks of its own beside the gate
+//   product and the selection adds it (few experts: fold_residual_kernel first); then hist_top_block.
+// moe_route_predict: both gates as two "jobs" of the same launches (blockIdx.z); beyond decode sizes the histogram of the
+// prediction is one more block of hist_scan_perm_kernel.
 #include "moe_common.h"
 
 #define ROUTE_TOKENS 16      // tokens per block of gate_topk_kernel
@@ -45,23 +46,18 @@ __device__ __forceinline__ float residual_dot(int d, const float *__restrict__ r
 }
 
 // The p largest workloads by descending value, equal values by ascending index; one wavefront, lane l holding the
-// workloads c0 of expert l and c1 of expert l + 64.
+// workloads c0 of expert l and c1 of expert l + 64.  A workload is at most T < 2^24 (T d < 2^31, d >= 128), so workload and
+// index fit one int whose maximum is the next entry: p maxima on the DPP crossbar (through LDS shuffles of workload and
+// index, 8 of 128 took 3 us of a decode step).
 __device__ __forceinline__ void top_p_of(int c0, int c1, int N, int p, int32_t *__restrict__ top, int lane)
 {
-    if (lane >= N) c0 = -1;
-    if (lane + 64 >= N) c1 = -1;
+    int k0 = lane < N ? (c0 << 7 | (127 - lane)) : -1;
+    int k1 = lane + 64 < N ? (c1 << 7 | (63 - lane)) : -1;
     for (int s = 0; s < p; ++s) {
-        int bc, bi;
-        if (c0 >= c1) { bc = c0; bi = lane; } else { bc = c1; bi = lane + 64; }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            int oc = __shfl_xor(bc, o, MOE_WAVE);
-            int oi = __shfl_xor(bi, o, MOE_WAVE);
-            if (oc > bc || (oc == bc && oi < bi)) { bc = oc; bi = oi; }
-        }
-        if (bi == lane) c0 = -1;
-        if (bi == lane + 64) c1 = -1;
-        if (lane == 0) top[s] = bi;
+        const int best = wave_max_int_dpp(k0 > k1 ? k0 : k1);
+        if (k0 == best) k0 = -1;
+        if (k1 == best) k1 = -1;
+        if (lane == 0) top[s] = 127 - (best & 127);
     }
 }
 
@@ -225,6 +221,7 @@ struct gate_job {
     float *topk_w;             // [T,k]
     int32_t *counts;           // non-null: single-block launch that also does the histogram (and, with perm, scan and permutation)
     int32_t *offsets, *perm, *inv_perm;
+    float *fold_out;           // non-null: bias + res_vec . W[e] [N], by the last blockIdx.z of the gate launch; the selection adds it
     const float *logits_in;    // non-null: skip the gate product, select from these [T,N] logits
     float *logits_out;         // non-null: only compute the logits of experts 16*NT*blockIdx.y .. and store them [T,N]
     int32_t *top;              // with counts and without perm: the p largest workloads
@@ -238,8 +235,17 @@ __global__ __launch_bounds__(ROUTE_THREADS) void gate_topk_kernel(int T, int d, 
 {
     const gate_job &J = blockIdx.z == 0 ? job0 : job1;
     const uint16_t *__restrict__ gate_w = J.gate_w;
-    const float *__restrict__ bias = J.bias;
-    const float *__restrict__ res_vec = J.res_vec;
+    if (J.fold_out != nullptr && blockIdx.z == gridDim.z - 1) {
+        // the residual folded into the bias, one wave per expert
+        const int n_waves = gridDim.x * gridDim.y * ROUTE_WAVES;
+        for (int e = (blockIdx.y * gridDim.x + blockIdx.x) * ROUTE_WAVES + (threadIdx.x >> 6); e < N; e += n_waves) {
+            const float acc = residual_dot(d, J.res_vec, gate_w + (size_t)e * d, threadIdx.x & 63);
+            if ((threadIdx.x & 63) == 0) J.fold_out[e] = acc + (J.bias != nullptr ? J.bias[e] : 0.f);
+        }
+        return;
+    }
+    const float *__restrict__ bias = J.fold_out != nullptr ? nullptr : J.bias;
+    const float *__restrict__ res_vec = J.fold_out != nullptr ? nullptr : J.res_vec;
     const int norm_mode = J.norm_mode;
     int32_t *__restrict__ topk_idx = J.topk_idx;
     float *__restrict__ topk_w = J.topk_w;
@@ -417,8 +423,12 @@ __global__ __launch_bounds__(SELECT_THREADS) void select_rows_kernel(int T, int 
     if (t >= T) return;
     const float NEG = -__builtin_huge_valf();
     const float *row = J.logits_in + (size_t)t * N;
-    const float v0 = lane < N ? row[lane] : NEG;
-    const float v1 = lane + 64 < N ? row[lane + 64] : NEG;
+    float v0 = lane < N ? row[lane] : NEG;
+    float v1 = lane + 64 < N ? row[lane + 64] : NEG;
+    if (J.fold_out != nullptr) {
+        if (lane < N) v0 += J.fold_out[lane];
+        if (lane + 64 < N) v1 += J.fold_out[lane + 64];
+    }
     int my_idx;
     float my_p, sel;
     select_token(v0, v1, N, k, lane, my_idx, my_p, sel);
@@ -429,91 +439,154 @@ __global__ __launch_bounds__(SELECT_THREADS) void select_rows_kernel(int T, int 
 }
 
 // ---------------------------------------------------------------------------------------------------
-// One block per expert e.  Pass 1 counts, in registers, the selections that are below e and equal to e (their
-// block-wide sums are offsets[e] and counts[e]: no global zero-fill, no cross-block atomics, no shared bins to
-// fight over); pass 2 places the rows of expert e in ascending r with wave ballots, so the permutation is stable
-// and the same on every run.  Selections are read 16 K at a time, 64 per thread, all loads in flight at once;
-// when T*k <= 16 K both passes work from the same registers.
-#define HSP_PER_THREAD 64
-#define HSP_SUPER (256 * HSP_PER_THREAD)
-__global__ __launch_bounds__(256) void hist_scan_perm_kernel(
-    int R, int N, const int32_t *__restrict__ topk_idx, int32_t *__restrict__ counts,
-    int32_t *__restrict__ offsets, int32_t *__restrict__ perm, int32_t *__restrict__ inv_perm)
-{
-    __shared__ int red[2][4];
-    __shared__ int wave_tot[HSP_PER_THREAD / 4][4];
-    __shared__ int my_off;
-    const int e = blockIdx.x;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+// A prediction's histogram: R selections idx, the N workloads and the p largest of them.
+struct top_job {
+    const int32_t *idx;
+    int32_t *pred_counts, *top;
+    int p;
+};
 
-    // entry j of this thread in super-chunk c0: r = c0 + (j/4)*1024 + wave*256 + (j%4)*64 + lane
-    int v[HSP_PER_THREAD];
+// Workload histogram of R predicted selections and its p largest entries.  One block of 16 wavefronts, each with a
+// private LDS histogram (one shared set of 128 bins serialises on the popular experts), summed in wave order.
+#define HT_THREADS 1024
+#define HT_BATCH 8           // selections on their way per thread, so that 8192 of them cost one read latency
+__device__ __forceinline__ void hist_top_block(int R, int N, const top_job &J)
+{
+    __shared__ int sub[HT_THREADS / 64][MOE_MAX_EXPERTS];
+    __shared__ int hist[MOE_MAX_EXPERTS];
+    const int wave = threadIdx.x >> 6;
+    for (int j = threadIdx.x; j < (HT_THREADS / 64) * MOE_MAX_EXPERTS; j += HT_THREADS) (&sub[0][0])[j] = 0;
+    __syncthreads();
+    for (int r0 = threadIdx.x; r0 < R; r0 += HT_BATCH * HT_THREADS) {
+        int v[HT_BATCH];
+#pragma unroll
+        for (int j = 0; j < HT_BATCH; ++j) v[j] = r0 + j * HT_THREADS < R ? J.idx[r0 + j * HT_THREADS] : -1;
+#pragma unroll
+        for (int j = 0; j < HT_BATCH; ++j)
+            if (v[j] >= 0) atomicAdd(&sub[wave][v[j] & (MOE_MAX_EXPERTS - 1)], 1);
+    }
+    __syncthreads();
+    if (threadIdx.x < MOE_MAX_EXPERTS) {
+        int c = 0;
+#pragma unroll
+        for (int w = 0; w < HT_THREADS / 64; ++w) c += sub[w][threadIdx.x];
+        hist[threadIdx.x] = c;
+        if ((int)threadIdx.x < N) J.pred_counts[threadIdx.x] = c;
+    }
+    __syncthreads();
+    if (threadIdx.x < 64) top_p_of(hist[threadIdx.x], hist[threadIdx.x + 64], N, J.p, J.top, threadIdx.x);
+}
+
+__global__ __launch_bounds__(HT_THREADS) void hist_top_kernel(int R, int N, top_job J) { hist_top_block(R, N, J); }
+
+// One block of 16 waves per expert e.  Every wave takes a contiguous run of 64 PT selections, so that its workload is the
+// popcount of PT ballots and one number per wave is all the block has to exchange: the selections below e (their
+// block-wide sum is offsets[e]) and equal to e (counts[e], and the positions of a wave's rows).  No global zero-fill, no
+// cross-block atomics, stable and the same on every run.  R up to 1024 PT selections stay in registers between counting and
+// placing; more are read a second time, 16 K at a time.
+// What bounds it is latency (a launch, two dependent reads, one barrier), so PT follows R: with 64 entries a thread whatever
+// R was, 400 selections of 8 experts took 12.4 us and 12288 of 64 took 14.3 us; now 4.9 and 5.5 us.
+#define HSP_THREADS 1024
+#define HSP_WAVES (HSP_THREADS / 64)
+template <int PT>
+__global__ __launch_bounds__(HSP_THREADS) void hist_scan_perm_kernel(
+    int R, int N, const int32_t *__restrict__ topk_idx, int32_t *__restrict__ counts,
+    int32_t *__restrict__ offsets, int32_t *__restrict__ perm, int32_t *__restrict__ inv_perm, top_job top /* block N, if any */)
+{
+    static_assert(HSP_THREADS == HT_THREADS, "one block size for both");
+    if ((int)blockIdx.x == N) {
+        hist_top_block(R, N, top);
+        return;
+    }
+    __shared__ int tot[2][HSP_WAVES];
+    const int e = blockIdx.x;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    constexpr int SUPER = HSP_THREADS * PT;
+
+    // entry j of this thread in super-chunk c0: r = c0 + wave * 64 PT + j * 64 + lane
+    int v[PT];
     auto load_super = [&](int c0) {
 #pragma unroll
-        for (int j = 0; j < HSP_PER_THREAD; ++j) {
-            const int r = c0 + (j >> 2) * 1024 + wave * 256 + (j & 3) * 64 + lane;
+        for (int j = 0; j < PT; ++j) {
+            const int r = c0 + (wave * PT + j) * 64 + lane;
             v[j] = r < R ? topk_idx[r] : -1;
         }
     };
-    int below = 0, equal = 0;
-    for (int c0 = 0; c0 < R; c0 += HSP_SUPER) {
+    int below = 0, equal = 0;                               // of this wave, uniform
+    for (int c0 = 0; c0 < R; c0 += SUPER) {
         load_super(c0);
 #pragma unroll
-        for (int j = 0; j < HSP_PER_THREAD; ++j) {
-            below += (unsigned)v[j] < (unsigned)e;          // padding entries are -1 = huge unsigned
-            equal += v[j] == e;
+        for (int j = 0; j < PT; ++j) {
+            below += __popcll(__ballot((unsigned)v[j] < (unsigned)e));   // padding entries are -1 = huge unsigned
+            equal += __popcll(__ballot(v[j] == e));
         }
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        below += __shfl_xor(below, o, MOE_WAVE);
-        equal += __shfl_xor(equal, o, MOE_WAVE);
-    }
-    if (lane == 0) { red[0][wave] = below; red[1][wave] = equal; }
+    if (lane == 0) { tot[0][wave] = below; tot[1][wave] = equal; }
     __syncthreads();
+    int off = 0, cnt = 0, before = 0;                       // before: rows of e in the waves below this one
+#pragma unroll
+    for (int w = 0; w < HSP_WAVES; ++w) {
+        off += tot[0][w];
+        before += w < wave ? tot[1][w] : 0;
+        cnt += tot[1][w];
+    }
     if (threadIdx.x == 0) {
-        const int off = red[0][0] + red[0][1] + red[0][2] + red[0][3];
-        const int cnt = red[1][0] + red[1][1] + red[1][2] + red[1][3];
-        my_off = off;
         counts[e] = cnt;
         offsets[e] = off;
         if (e == N - 1) offsets[N] = off + cnt;
     }
-    __syncthreads();
-    int base = my_off;                                      // running output position, uniform
     const unsigned long long lower = (1ull << lane) - 1ull;
-    for (int c0 = 0; c0 < R; c0 += HSP_SUPER) {
-        if (R > HSP_SUPER) load_super(c0);                  // otherwise v[] still holds the only super-chunk
-        unsigned long long bal[HSP_PER_THREAD];
+    auto place = [&](int c0, int pos) {
 #pragma unroll
-        for (int c = 0; c < HSP_PER_THREAD / 4; ++c) {
-            int tot = 0;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                bal[4 * c + j] = __ballot(v[4 * c + j] == e);
-                tot += __popcll(bal[4 * c + j]);
+        for (int j = 0; j < PT; ++j) {
+            const unsigned long long b = __ballot(v[j] == e);
+            if (v[j] == e) {
+                const int r = c0 + (wave * PT + j) * 64 + lane;
+                const int p = pos + __popcll(b & lower);
+                perm[p] = r;
+                inv_perm[r] = p;
             }
-            if (lane == 0) wave_tot[c][wave] = tot;
+            pos += __popcll(b);
         }
-        __syncthreads();
-#pragma unroll
-        for (int c = 0; c < HSP_PER_THREAD / 4; ++c) {
-            int pos = base;
-            for (int w = 0; w < wave; ++w) pos += wave_tot[c][w];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                if (v[4 * c + j] == e) {
-                    const int r = c0 + c * 1024 + wave * 256 + j * 64 + lane;
-                    const int p = pos + __popcll(bal[4 * c + j] & lower);
-                    perm[p] = r;
-                    inv_perm[r] = p;
-                }
-                pos += __popcll(bal[4 * c + j]);
-            }
-            base += wave_tot[c][0] + wave_tot[c][1] + wave_tot[c][2] + wave_tot[c][3];
-        }
-        __syncthreads();
+    };
+    if (R <= SUPER) {
+        place(0, off + before);
+        return;
     }
+    for (int c0 = 0; c0 < R; c0 += SUPER) {                 // off: running output position of the super-chunk, uniform
+        load_super(c0);
+        equal = 0;
+#pragma unroll
+        for (int j = 0; j < PT; ++j) equal += __popcll(__ballot(v[j] == e));
+        __syncthreads();                                    // the totals of the chunk before have been read
+        if (lane == 0) tot[1][wave] = equal;
+        __syncthreads();
+        before = cnt = 0;
+#pragma unroll
+        for (int w = 0; w < HSP_WAVES; ++w) {
+            before += w < wave ? tot[1][w] : 0;
+            cnt += tot[1][w];
+        }
+        place(c0, off + before);
+        off += cnt;
+    }
+}
+
+// top: the histogram of a prediction of the same size in the same launch, or null
+static int launch_hist_scan_perm(int R, int N, const int32_t *topk_idx, int32_t *counts, int32_t *offsets, int32_t *perm,
+                                 int32_t *inv_perm, const top_job *top, hipStream_t st)
+{
+    const top_job none = {};
+#define HSP(pt)                                                                                                        \
+    hipLaunchKernelGGL(hist_scan_perm_kernel<pt>, dim3(N + (top != nullptr ? 1 : 0)), dim3(HSP_THREADS), 0, st, R, N, topk_idx, \
+                       counts, offsets, perm, inv_perm, top != nullptr ? *top : none)
+    if (R <= HSP_THREADS) HSP(1);
+    else if (R <= 4 * HSP_THREADS) HSP(4);
+    else HSP(16);
+#undef HSP
+    MOE_CHECK_LAUNCH();
+    return MOE_OK;
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -524,30 +597,6 @@ __global__ __launch_bounds__(64) void fold_residual_kernel(int d, const float *_
     const int e = blockIdx.x, lane = threadIdx.x;
     const float acc = residual_dot(d, res_vec, gate_w + (size_t)e * d, lane);
     if (lane == 0) bias_out[e] = acc + (bias != nullptr ? bias[e] : 0.f);
-}
-
-// Workload histogram of R predicted selections and its p largest entries.  One block of 16 wavefronts, each with a
-// private LDS histogram (one shared set of 128 bins serialises on the popular experts), summed in wave order.
-#define HT_THREADS 1024
-__global__ __launch_bounds__(HT_THREADS) void hist_top_kernel(int R, int N, int p, const int32_t *__restrict__ idx,
-                                                              int32_t *__restrict__ pred_counts, int32_t *__restrict__ top)
-{
-    __shared__ int sub[HT_THREADS / 64][MOE_MAX_EXPERTS];
-    __shared__ int hist[MOE_MAX_EXPERTS];
-    const int wave = threadIdx.x >> 6;
-    for (int j = threadIdx.x; j < (HT_THREADS / 64) * MOE_MAX_EXPERTS; j += HT_THREADS) (&sub[0][0])[j] = 0;
-    __syncthreads();
-    for (int r = threadIdx.x; r < R; r += HT_THREADS) atomicAdd(&sub[wave][idx[r] & (MOE_MAX_EXPERTS - 1)], 1);
-    __syncthreads();
-    if (threadIdx.x < MOE_MAX_EXPERTS) {
-        int c = 0;
-#pragma unroll
-        for (int w = 0; w < HT_THREADS / 64; ++w) c += sub[w][threadIdx.x];
-        hist[threadIdx.x] = c;
-        if ((int)threadIdx.x < N) pred_counts[threadIdx.x] = c;
-    }
-    __syncthreads();
-    if (threadIdx.x < 64) top_p_of(hist[threadIdx.x], hist[threadIdx.x + 64], N, p, top, threadIdx.x);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -631,8 +680,9 @@ static gate_job make_job(const void *gate_w, const float *bias, int norm_mode, i
     return j;
 }
 
-// Launches the gate kernels for one job, or for two jobs side by side (decode-sized batches only: both then take the
-// same path).  ws_logits[i]: [max(T,16), N] scratch of job i for the paths that store logits, or null.
+// Launches the gate kernels for one job, or for two jobs side by side (both of the same size, so they take the same
+// path).  ws_logits[i]: [max(T,16), N] scratch of job i for the paths that store logits, or null.  Beyond decode sizes a
+// job with a residual has fold_out set.
 static int launch_gate_topk(const moe_shape *s, const void *h, hipStream_t st, int n_jobs, gate_job *jobs, float *const *ws_logits)
 {
     const int NT = (s->N + 15) / 16;
@@ -665,16 +715,29 @@ static int launch_gate_topk(const moe_shape *s, const void *h, hipStream_t st, i
         for (int i = 0; i < 2; ++i) {
             const int ji = i < n_jobs ? i : n_jobs - 1;
             lg[i] = make_job(jobs[ji].gate_w, jobs[ji].bias, jobs[ji].norm_mode, nullptr, nullptr);
+            lg[i].res_vec = jobs[ji].res_vec;
+            lg[i].fold_out = jobs[ji].fold_out;
             lg[i].logits_out = ws_logits[ji];
             sel[i].logits_in = ws_logits[ji];
         }
-        hipLaunchKernelGGL(gate_topk_kernel<2>, dim3(grid.x, (s->N + 31) / 32, n_jobs), block, 0, st, s->T, s->d, s->N, s->k, hp,
+        const int planes = n_jobs + (lg[1].fold_out != nullptr ? 1 : 0);
+        hipLaunchKernelGGL(gate_topk_kernel<2>, dim3(grid.x, (s->N + 31) / 32, planes), block, 0, st, s->T, s->d, s->N, s->k, hp,
                            lg[0], lg[1]);
         MOE_CHECK_LAUNCH();
         hipLaunchKernelGGL(select_rows_kernel, dim3((s->T + SELECT_THREADS / 64 - 1) / (SELECT_THREADS / 64), 1, n_jobs),
                            dim3(SELECT_THREADS), 0, st, s->T, s->N, s->k, sel[0], sel[1]);
         MOE_CHECK_LAUNCH();
         return MOE_OK;
+    }
+    for (int i = 0; i < 2; ++i) {
+        if (sel[i].fold_out == nullptr) continue;
+        // few experts: the gate kernel selects too and needs the folded bias at its start
+        if (i == 1)
+            hipLaunchKernelGGL(fold_residual_kernel, dim3(s->N), dim3(64), 0, st, s->d, sel[i].res_vec, sel[i].gate_w, sel[i].bias,
+                               sel[i].fold_out);
+        sel[i].bias = sel[i].fold_out;
+        sel[i].res_vec = nullptr;
+        sel[i].fold_out = nullptr;
     }
 #define GT(n)                                                                                                  \
     case n:                                                                                                    \
@@ -714,7 +777,8 @@ static gate_job route_job(const moe_shape *s, const void *gate_w, const float *g
     return j;
 }
 
-// prediction job of a decode-sized batch: residual folded inside the gate kernel, histogram and top-p in the selecting block
+// prediction job: at decode sizes the residual is folded inside the gate kernel and the selecting block does histogram and
+// top-p; beyond, the folded bias goes through fold_out and predict_top names what the histogram reads and writes
 static gate_job predict_job(const moe_shape *s, const float *res_vec, const void *next_gate_w, const float *next_gate_bias, int p,
                             int32_t *pred_counts, int32_t *top_experts, void *workspace)
 {
@@ -725,9 +789,13 @@ static gate_job predict_job(const moe_shape *s, const float *res_vec, const void
     float *w = (float *)(ws + moe_align256(MOE_MAX_EXPERTS * 4) + moe_align256(R * 4));
     gate_job j = make_job(next_gate_w, next_gate_bias, MOE_NORM_NONE, idx, w);
     j.res_vec = res_vec;
-    j.counts = pred_counts;
-    j.top = top_experts;
-    j.p = p;
+    if (single_block_routing(s)) {
+        j.counts = pred_counts;
+        j.top = top_experts;
+        j.p = p;
+    } else {
+        j.fold_out = (float *)ws;
+    }
     return j;
 }
 
@@ -739,55 +807,37 @@ int moe_route_impl(const moe_shape *s, const void *h, const void *gate_w, const 
     float *wl[1] = {route_logits_scratch(s, workspace, 0)};
     int rc = launch_gate_topk(s, h, st, 1, &j, wl);
     if (rc != MOE_OK || single_block_routing(s)) return rc;
-    hipLaunchKernelGGL(hist_scan_perm_kernel, dim3(s->N), dim3(256), 0, st, s->T * s->k, s->N, topk_idx, counts,
-                       offsets, perm, inv_perm);
-    MOE_CHECK_LAUNCH();
-    return MOE_OK;
+    return launch_hist_scan_perm(s->T * s->k, s->N, topk_idx, counts, offsets, perm, inv_perm, nullptr, st);
 }
 
 int moe_predict_impl(const moe_shape *s, const void *h, const float *res_vec, const void *next_gate_w,
                      const float *next_gate_bias, int p, int32_t *pred_counts, int32_t *top_experts, void *workspace,
                      hipStream_t st)
 {
-    if (single_block_routing(s)) {
-        gate_job j = predict_job(s, res_vec, next_gate_w, next_gate_bias, p, pred_counts, top_experts, workspace);
-        float *wl[1] = {route_logits_scratch(s, workspace, 1)};
-        return launch_gate_topk(s, h, st, 1, &j, wl);
-    }
-    moe_ws_layout L = moe_ws(s);
-    char *ws = (char *)workspace + L.route;
-    float *bias2 = (float *)ws;
-    size_t R = (size_t)s->T * s->k;
-    int32_t *idx = (int32_t *)(ws + moe_align256(MOE_MAX_EXPERTS * 4));
-    float *w = (float *)(ws + moe_align256(MOE_MAX_EXPERTS * 4) + moe_align256(R * 4));
-    hipLaunchKernelGGL(fold_residual_kernel, dim3(s->N), dim3(64), 0, st, s->d, res_vec, (const uint16_t *)next_gate_w,
-                       next_gate_bias, bias2);
-    MOE_CHECK_LAUNCH();
-    gate_job j = make_job(next_gate_w, bias2, MOE_NORM_NONE, idx, w);
+    gate_job j = predict_job(s, res_vec, next_gate_w, next_gate_bias, p, pred_counts, top_experts, workspace);
     float *wl[1] = {route_logits_scratch(s, workspace, 1)};
     int rc = launch_gate_topk(s, h, st, 1, &j, wl);
-    if (rc != MOE_OK) return rc;
-    hipLaunchKernelGGL(hist_top_kernel, dim3(1), dim3(HT_THREADS), 0, st, (int)R, s->N, p, idx, pred_counts, top_experts);
+    if (rc != MOE_OK || single_block_routing(s)) return rc;
+    const top_job top = {j.topk_idx, pred_counts, top_experts, p};
+    hipLaunchKernelGGL(hist_top_kernel, dim3(1), dim3(HT_THREADS), 0, st, s->T * s->k, s->N, top);
     MOE_CHECK_LAUNCH();
     return MOE_OK;
 }
 
-// Routing of this layer and workload prediction of the next in one pass: at decode sizes the two gates are
-// evaluated by the same two launches (blockIdx.z = 0 routes, 1 predicts); larger batches run one after the other.
+// Routing of this layer and workload prediction of the next in one pass: the two gates are evaluated by the same launches
+// (blockIdx.z = 0 routes, 1 predicts).  Beyond decode sizes that is three launches instead of eight: 1531 tokens, 128 experts 69 -> 32 us.
 int moe_route_predict_impl(const moe_shape *s, const void *h, const void *gate_w, const float *gate_bias, int norm_mode,
                            int32_t *topk_idx, float *topk_w, int32_t *counts, int32_t *offsets, int32_t *perm,
                            int32_t *inv_perm, const float *res_vec, const void *next_gate_w, const float *next_gate_bias,
                            int p, int32_t *pred_counts, int32_t *top_experts, void *workspace, hipStream_t st)
 {
-    if (!single_block_routing(s)) {
-        int rc = moe_route_impl(s, h, gate_w, gate_bias, norm_mode, topk_idx, topk_w, counts, offsets, perm, inv_perm, workspace, st);
-        if (rc != MOE_OK) return rc;
-        return moe_predict_impl(s, h, res_vec, next_gate_w, next_gate_bias, p, pred_counts, top_experts, workspace, st);
-    }
     gate_job jobs[2] = {route_job(s, gate_w, gate_bias, norm_mode, topk_idx, topk_w, counts, offsets, perm, inv_perm),
                         predict_job(s, res_vec, next_gate_w, next_gate_bias, p, pred_counts, top_experts, workspace)};
     float *wl[2] = {route_logits_scratch(s, workspace, 0), route_logits_scratch(s, workspace, 1)};
-    return launch_gate_topk(s, h, st, 2, jobs, wl);
+    int rc = launch_gate_topk(s, h, st, 2, jobs, wl);
+    if (rc != MOE_OK || single_block_routing(s)) return rc;
+    const top_job top = {jobs[1].topk_idx, pred_counts, top_experts, p};
+    return launch_hist_scan_perm(s->T * s->k, s->N, topk_idx, counts, offsets, perm, inv_perm, &top, st);
 }
 
 int moe_dense_route_impl(const moe_shape *s, int32_t *counts, int32_t *offsets, int32_t *perm, hipStream_t st)
