@@ -18,10 +18,9 @@
 //     covered by the other's MFMAs, and the accumulators stay in place (no AGPR shuffling).
 //   * The MFMA takes weight rows as A and token rows as B, so a lane ends up with 4 consecutive output columns
 //     of one token: SwiGLU is applied in registers and the result leaves as one 8-byte store.
-// A work item is (expert, 128-row token tile, weight tile); the item list is built on the device from
-// counts/offsets/mask (tile_schedule_kernel), so empty and masked-off experts cost nothing and there is no host
-// round trip.  Up to 128 tokens an expert has at most one token tile and every wave derives the list of working
-// experts itself from two ballots, so no schedule kernel runs.  Block ids are remapped so that every XCD (own
+// A work item is (expert, 128-row token tile, weight tile); every wave derives the item list from counts and mask
+// (moe_rank_tiles; up to 128 tokens an expert has at most one token tile and two ballots do), so empty and masked-off
+// experts cost nothing, there is no host round trip and no schedule pass ahead of the launch.  Block ids are remapped so that every XCD (own
 // L2) works on a contiguous run of items ordered expert-major, weight tile, token tile: the token tiles that
 // share a weight tile run side by side on one XCD (measured: the same items spread round-robin over the XCDs
 // run up to 40 % slower, even with one token tile per expert).
@@ -29,7 +28,7 @@
 // row count (16, 32, 64, 96, 112 or 128 rows).
 // What only the device knows (counts and mask) also shapes the launch there: with few working tiles the up projection
 // switches to half-width items and the down projection splits the K range of its tiles over several items (fp32 partial
-// sums, summed in split order by tiled_finish_kernel); with many, the schedule kernel picks the token-tile height of
+// sums, summed in split order by tiled_finish_kernel); with many, the blocks pick the token-tile height of
 // the down projection so that its items fill whole rounds of compute units.
 // Each item walks K as a ring starting at an expert-dependent offset, so that the token tiles that share a weight tile
 // stay in step (started at different points they run 18 % slower); the summation order is a function of the expert
@@ -67,8 +66,7 @@ extern "C" int moe_debug_set_trace(unsigned long long *records)
 #define NUM_XCD MOE_NUM_XCD
 #define TILED_THREADS 512
 
-// Tile tables, one per projection: int32 hdr[4] = {n_token_tiles, tile height, 0, 0}; then int4 per token tile
-// {expert, first_tile, n_tiles_of_expert, 0}.  The up projection uses 128-row tiles.  The down projection has few
+// The up projection uses 128-row tiles.  The down projection has few
 // items (8 column tiles of 512 per token tile at d = 4096), so the number of rounds the launch needs on 256 compute
 // units moves its duration in steps: 27 token tiles are 216 items, one round with 40 units idle, and 30 tiles of 112
 // rows are 240 items, still one round of shorter items.  The tile height of the down projection is therefore chosen
@@ -81,90 +79,20 @@ __device__ __forceinline__ int sched_cost(int tiles, int n_ntc, int tm)
     return rounds2 * (tm + 64);
 }
 
-__device__ __forceinline__ int wave_sum_int(int v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, MOE_WAVE);
-    return v;
-}
+__device__ __forceinline__ moe_tiles tiles_128(const moe_rows &c) { return moe_rank_tiles((c.c0 + 127) / 128, (c.c1 + 127) / 128); }
 
-// exclusive prefix sum over the 128 threads of the block (two waves); *total receives the sum
-__device__ __forceinline__ int block_exclusive_scan(int v, int *wave_total /* LDS, 2 ints */, int *total)
+// the token tiles of the down projection and their height tm
+__device__ __forceinline__ moe_tiles down_tiles(const moe_rows &c, int n_ntc, int &tm)
 {
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    int incl = v;
-#pragma unroll
-    for (int o = 1; o < MOE_WAVE; o <<= 1) {
-        const int t = __shfl_up(incl, o, MOE_WAVE);
-        if (lane >= o) incl += t;
-    }
-    if (lane == MOE_WAVE - 1) wave_total[w] = incl;
-    __syncthreads();
-    *total = wave_total[0] + wave_total[1];
-    return incl - v + (w == 1 ? wave_total[0] : 0);
-}
-
-__global__ __launch_bounds__(MOE_MAX_EXPERTS) void tile_schedule_kernel(int N, const int32_t *__restrict__ counts,
-                                                                        const uint8_t *__restrict__ mask, int n_ntc_down,
-                                                                        int wide_steps /* 0: tiled down projection */,
-                                                                        int32_t *__restrict__ sched_up,
-                                                                        int32_t *__restrict__ sched_down)
-{
-    __shared__ int wsum[3][2], wtot[4][2], wcost[2];
-    const int e = threadIdx.x, w = e >> 6;
-    const int c = (e < N && counts[e] > 0 && (mask == nullptr || mask[e] != 0)) ? counts[e] : 0;
-    const int n128 = (c + 127) / 128, n112 = (c + 111) / 112, n96 = (c + 95) / 96;
-    const int wide_cost = wave_sum_int(c > 0 ? (c - 1) / WIDE_TM * 16 + wide_cost16((c - 1) % WIDE_TM + 1) : 0);
-    const int s128 = wave_sum_int(n128), s112 = wave_sum_int(n112), s96 = wave_sum_int(n96);
-    if ((e & 63) == 0) {
-        wsum[0][w] = s128;
-        wsum[1][w] = s112;
-        wsum[2][w] = s96;
-        wcost[w] = wide_cost;
-    }
-    __syncthreads();
-    // every thread takes the same decision from the same totals
-    const int t128 = wsum[0][0] + wsum[0][1], t112 = wsum[1][0] + wsum[1][1], t96 = wsum[2][0] + wsum[2][1];
-    int tm = 128, best = sched_cost(t128, n_ntc_down, 128);
-    if (wide_steps == 0 && t128 * n_ntc_down >= 256) {      // below that the K range is split instead
-        const int c112 = sched_cost(t112, n_ntc_down, 112), c96 = sched_cost(t96, n_ntc_down, 96);
-        if (c112 < best) { best = c112; tm = 112; }
-        if (c96 < best) { best = c96; tm = 96; }
-    }
-    const int n_dn = wide_steps > 0 ? (c + WIDE_TM - 1) / WIDE_TM : tm == 128 ? n128 : tm == 112 ? n112 : n96;
-    int tot_up, tot_dn;
-    const int first_up = block_exclusive_scan(n128, wtot[0], &tot_up);
-    const int first_dn = block_exclusive_scan(n_dn, wtot[1], &tot_dn);
-    if (e == 0) {
-        sched_up[0] = tot_up;
-        sched_up[1] = TM;
-        sched_up[2] = sched_up[3] = 0;
-        sched_down[0] = tot_dn;
-        sched_down[1] = tm;
-        sched_down[2] = sched_down[3] = 0;
-        if (wide_steps > 0) {
-            const int items = tot_dn * n_ntc_down, rest = items % 256;
-            const int pieces = wide_pieces(rest, (wcost[0] + wcost[1]) * n_ntc_down - (items - rest) * 16, wide_steps);
-            sched_down[1] = pieces > 1 ? items - rest : items;
-            sched_down[2] = pieces;
-        }
-    }
-    int4 *tab = reinterpret_cast<int4 *>(sched_up + 4);
-#ifdef MOE_RAGGED_LAST
-    {
-        // full tiles of all experts first, then the ragged last tiles: a group is {expert, first list entry, tiles, first tile of the expert}
-        const int nfull = c / TM, rag = (c % TM) != 0 ? 1 : 0;
-        int tot_full, tot_rag;
-        const int first_full = block_exclusive_scan(nfull, wtot[2], &tot_full);
-        const int first_rag = tot_full + block_exclusive_scan(rag, wtot[3], &tot_rag);
-        for (int j = 0; j < nfull; ++j) tab[first_full + j] = make_int4(e, first_full, nfull, 0);
-        if (rag) tab[first_rag] = make_int4(e, first_rag, 1, nfull);
-    }
-#else
-    for (int j = 0; j < n128; ++j) tab[first_up + j] = make_int4(e, first_up, n128, 0);
-#endif
-    tab = reinterpret_cast<int4 *>(sched_down + 4);
-    for (int j = 0; j < n_dn; ++j) tab[first_dn + j] = make_int4(e, first_dn, n_dn, 0);
+    const moe_tiles t128 = tiles_128(c);
+    tm = 128;
+    if (t128.total * n_ntc < 256) return t128;              // the K range is split instead
+    const int a112 = (c.c0 + 111) / 112, b112 = (c.c1 + 111) / 112, a96 = (c.c0 + 95) / 96, b96 = (c.c1 + 95) / 96;
+    int best = sched_cost(t128.total, n_ntc, 128);
+    const int c112 = sched_cost(wave_sum_int_dpp(a112 + b112), n_ntc, 112), c96 = sched_cost(wave_sum_int_dpp(a96 + b96), n_ntc, 96);
+    if (c112 < best) { best = c112; tm = 112; }
+    if (c96 < best) { best = c96; tm = 96; }
+    return tm == 128 ? t128 : tm == 112 ? moe_rank_tiles(a112, b112) : moe_rank_tiles(a96, b96);
 }
 
 // MODE 0: up (W1|W3 + SwiGLU -> act); a wave owns NF/2 fragments of W1 and the same NF/2 of W3.
@@ -410,7 +338,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void ffn_tiled_kernel(
     int d, int I, int k, int N, const uint16_t *__restrict__ xsrc,   // MODE 0: h [T,d]; MODE 1: act [R,I]
     const int32_t *__restrict__ perm, const int32_t *__restrict__ offsets, const int32_t *__restrict__ counts,
     const uint16_t *__restrict__ wa, const uint16_t *__restrict__ wb,   // MODE 0: packed w1, w3; MODE 1: packed w2, unused
-    const int32_t *__restrict__ sched, const uint8_t *__restrict__ mask,   // DIRECT: mask instead of a schedule
+    const uint8_t *__restrict__ mask,
     uint16_t *__restrict__ out,                                            // MODE 0: act [R,I]; MODE 1: y [R,d]
     int nsp_max, float *__restrict__ part, int R,   // MODE 1: up to nsp_max K splits per tile, partial sums in part [nsp,R,d] fp32
     int group)                                      // column tiles that alternate inside the item order of an expert (1: column tile major)
@@ -426,9 +354,9 @@ __global__ __launch_bounds__(WAVES * 64, 2) void ffn_tiled_kernel(
     // ---- which item: (expert, token tile, column tile, K split).  The number of K splits follows from the number of
     // tiles that have work, which only the device knows (counts and mask live there)
     MOE_TRACE_BEGIN();
-    int e, mt, nt, nsp = 1;
+    int e, mt, nt, nsp = 1, tmk = TM;      // tmk: token rows per tile of this launch
     if (DIRECT) {
-        // at most one token tile per expert (T <= 128): no schedule has been built
+        // at most one token tile per expert (T <= 128)
         unsigned long long act_lo, act_hi;
         const int n_work = moe_working_experts(N, counts, mask, act_lo, act_hi);
         if (MODE == 1) nsp = moe_dev_splits(n_work * n_ntc, nsp_max);
@@ -439,33 +367,34 @@ __global__ __launch_bounds__(WAVES * 64, 2) void ffn_tiled_kernel(
         if (!moe_item_of(act_lo, act_hi, n_ntc * nsp, blockIdx.x, e, nt)) return;
         mt = 0;
     } else {
-        if (MODE == 1) nsp = moe_dev_splits(sched[0] * n_ntc, nsp_max);
-        if (CAN_NARROW && up_items_narrow(sched[0] * n_ntc)) {
+        const moe_rows rows = moe_masked_rows(N, counts, mask);
+        const moe_tiles tiles = MODE == 0 ? tiles_128(rows) : down_tiles(rows, n_ntc, tmk);
+        if (MODE == 1) nsp = moe_dev_splits(tiles.total * n_ntc, nsp_max);
+        if (CAN_NARROW && up_items_narrow(tiles.total * n_ntc)) {
             narrow = true;
             n_ntc = (I + NT_COLS / 2 - 1) / (NT_COLS / 2);
         }
         const int n_nt = n_ntc * nsp;
-        const int total = sched[0] * n_nt;
+        const int total = tiles.total * n_nt;
         const int pid = blockIdx.x;
         if (pid >= total) return;
         const int q = total / NUM_XCD, rem = total % NUM_XCD;
         const int xcd = pid % NUM_XCD, loc = pid / NUM_XCD;
         const int L = xcd < rem ? xcd * (q + 1) + loc : rem * (q + 1) + (xcd - rem) * q + loc;
-        const int4 ent = reinterpret_cast<const int4 *>(sched + 4)[L / n_nt];
-        e = ent.x;
-        const int local = L - ent.y * n_nt;
+        int first, n;
+        moe_find_tile(tiles, L / n_nt, e, first, n);
+        const int local = L - first * n_nt;
         // Item order inside an expert: groups of `group` column tiles; inside a group the token tiles in turn, each with
         // the group's column tiles side by side.  Blocks that follow each other in the list start close in time, so the
         // blocks that share a token tile (same mt) and those that share a weight tile (same nt) both stay near each other.
-        const int per_group = group * ent.z;
+        const int per_group = group * n;
         const int g0 = local / per_group, within = local - g0 * per_group;
         const int gsz = min(group, n_nt - g0 * group);         // the last group may hold fewer column tiles
-        mt = ent.w + within / gsz;
+        mt = within / gsz;
         nt = g0 * group + within % gsz;
     }
     const int sp = nt % nsp;      // column tile nt / nsp, K split nt % nsp
     nt /= nsp;
-    const int tmk = (DIRECT || MODE == 0) ? TM : sched[1];      // token rows per tile of this launch
     const int row0 = offsets[e] + mt * tmk;
     int nrows = counts[e] - mt * tmk;
     nrows = nrows > tmk ? tmk : nrows;
@@ -515,7 +444,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void ffn_tiled_kernel(
 // y[p,:] = bf16( sum over the K splits, in split order ), when the down projection of this launch split K (the same
 // device-side decision as in ffn_tiled_kernel; nothing to do otherwise: the tiles wrote y themselves)
 __global__ __launch_bounds__(256) void tiled_finish_kernel(int d, int R, int N, int n_ntc, int nsp_max, int direct,
-                                                           const int32_t *__restrict__ sched, const float *__restrict__ partial,
+                                                           const float *__restrict__ partial,
                                                            const int32_t *__restrict__ offsets, const int32_t *__restrict__ counts,
                                                            const uint8_t *__restrict__ mask, uint16_t *__restrict__ y)
 {
@@ -524,7 +453,8 @@ __global__ __launch_bounds__(256) void tiled_finish_kernel(int d, int R, int N, 
         unsigned long long act_lo, act_hi;
         tiles = moe_working_experts(N, counts, mask, act_lo, act_hi);
     } else {
-        tiles = sched[0];
+        int tm;
+        tiles = down_tiles(moe_masked_rows(N, counts, mask), n_ntc, tm).total;
     }
     const int nsp = moe_dev_splits(tiles * n_ntc, nsp_max);
     if (nsp == 1) return;
@@ -555,7 +485,7 @@ static int tiled_item_group(int mode)
 
 template <int MODE, int NF, int NTT, bool DIRECT, int NSETS, bool FENCED, int WAVES>
 static void launch_tiled(const moe_shape *s, long max_mt, const uint16_t *x, const int32_t *perm, const int32_t *offsets,
-                         const int32_t *counts, const uint16_t *wa, const uint16_t *wb, const int32_t *sched,
+                         const int32_t *counts, const uint16_t *wa, const uint16_t *wb,
                          const uint8_t *mask, uint16_t *out, int nsp_max, float *part, hipStream_t st)
 {
     constexpr int cols = WAVES * 16 * (MODE == 0 ? NF / 2 : NF);
@@ -568,7 +498,7 @@ static void launch_tiled(const moe_shape *s, long max_mt, const uint16_t *x, con
     const long n_e = s->N < (long)s->T * s->k ? s->N : (long)s->T * s->k;   // DIRECT: experts that can be non-empty
     const dim3 grid((unsigned)((DIRECT ? n_e : max_mt) * n_nt));
     hipLaunchKernelGGL((ffn_tiled_kernel<MODE, NF, NTT, DIRECT, NSETS, FENCED, WAVES>), grid, dim3(WAVES * 64), 0, st, s->d, s->I, s->k,
-                       s->N, x, perm, offsets, counts, wa, wb, sched, mask, out, nsp_max, part, R, tiled_item_group(MODE));
+                       s->N, x, perm, offsets, counts, wa, wb, mask, out, nsp_max, part, R, tiled_item_group(MODE));
 }
 
 // Weight fragments per wave (NF), 16-row token subtiles per tile (NTT) and weight register sets (NSETS).  An expert
@@ -580,14 +510,14 @@ static void launch_tiled(const moe_shape *s, long max_mt, const uint16_t *x, con
 template <int MODE>
 static void dispatch_tiled(const moe_shape *s, int nf, int waves, long max_mt, const uint16_t *x, const int32_t *perm,
                            const int32_t *offsets, const int32_t *counts, const uint16_t *wa, const uint16_t *wb,
-                           const int32_t *sched, const uint8_t *mask, uint16_t *out, int nsp_max, float *part, hipStream_t st)
+                           const uint8_t *mask, uint16_t *out, int nsp_max, float *part, hipStream_t st)
 {
     const int K = MODE == 0 ? s->d : s->I;
     const bool deep = K % (256 * nsp_max) == 0 && K >= 2048;   // a short K does not pay for the longer prologue
-#define GO(NF_, NTT_, D_, NS_, F_) launch_tiled<MODE, NF_, NTT_, D_, NS_, F_, 8>(s, max_mt, x, perm, offsets, counts, wa, wb, sched, mask, out, nsp_max, part, st)
+#define GO(NF_, NTT_, D_, NS_, F_) launch_tiled<MODE, NF_, NTT_, D_, NS_, F_, 8>(s, max_mt, x, perm, offsets, counts, wa, wb, mask, out, nsp_max, part, st)
     if (waves == 4) {
         // two independent 4-wave blocks per compute unit (scheduled launches with full-height tiles only)
-        launch_tiled<MODE, 4, 8, false, 4, false, 4>(s, max_mt, x, perm, offsets, counts, wa, wb, sched, mask, out, nsp_max, part, st);
+        launch_tiled<MODE, 4, 8, false, 4, false, 4>(s, max_mt, x, perm, offsets, counts, wa, wb, mask, out, nsp_max, part, st);
         return;
     }
 #define GO3(NTT_, D_)                                                          \
@@ -629,13 +559,11 @@ int moe_ffn_tiled_impl(const moe_shape *s, const void *h, const int32_t *perm, c
     const long R = (long)s->T * k;
     moe_ws_layout L = moe_ws(s);
     uint16_t *act = (uint16_t *)((char *)workspace + L.act);
-    int32_t *sched = (int32_t *)((char *)workspace + L.sched);                     // up projection's tile table
-    int32_t *sched_down = sched + moe_sched_table_bytes(s) / 4;
     const long max_mt = R / TM + (N < R ? N : R), max_mt_down = R / MOE_TILE_M_MIN + (N < R ? N : R);
     // token tiles to expect: every expert that can be non-empty has one, large experts have several
     const long est_mt = (R + TM - 1) / TM > (N < R ? N : R) ? (R + TM - 1) / TM : (N < R ? N : R);
 
-    // the down projection's tile shape (needed by the schedule, which the up stage builds for both)
+    // the down projection's tile shape
     int nf = s->T <= MOE_SKINNY_MAX_T ? 1
              : est_mt * ((d + 511) / 512) >= 256 ? 4 : est_mt * ((d + 255) / 256) >= 256 ? 2 : 1;
     // blocks of 4 waves, two of them per compute unit, for scheduled launches (experiment switch)
@@ -645,20 +573,13 @@ int moe_ffn_tiled_impl(const moe_shape *s, const void *h, const int32_t *perm, c
     const int waves_down = s->T > TM && env_dn == 4 && nf == 4 ? 4 : 8;
     const bool wide = moe_wide_down(s);
     const int n_ntc = wide ? (d + WIDE_TN - 1) / WIDE_TN : (d + 16 * waves_down * nf - 1) / (16 * waves_down * nf);
-    // The tile tables are built at the start of every call, also of one that runs the down stage alone: that call then
-    // never reads a table that an earlier call did not build or built from other counts or another mask.
-    if (s->T > TM) {
-        hipLaunchKernelGGL(tile_schedule_kernel, dim3(1), dim3(MOE_MAX_EXPERTS), 0, st, N, counts, expert_mask, n_ntc,
-                           wide ? s->I / 32 : 0, sched, sched_down);
-        MOE_CHECK_LAUNCH();
-    }
     if (stages & MOE_FFN_STAGE_UP) {
         dispatch_tiled<0>(s, 4, waves_up, max_mt, (const uint16_t *)h, perm, offsets, counts, (const uint16_t *)w1,
-                          (const uint16_t *)w3, sched, expert_mask, act, 1, nullptr, st);
+                          (const uint16_t *)w3, expert_mask, act, 1, nullptr, st);
         MOE_CHECK_LAUNCH();
     }
     if ((stages & MOE_FFN_STAGE_DOWN) && wide)
-        return moe_ffn_wide_down(s, offsets, counts, act, w2, y, sched_down, (float *)((char *)workspace + L.partial), st);
+        return moe_ffn_wide_down(s, offsets, counts, act, w2, y, expert_mask, (float *)((char *)workspace + L.partial), st);
     if (stages & MOE_FFN_STAGE_DOWN) {
         // nf: the widest weight tile that still leaves every compute unit a block (512 columns, then 256 columns), else
         // the narrowest (128 columns); and when even that leaves compute units idle -- few experts with rows, or few of
@@ -667,12 +588,12 @@ int moe_ffn_tiled_impl(const moe_shape *s, const void *h, const int32_t *perm, c
         const int nsp_max = moe_tiled_down_max_splits(s);
         float *part = (float *)((char *)workspace + L.partial);
         dispatch_tiled<1>(s, nf, waves_down, max_mt_down, (const uint16_t *)act, perm, offsets, counts, (const uint16_t *)w2,
-                          (const uint16_t *)nullptr, sched_down, expert_mask, (uint16_t *)y, nsp_max, part, st);
+                          (const uint16_t *)nullptr, expert_mask, (uint16_t *)y, nsp_max, part, st);
         MOE_CHECK_LAUNCH();
         if (nsp_max > 1) {
             const int max_rows = s->T < (int)R ? s->T : (int)R;
             hipLaunchKernelGGL(tiled_finish_kernel, dim3(max_rows, N), dim3(256), 0, st, d, (int)R, N, n_ntc, nsp_max,
-                               s->T <= TM ? 1 : 0, sched_down, part, offsets, counts, expert_mask, (uint16_t *)y);
+                               s->T <= TM ? 1 : 0, part, offsets, counts, expert_mask, (uint16_t *)y);
             MOE_CHECK_LAUNCH();
         }
     }

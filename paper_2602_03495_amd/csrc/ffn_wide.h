@@ -5,7 +5,7 @@
 // microseconds, so what decides the duration of a launch is how well its items fill the compute units.
 //   * The whole rounds of 256 items run as they are; the items of the last, partial round are cut along K into pieces
 //     that fill the chip once more (fp32 partial sums, added in piece order by wide_finish_kernel).  Everything follows
-//     from counts and mask on the device (tile_schedule_kernel).
+//     from counts and mask on the device (wide_plan_of).
 //   * 4 waves per block, one per SIMD, 256 accumulator registers per lane: the largest tile the register file holds
 //     asks L2 for 32 KB per k32 step and 4.2 MFLOP.  A wave owns 64 output columns, i.e. 4 weight fragments per step in
 //     the packed order of moe_pack_weights, loaded global -> VGPR seven steps ahead.
@@ -27,9 +27,6 @@
 
 #define WIDE_MAX_SPLIT 16       // most pieces of one item
 
-// Tile table: int32 hdr[4] = {row tiles, items that run whole, pieces per item of the rest, 0}; then one int4 per row
-// tile {expert, first tile of the expert, its tiles, 0}.
-//
 // Pieces: whole rounds of 256 items run as they are, the `rest` items beyond them are cut into S pieces each.  An item of
 // few rows is shorter (measured at K = 14336: 166 us with up to 32 rows, 186, 215 and 288 with up to 64, 128 and 192, 360
 // with more), so the whole rounds have room for some of the pieces: rest16 is what exceeds them, in sixteenths of a full
@@ -37,19 +34,38 @@
 // pipeline and writing its partial sums, the finishing pass about 25 plus what it reads (256 KB per piece).
 __device__ __forceinline__ int wide_cost16(int rows) { return rows <= 32 ? 7 : rows <= 64 ? 8 : rows <= 128 ? 10 : rows <= 192 ? 13 : 16; }
 
+// Lane s weighs up s pieces; the cheapest, of equals the fewest, is taken.  All 64 lanes must call it.
 __device__ __forceinline__ int wide_pieces(int rest, int rest16, int steps)
 {
-    int best_s = 1, best = steps + 14;
-    for (int s = 2; s <= WIDE_MAX_SPLIT && rest > 0; ++s) {
-        if (rest * s > WIDE_MAX_PIECES || steps / s < 16) break;
+    const int s = threadIdx.x & 63;
+    int cost = 0x7fffffff;
+    if (s == 1) {
+        cost = (steps + 14) << 5 | 1;
+    } else if (s >= 2 && s <= WIDE_MAX_SPLIT && rest > 0 && rest * s <= WIDE_MAX_PIECES && steps >= 16 * s) {
         const int by_count = (rest * s + 255) / 256, by_work = rest16 * s > 4096 + 256 ? (rest16 * s + 4095 - 256) / 4096 : 1;
-        const int c = (by_count + by_work) * (steps / s + 14) / 2 + 25 + rest * s / 7;
-        if (c < best) {
-            best = c;
-            best_s = s;
-        }
+        cost = ((by_count + by_work) * (steps / s + 14) / 2 + 25 + rest * s / 7) << 5 | s;
     }
-    return best_s;
+    return -wave_max_int_dpp(-cost) & 31;
+}
+
+// The items of a launch: row tiles, those items that run whole, pieces per item of the rest.
+struct wide_plan {
+    moe_tiles tiles;
+    int items, whole, pieces;
+};
+__device__ __forceinline__ int wide_cost16_of(int c) { return c > 0 ? (c - 1) / WIDE_TM * 16 + wide_cost16((c - 1) % WIDE_TM + 1) : 0; }
+__device__ __forceinline__ wide_plan wide_plan_of(int N, const int32_t *__restrict__ counts, const uint8_t *__restrict__ mask, int n_nt,
+                                                  int steps)
+{
+    const moe_rows c = moe_masked_rows(N, counts, mask);
+    wide_plan p;
+    p.tiles = moe_rank_tiles((c.c0 + WIDE_TM - 1) / WIDE_TM, (c.c1 + WIDE_TM - 1) / WIDE_TM);
+    p.items = p.tiles.total * n_nt;
+    const int rest = p.items % 256;
+    const int cost = wave_sum_int_dpp(wide_cost16_of(c.c0) + wide_cost16_of(c.c1));
+    p.pieces = wide_pieces(rest, cost * n_nt - (p.items - rest) * 16, steps);
+    p.whole = p.pieces > 1 ? p.items - rest : p.items;
+    return p;
 }
 
 #define WIDE_THREADS 256
@@ -264,24 +280,26 @@ struct wide_item {
     int e, nt, row0, nrows;
 };
 
-__device__ __forceinline__ wide_item wide_item_of(int L, int n_nt, const int32_t *__restrict__ sched,
-                                                  const int32_t *__restrict__ offsets, const int32_t *__restrict__ counts)
+__device__ __forceinline__ wide_item wide_item_of(int L, int n_nt, const moe_tiles &tiles, const int32_t *__restrict__ offsets,
+                                                  const int32_t *__restrict__ counts)
 {
-    const int4 ent = reinterpret_cast<const int4 *>(sched + 4)[L / n_nt];
-    const int local = L - ent.y * n_nt;
-    const int nt = local / ent.z, mt = local - nt * ent.z;     // the row tiles that share a weight tile follow each other
-    const int rows = counts[ent.x] - mt * WIDE_TM;
-    return wide_item{ent.x, nt, offsets[ent.x] + mt * WIDE_TM, rows > WIDE_TM ? WIDE_TM : rows};
+    int e, first, n;
+    moe_find_tile(tiles, L / n_nt, e, first, n);
+    const int local = L - first * n_nt;
+    const int nt = local / n, mt = local - nt * n;             // the row tiles that share a weight tile follow each other
+    const int rows = counts[e] - mt * WIDE_TM;
+    return wide_item{e, nt, offsets[e] + mt * WIDE_TM, rows > WIDE_TM ? WIDE_TM : rows};
 }
 
-__global__ __launch_bounds__(WIDE_THREADS, 1) void ffn_wide_kernel(int d, int I, const uint16_t *__restrict__ act,
+__global__ __launch_bounds__(WIDE_THREADS, 1) void ffn_wide_kernel(int d, int I, int N, const uint16_t *__restrict__ act,
                                                                    const int32_t *__restrict__ offsets, const int32_t *__restrict__ counts,
-                                                                   const uint16_t *__restrict__ w2, const int32_t *__restrict__ sched,
+                                                                   const uint16_t *__restrict__ w2, const uint8_t *__restrict__ mask,
                                                                    uint16_t *__restrict__ y, float *__restrict__ partial)
 {
     __shared__ __attribute__((aligned(1024))) char lds[WIDE_BUFS * WIDE_BUF_BYTES];
     const int n_nt = (d + WIDE_TN - 1) / WIDE_TN;
-    const int items = sched[0] * n_nt, whole = sched[1], S = sched[2];
+    const wide_plan plan = wide_plan_of(N, counts, mask, n_nt, I / 32);
+    const int items = plan.items, whole = plan.whole, S = plan.pieces;
     const int pid = blockIdx.x;
     int total = whole, base = 0, r = 1;
     if (pid >= whole) {                                        // pieces: all first pieces, then all second ones, ...
@@ -303,7 +321,7 @@ __global__ __launch_bounds__(WIDE_THREADS, 1) void ffn_wide_kernel(int d, int I,
         nk = (sp + 1) * quads / S * 4 - k0;
         part = partial + (size_t)L * WIDE_TM * WIDE_TN;
     }
-    const wide_item it = wide_item_of(item, n_nt, sched, offsets, counts);
+    const wide_item it = wide_item_of(item, n_nt, plan.tiles, offsets, counts);
     MOE_TRACE_BEGIN();
 #define BODY(n) wide_body<n>(lds, d, I, act, w2, it.e, it.nt, it.row0, it.nrows, k0, nk, y, part)
     if (it.nrows <= 32) BODY(2);
@@ -316,15 +334,16 @@ __global__ __launch_bounds__(WIDE_THREADS, 1) void ffn_wide_kernel(int d, int I,
 }
 
 // y rows of the items that ran in pieces: the partial sums added in piece order
-__global__ __launch_bounds__(256) void wide_finish_kernel(int d, const int32_t *__restrict__ offsets, const int32_t *__restrict__ counts,
-                                                          const int32_t *__restrict__ sched, const float *__restrict__ partial,
+__global__ __launch_bounds__(256) void wide_finish_kernel(int d, int steps, int N, const int32_t *__restrict__ offsets,
+                                                          const int32_t *__restrict__ counts, const uint8_t *__restrict__ mask, const float *__restrict__ partial,
                                                           uint16_t *__restrict__ y)
 {
     const int n_nt = (d + WIDE_TN - 1) / WIDE_TN;
-    const int whole = sched[1], S = sched[2], r = sched[0] * n_nt - whole;
+    const wide_plan plan = wide_plan_of(N, counts, mask, n_nt, steps);
+    const int whole = plan.whole, S = plan.pieces, r = plan.items - whole;
     const int j = blockIdx.y;
     if (S == 1 || j >= r) return;
-    const wide_item it = wide_item_of(whole + j, n_nt, sched, offsets, counts);
+    const wide_item it = wide_item_of(whole + j, n_nt, plan.tiles, offsets, counts);
     const int c = (threadIdx.x & 31) * 8;
     if (it.nt * WIDE_TN + c >= d) return;
     for (int row = blockIdx.x * 8 + (threadIdx.x >> 5); row < it.nrows; row += 8 * gridDim.x) {
@@ -341,17 +360,17 @@ __global__ __launch_bounds__(256) void wide_finish_kernel(int d, const int32_t *
 }
 
 static int moe_ffn_wide_down(const moe_shape *s, const int32_t *offsets, const int32_t *counts, const void *act, const void *w2,
-                      void *y, const int32_t *sched, float *partial, hipStream_t st)
+                      void *y, const uint8_t *mask, float *partial, hipStream_t st)
 {
     const int d = s->d, I = s->I, N = s->N, R = s->T * s->k;
     const int n_nt = (d + WIDE_TN - 1) / WIDE_TN;
     const long max_items = ((long)R / WIDE_TM + (N < R ? N : R)) * n_nt;
     const long blocks = max_items + WIDE_MAX_PIECES;          // whole items and pieces
-    hipLaunchKernelGGL(ffn_wide_kernel, dim3((unsigned)blocks), dim3(WIDE_THREADS), 0, st, d, I, (const uint16_t *)act, offsets, counts,
-                       (const uint16_t *)w2, sched, (uint16_t *)y, partial);
+    hipLaunchKernelGGL(ffn_wide_kernel, dim3((unsigned)blocks), dim3(WIDE_THREADS), 0, st, d, I, N, (const uint16_t *)act, offsets, counts,
+                       (const uint16_t *)w2, mask, (uint16_t *)y, partial);
     MOE_CHECK_LAUNCH();
     const long cut = max_items < WIDE_MAX_PIECES / 2 ? max_items : WIDE_MAX_PIECES / 2;      // an item that is cut has two pieces or more
-    hipLaunchKernelGGL(wide_finish_kernel, dim3(4, (unsigned)cut), dim3(256), 0, st, d, offsets, counts, sched, partial, (uint16_t *)y);
+    hipLaunchKernelGGL(wide_finish_kernel, dim3(4, (unsigned)cut), dim3(256), 0, st, d, I / 32, N, offsets, counts, mask, partial, (uint16_t *)y);
     MOE_CHECK_LAUNCH();
     return MOE_OK;
 }

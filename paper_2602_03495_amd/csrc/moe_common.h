@@ -144,6 +144,64 @@ __device__ __forceinline__ bool moe_working_item(int N, const int32_t *__restric
     return moe_item_of(act_lo, act_hi, per_expert, pid, e, local);
 }
 
+// ---- token tiles of the experts that have rows and are masked on, derived by every wave ---------------------
+// Lane l holds the rows of experts l and l + 64 (0: masked off), the tiles they make at the launch's tile height and their
+// places in the expert-major tile list (a prefix sum on the DPP crossbar).  A table written by a kernel ahead of the
+// launch cost that kernel (4.7-6.5 us per FFN call, T > 128) and two dependent reads per block; this costs a block one read
+// and about 60 instructions.  All 64 lanes must call these.
+struct moe_rows {
+    int c0, c1;
+};
+struct moe_tiles {
+    int n0, n1, first0, first1, total;
+};
+
+__device__ __forceinline__ moe_rows moe_masked_rows(int N, const int32_t *__restrict__ counts, const uint8_t *__restrict__ mask)
+{
+    const int l = threadIdx.x & 63;
+    moe_rows c = {0, 0};
+    if (l < N && (mask == nullptr || mask[l] != 0)) c.c0 = max(counts[l], 0);
+    if (l + 64 < N && (mask == nullptr || mask[l + 64] != 0)) c.c1 = max(counts[l + 64], 0);
+    return c;
+}
+
+// sum over the wave of v, uniform, and the sum over lanes 0 .. l (inclusive) in v
+__device__ __forceinline__ int wave_scan_int_dpp(int &v)
+{
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);      // lanes 1, 2, 4, 8 below, within rows of 16
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+    const int r0 = __builtin_amdgcn_readlane(v, 15), r1 = r0 + __builtin_amdgcn_readlane(v, 31);
+    const int r2 = r1 + __builtin_amdgcn_readlane(v, 47), r3 = r2 + __builtin_amdgcn_readlane(v, 63);
+    const int row = (threadIdx.x & 63) >> 4;
+    v += row == 0 ? 0 : row == 1 ? r0 : row == 2 ? r1 : r2;
+    return r3;
+}
+__device__ __forceinline__ int wave_sum_int_dpp(int v) { return wave_scan_int_dpp(v); }
+
+// n0, n1: tiles of this lane's experts
+__device__ __forceinline__ moe_tiles moe_rank_tiles(int n0, int n1)
+{
+    moe_tiles t = {n0, n1, n0, n1, 0};
+    const int lo = wave_scan_int_dpp(t.first0);
+    t.total = lo + wave_scan_int_dpp(t.first1);
+    t.first0 -= n0;
+    t.first1 += lo - n1;
+    return t;
+}
+
+// tile i of the list (i < total): expert, its first tile, its tiles (all uniform)
+__device__ __forceinline__ void moe_find_tile(const moe_tiles &t, int i, int &e, int &first, int &n)
+{
+    const unsigned long long in_lo = __ballot(i >= t.first0 && i < t.first0 + t.n0);
+    const unsigned long long in_hi = __ballot(i >= t.first1 && i < t.first1 + t.n1);
+    const int l = __ffsll((unsigned long long)(in_lo != 0ull ? in_lo : in_hi)) - 1;
+    e = in_lo != 0ull ? l : l + 64;
+    first = in_lo != 0ull ? __builtin_amdgcn_readlane(t.first0, l) : __builtin_amdgcn_readlane(t.first1, l);
+    n = in_lo != 0ull ? __builtin_amdgcn_readlane(t.n0, l) : __builtin_amdgcn_readlane(t.n1, l);
+}
+
 // K splits of the tiled down projection, decided on the device from the number of tile items that have work.  The
 // cost of a launch is taken as (rounds of 256 compute units) x (item time, 1/nsp of an unsplit item); starting from no
 // split, the next power of two up to nsp_max is taken whenever it lowers that cost by 15 % or more.  224 items stay
@@ -174,7 +232,6 @@ static inline size_t moe_align256(size_t x) { return (x + 255) & ~(size_t)255; }
 struct moe_ws_layout {
     size_t act;        // [T*k, I] bf16 inner activations
     size_t partial;    // [nsplit, T*k, d] fp32 split-K partial sums of the down projection (skinny path, or the tiled path's K splits)
-    size_t sched;      // tile schedule of the tiled path
     size_t route;      // routing scratch: folded bias [N], idx [T*k], w [T*k] (prediction), 2 x logits [max(T,16), N] (gate product and selection in separate launches)
     size_t total;
 };
@@ -220,12 +277,6 @@ static inline bool moe_wide_down(const moe_shape *s)
     return s->T > 128 && s->I >= 8192 && (size_t)s->T * s->k * s->I * 2 >= ((size_t)48 << 20) && (size_t)s->d * s->I * 2 < ((size_t)1 << 32);
 }
 
-// one tile table of the tiled path: int32 hdr[4] + one int4 per token tile, sized for the smallest tile height
-static inline size_t moe_sched_table_bytes(const moe_shape *s)
-{
-    return moe_align256(((size_t)s->T * s->k / MOE_TILE_M_MIN + MOE_MAX_EXPERTS + 8) * 16);
-}
-
 // one [max(T, 16), N] fp32 block of gate logits (the gate product and the selection are separate launches when the
 // gate matrix has many rows)
 static inline size_t moe_logits_scratch_bytes(const moe_shape *s)
@@ -247,8 +298,6 @@ static inline moe_ws_layout moe_ws(const moe_shape *s)
     if (nsp > 1 && (size_t)nsp * R * s->d * 4 > part) part = (size_t)nsp * R * s->d * 4;
     if (moe_wide_down(s)) part = (size_t)WIDE_MAX_PIECES * WIDE_TM * WIDE_TN * 4;
     off += moe_align256(part);
-    L.sched = off;
-    off += 2 * moe_sched_table_bytes(s);              // one table for the up projection, one for the down projection
     L.route = off;
     off += moe_align256(MOE_MAX_EXPERTS * 4) + 2 * moe_align256(R * 4) + 2 * moe_logits_scratch_bytes(s);
     L.total = off;
