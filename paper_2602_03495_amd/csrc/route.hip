@@ -222,20 +222,69 @@ struct gate_job {
     int32_t *counts;           // non-null: single-block launch that also does the histogram (and, with perm, scan and permutation)
     int32_t *offsets, *perm, *inv_perm;
     float *fold_out;           // non-null: bias + res_vec . W[e] [N], by the last blockIdx.z of the gate launch; the selection adds it
-    const float *logits_in;    // non-null: skip the gate product, select from these [T,N] logits
-    float *logits_out;         // non-null: only compute the logits of experts 16*NT*blockIdx.y .. and store them [T,N]
+    const float *logits_in;    // select_*_kernel: the [T,N] logits to select from
+    float *logits_out;         // gate_topk_kernel<NT, true>: where the logits go [T,N]
     int32_t *top;              // with counts and without perm: the p largest workloads
     int p;
     shared_tail x;             // x.S > 0 (with perm, decode-sized launches only): also write the tables with the shared experts appended
 };
 
-template <int NT>   // NT = ceil(N / 16) expert tiles
-__global__ __launch_bounds__(ROUTE_THREADS) void gate_topk_kernel(int T, int d, int N, int k, const uint16_t *__restrict__ h,
-                                                                  gate_job job0, gate_job job1)
+// picked by index, so that a block reads the one it works on: with the choice between two arguments every field of both
+// was held in scalar registers and some spilled
+struct gate_jobs {
+    gate_job job[2];
+};
+
+// The second half of gate_topk_kernel: selection from the logits lg of the block's 16 tokens and, for a decode-sized batch,
+// the tables.  part: scratch of the product, reused.
+template <int NT>
+__device__ __forceinline__ void gate_select(int T, int N, int k, int t0, float (&lg)[ROUTE_TOKENS][NT * 16 + 4],
+                                            float (&part)[ROUTE_WAVES][ROUTE_TOKENS][NT * 16 + 1], const gate_job &J)
 {
-    const gate_job &J = blockIdx.z == 0 ? job0 : job1;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    __syncthreads();
+
+    // ---- softmax + top-k: one wave per token, lane l owns experts l and l+64.  k rounds of: wave-wide max on the
+    // DPP crossbar, then the lowest expert index holding that value (ballot + find-first-set; the lower 64 experts
+    // are asked first), which is the tie rule "equal scores by ascending index".
+    for (int q = 0; q < ROUTE_TOKENS / ROUTE_WAVES; ++q) {
+        const int tt = wave * (ROUTE_TOKENS / ROUTE_WAVES) + q;
+        const int t = t0 + tt;
+        if (t >= T) break;                                   // uniform per wave
+        const float NEG = -__builtin_huge_valf();
+        const float v0 = lane < N ? lg[tt][lane] : NEG;
+        const float v1 = (NT > 4 && lane + 64 < N) ? lg[tt][lane + 64] : NEG;
+        int my_idx;
+        float my_p, sel;
+        select_token(v0, v1, N, k, lane, my_idx, my_p, sel);
+        if (lane < k) {
+            J.topk_idx[(size_t)t * k + lane] = my_idx;
+            J.topk_w[(size_t)t * k + lane] = J.norm_mode == MOE_NORM_RENORM ? my_p / sel : my_p;
+            if (J.counts != nullptr) {                                                                  // keep for the tail below
+                reinterpret_cast<int *>(&part[0][0][0])[tt * k + lane] = my_idx;
+                (&part[1][0][0])[tt * k + lane] = J.norm_mode == MOE_NORM_RENORM ? my_p / sel : my_p;
+            }
+        }
+    }
+    if (J.counts == nullptr) return;
+
+    // ---- decode-sized batch (one block, T <= 16): histogram, scan and stable permutation right here ----------
+    __shared__ unsigned tokmask[MOE_MAX_EXPERTS];
+    __shared__ int off_s[MOE_MAX_EXPERTS];
+    decode_tables(reinterpret_cast<const int *>(&part[0][0][0]), tokmask, off_s, T, N, k, J.counts, J.offsets, J.perm, J.inv_perm, J.top, J.p,
+                  &part[1][0][0], &part[2][0][0], J.x);
+}
+
+// NT: 16-expert tiles of a block.  LOGITS: only the logits of the experts 16 NT blockIdx.y .. are computed and stored; else
+// NT = ceil(N / 16) and the block selects too.  (One kernel for both held the fields of every path in scalar registers and
+// spilled them.)
+template <int NT, bool LOGITS>
+__global__ __launch_bounds__(ROUTE_THREADS) void gate_topk_kernel(int T, int d, int N, int k, const uint16_t *__restrict__ h,
+                                                                  gate_jobs jobs)
+{
+    const gate_job &J = jobs.job[blockIdx.z == 0 ? 0 : 1];
     const uint16_t *__restrict__ gate_w = J.gate_w;
-    if (J.fold_out != nullptr && blockIdx.z == gridDim.z - 1) {
+    if (LOGITS && J.fold_out != nullptr && blockIdx.z == gridDim.z - 1) {
         // the residual folded into the bias, one wave per expert
         const int n_waves = gridDim.x * gridDim.y * ROUTE_WAVES;
         for (int e = (blockIdx.y * gridDim.x + blockIdx.x) * ROUTE_WAVES + (threadIdx.x >> 6); e < N; e += n_waves) {
@@ -244,19 +293,9 @@ __global__ __launch_bounds__(ROUTE_THREADS) void gate_topk_kernel(int T, int d, 
         }
         return;
     }
-    const float *__restrict__ bias = J.fold_out != nullptr ? nullptr : J.bias;
-    const float *__restrict__ res_vec = J.fold_out != nullptr ? nullptr : J.res_vec;
-    const int norm_mode = J.norm_mode;
-    int32_t *__restrict__ topk_idx = J.topk_idx;
-    float *__restrict__ topk_w = J.topk_w;
-    int32_t *__restrict__ counts = J.counts;
-    int32_t *__restrict__ offsets = J.offsets;
-    int32_t *__restrict__ perm = J.perm;
-    int32_t *__restrict__ inv_perm = J.inv_perm;
-    const float *__restrict__ logits_in = J.logits_in;
+    const float *__restrict__ bias = LOGITS && J.fold_out != nullptr ? nullptr : J.bias;
+    const float *__restrict__ res_vec = LOGITS && J.fold_out != nullptr ? nullptr : J.res_vec;
     float *__restrict__ logits_out = J.logits_out;
-    int32_t *__restrict__ top = J.top;
-    const int p = J.p;
 
     constexpr int NP = NT * 16;                       // padded expert count
     __shared__ float part[ROUTE_WAVES][ROUTE_TOKENS][NP + 1];   // per-wave partial logits
@@ -266,7 +305,7 @@ __global__ __launch_bounds__(ROUTE_THREADS) void gate_topk_kernel(int T, int d, 
     const int wave = threadIdx.x >> 6;
     const int t0 = blockIdx.x * ROUTE_TOKENS;
     const int i = lane & 15, g = lane >> 4;
-    const int e_base = logits_out != nullptr ? blockIdx.y * NP : 0;   // first expert of this block
+    const int e_base = LOGITS ? blockIdx.y * NP : 0;   // first expert of this block
 
     // ---- logits: D[token][expert] += A[token][k] * B[k][expert], 32 k per MFMA -------------------
     int tr = t0 + i;
@@ -287,7 +326,7 @@ __global__ __launch_bounds__(ROUTE_THREADS) void gate_topk_kernel(int T, int d, 
     // its steps before the first MFMA so that the block has ~8 x 4 x (1 + NT) loads in flight (eight at a time
     // measured no faster)
     constexpr int BATCH = 4;
-    const int nsteps = logits_in != nullptr ? 0 : d >> 5;
+    const int nsteps = d >> 5;
     int s = wave;
     for (; s + (BATCH - 1) * ROUTE_WAVES < nsteps; s += BATCH * ROUTE_WAVES) {
         u32x4 a[BATCH], b[BATCH][NT];
@@ -314,81 +353,41 @@ __global__ __launch_bounds__(ROUTE_THREADS) void gate_topk_kernel(int T, int d, 
     }
     // bias of the block's experts, with the residual vector folded in: (h + res_vec).W + b = h.W + (res_vec.W + b)
     __shared__ float bias_s[NP];
-    if (logits_in == nullptr) {
-        for (int el = wave; el < NP; el += ROUTE_WAVES) {
-            const int e = e_base + el;
-            float b = 0.f;
-            if (e < N) {
-                b = bias != nullptr ? bias[e] : 0.f;
-                if (res_vec != nullptr) b = residual_dot(d, res_vec, gate_w + (size_t)e * d, lane) + b;
-            }
-            if (lane == 0) bias_s[el] = b;
+    for (int el = wave; el < NP; el += ROUTE_WAVES) {
+        const int e = e_base + el;
+        float b = 0.f;
+        if (e < N) {
+            b = bias != nullptr ? bias[e] : 0.f;
+            if (res_vec != nullptr) b = residual_dot(d, res_vec, gate_w + (size_t)e * d, lane) + b;
         }
+        if (lane == 0) bias_s[el] = b;
     }
-    if (logits_in == nullptr) {
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
+    for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-                part[wave][4 * g + r][nt * 16 + i] = acc[nt][r];
-    }
+        for (int r = 0; r < 4; ++r)
+            part[wave][4 * g + r][nt * 16 + i] = acc[nt][r];
     __syncthreads();
     for (int idx = threadIdx.x; idx < ROUTE_TOKENS * NP; idx += ROUTE_THREADS) {
         int tt = idx / NP, e = idx % NP;
-        float v;
-        if (logits_in != nullptr) {
-            v = (t0 + tt < T && e < N) ? logits_in[(size_t)(t0 + tt) * N + e] : 0.f;
-        } else {
-            v = ((part[0][tt][e] + part[1][tt][e]) + (part[2][tt][e] + part[3][tt][e])) +
-                ((part[4][tt][e] + part[5][tt][e]) + (part[6][tt][e] + part[7][tt][e]));
-            if (e_base + e < N) v += bias_s[e];
-        }
-        if (logits_out != nullptr) {
+        float v = ((part[0][tt][e] + part[1][tt][e]) + (part[2][tt][e] + part[3][tt][e])) +
+                  ((part[4][tt][e] + part[5][tt][e]) + (part[6][tt][e] + part[7][tt][e]));
+        if (e_base + e < N) v += bias_s[e];
+        if constexpr (LOGITS) {
             if (t0 + tt < T && e_base + e < N) logits_out[(size_t)(t0 + tt) * N + e_base + e] = v;
         } else {
             lg[tt][e] = v;
         }
     }
-    if (logits_out != nullptr) return;
-    __syncthreads();
-
-    // ---- softmax + top-k: one wave per token, lane l owns experts l and l+64.  k rounds of: wave-wide max on the
-    // DPP crossbar, then the lowest expert index holding that value (ballot + find-first-set; the lower 64 experts
-    // are asked first), which is the tie rule "equal scores by ascending index".
-    for (int q = 0; q < ROUTE_TOKENS / ROUTE_WAVES; ++q) {
-        const int tt = wave * (ROUTE_TOKENS / ROUTE_WAVES) + q;
-        const int t = t0 + tt;
-        if (t >= T) break;                                   // uniform per wave
-        const float NEG = -__builtin_huge_valf();
-        const float v0 = lane < N ? lg[tt][lane] : NEG;
-        const float v1 = (NT > 4 && lane + 64 < N) ? lg[tt][lane + 64] : NEG;
-        int my_idx;
-        float my_p, sel;
-        select_token(v0, v1, N, k, lane, my_idx, my_p, sel);
-        if (lane < k) {
-            topk_idx[(size_t)t * k + lane] = my_idx;
-            topk_w[(size_t)t * k + lane] = norm_mode == MOE_NORM_RENORM ? my_p / sel : my_p;
-            if (counts != nullptr) {                                                                  // keep for the tail below
-                reinterpret_cast<int *>(&part[0][0][0])[tt * k + lane] = my_idx;
-                (&part[1][0][0])[tt * k + lane] = norm_mode == MOE_NORM_RENORM ? my_p / sel : my_p;
-            }
-        }
-    }
-    if (counts == nullptr) return;
-
-    // ---- decode-sized batch (one block, T <= 16): histogram, scan and stable permutation right here ----------
-    __shared__ unsigned tokmask[MOE_MAX_EXPERTS];
-    __shared__ int off_s[MOE_MAX_EXPERTS];
-    decode_tables(reinterpret_cast<const int *>(&part[0][0][0]), tokmask, off_s, T, N, k, counts, offsets, perm, inv_perm, top, p,
-                  &part[1][0][0], &part[2][0][0], J.x);
+    if constexpr (!LOGITS) gate_select<NT>(T, N, k, t0, lg, part, J);
 }
 
 // Selection for a decode-sized batch from stored logits [T, N] (bias already added): one wavefront per token, then
 // the tables of decode_tables.  One block of 16 waves per job (blockIdx.z).
 #define SELECT_THREADS 1024
-__global__ __launch_bounds__(SELECT_THREADS) void select_decode_kernel(int T, int N, int k, gate_job job0, gate_job job1)
+__global__ __launch_bounds__(SELECT_THREADS) void select_decode_kernel(int T, int N, int k, gate_jobs jobs)
 {
-    const gate_job &J = blockIdx.z == 0 ? job0 : job1;
+    const gate_job &J = jobs.job[blockIdx.z == 0 ? 0 : 1];
     __shared__ int sel_idx[ROUTE_TOKENS * MOE_MAX_TOPK];
     __shared__ float sel_w[ROUTE_TOKENS * MOE_MAX_TOPK], cs[ROUTE_TOKENS];
     __shared__ unsigned tokmask[MOE_MAX_EXPERTS];
@@ -415,9 +414,9 @@ __global__ __launch_bounds__(SELECT_THREADS) void select_decode_kernel(int T, in
 }
 
 // Selection from stored logits [T, N] for any batch size: one wavefront per token, 16 tokens per block.
-__global__ __launch_bounds__(SELECT_THREADS) void select_rows_kernel(int T, int N, int k, gate_job job0, gate_job job1)
+__global__ __launch_bounds__(SELECT_THREADS) void select_rows_kernel(int T, int N, int k, gate_jobs jobs)
 {
-    const gate_job &J = blockIdx.z == 0 ? job0 : job1;
+    const gate_job &J = jobs.job[blockIdx.z == 0 ? 0 : 1];
     const int lane = threadIdx.x & 63;
     const int t = blockIdx.x * (SELECT_THREADS / 64) + (threadIdx.x >> 6);
     if (t >= T) return;
@@ -688,22 +687,22 @@ static int launch_gate_topk(const moe_shape *s, const void *h, hipStream_t st, i
     const int NT = (s->N + 15) / 16;
     dim3 grid((s->T + ROUTE_TOKENS - 1) / ROUTE_TOKENS, 1, n_jobs), block(ROUTE_THREADS);
     const uint16_t *hp = (const uint16_t *)h;
-    gate_job sel[2] = {jobs[0], jobs[n_jobs - 1]};
+    gate_jobs sel = {{jobs[0], jobs[n_jobs - 1]}};
     if (s->T <= ROUTE_TOKENS && NT >= 2 && ws_logits[0] != nullptr) {
         // decode-sized batch with many experts: one block would stream the whole gate matrix alone, so the gate
         // product is spread over one block per 16 experts and the selection runs from the stored logits
-        gate_job lg[2];
+        gate_jobs lg;
         for (int i = 0; i < 2; ++i) {
             const int ji = i < n_jobs ? i : n_jobs - 1;
-            lg[i] = make_job(jobs[ji].gate_w, jobs[ji].bias, jobs[ji].norm_mode, nullptr, nullptr);
-            lg[i].res_vec = jobs[ji].res_vec;
-            lg[i].logits_out = ws_logits[ji];
-            sel[i].logits_in = ws_logits[ji];
+            lg.job[i] = make_job(jobs[ji].gate_w, jobs[ji].bias, jobs[ji].norm_mode, nullptr, nullptr);
+            lg.job[i].res_vec = jobs[ji].res_vec;
+            lg.job[i].logits_out = ws_logits[ji];
+            sel.job[i].logits_in = ws_logits[ji];
         }
-        hipLaunchKernelGGL(gate_topk_kernel<1>, dim3(1, NT, n_jobs), block, 0, st, s->T, s->d, s->N, s->k, hp, lg[0], lg[1]);
+        hipLaunchKernelGGL((gate_topk_kernel<1, true>), dim3(1, NT, n_jobs), block, 0, st, s->T, s->d, s->N, s->k, hp, lg);
         MOE_CHECK_LAUNCH();
         // T <= 16 and k <= 8: at most 128 selections, so the selecting block also builds the tables
-        hipLaunchKernelGGL(select_decode_kernel, dim3(1, 1, n_jobs), dim3(SELECT_THREADS), 0, st, s->T, s->N, s->k, sel[0], sel[1]);
+        hipLaunchKernelGGL(select_decode_kernel, dim3(1, 1, n_jobs), dim3(SELECT_THREADS), 0, st, s->T, s->N, s->k, sel);
         MOE_CHECK_LAUNCH();
         return MOE_OK;
     }
@@ -711,37 +710,37 @@ static int launch_gate_topk(const moe_shape *s, const void *h, hipStream_t st, i
         // many experts: a block that evaluated all of them for its 16 tokens would leave half the chip idle and spend
         // its time on the gate rows, so the gate product runs as (token blocks x 32-expert slices) and the selection,
         // one wavefront per token, reads the stored logits
-        gate_job lg[2];
+        gate_jobs lg;
         for (int i = 0; i < 2; ++i) {
             const int ji = i < n_jobs ? i : n_jobs - 1;
-            lg[i] = make_job(jobs[ji].gate_w, jobs[ji].bias, jobs[ji].norm_mode, nullptr, nullptr);
-            lg[i].res_vec = jobs[ji].res_vec;
-            lg[i].fold_out = jobs[ji].fold_out;
-            lg[i].logits_out = ws_logits[ji];
-            sel[i].logits_in = ws_logits[ji];
+            lg.job[i] = make_job(jobs[ji].gate_w, jobs[ji].bias, jobs[ji].norm_mode, nullptr, nullptr);
+            lg.job[i].res_vec = jobs[ji].res_vec;
+            lg.job[i].fold_out = jobs[ji].fold_out;
+            lg.job[i].logits_out = ws_logits[ji];
+            sel.job[i].logits_in = ws_logits[ji];
         }
-        const int planes = n_jobs + (lg[1].fold_out != nullptr ? 1 : 0);
-        hipLaunchKernelGGL(gate_topk_kernel<2>, dim3(grid.x, (s->N + 31) / 32, planes), block, 0, st, s->T, s->d, s->N, s->k, hp,
-                           lg[0], lg[1]);
+        const int planes = n_jobs + (lg.job[1].fold_out != nullptr ? 1 : 0);
+        hipLaunchKernelGGL((gate_topk_kernel<2, true>), dim3(grid.x, (s->N + 31) / 32, planes), block, 0, st, s->T, s->d, s->N, s->k, hp,
+                           lg);
         MOE_CHECK_LAUNCH();
         hipLaunchKernelGGL(select_rows_kernel, dim3((s->T + SELECT_THREADS / 64 - 1) / (SELECT_THREADS / 64), 1, n_jobs),
-                           dim3(SELECT_THREADS), 0, st, s->T, s->N, s->k, sel[0], sel[1]);
+                           dim3(SELECT_THREADS), 0, st, s->T, s->N, s->k, sel);
         MOE_CHECK_LAUNCH();
         return MOE_OK;
     }
     for (int i = 0; i < 2; ++i) {
-        if (sel[i].fold_out == nullptr) continue;
+        if (sel.job[i].fold_out == nullptr) continue;
         // few experts: the gate kernel selects too and needs the folded bias at its start
         if (i == 1)
-            hipLaunchKernelGGL(fold_residual_kernel, dim3(s->N), dim3(64), 0, st, s->d, sel[i].res_vec, sel[i].gate_w, sel[i].bias,
-                               sel[i].fold_out);
-        sel[i].bias = sel[i].fold_out;
-        sel[i].res_vec = nullptr;
-        sel[i].fold_out = nullptr;
+            hipLaunchKernelGGL(fold_residual_kernel, dim3(s->N), dim3(64), 0, st, s->d, sel.job[i].res_vec, sel.job[i].gate_w, sel.job[i].bias,
+                               sel.job[i].fold_out);
+        sel.job[i].bias = sel.job[i].fold_out;
+        sel.job[i].res_vec = nullptr;
+        sel.job[i].fold_out = nullptr;
     }
 #define GT(n)                                                                                                  \
     case n:                                                                                                    \
-        hipLaunchKernelGGL(gate_topk_kernel<n>, grid, block, 0, st, s->T, s->d, s->N, s->k, hp, sel[0], sel[1]); \
+        hipLaunchKernelGGL((gate_topk_kernel<n, false>), grid, block, 0, st, s->T, s->d, s->N, s->k, hp, sel); \
         break;
     switch (NT) {
         GT(1) GT(2) GT(3) GT(4) GT(5) GT(6) GT(7) GT(8)
