@@ -170,7 +170,7 @@ int moe_expert_ffn(const moe_shape *s, const void *h, const int32_t *perm, const
  * MOE_FFN_STAGE_UP writes the bf16 inner activations silu(W1 x) * (W3 x) of all rows into the workspace,
  * MOE_FFN_STAGE_DOWN multiplies them by W2 into y.  A DOWN call must follow an UP call with the same
  * arguments and workspace on the same stream; one that does not stays within its buffers (every call
- * builds its own tile tables from counts and expert_mask) but multiplies whatever activations the
+ * finds its tiles from counts and expert_mask itself) but multiplies whatever activations the
  * workspace holds.  MOE_FFN_STAGE_ALL is moe_expert_ffn.
  */
 #define MOE_FFN_STAGE_UP   1
@@ -183,15 +183,15 @@ int moe_expert_ffn_stage(const moe_shape *s, const void *h, const int32_t *perm,
 /*
  * moe_expert_ffn for callers that cannot allocate device memory or carry a workspace: code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same kernels and bit-identical results, but
- * the scratch (inner activations, split-K partial sums, tile tables) lives in an array that is part of the library's
+ * the scratch (inner activations, split-K partial sums) lives in an array that is part of the library's
  * code object: moe_static_scratch_bytes() bytes (32 MiB) on every GPU the library runs on, held until the process ends.
  * The call allocates and frees nothing.
  *   - Shapes whose moe_workspace_bytes() exceeds moe_static_scratch_bytes() are rejected with MOE_ETOOLARGE before
  *     anything is launched (all decode shapes fit: T <= 16 needs at most 3.7 MB + 8.4 MB at d = 4096, I = 14336;
  *     prefill shapes fit while T*k*I*2 bytes of activations do).
  *   - All calls on one GPU share that GPU's array: calls that overlap in time on one GPU (different streams or
- *     threads) race; calls in stream order do not.  Nothing in the array has to start at zero: every call builds its
- *     own tile tables and writes each activation and partial sum before reading it.
+ *     threads) race; calls in stream order do not.  Nothing in the array has to start at zero: every call
+ *     writes each activation and partial sum before reading it.
  *   - The array's device address is looked up on the first call on each device (hipGetSymbolAddress, no allocation);
  *     the device that is current at the call must be the one that owns the other buffers.
  */
