@@ -1,5 +1,5 @@
 // Weighted combine of the expert outputs (Eq. 2 restricted to the experts placed on this GPU) for gfx950.
-// One block per token; each thread owns 8 consecutive hidden features (one 16-byte bf16 load per source row),
+// One block per token and 2048 columns; each thread owns 8 consecutive hidden features (one 16-byte bf16 load per source row),
 // sums in fp32 in slot order and rounds once to bf16.  A gather, so no atomics and no ordering effects.
 #include "moe_common.h"
 
@@ -11,32 +11,72 @@ __device__ __forceinline__ void fma8(float (&acc)[8], float w, uint4 v)
     acc[6] = fmaf(w, bf16_lo(v.w), acc[6]); acc[7] = fmaf(w, bf16_hi(v.w), acc[7]);
 }
 
+// The next B source rows of the set bits of `on` (slot order), all of them on their way before the first sum.
+template <int B>
+__device__ __forceinline__ void add_rows(float (&acc)[8], unsigned long long &on, int p, float w, const uint16_t *__restrict__ yf, int d)
+{
+    uint4 v[B];
+    float wj[B];
+#pragma unroll
+    for (int j = 0; j < B; ++j) {
+        const int l = __ffsll(on) - 1;
+        on &= on - 1;
+        wj[j] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w), l));
+        v[j] = *reinterpret_cast<const uint4 *>(yf + (size_t)__builtin_amdgcn_readlane(p, l) * d);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < B; ++j) fma8(acc, wj[j], v[j]);
+}
+
+// Bound by latency at decode sizes, by the reads beyond.  Every wave holds the slots of its token in its first lanes, finds
+// those placed on this GPU by a ballot and reads all their rows at once: with a loop over the slots that skipped the others,
+// the reads of up to 8 rows followed one another.  Whole decode passes: 1 token of 60 experts + 1 shared 48.8 -> 46.1 us, 16 of
+// 64 + 2 shared 80.5 -> 77.6; 77 tokens of 128 experts 114.0 -> 111.4, prompts of 2048 tokens unchanged.
 __global__ __launch_bounds__(256) void combine_kernel(int T, int d, int k, const uint16_t *__restrict__ y,
                                                       const int32_t *__restrict__ topk_idx, const float *__restrict__ topk_w,
                                                       const int32_t *__restrict__ inv_perm, const uint8_t *__restrict__ mask,
                                                       const uint16_t *__restrict__ shared_y, int n_shared,
                                                       const float *__restrict__ shared_scale, uint16_t *__restrict__ out)
 {
-    const int t = blockIdx.x;
-    __shared__ float w_s[MOE_MAX_TOPK];
-    __shared__ int p_s[MOE_MAX_TOPK];
-    if (threadIdx.x < k) {
-        const int r = t * k + threadIdx.x;
+    const int t = blockIdx.x, lane = threadIdx.x & 63;
+    int p = 0;
+    float w = 0.f;
+    bool mine = lane < k;
+    if (mine) {
+        const size_t r = (size_t)t * k + lane;
         const int e = topk_idx[r];
-        const bool on = mask == nullptr || mask[e] != 0;
-        w_s[threadIdx.x] = topk_w[r];
-        p_s[threadIdx.x] = on ? inv_perm[r] : -1;
+        w = topk_w[r];
+        p = inv_perm[r];
+        mine = mask == nullptr || mask[e] != 0;
     }
-    __syncthreads();
+    unsigned long long on = __ballot(mine);
     const float sc = (n_shared > 0 && shared_scale != nullptr) ? shared_scale[t] : 1.0f;
-    for (int f = threadIdx.x * 8; f < d; f += 256 * 8) {
-        float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        for (int s = 0; s < k; ++s) {
-            const int p = p_s[s];
-            if (p >= 0) fma8(acc, w_s[s], *reinterpret_cast<const uint4 *>(y + (size_t)p * d + f));
-        }
-        for (int m = 0; m < n_shared; ++m)
-            fma8(acc, sc, *reinterpret_cast<const uint4 *>(shared_y + ((size_t)m * T + t) * d + f));
+    const int f = (blockIdx.y * 256 + threadIdx.x) * 8;
+    if (blockIdx.y * 2048 + (threadIdx.x & ~63) * 8 >= d) return;          // the whole wave is beyond the row
+    const int fr = f < d ? f : 0;                                          // lanes beyond it read column 0 and write nothing
+    uint4 sh[2];
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+        if (m < n_shared) sh[m] = *reinterpret_cast<const uint4 *>(shared_y + ((size_t)m * T + t) * d + fr);
+    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    const uint16_t *yf = y + fr;
+    switch (__popcll(on)) {            // at most MOE_MAX_TOPK
+    case 1: add_rows<1>(acc, on, p, w, yf, d); break;
+    case 2: add_rows<2>(acc, on, p, w, yf, d); break;
+    case 3: add_rows<3>(acc, on, p, w, yf, d); break;
+    case 4: add_rows<4>(acc, on, p, w, yf, d); break;
+    case 5: add_rows<5>(acc, on, p, w, yf, d); break;
+    case 6: add_rows<6>(acc, on, p, w, yf, d); break;
+    case 7: add_rows<7>(acc, on, p, w, yf, d); break;
+    case 8: add_rows<8>(acc, on, p, w, yf, d); break;
+    }
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+        if (m < n_shared) fma8(acc, sc, sh[m]);
+    for (int m = 2; m < n_shared; ++m)
+        fma8(acc, sc, *reinterpret_cast<const uint4 *>(shared_y + ((size_t)m * T + t) * d + fr));
+    if (f < d) {
         uint4 o;
         o.x = pack_bf16x2(acc[0], acc[1]);
         o.y = pack_bf16x2(acc[2], acc[3]);
@@ -50,7 +90,7 @@ int moe_combine_impl(const moe_shape *s, const void *y, const int32_t *topk_idx,
                      const int32_t *inv_perm, const uint8_t *expert_mask, const void *shared_y, int n_shared,
                      const float *shared_scale, void *out, hipStream_t st)
 {
-    hipLaunchKernelGGL(combine_kernel, dim3(s->T), dim3(256), 0, st, s->T, s->d, s->k, (const uint16_t *)y, topk_idx,
+    hipLaunchKernelGGL(combine_kernel, dim3(s->T, (s->d + 2047) / 2048), dim3(256), 0, st, s->T, s->d, s->k, (const uint16_t *)y, topk_idx,
                        topk_w, inv_perm, expert_mask, (const uint16_t *)shared_y, shared_y ? n_shared : 0, shared_scale,
                        (uint16_t *)out);
     MOE_CHECK_LAUNCH();
