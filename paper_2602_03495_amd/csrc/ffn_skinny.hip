@@ -265,8 +265,10 @@ int moe_ffn_skinny_impl(const moe_shape *s, const void *h, const int32_t *perm, 
     }
     // ---- down projection ---------------------------------------------------------------------------
     // With a short inner size a wave's share of K is a handful of steps and the cross-wave reduction dominates:
-    // the tiled kernel, where every wave owns whole weight rows, is the faster one there.
-    if ((stages & MOE_FFN_STAGE_DOWN) && I <= MOE_SKINNY_DOWN_MIN_I)
+    // the tiled kernel, where every wave owns whole weight rows, is the faster one there, as long as its items of 128
+    // columns reach every compute unit.  Down projection, tiled against this path (d = 2048): I = 1408, 4 experts at work
+    // 12.6 and 7.0 us, 8 13.4 and 10.4, 12 14.5 and 13.5, 14 16.1 and 16.5; I = 768, 8 experts 9.6 and 7.5, 16 12.0 and 12.4.
+    if ((stages & MOE_FFN_STAGE_DOWN) && I <= MOE_SKINNY_DOWN_MIN_I && (long)est_active * ((d + 127) / 128) >= 256)
         return moe_ffn_tiled_impl(s, h, perm, offsets, counts, w1, w3, w2, expert_mask, y, workspace, MOE_FFN_STAGE_DOWN, st);
     if (stages & MOE_FFN_STAGE_DOWN) {
         const int total = I >> 5;

@@ -245,7 +245,7 @@ struct moe_ws_layout {
 #define WIDE_TM 256                 // activation rows per item
 #define WIDE_TN 256                 // output columns per item
 #define WIDE_MAX_PIECES 440         // most pieces of items of a launch (115 MB of fp32 partial sums)
-#define MOE_SKINNY_DOWN_MIN_I 2048  // decode-sized down projections with I up to this run on the tiled kernel
+#define MOE_SKINNY_DOWN_MIN_I 2048  // decode-sized down projections with I up to this run on the tiled kernel where it has 256 items or more
 
 static inline int moe_skinny_nsplit(int K)
 {
