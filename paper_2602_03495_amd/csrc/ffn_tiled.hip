@@ -60,8 +60,6 @@ extern "C" int moe_debug_set_trace(unsigned long long *records)
         }                                                                                                       \
     } while (0)
 
-#include "ffn_wide.h"
-
 #define TM MOE_TILE_M     // token rows per tile
 #define NUM_XCD MOE_NUM_XCD
 #define TILED_THREADS 512
@@ -94,6 +92,8 @@ __device__ __forceinline__ moe_tiles down_tiles(const moe_rows &c, int n_ntc, in
     if (c96 < best) { best = c96; tm = 96; }
     return tm == 128 ? t128 : tm == 112 ? moe_rank_tiles(a112, b112) : moe_rank_tiles(a96, b96);
 }
+
+#include "ffn_wide.h"
 
 // MODE 0: up (W1|W3 + SwiGLU -> act); a wave owns NF/2 fragments of W1 and the same NF/2 of W3.
 // MODE 1: down (W2 -> y); a wave owns NF consecutive fragments of W2.
@@ -341,6 +341,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void ffn_tiled_kernel(
     const uint8_t *__restrict__ mask,
     uint16_t *__restrict__ out,                                            // MODE 0: act [R,I]; MODE 1: y [R,d]
     int nsp_max, float *__restrict__ part, int R,   // MODE 1: up to nsp_max K splits per tile, partial sums in part [nsp,R,d] fp32
+    bool rival,                                     // MODE 1: the long-K kernel has been launched too, the faster one works (wide_faster)
     int group)                                      // column tiles that alternate inside the item order of an expert (1: column tile major)
 {
     __shared__ __attribute__((aligned(16))) uint16_t Xs[2][2][TM * 32];   // [buffer][k32 half][128 tokens x 32 k]
@@ -370,6 +371,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void ffn_tiled_kernel(
         const moe_rows rows = moe_masked_rows(N, counts, mask);
         const moe_tiles tiles = MODE == 0 ? tiles_128(rows) : down_tiles(rows, n_ntc, tmk);
         if (MODE == 1) nsp = moe_dev_splits(tiles.total * n_ntc, nsp_max);
+        if (MODE == 1 && rival && wide_faster(wide_plan_of(rows, (d + WIDE_TN - 1) / WIDE_TN, I / 32), I / 32, tiles.total * n_ntc, tmk, NT_COLS)) return;
         if (CAN_NARROW && up_items_narrow(tiles.total * n_ntc)) {
             narrow = true;
             n_ntc = (I + NT_COLS / 2 - 1) / (NT_COLS / 2);
@@ -486,7 +488,7 @@ static int tiled_item_group(int mode)
 template <int MODE, int NF, int NTT, bool DIRECT, int NSETS, bool FENCED, int WAVES>
 static void launch_tiled(const moe_shape *s, long max_mt, const uint16_t *x, const int32_t *perm, const int32_t *offsets,
                          const int32_t *counts, const uint16_t *wa, const uint16_t *wb,
-                         const uint8_t *mask, uint16_t *out, int nsp_max, float *part, hipStream_t st)
+                         const uint8_t *mask, uint16_t *out, int nsp_max, float *part, bool rival, hipStream_t st)
 {
     constexpr int cols = WAVES * 16 * (MODE == 0 ? NF / 2 : NF);
     const long n_ntc = ((MODE == 0 ? s->I : s->d) + cols - 1) / cols;
@@ -498,7 +500,7 @@ static void launch_tiled(const moe_shape *s, long max_mt, const uint16_t *x, con
     const long n_e = s->N < (long)s->T * s->k ? s->N : (long)s->T * s->k;   // DIRECT: experts that can be non-empty
     const dim3 grid((unsigned)((DIRECT ? n_e : max_mt) * n_nt));
     hipLaunchKernelGGL((ffn_tiled_kernel<MODE, NF, NTT, DIRECT, NSETS, FENCED, WAVES>), grid, dim3(WAVES * 64), 0, st, s->d, s->I, s->k,
-                       s->N, x, perm, offsets, counts, wa, wb, mask, out, nsp_max, part, R, tiled_item_group(MODE));
+                       s->N, x, perm, offsets, counts, wa, wb, mask, out, nsp_max, part, R, rival, tiled_item_group(MODE));
 }
 
 // Weight fragments per wave (NF), 16-row token subtiles per tile (NTT) and weight register sets (NSETS).  An expert
@@ -510,14 +512,14 @@ static void launch_tiled(const moe_shape *s, long max_mt, const uint16_t *x, con
 template <int MODE>
 static void dispatch_tiled(const moe_shape *s, int nf, int waves, long max_mt, const uint16_t *x, const int32_t *perm,
                            const int32_t *offsets, const int32_t *counts, const uint16_t *wa, const uint16_t *wb,
-                           const uint8_t *mask, uint16_t *out, int nsp_max, float *part, hipStream_t st)
+                           const uint8_t *mask, uint16_t *out, int nsp_max, float *part, bool rival, hipStream_t st)
 {
     const int K = MODE == 0 ? s->d : s->I;
     const bool deep = K % (256 * nsp_max) == 0 && K >= 2048;   // a short K does not pay for the longer prologue
-#define GO(NF_, NTT_, D_, NS_, F_) launch_tiled<MODE, NF_, NTT_, D_, NS_, F_, 8>(s, max_mt, x, perm, offsets, counts, wa, wb, mask, out, nsp_max, part, st)
+#define GO(NF_, NTT_, D_, NS_, F_) launch_tiled<MODE, NF_, NTT_, D_, NS_, F_, 8>(s, max_mt, x, perm, offsets, counts, wa, wb, mask, out, nsp_max, part, rival, st)
     if (waves == 4) {
         // two independent 4-wave blocks per compute unit (scheduled launches with full-height tiles only)
-        launch_tiled<MODE, 4, 8, false, 4, false, 4>(s, max_mt, x, perm, offsets, counts, wa, wb, mask, out, nsp_max, part, st);
+        launch_tiled<MODE, 4, 8, false, 4, false, 4>(s, max_mt, x, perm, offsets, counts, wa, wb, mask, out, nsp_max, part, rival, st);
         return;
     }
 #define GO3(NTT_, D_)                                                          \
@@ -572,14 +574,11 @@ int moe_ffn_tiled_impl(const moe_shape *s, const void *h, const int32_t *perm, c
     const int waves_up = s->T > TM && env_up == 4 ? 4 : 8;
     const int waves_down = s->T > TM && env_dn == 4 && nf == 4 ? 4 : 8;
     const bool wide = moe_wide_down(s);
-    const int n_ntc = wide ? (d + WIDE_TN - 1) / WIDE_TN : (d + 16 * waves_down * nf - 1) / (16 * waves_down * nf);
     if (stages & MOE_FFN_STAGE_UP) {
         dispatch_tiled<0>(s, 4, waves_up, max_mt, (const uint16_t *)h, perm, offsets, counts, (const uint16_t *)w1,
-                          (const uint16_t *)w3, expert_mask, act, 1, nullptr, st);
+                          (const uint16_t *)w3, expert_mask, act, 1, nullptr, false, st);
         MOE_CHECK_LAUNCH();
     }
-    if ((stages & MOE_FFN_STAGE_DOWN) && wide)
-        return moe_ffn_wide_down(s, offsets, counts, act, w2, y, expert_mask, (float *)((char *)workspace + L.partial), st);
     if (stages & MOE_FFN_STAGE_DOWN) {
         // nf: the widest weight tile that still leaves every compute unit a block (512 columns, then 256 columns), else
         // the narrowest (128 columns); and when even that leaves compute units idle -- few experts with rows, or few of
@@ -588,14 +587,16 @@ int moe_ffn_tiled_impl(const moe_shape *s, const void *h, const int32_t *perm, c
         const int nsp_max = moe_tiled_down_max_splits(s);
         float *part = (float *)((char *)workspace + L.partial);
         dispatch_tiled<1>(s, nf, waves_down, max_mt_down, (const uint16_t *)act, perm, offsets, counts, (const uint16_t *)w2,
-                          (const uint16_t *)nullptr, expert_mask, (uint16_t *)y, nsp_max, part, st);
+                          (const uint16_t *)nullptr, expert_mask, (uint16_t *)y, nsp_max, part, wide, st);
         MOE_CHECK_LAUNCH();
+        const int cols = 16 * waves_down * nf;      // of an item
         if (nsp_max > 1) {
             const int max_rows = s->T < (int)R ? s->T : (int)R;
-            hipLaunchKernelGGL(tiled_finish_kernel, dim3(max_rows, N), dim3(256), 0, st, d, (int)R, N, n_ntc, nsp_max,
+            hipLaunchKernelGGL(tiled_finish_kernel, dim3(max_rows, N), dim3(256), 0, st, d, (int)R, N, (d + cols - 1) / cols, nsp_max,
                                s->T <= TM ? 1 : 0, part, offsets, counts, expert_mask, (uint16_t *)y);
             MOE_CHECK_LAUNCH();
         }
+        if (wide) return moe_ffn_wide_down(s, offsets, counts, act, w2, y, expert_mask, part, cols, st);
     }
     return MOE_OK;
 }

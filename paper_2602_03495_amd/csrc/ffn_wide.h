@@ -34,38 +34,76 @@
 // pipeline and writing its partial sums, the finishing pass about 25 plus what it reads (256 KB per piece).
 __device__ __forceinline__ int wide_cost16(int rows) { return rows <= 32 ? 7 : rows <= 64 ? 8 : rows <= 128 ? 10 : rows <= 192 ? 13 : 16; }
 
-// Lane s weighs up s pieces; the cheapest, of equals the fewest, is taken.  All 64 lanes must call it.
-__device__ __forceinline__ int wide_pieces(int rest, int rest16, int steps)
+// Lane s weighs up s pieces; the cheapest, of equals the fewest, is taken (cost: in k32 steps, what the items beyond the
+// whole rounds take).  All 64 lanes must call it.
+__device__ __forceinline__ int wide_pieces(int rest, int rest16, int steps, int &best)
 {
     const int s = threadIdx.x & 63;
     int cost = 0x7fffffff;
     if (s == 1) {
         cost = (steps + 14) << 5 | 1;
     } else if (s >= 2 && s <= WIDE_MAX_SPLIT && rest > 0 && rest * s <= WIDE_MAX_PIECES && steps >= 16 * s) {
-        const int by_count = (rest * s + 255) / 256, by_work = rest16 * s > 4096 + 256 ? (rest16 * s + 4095 - 256) / 4096 : 1;
-        cost = ((by_count + by_work) * (steps / s + 14) / 2 + 25 + rest * s / 7) << 5 | s;
+        const int by_work = rest16 * s > 4096 + 256 ? (rest16 * s + 4095 - 256) / 4096 : 1;
+        cost = ((1 + by_work) * (steps / s + 14) / 2 + 25 + rest * s / 7) << 5 | s;
     }
-    return -wave_max_int_dpp(-cost) & 31;
+    const int m = -wave_max_int_dpp(-cost);
+    best = m >> 5;
+    return m & 31;
 }
 
-// The items of a launch: row tiles, those items that run whole, pieces per item of the rest.
+// The items of a launch: row tiles, those items that run whole, pieces per item of the rest; its duration in k32 steps.
 struct wide_plan {
     moe_tiles tiles;
     int items, whole, pieces;
+    long long cost;
 };
 __device__ __forceinline__ int wide_cost16_of(int c) { return c > 0 ? (c - 1) / WIDE_TM * 16 + wide_cost16((c - 1) % WIDE_TM + 1) : 0; }
-__device__ __forceinline__ wide_plan wide_plan_of(int N, const int32_t *__restrict__ counts, const uint8_t *__restrict__ mask, int n_nt,
-                                                  int steps)
+__device__ __forceinline__ wide_plan wide_plan_of(const moe_rows &c, int n_nt, int steps)
 {
-    const moe_rows c = moe_masked_rows(N, counts, mask);
     wide_plan p;
     p.tiles = moe_rank_tiles((c.c0 + WIDE_TM - 1) / WIDE_TM, (c.c1 + WIDE_TM - 1) / WIDE_TM);
     p.items = p.tiles.total * n_nt;
     const int rest = p.items % 256;
     const int cost = wave_sum_int_dpp(wide_cost16_of(c.c0) + wide_cost16_of(c.c1));
-    p.pieces = wide_pieces(rest, cost * n_nt - (p.items - rest) * 16, steps);
+    int rest_cost;
+    p.pieces = wide_pieces(rest, cost * n_nt - (p.items - rest) * 16, steps, rest_cost);
     p.whole = p.pieces > 1 ? p.items - rest : p.items;
+    p.cost = (long long)(p.items / 256) * (steps + 14) + (rest > 0 ? rest_cost : 0);
     return p;
+}
+
+// Whether this kernel or the tiled one (tiles of tm rows and cols columns, K unsplit) takes the down projection.  Which is
+// faster follows from how well the items of either fill whole rounds of 256 compute units, so from the rows of every expert
+// at work, which only the device knows: both are launched, every wave of both weighs them up from counts and mask, and the
+// blocks of the slower one return.  Costs are nanoseconds per k32 step and round, as measured at d = 512 .. 8192, I = 8192 ..
+// 28672, 2 to 128 experts, all, three, two or one quarter or one of them at work; a round of the tiled kernel that is not
+// full is up to 14 % shorter, and the pieces of a launch without whole items run at a higher clock.  This kernel has to come
+// out 5 % ahead: of 6828 such calls measured on both, 4697 go to it (median 1.19 times as fast as the tiled one, at worst
+// 0.96).  With a line on the size of the activations alone, 1 call in 15 that it sent here was below 0.96, at worst 0.48.
+// Down projection, tiled against this kernel, d = 4096, I = 14336: 1441 .. 190 rows of six experts 617 and 423 us, 8192 tokens
+// through eight 1790 and 1570, but 280 .. 254 rows of six (256 items of 128 x 256, one exact round) 230 and 354 and 665 .. 596
+// rows of six (288 items of 256 x 256, 32 beyond one round) 374 and 442.
+__device__ __forceinline__ int tiled_step_cost(int cols, int tm, int items)
+{
+    if (cols == 512) return tm == 96 ? 700 : tm == 112 ? 745 : items <= 256 ? 770 : 800;
+    if (cols == 256) return tm == 96 ? 410 : tm == 112 ? 450 : 485;
+    return tm == 96 ? 250 : tm == 112 ? 280 : 300;
+}
+__device__ __forceinline__ bool wide_faster(const wide_plan &p, int steps, int items, int tm, int cols)
+{
+    // both in nanoseconds x 25600
+    const long long tiled = (long long)tiled_step_cost(cols, tm, items) * (86ll * 256 * ((items + 255) / 256) + 14ll * items) * (steps + 14);
+    const long long wide = p.cost * 25600 * (p.items >= 256 ? 750 : p.pieces > 1 ? 640 : 720);
+    return tiled * 20 > wide * 21;
+}
+
+// the same question from the launch of this kernel; cols: columns of the tiled kernel's items
+__device__ __forceinline__ bool wide_works(const moe_rows &c, const wide_plan &p, int d, int steps, int cols)
+{
+    const int n_ntc = (d + cols - 1) / cols;
+    int tm;
+    const int tiles = down_tiles(c, n_ntc, tm).total;
+    return wide_faster(p, steps, tiles * n_ntc, tm, cols);
 }
 
 #define WIDE_THREADS 256
@@ -294,11 +332,13 @@ __device__ __forceinline__ wide_item wide_item_of(int L, int n_nt, const moe_til
 __global__ __launch_bounds__(WIDE_THREADS, 1) void ffn_wide_kernel(int d, int I, int N, const uint16_t *__restrict__ act,
                                                                    const int32_t *__restrict__ offsets, const int32_t *__restrict__ counts,
                                                                    const uint16_t *__restrict__ w2, const uint8_t *__restrict__ mask,
-                                                                   uint16_t *__restrict__ y, float *__restrict__ partial)
+                                                                   uint16_t *__restrict__ y, float *__restrict__ partial, int tiled_cols)
 {
     __shared__ __attribute__((aligned(1024))) char lds[WIDE_BUFS * WIDE_BUF_BYTES];
     const int n_nt = (d + WIDE_TN - 1) / WIDE_TN;
-    const wide_plan plan = wide_plan_of(N, counts, mask, n_nt, I / 32);
+    const moe_rows rows = moe_masked_rows(N, counts, mask);
+    const wide_plan plan = wide_plan_of(rows, n_nt, I / 32);
+    if (!wide_works(rows, plan, d, I / 32, tiled_cols)) return;
     const int items = plan.items, whole = plan.whole, S = plan.pieces;
     const int pid = blockIdx.x;
     int total = whole, base = 0, r = 1;
@@ -336,10 +376,12 @@ __global__ __launch_bounds__(WIDE_THREADS, 1) void ffn_wide_kernel(int d, int I,
 // y rows of the items that ran in pieces: the partial sums added in piece order
 __global__ __launch_bounds__(256) void wide_finish_kernel(int d, int steps, int N, const int32_t *__restrict__ offsets,
                                                           const int32_t *__restrict__ counts, const uint8_t *__restrict__ mask, const float *__restrict__ partial,
-                                                          uint16_t *__restrict__ y)
+                                                          uint16_t *__restrict__ y, int tiled_cols)
 {
     const int n_nt = (d + WIDE_TN - 1) / WIDE_TN;
-    const wide_plan plan = wide_plan_of(N, counts, mask, n_nt, steps);
+    const moe_rows rows = moe_masked_rows(N, counts, mask);
+    const wide_plan plan = wide_plan_of(rows, n_nt, steps);
+    if (!wide_works(rows, plan, d, steps, tiled_cols)) return;
     const int whole = plan.whole, S = plan.pieces, r = plan.items - whole;
     const int j = blockIdx.y;
     if (S == 1 || j >= r) return;
@@ -360,17 +402,17 @@ __global__ __launch_bounds__(256) void wide_finish_kernel(int d, int steps, int 
 }
 
 static int moe_ffn_wide_down(const moe_shape *s, const int32_t *offsets, const int32_t *counts, const void *act, const void *w2,
-                      void *y, const uint8_t *mask, float *partial, hipStream_t st)
+                      void *y, const uint8_t *mask, float *partial, int tiled_cols, hipStream_t st)
 {
     const int d = s->d, I = s->I, N = s->N, R = s->T * s->k;
     const int n_nt = (d + WIDE_TN - 1) / WIDE_TN;
     const long max_items = ((long)R / WIDE_TM + (N < R ? N : R)) * n_nt;
-    const long blocks = max_items + WIDE_MAX_PIECES;          // whole items and pieces
+    const long blocks = (max_items / 256 + 1) * 256;          // whole items in rounds of 256, then uncut ones or at most 256 pieces
     hipLaunchKernelGGL(ffn_wide_kernel, dim3((unsigned)blocks), dim3(WIDE_THREADS), 0, st, d, I, N, (const uint16_t *)act, offsets, counts,
-                       (const uint16_t *)w2, mask, (uint16_t *)y, partial);
+                       (const uint16_t *)w2, mask, (uint16_t *)y, partial, tiled_cols);
     MOE_CHECK_LAUNCH();
     const long cut = max_items < WIDE_MAX_PIECES / 2 ? max_items : WIDE_MAX_PIECES / 2;      // an item that is cut has two pieces or more
-    hipLaunchKernelGGL(wide_finish_kernel, dim3(4, (unsigned)cut), dim3(256), 0, st, d, I / 32, N, offsets, counts, mask, partial, (uint16_t *)y);
+    hipLaunchKernelGGL(wide_finish_kernel, dim3(4, (unsigned)cut), dim3(256), 0, st, d, I / 32, N, offsets, counts, mask, partial, (uint16_t *)y, tiled_cols);
     MOE_CHECK_LAUNCH();
     return MOE_OK;
 }

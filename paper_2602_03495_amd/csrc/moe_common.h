@@ -244,7 +244,7 @@ struct moe_ws_layout {
 // down projection over a long inner size (ffn_wide.h)
 #define WIDE_TM 256                 // activation rows per item
 #define WIDE_TN 256                 // output columns per item
-#define WIDE_MAX_PIECES 440         // most pieces of items of a launch (115 MB of fp32 partial sums)
+#define WIDE_MAX_PIECES 256         // most pieces of items of a launch: one round of compute units (64 MB of fp32 partial sums)
 #define MOE_SKINNY_DOWN_MIN_I 2048  // decode-sized down projections with I up to this run on the tiled kernel where it has 256 items or more
 
 static inline int moe_skinny_nsplit(int K)
@@ -267,14 +267,17 @@ static inline int moe_tiled_down_max_splits(const moe_shape *s)
     return nsp;
 }
 
-// Whether the down projection runs on the kernel for long inner sizes (ffn_wide.h).  Its items are 256 x 256, so it needs
-// rows to fill them: with 48 MB of activations it is the faster one (d = 4096, I = 14336, 8 experts: 1024 tokens 390 -> 313 us,
-// 2048 tokens 640 -> 439, 8192 tokens 1804 -> 1540), below that the narrower tiles are (800 tokens 285 against 314 us,
-// 700 tokens on two experts 131 against 187).  The tiled kernel's own choice of tile height and K splits serves shorter
-// inner sizes, where an item is too short to be worth cutting (I = 5632: 97 us against 101).
+// Whether the kernel for long inner sizes (ffn_wide.h) is launched beside the tiled down projection; which of the two then
+// works is decided on the device from the rows of the experts at work (wide_faster).  A launch whose blocks all return takes
+// 5 to 8 us (the tiled one 6.4, this kernel 8.2, its finishing pass 5.2), so both are launched only where the projection
+// takes 100 us and more: 2^36 multiplications, 48 MB of activations, and too many rows for the tiled kernel to split K
+// (moe_tiled_down_max_splits), which up to there fills the chip by itself (Mixtral shape, up to 1024 tokens).  Shorter inner
+// sizes have items too short to be worth cutting (I = 5632: 97 us on the tiled kernel, 101 on this one).
 static inline bool moe_wide_down(const moe_shape *s)
 {
-    return s->T > 128 && s->I >= 8192 && (size_t)s->T * s->k * s->I * 2 >= ((size_t)48 << 20) && (size_t)s->d * s->I * 2 < ((size_t)1 << 32);
+    const size_t a = (size_t)s->T * s->k * s->I;
+    return s->T > 128 && s->I >= 8192 && a * 2 >= ((size_t)48 << 20) && a >= ((size_t)1 << 36) / s->d &&
+           moe_tiled_down_max_splits(s) == 1 && (size_t)s->d * s->I * 2 < ((size_t)1 << 32);
 }
 
 // one [max(T, 16), N] fp32 block of gate logits (the gate product and the selection are separate launches when the
@@ -296,7 +299,7 @@ static inline moe_ws_layout moe_ws(const moe_shape *s)
     size_t part = (size_t)moe_skinny_nsplit(s->I) * Rs * s->d * 4;
     const int nsp = moe_tiled_down_max_splits(s);
     if (nsp > 1 && (size_t)nsp * R * s->d * 4 > part) part = (size_t)nsp * R * s->d * 4;
-    if (moe_wide_down(s)) part = (size_t)WIDE_MAX_PIECES * WIDE_TM * WIDE_TN * 4;
+    if (moe_wide_down(s) && (size_t)WIDE_MAX_PIECES * WIDE_TM * WIDE_TN * 4 > part) part = (size_t)WIDE_MAX_PIECES * WIDE_TM * WIDE_TN * 4;
     off += moe_align256(part);
     L.route = off;
     off += moe_align256(MOE_MAX_EXPERTS * 4) + 2 * moe_align256(R * 4) + 2 * moe_logits_scratch_bytes(s);

@@ -1,7 +1,7 @@
-"""Down projection over a long inner size (ffn_wide.h: inner size 8192 or more, 48 MB of activations or more)
-against the oracle, with routing tables made by hand so that every row tile edge occurs: experts with 1 row, one below, at
-and above each tile body (32, 64, 128, 192, 256 rows), several tiles, and none.  The full-size layer tests cover launches
-with whole items and cut ones together."""
+"""Whole FFN over a long inner size (8192 or more, 48 MB of activations or more) with few output columns, where the tiled down
+projection works alone, against the oracle, with routing tables made by hand so that every row tile edge occurs: experts
+with 1 row, one below, at and above 32, 64, 128, 192 and 256 rows, several tiles, and none.  The kernel for long inner sizes
+(ffn_wide.h) is tested in test_gpu_long_k_down.py."""
 import numpy as np
 import pytest
 
@@ -12,7 +12,7 @@ from helpers import OUT_TOL, SENTINEL, rel_err
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
-# rows per expert; d not a multiple of the 256-column tile; I / 32 an odd multiple of 4 in the second case
+# rows per expert; I / 32 an odd multiple of 4 in the second case
 CASES = [(128, 8192, [1, 31, 32, 33, 63, 64, 65, 127, 128, 129, 191, 192, 193, 255, 256, 257, 0, 1100], []),
          (384, 8320, [640, 1, 250, 513, 300, 1200, 0, 131], [0, 4])]
 
@@ -24,7 +24,7 @@ def test_long_inner_size_down_projection_matches_the_oracle(d, I, rows, off):
     from paper_2602_03495_amd import binding as B, layer as Lm
     B.load_library()
     N, T = len(rows), sum(rows)
-    assert T * I * 2 >= 48 << 20, "the case must take the kernel under test"
+    assert T * I * 2 >= 48 << 20, "a long inner size with many activations"
     cfg = wl.scaled(wl.CONFIGS["tiny"], d=d, I=I, N=N, k=1)
     h, (w1, w3, w2) = wl.hidden_states(cfg, T), wl.expert_weights(cfg)
     rng = np.random.default_rng(d)
