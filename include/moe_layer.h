@@ -71,7 +71,11 @@ typedef struct moe_shape {
 
 const char *moe_strerror(int code);
 
-/* Bytes of device workspace that any call with this shape may use.  [host] pointers only. */
+/*
+ * Bytes of device workspace that any call with this shape may use.  [host] pointers only.  That is the inner activations
+ * (T*k*I*2), the partial sums of a down projection whose K is split (64 MiB at most for I up to 65536) and the routing
+ * scratch (8*T*(N+k) and a little).
+ */
 int moe_workspace_bytes(const moe_shape *s, size_t *bytes);
 
 /*

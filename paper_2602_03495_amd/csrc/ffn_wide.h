@@ -25,8 +25,6 @@
 
 #include "moe_common.h"
 
-#define WIDE_MAX_SPLIT 16       // most pieces of one item
-
 // Pieces: whole rounds of 256 items run as they are, the `rest` items beyond them are cut into S pieces each.  An item of
 // few rows is shorter (measured at K = 14336: 166 us with up to 32 rows, 186, 215 and 288 with up to 64, 128 and 192, 360
 // with more), so the whole rounds have room for some of the pieces: rest16 is what exceeds them, in sixteenths of a full
@@ -404,9 +402,8 @@ __global__ __launch_bounds__(256) void wide_finish_kernel(int d, int steps, int 
 static int moe_ffn_wide_down(const moe_shape *s, const int32_t *offsets, const int32_t *counts, const void *act, const void *w2,
                       void *y, const uint8_t *mask, float *partial, int tiled_cols, hipStream_t st)
 {
-    const int d = s->d, I = s->I, N = s->N, R = s->T * s->k;
-    const int n_nt = (d + WIDE_TN - 1) / WIDE_TN;
-    const long max_items = ((long)R / WIDE_TM + (N < R ? N : R)) * n_nt;
+    const int d = s->d, I = s->I, N = s->N;
+    const long max_items = (long)moe_wide_max_items(s);
     const long blocks = (max_items / 256 + 1) * 256;          // whole items in rounds of 256, then uncut ones or at most 256 pieces
     hipLaunchKernelGGL(ffn_wide_kernel, dim3((unsigned)blocks), dim3(WIDE_THREADS), 0, st, d, I, N, (const uint16_t *)act, offsets, counts,
                        (const uint16_t *)w2, mask, (uint16_t *)y, partial, tiled_cols);

@@ -244,6 +244,7 @@ struct moe_ws_layout {
 // down projection over a long inner size (ffn_wide.h)
 #define WIDE_TM 256                 // activation rows per item
 #define WIDE_TN 256                 // output columns per item
+#define WIDE_MAX_SPLIT 16           // most pieces of one item
 #define WIDE_MAX_PIECES 256         // most pieces of items of a launch: one round of compute units (64 MB of fp32 partial sums)
 #define MOE_SKINNY_DOWN_MIN_I 2048  // decode-sized down projections with I up to this run on the tiled kernel where it has 256 items or more
 
@@ -280,6 +281,18 @@ static inline bool moe_wide_down(const moe_shape *s)
            moe_tiled_down_max_splits(s) == 1 && (size_t)s->d * s->I * 2 < ((size_t)1 << 32);
 }
 
+// Most items of that kernel, and most pieces a launch of it can cut: its partial sums.
+static inline size_t moe_wide_max_items(const moe_shape *s)
+{
+    const size_t R = (size_t)s->T * s->k, N = (size_t)s->N;
+    return (R / WIDE_TM + (N < R ? N : R)) * (size_t)((s->d + WIDE_TN - 1) / WIDE_TN);
+}
+static inline size_t moe_wide_max_pieces(const moe_shape *s)
+{
+    const size_t n = WIDE_MAX_SPLIT * moe_wide_max_items(s);
+    return n < WIDE_MAX_PIECES ? n : WIDE_MAX_PIECES;
+}
+
 // one [max(T, 16), N] fp32 block of gate logits (the gate product and the selection are separate launches when the
 // gate matrix has many rows)
 static inline size_t moe_logits_scratch_bytes(const moe_shape *s)
@@ -299,7 +312,8 @@ static inline moe_ws_layout moe_ws(const moe_shape *s)
     size_t part = (size_t)moe_skinny_nsplit(s->I) * Rs * s->d * 4;
     const int nsp = moe_tiled_down_max_splits(s);
     if (nsp > 1 && (size_t)nsp * R * s->d * 4 > part) part = (size_t)nsp * R * s->d * 4;
-    if (moe_wide_down(s) && (size_t)WIDE_MAX_PIECES * WIDE_TM * WIDE_TN * 4 > part) part = (size_t)WIDE_MAX_PIECES * WIDE_TM * WIDE_TN * 4;
+    const size_t pieces = moe_wide_down(s) ? moe_wide_max_pieces(s) * WIDE_TM * WIDE_TN * 4 : 0;
+    if (pieces > part) part = pieces;
     off += moe_align256(part);
     L.route = off;
     off += moe_align256(MOE_MAX_EXPERTS * 4) + 2 * moe_align256(R * 4) + 2 * moe_logits_scratch_bytes(s);

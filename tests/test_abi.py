@@ -173,3 +173,20 @@ def test_route_shared_rejects_bad_arguments_before_launching(lib):
         assert call(2, p, z, *(ok[:i] + (z,) + ok[i + 1:])) == MOE_EINVAL
     assert lib.moe_route_shared(C.byref(s), 2, p, p, z, 5, z, *ok, p, z) == MOE_EINVAL                  # bad norm mode
     assert lib.moe_route_shared(C.byref(s), 2, p, p, z, 1, z, *ok, C.c_void_p(0x1010), z) == MOE_EWORKSPACE
+
+
+@pytest.mark.parametrize("T,d,N,k,I", [(17, 4096, 8, 2, 14336), (878, 4096, 8, 2, 14336), (1024, 4096, 8, 2, 14336), (1025, 4096, 8, 2, 14336),
+                                       (2048, 4096, 8, 2, 14336), (8192, 4096, 8, 2, 14336), (2304, 2048, 32, 4, 8192), (439, 256, 8, 2, 28672),
+                                       (1756, 1024, 128, 1, 14336), (3072, 8192, 128, 8, 8192), (4096, 2048, 60, 4, 1408)])
+def test_workspace_is_the_activations_the_partial_sums_and_the_routing_scratch(lib, T, d, N, k, I):
+    n = C.c_size_t(0)
+    assert lib.moe_workspace_bytes(C.byref(Shape(T, d, N, k, I, 0)), C.byref(n)) == MOE_OK
+    assert T * k * I * 2 <= n.value <= T * k * I * 2 + (64 << 20) + 8 * T * (N + k) + 4096
+
+
+def test_partial_sums_of_a_narrow_layer_are_bounded_by_its_items(lib):
+    # one expert, 128 columns: 5 items of 256 rows, at most 16 pieces each, a piece of 256 x 256 fp32 sums
+    n = C.c_size_t(0)
+    T, d, I = 1024, 128, (1 << 19) + 128                       # an inner size that the tiled kernel cannot split
+    assert lib.moe_workspace_bytes(C.byref(Shape(T, d, 1, 1, I, 0)), C.byref(n)) == MOE_OK
+    assert n.value <= T * I * 2 + 16 * 5 * 256 * 256 * 4 + 8 * T * 2 + 4096
