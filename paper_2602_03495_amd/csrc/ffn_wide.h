@@ -113,12 +113,16 @@ __device__ __forceinline__ bool wide_works(const moe_rows &c, const wide_plan &p
 
 // 16 bytes per lane from buffer rsrc at voff + soff to LDS bytes lds_off + 16 * lane (all but voff wave-uniform).  Inline
 // assembly, because the compiler waits for every LDS-direct load it knows of before the next LDS read; the waits for these
-// are placed by hand (wait_vmem).  One wait state between the write of m0 and its use.
+// are placed by hand (wait_vmem).  One wait state between the write of m0 and its use; m0 is a clobber, so that the compiler
+// does not carry a value of its own in it past this (it warns because it never allocates m0, only sets it where it needs it).
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void load_to_lds(u32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t lds_off)
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds_off), "v"(voff), "s"(rsrc), "s"(soff)
-                 : "memory");
+                 : "memory", "m0");
 }
+#pragma clang diagnostic pop
 
 // at most N vector loads of this wave (register and LDS-direct alike, they complete in order) are still on their way.  Weight
 // loads may be moved by the optimiser (it sinks those before the loop into it and drops those whose result is not used),
