@@ -450,6 +450,10 @@ __global__ __launch_bounds__(256) void tiled_finish_kernel(int d, int R, int N, 
                                                            const int32_t *__restrict__ offsets, const int32_t *__restrict__ counts,
                                                            const uint8_t *__restrict__ mask, uint16_t *__restrict__ y)
 {
+    // first, because most blocks have no row (there is one for every token and expert): ranking the tiles in all 48000 of
+    // 3000 tokens and 16 experts took 25 of 99 us (d = 1024, I = 4096)
+    const int e = blockIdx.y, j = blockIdx.x;
+    if (j >= counts[e] || (mask != nullptr && mask[e] == 0)) return;
     int tiles;
     if (direct) {
         unsigned long long act_lo, act_hi;
@@ -460,8 +464,6 @@ __global__ __launch_bounds__(256) void tiled_finish_kernel(int d, int R, int N, 
     }
     const int nsp = moe_dev_splits(tiles * n_ntc, nsp_max);
     if (nsp == 1) return;
-    const int e = blockIdx.y, j = blockIdx.x;
-    if (j >= counts[e] || (mask != nullptr && mask[e] == 0)) return;
     const size_t p = (size_t)offsets[e] + j;
     for (int f = threadIdx.x * 4; f < d; f += 1024) {
         float4 a = *reinterpret_cast<const float4 *>(partial + p * d + f);
