@@ -31,8 +31,7 @@ __device__ __forceinline__ void add_rows(float (&acc)[8], unsigned long long &on
 
 // Bound by latency at decode sizes, by the reads beyond.  Every wave holds the slots of its token in its first lanes, finds
 // those placed on this GPU by a ballot and reads all their rows at once: with a loop over the slots that skipped the others,
-// the reads of up to 8 rows followed one another.  Whole decode passes: 1 token of 60 experts + 1 shared 48.8 -> 46.1 us, 16 of
-// 64 + 2 shared 80.5 -> 77.6; 77 tokens of 128 experts 114.0 -> 111.4, prompts of 2048 tokens unchanged.
+// the reads of up to 8 rows followed one another (16 tokens, 8 slots, d = 2048: 3.7 us, now 2.5).
 __global__ __launch_bounds__(256) void combine_kernel(int T, int d, int k, const uint16_t *__restrict__ y,
                                                       const int32_t *__restrict__ topk_idx, const float *__restrict__ topk_w,
                                                       const int32_t *__restrict__ inv_perm, const uint8_t *__restrict__ mask,
@@ -40,6 +39,8 @@ __global__ __launch_bounds__(256) void combine_kernel(int T, int d, int k, const
                                                       const float *__restrict__ shared_scale, uint16_t *__restrict__ out)
 {
     const int t = blockIdx.x, lane = threadIdx.x & 63;
+    const int f = (blockIdx.y * 256 + threadIdx.x) * 8;
+    if (blockIdx.y * 2048 + (threadIdx.x & ~63) * 8 >= d) return;          // the whole wave is beyond the row: no table reads either
     int p = 0;
     float w = 0.f;
     bool mine = lane < k;
@@ -52,8 +53,6 @@ __global__ __launch_bounds__(256) void combine_kernel(int T, int d, int k, const
     }
     unsigned long long on = __ballot(mine);
     const float sc = (n_shared > 0 && shared_scale != nullptr) ? shared_scale[t] : 1.0f;
-    const int f = (blockIdx.y * 256 + threadIdx.x) * 8;
-    if (blockIdx.y * 2048 + (threadIdx.x & ~63) * 8 >= d) return;          // the whole wave is beyond the row
     const int fr = f < d ? f : 0;                                          // lanes beyond it read column 0 and write nothing
     uint4 sh[2];
 #pragma unroll
@@ -86,13 +85,58 @@ __global__ __launch_bounds__(256) void combine_kernel(int T, int d, int k, const
     }
 }
 
+// The same sums for many tokens with few slots: a block walks the columns of its token, whose tables it reads once, and holds
+// few rows at a time, so that 8 waves run on a SIMD (combine_kernel, with room for 8 rows per lane, has 5).
+__global__ __launch_bounds__(256) void combine_walk_kernel(int T, int d, int k, const uint16_t *__restrict__ y,
+                                                           const int32_t *__restrict__ topk_idx, const float *__restrict__ topk_w,
+                                                           const int32_t *__restrict__ inv_perm, const uint8_t *__restrict__ mask,
+                                                           const uint16_t *__restrict__ shared_y, int n_shared,
+                                                           const float *__restrict__ shared_scale, uint16_t *__restrict__ out)
+{
+    const int t = blockIdx.x;
+    __shared__ float w_s[MOE_MAX_TOPK];
+    __shared__ int p_s[MOE_MAX_TOPK];
+    if (threadIdx.x < k) {
+        const size_t r = (size_t)t * k + threadIdx.x;
+        const int e = topk_idx[r];
+        const bool on = mask == nullptr || mask[e] != 0;
+        w_s[threadIdx.x] = topk_w[r];
+        p_s[threadIdx.x] = on ? inv_perm[r] : -1;
+    }
+    __syncthreads();
+    const float sc = (n_shared > 0 && shared_scale != nullptr) ? shared_scale[t] : 1.0f;
+    for (int f = threadIdx.x * 8; f < d; f += 256 * 8) {
+        float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        for (int s = 0; s < k; ++s) {
+            const int p = p_s[s];
+            if (p >= 0) fma8(acc, w_s[s], *reinterpret_cast<const uint4 *>(y + (size_t)p * d + f));
+        }
+        for (int m = 0; m < n_shared; ++m)
+            fma8(acc, sc, *reinterpret_cast<const uint4 *>(shared_y + ((size_t)m * T + t) * d + f));
+        uint4 o;
+        o.x = pack_bf16x2(acc[0], acc[1]);
+        o.y = pack_bf16x2(acc[2], acc[3]);
+        o.z = pack_bf16x2(acc[4], acc[5]);
+        o.w = pack_bf16x2(acc[6], acc[7]);
+        *reinterpret_cast<uint4 *>(out + (size_t)t * d + f) = o;
+    }
+}
+
+// combine_kernel's speed over combine_walk_kernel's, no mask / half of the experts on (d = 4096): 2 slots and 200 tokens 1.33 /
+// 1.30, 800 tokens 1.05 / 0.99, 1500 0.95 / 0.88, 12000 0.89 / 0.85; 1 slot and 12000 tokens 1.00 / 0.72.  With 5 slots or
+// more, and up to 1024 columns, it is level or ahead at every size (0.94 to 2.4, and 1.0 to 1.5); with 4, 0.88 to 1.65.
+static bool combine_walks(const moe_shape *s) { return s->k <= 3 && s->d > 1024 && s->T > 1024; }
+
 int moe_combine_impl(const moe_shape *s, const void *y, const int32_t *topk_idx, const float *topk_w,
                      const int32_t *inv_perm, const uint8_t *expert_mask, const void *shared_y, int n_shared,
                      const float *shared_scale, void *out, hipStream_t st)
 {
-    hipLaunchKernelGGL(combine_kernel, dim3(s->T, (s->d + 2047) / 2048), dim3(256), 0, st, s->T, s->d, s->k, (const uint16_t *)y, topk_idx,
-                       topk_w, inv_perm, expert_mask, (const uint16_t *)shared_y, shared_y ? n_shared : 0, shared_scale,
-                       (uint16_t *)out);
+#define COMBINE(kernel, grid)                                                                                                   \
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, s->T, s->d, s->k, (const uint16_t *)y, topk_idx, topk_w, inv_perm, expert_mask, \
+                       (const uint16_t *)shared_y, shared_y ? n_shared : 0, shared_scale, (uint16_t *)out)
+    if (combine_walks(s)) COMBINE(combine_walk_kernel, dim3(s->T));
+    else COMBINE(combine_kernel, dim3(s->T, (s->d + 2047) / 2048));
+#undef COMBINE
     MOE_CHECK_LAUNCH();
     return MOE_OK;
 }
