@@ -1,6 +1,8 @@
 """Token tiles beyond 128 tokens, which every wave of the tiled projections ranks from counts and mask (moe_rank_tiles):
-hand-made tables with experts on both sides of lane 63 / 64, rows at every edge of the three tile heights (96, 112, 128),
-empty and masked experts first, last and in runs, and a single working expert.  Every row against the oracle."""
+hand-made tables with experts on both sides of lane 63 / 64, rows at the edges of 16, 96, 112 and 128, empty and masked experts
+first, last and in runs, and a single working expert, every row against the oracle (these tables are small, and the down
+projection takes tiles of 128 rows for all but one); then tables for which it takes every tile height and number of K
+splits, with the tiles read off the block timeline."""
 import numpy as np
 import pytest
 
@@ -68,4 +70,84 @@ def test_every_row_of_hand_made_tables(name, d):
     ref = oracle.expert_rows(h, topk_idx, w1, w3, w2, mask, tokens=perm[on])[:, 0]
     got = wl.bf16_bits_to_f32(bits[on])
     worst = max(rel_err(got[i], ref[i]) for i in range(len(got)))
+    assert worst <= OUT_TOL, worst
+
+
+def _down_launch(rows, T, d, I):
+    """What the tiled down projection does with these rows (k = 1, all experts on), as the kernels decide it: token-tile
+    height and K splits."""
+    N, tiles = len(rows), lambda h: int(sum(-(-int(r) // h) for r in rows))
+    est = max(-(-T // 128), min(N, T))
+    nf = 4 if est * -(-d // 512) >= 256 else 2 if est * -(-d // 256) >= 256 else 1
+    n_ntc = -(-d // (128 * nf))
+    nsp_max = 1
+    while nsp_max < 8 and (I // 32) % (16 * nsp_max) == 0 and I // 32 // (2 * nsp_max) >= 32 and 2 * nsp_max * T * d * 4 <= 64 << 20:
+        nsp_max *= 2
+    height = 128
+    if tiles(128) * n_ntc >= 256:
+        def cost(h):
+            items = tiles(h) * n_ntc
+            return (2 * -(-items // 256) if items <= 512 else (2 * items + 255) // 256 + 1) * (h + 64)
+        height = min((128, 112, 96), key=cost)                      # of equals the tallest
+    items = tiles(height) * n_ntc
+    nsp, best, finer = 1, -(-items // 256) * 64, 2
+    while finer <= nsp_max:
+        c = -(-items * finer // 256) * (64 // finer)
+        if c * 100 <= best * 85:
+            nsp, best = finer, c
+        finer *= 2
+    return height, nsp
+
+
+# rows per expert, d, I, height and K splits of the down projection
+LAUNCHES = {
+    "128 rows": ([128 * (1 + e % 2) for e in range(128)], 256, 128, 128, 1),
+    "112 rows": ([193 + e % 32 for e in range(128)], 256, 128, 112, 1),
+    "96 rows": ([96 * (1 + e % 2) - e % 5 for e in range(128)], 256, 128, 96, 1),
+    "2 splits": ([129, 0, 31, 100, 1], 384, 2048, 128, 2),
+    "4 splits": ([1, 0, 257, 16, 112], 256, 4096, 128, 4),
+    "8 splits": ([33, 128, 0, 96, 17], 640, 8192, 128, 8),
+    "4 of 8 splits": ([128] * 14 + [1, 100], 512, 8192, 128, 4),
+}
+
+
+@pytest.mark.parametrize("name", LAUNCHES)
+def test_every_tile_height_and_split_of_the_down_projection(name):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2602_03495_amd import binding as B, layer as Lm
+    B.load_library()
+    rows, d, I, height, nsp = LAUNCHES[name]
+    N, T = len(rows), sum(rows)
+    assert _down_launch(rows, T, d, I) == (height, nsp), _down_launch(rows, T, d, I)
+    cfg = wl.scaled(wl.CONFIGS["tiny"], d=d, I=I, N=N, k=1)
+    h, (w1, w3, w2) = wl.hidden_states(cfg, T), wl.expert_weights(cfg)
+    perm = np.random.default_rng(N).permutation(T).astype(np.int32)
+    topk_idx = np.empty((T, 1), np.int32)
+    topk_idx[perm, 0] = np.repeat(np.arange(N), rows)
+    offsets = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+    s = B.shape(T, d, N, 1, I)
+    y = torch.empty((T, d), dtype=torch.bfloat16, device="cuda")
+    y.view(torch.int16).fill_(SENTINEL)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    packed = [B.moe_pack_weights(Lm.to_device_bf16(w)) for w in (w1, w3, w2)]
+    records = torch.zeros(2 * B.TRACE_MAX_BLOCKS * 8, dtype=torch.int64, device="cuda")
+    print(f"down projection launch {name} d={d} I={I} T={T}", flush=True)
+    B.moe_debug_set_trace(records)
+    B.moe_expert_ffn(s, Lm.to_device_bf16(h), dev(perm), dev(offsets), dev(np.array(rows, np.int32)), *packed, None, y, B.alloc_workspace(s))
+    torch.cuda.synchronize()
+    B.moe_debug_set_trace(None)
+    t = records.cpu().numpy().reshape(2, B.TRACE_MAX_BLOCKS, 8)[1]
+    t = t[t[:, 7] == 1]
+    tiles = sorted((e, min(height, n - m)) for e, n in enumerate(rows) for m in range(0, n, height))
+    col = sorted(map(tuple, t[t[:, 6] == 0][:, 4:6].tolist()))
+    assert col == sorted(tiles * nsp), "the launch's tiles of the first columns"
+    # the first and last rows of every expert, and of its tiles
+    edge = {o + j for o, n in zip(offsets, rows) for m in range(0, n, height) for j in (m, min(n, m + height) - 1)}
+    pick = np.array(sorted(edge))[:: max(1, len(edge) // 400)]
+    ref = oracle.expert_rows(h, topk_idx, w1, w3, w2, np.ones(N, np.uint8), tokens=perm[pick].astype(np.int32))[:, 0]
+    bits = Lm.from_device_bf16(y)
+    assert not np.any(np.all(bits == SENTINEL, axis=1)), "a row was not written"
+    got = wl.bf16_bits_to_f32(bits[pick])
+    worst = max(rel_err(got[i], ref[i]) for i in range(len(pick)))
     assert worst <= OUT_TOL, worst
