@@ -18,7 +18,9 @@
  *     before anything is launched; on an error nothing has been enqueued and no device memory has
  *     been touched.  moe_strerror() names a code.
  *   - Same inputs give bit-identical outputs from run to run (no floating-point atomics; the
- *     token permutation is stable).
+ *     token permutation is stable).  The inputs are those of the whole call: how the K range of a projection is
+ *     cut, and which kernel takes it, follow from T, counts and expert_mask, so the same token can round
+ *     differently in another batch, or when other experts are masked off.
  *
  * Shape limits: 1 <= k <= 8, k <= N <= 128, T >= 1, T*k < 2^31, T*d < 2^31, d a multiple of 128 (<= 8192),
  * I a multiple of 128.

@@ -264,10 +264,12 @@ int moe_ffn_skinny_impl(const moe_shape *s, const void *h, const int32_t *perm, 
         MOE_CHECK_LAUNCH();
     }
     // ---- down projection ---------------------------------------------------------------------------
-    // With a short inner size a wave's share of K is a handful of steps and the cross-wave reduction dominates:
-    // the tiled kernel, where every wave owns whole weight rows, is the faster one there, as long as its items of 128
-    // columns reach every compute unit.  Down projection, tiled against this path (d = 2048): I = 1408, 4 experts at work
-    // 12.6 and 7.0 us, 8 13.4 and 10.4, 12 14.5 and 13.5, 14 16.1 and 16.5; I = 768, 8 experts 9.6 and 7.5, 16 12.0 and 12.4.
+    // With a short inner size a wave's share of K is a handful of steps; the tiled kernel, where every wave owns whole weight
+    // rows, takes the projection where its items of 128 columns reach every compute unit.  Below that line this path is ahead on
+    // every shape measured (tiled / this path, us): d = 2048, I = 1408, 1 token: 4 experts at work 12.3 / 6.5, 6 13.4 / 8.4, 8 14.4
+    // / 10.4; d = 2048, I = 768, 8 experts 9.1 / 7.0; d = 512, I = 2048, 18 experts 16.2 / 11.2.  The line is a safe one, not the
+    // crossing: above it this path was level or ahead too (d = 2048, I = 1408, 24 experts 28.5 / 24.8, 31 33.3 / 34.0; d = 2048, I =
+    // 768, 12 experts 10.2 / 10.4, 34 25.3 / 24.0; d = 4096, I = 2048, 8 experts 25.9 / 26.4, 17 59.2 / 47.7).
     if ((stages & MOE_FFN_STAGE_DOWN) && I <= MOE_SKINNY_DOWN_MIN_I && (long)est_active * ((d + 127) / 128) >= 256)
         return moe_ffn_tiled_impl(s, h, perm, offsets, counts, w1, w3, w2, expert_mask, y, workspace, MOE_FFN_STAGE_DOWN, st);
     if (stages & MOE_FFN_STAGE_DOWN) {

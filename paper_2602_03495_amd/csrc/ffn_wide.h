@@ -7,7 +7,8 @@
 //     that fill the chip once more (fp32 partial sums, added in piece order by wide_finish_kernel).  Everything follows
 //     from counts and mask on the device (wide_plan_of).
 //   * 4 waves per block, one per SIMD, 256 accumulator registers per lane: the largest tile the register file holds
-//     asks L2 for 32 KB per k32 step and 4.2 MFLOP.  A wave owns 64 output columns, i.e. 4 weight fragments per step in
+//     asks L2 for 32 KB per k32 step and 4.2 MFLOP (a little more than it holds: the epilogue of the 256-row body, with the
+//     bf16 and the fp32 stores both live, parks 13 accumulators per lane in scratch).  A wave owns 64 output columns, i.e. 4 weight fragments per step in
 //     the packed order of moe_pack_weights, loaded global -> VGPR seven steps ahead.
 //   * Activation rows go straight from global memory to LDS (buffer_load ... lds, no VGPR, no LDS store): four buffers
 //     of k64 stages, issued two and a half stages ahead.  The barrier that hands a stage over sits in the middle of the
@@ -17,9 +18,9 @@
 //     four passes of 16 lanes) hits 16 different 16-byte bank groups in every pass.
 //   * The loads that run past the end of an item's K range are switched off by a buffer descriptor of zero bytes (no
 //     branch, no traffic); all vector loads are bounds-checked by their descriptors.
-// Measured (d = 4096, I = 14336, the down projection alone, against the 128 x 512 tiles of ffn_tiled.hip): 3845 rows of
-// six experts 620 -> 420 us (0.73 -> 1.09 PFLOP/s), 16384 rows of eight 1804 -> 1540 us (1.07 -> 1.25); eight experts of
-// 512 rows, one exact round on both kernels, 377 -> 339 us.  What bounds it: the matrix cores at the clock they get under
+// Measured (d = 4096, I = 14336, the down projection alone, against the tiles of ffn_tiled.hip): 3822 rows of six experts 617 ->
+// 423 us (0.73 -> 1.06 PFLOP/s), 16384 rows of eight 1792 -> 1570 us (1.07 -> 1.23).  It is launched beside the tiled kernel, and
+// which of the two works is decided on the device (wide_faster).  What bounds it: the matrix cores at the clock they get under
 // load -- with every load a cache hit the same launch takes 338 us, with zeros for operands (no power limit) a fifth less.
 #pragma once
 
