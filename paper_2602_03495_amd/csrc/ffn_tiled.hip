@@ -341,7 +341,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void ffn_tiled_kernel(
     const uint8_t *__restrict__ mask,
     uint16_t *__restrict__ out,                                            // MODE 0: act [R,I]; MODE 1: y [R,d]
     int nsp_max, float *__restrict__ part, int R,   // MODE 1: up to nsp_max K splits per tile, partial sums in part [nsp,R,d] fp32
-    bool rival,                                     // MODE 1: the long-K kernel has been launched too, the faster one works (wide_faster)
+    int32_t *__restrict__ rival,                    // MODE 1, non-null: the long-K kernel follows; whether it is the one that works (wide_faster)
     int group)                                      // column tiles that alternate inside the item order of an expert (1: column tile major)
 {
     __shared__ __attribute__((aligned(16))) uint16_t Xs[2][2][TM * 32];   // [buffer][k32 half][128 tokens x 32 k]
@@ -371,7 +371,11 @@ __global__ __launch_bounds__(WAVES * 64, 2) void ffn_tiled_kernel(
         const moe_rows rows = moe_masked_rows(N, counts, mask);
         const moe_tiles tiles = MODE == 0 ? tiles_128(rows) : down_tiles(rows, n_ntc, tmk);
         if (MODE == 1) nsp = moe_dev_splits(tiles.total * n_ntc, nsp_max);
-        if (MODE == 1 && rival && wide_faster(wide_plan_of(rows, (d + WIDE_TN - 1) / WIDE_TN, I / 32), I / 32, tiles.total * n_ntc, tmk, NT_COLS)) return;
+        if (MODE == 1 && rival != nullptr) {
+            const bool wide = wide_faster(wide_plan_of(rows, (d + WIDE_TN - 1) / WIDE_TN, I / 32), I / 32, tiles.total * n_ntc, tmk, NT_COLS);
+            if (blockIdx.x == 0 && threadIdx.x == 0) *rival = wide;
+            if (wide) return;
+        }
         if (CAN_NARROW && up_items_narrow(tiles.total * n_ntc)) {
             narrow = true;
             n_ntc = (I + NT_COLS / 2 - 1) / (NT_COLS / 2);
@@ -490,7 +494,7 @@ static int tiled_item_group(int mode)
 template <int MODE, int NF, int NTT, bool DIRECT, int NSETS, bool FENCED, int WAVES>
 static void launch_tiled(const moe_shape *s, long max_mt, const uint16_t *x, const int32_t *perm, const int32_t *offsets,
                          const int32_t *counts, const uint16_t *wa, const uint16_t *wb,
-                         const uint8_t *mask, uint16_t *out, int nsp_max, float *part, bool rival, hipStream_t st)
+                         const uint8_t *mask, uint16_t *out, int nsp_max, float *part, int32_t *rival, hipStream_t st)
 {
     constexpr int cols = WAVES * 16 * (MODE == 0 ? NF / 2 : NF);
     const long n_ntc = ((MODE == 0 ? s->I : s->d) + cols - 1) / cols;
@@ -514,7 +518,7 @@ static void launch_tiled(const moe_shape *s, long max_mt, const uint16_t *x, con
 template <int MODE>
 static void dispatch_tiled(const moe_shape *s, int nf, int waves, long max_mt, const uint16_t *x, const int32_t *perm,
                            const int32_t *offsets, const int32_t *counts, const uint16_t *wa, const uint16_t *wb,
-                           const uint8_t *mask, uint16_t *out, int nsp_max, float *part, bool rival, hipStream_t st)
+                           const uint8_t *mask, uint16_t *out, int nsp_max, float *part, int32_t *rival, hipStream_t st)
 {
     const int K = MODE == 0 ? s->d : s->I;
     const bool deep = K % (256 * nsp_max) == 0 && K >= 2048;   // a short K does not pay for the longer prologue
@@ -575,10 +579,10 @@ int moe_ffn_tiled_impl(const moe_shape *s, const void *h, const int32_t *perm, c
     static const int env_dn = getenv("MOE_TILED_WAVES_DOWN") ? atoi(getenv("MOE_TILED_WAVES_DOWN")) : 0;
     const int waves_up = s->T > TM && env_up == 4 ? 4 : 8;
     const int waves_down = s->T > TM && env_dn == 4 && nf == 4 ? 4 : 8;
-    const bool wide = moe_wide_down(s);
+    int32_t *const wide = moe_wide_down(s) ? (int32_t *)((char *)workspace + L.choice) : nullptr;
     if (stages & MOE_FFN_STAGE_UP) {
         dispatch_tiled<0>(s, 4, waves_up, max_mt, (const uint16_t *)h, perm, offsets, counts, (const uint16_t *)w1,
-                          (const uint16_t *)w3, expert_mask, act, 1, nullptr, false, st);
+                          (const uint16_t *)w3, expert_mask, act, 1, nullptr, nullptr, st);
         MOE_CHECK_LAUNCH();
     }
     if (stages & MOE_FFN_STAGE_DOWN) {
@@ -598,7 +602,7 @@ int moe_ffn_tiled_impl(const moe_shape *s, const void *h, const int32_t *perm, c
                                s->T <= TM ? 1 : 0, part, offsets, counts, expert_mask, (uint16_t *)y);
             MOE_CHECK_LAUNCH();
         }
-        if (wide) return moe_ffn_wide_down(s, offsets, counts, act, w2, y, expert_mask, part, cols, st);
+        if (wide != nullptr) return moe_ffn_wide_down(s, offsets, counts, act, w2, y, expert_mask, part, wide, st);
     }
     return MOE_OK;
 }

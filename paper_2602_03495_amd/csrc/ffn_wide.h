@@ -7,9 +7,9 @@
 //     that fill the chip once more (fp32 partial sums, added in piece order by wide_finish_kernel).  Everything follows
 //     from counts and mask on the device (wide_plan_of).
 //   * 4 waves per block, one per SIMD, 256 accumulator registers per lane: the largest tile the register file holds
-//     asks L2 for 32 KB per k32 step and 4.2 MFLOP (a little more than it holds: the epilogue of the 256-row body, with the
-//     bf16 and the fp32 stores both live, parks 13 accumulators per lane in scratch).  A wave owns 64 output columns, i.e. 4 weight fragments per step in
-//     the packed order of moe_pack_weights, loaded global -> VGPR seven steps ahead.
+//     asks L2 for 32 KB per k32 step and 4.2 MFLOP (a little more than it holds: the epilogue of the 256-row body, with
+//     the bf16 and the fp32 stores both live, parks 13 accumulators per lane in scratch).  A wave owns 64 output columns,
+//     i.e. 4 weight fragments per step in the packed order of moe_pack_weights, loaded global -> VGPR seven steps ahead.
 //   * Activation rows go straight from global memory to LDS (buffer_load ... lds, no VGPR, no LDS store): four buffers
 //     of k64 stages, issued two and a half stages ahead.  The barrier that hands a stage over sits in the middle of the
 //     stage before it, so that no wave meets it with an empty MFMA queue.
@@ -33,9 +33,8 @@
 // pipeline and writing its partial sums, the finishing pass about 25 plus what it reads (256 KB per piece).
 __device__ __forceinline__ int wide_cost16(int rows) { return rows <= 32 ? 7 : rows <= 64 ? 8 : rows <= 128 ? 10 : rows <= 192 ? 13 : 16; }
 
-// Lane s weighs up s pieces; the cheapest, of equals the fewest, is taken (cost: in k32 steps, what the items beyond the
-// whole rounds take).  All 64 lanes must call it.
-__device__ __forceinline__ int wide_pieces(int rest, int rest16, int steps, int &best)
+// Lane s weighs up s pieces; the cheapest, of equals the fewest, is taken.  All 64 lanes must call it.
+__device__ __forceinline__ int wide_pieces(int rest, int rest16, int steps)
 {
     const int s = threadIdx.x & 63;
     int cost = 0x7fffffff;
@@ -45,16 +44,14 @@ __device__ __forceinline__ int wide_pieces(int rest, int rest16, int steps, int 
         const int by_work = rest16 * s > 4096 + 256 ? (rest16 * s + 4095 - 256) / 4096 : 1;
         cost = ((1 + by_work) * (steps / s + 14) / 2 + 25 + rest * s / 7) << 5 | s;
     }
-    const int m = -wave_max_int_dpp(-cost);
-    best = m >> 5;
-    return m & 31;
+    return -wave_max_int_dpp(-cost) & 31;
 }
 
-// The items of a launch: row tiles, those items that run whole, pieces per item of the rest; its duration in k32 steps.
+// The items of a launch: row tiles, those items that run whole, pieces per item of the rest; work16: the work of all items in
+// sixteenths of a full one.
 struct wide_plan {
     moe_tiles tiles;
-    int items, whole, pieces;
-    long long cost;
+    int items, whole, pieces, work16;
 };
 __device__ __forceinline__ int wide_cost16_of(int c) { return c > 0 ? (c - 1) / WIDE_TM * 16 + wide_cost16((c - 1) % WIDE_TM + 1) : 0; }
 __device__ __forceinline__ wide_plan wide_plan_of(const moe_rows &c, int n_nt, int steps)
@@ -63,46 +60,45 @@ __device__ __forceinline__ wide_plan wide_plan_of(const moe_rows &c, int n_nt, i
     p.tiles = moe_rank_tiles((c.c0 + WIDE_TM - 1) / WIDE_TM, (c.c1 + WIDE_TM - 1) / WIDE_TM);
     p.items = p.tiles.total * n_nt;
     const int rest = p.items % 256;
-    const int cost = wave_sum_int_dpp(wide_cost16_of(c.c0) + wide_cost16_of(c.c1));
-    int rest_cost;
-    p.pieces = wide_pieces(rest, cost * n_nt - (p.items - rest) * 16, steps, rest_cost);
+    p.work16 = wave_sum_int_dpp(wide_cost16_of(c.c0) + wide_cost16_of(c.c1)) * n_nt;
+    p.pieces = wide_pieces(rest, p.work16 - (p.items - rest) * 16, steps);
     p.whole = p.pieces > 1 ? p.items - rest : p.items;
-    p.cost = (long long)(p.items / 256) * (steps + 14) + (rest > 0 ? rest_cost : 0);
     return p;
 }
 
 // Whether this kernel or the tiled one (tiles of tm rows and cols columns, K unsplit) takes the down projection.  Which is
 // faster follows from how well the items of either fill whole rounds of 256 compute units, so from the rows of every expert
-// at work, which only the device knows: both are launched, every wave of both weighs them up from counts and mask, and the
-// blocks of the slower one return.  Costs are nanoseconds per k32 step and round, as measured at d = 512 .. 8192, I = 8192 ..
-// 28672, 2 to 128 experts, all, three, two or one quarter or one of them at work; a round of the tiled kernel that is not
-// full is up to 14 % shorter, and the pieces of a launch without whole items run at a higher clock.  This kernel has to come
-// out 5 % ahead: of 6828 such calls measured on both, 4697 go to it (median 1.19 times as fast as the tiled one, at worst
-// 0.96).  With a line on the size of the activations alone, 1 call in 15 that it sent here was below 0.96, at worst 0.48.
-// Down projection, tiled against this kernel, d = 4096, I = 14336: 1441 .. 190 rows of six experts 617 and 423 us, 8192 tokens
-// through eight 1790 and 1570, but 280 .. 254 rows of six (256 items of 128 x 256, one exact round) 230 and 354 and 665 .. 596
-// rows of six (288 items of 256 x 256, 32 beyond one round) 374 and 442.
-__device__ __forceinline__ int tiled_step_cost(int cols, int tm, int items)
+// at work, which only the device knows: both are launched, every wave of the tiled one weighs them up from counts and mask, its
+// first block writes the answer down, and the blocks of the slower one return.
+// Durations, fitted to 6828 calls (d = 512 .. 8192, I = 8192 .. 28672, 2 to 128 experts, all, three, two or one quarter or one of
+// them at work; 90 % of either within 10 %), in steps + 14 (filling and draining) times microseconds:
+//   this kernel   0.40 a round + 0.40 a round's worth of work (fewer rows, less power, higher clock); with the rest cut
+//                 0.575 a whole round + 0.19 its work + 0.47 the share of K of a piece + the finishing pass
+//   tiled kernel  a a round + b a round's worth of items, a and b by the shape of its items (tiled_step_cost)
+// This one has to come out 1 % ahead: 5380 of the calls go to it, median 1.17 times as fast as the tiled one, 4 of them below 0.96.
+// With a line on the size of the activations alone, 1 call in 15 that it sent here was below 0.96, at worst 0.48.
+// Down projection, tiled against this kernel, d = 4096, I = 14336: 1441 .. 190 rows of six experts 617 and 423 us, 1540 .. 126 rows of
+// six (256 items of 256 x 256) 375 and 331, 8192 tokens through eight 1790 and 1570, but 280 .. 254 rows of six (256 items of 128 x
+// 256, one exact round) 230 and 354 and 665 .. 596 rows of six (288 items of 256 x 256, 32 beyond one round) 374 and 442.
+struct tiled_step_cost {
+    int round, items;      // hundredths of a microsecond per k32 step
+};
+__device__ __forceinline__ tiled_step_cost tiled_step_cost_of(int cols, int tm)
 {
-    if (cols == 512) return tm == 96 ? 700 : tm == 112 ? 745 : items <= 256 ? 770 : 800;
-    if (cols == 256) return tm == 96 ? 410 : tm == 112 ? 450 : 485;
-    return tm == 96 ? 250 : tm == 112 ? 280 : 300;
+    if (cols == 512) return tm == 96 ? tiled_step_cost{55, 14} : tm == 112 ? tiled_step_cost{50, 24} : tiled_step_cost{58, 22};
+    if (cols == 256) return tm == 96 ? tiled_step_cost{26, 16} : tm == 112 ? tiled_step_cost{28, 18} : tiled_step_cost{36, 12};
+    return tm == 96 ? tiled_step_cost{17, 9} : tm == 112 ? tiled_step_cost{19, 10} : tiled_step_cost{22, 9};
 }
 __device__ __forceinline__ bool wide_faster(const wide_plan &p, int steps, int items, int tm, int cols)
 {
-    // both in nanoseconds x 25600
-    const long long tiled = (long long)tiled_step_cost(cols, tm, items) * (86ll * 256 * ((items + 255) / 256) + 14ll * items) * (steps + 14);
-    const long long wide = p.cost * 25600 * (p.items >= 256 ? 750 : p.pieces > 1 ? 640 : 720);
-    return tiled * 20 > wide * 21;
-}
-
-// the same question from the launch of this kernel; cols: columns of the tiled kernel's items
-__device__ __forceinline__ bool wide_works(const moe_rows &c, const wide_plan &p, int d, int steps, int cols)
-{
-    const int n_ntc = (d + cols - 1) / cols;
-    int tm;
-    const int tiles = down_tiles(c, n_ntc, tm).total;
-    return wide_faster(p, steps, tiles * n_ntc, tm, cols);
+    // both in 1 / 51200 us
+    const tiled_step_cost u = tiled_step_cost_of(cols, tm);
+    const long long tiled = 2ll * (u.round * 256ll * ((items + 255) / 256) + (long long)u.items * items) * (steps + 14);
+    const long long round = 256, rest = p.items % 256, work = p.work16 / 16;
+    const long long wide = p.pieces == 1 ? 80 * (round * ((p.items + 255) / 256) + work) * (steps + 14)
+                                         : (115 * round * (p.items / 256) + 38 * work) * (steps + 14) +
+                                               round * (94 * (steps / p.pieces + 14) + 117 * (25 + rest * p.pieces / 7));
+    return tiled * 100 > wide * 101;
 }
 
 #define WIDE_THREADS 256
@@ -335,13 +331,12 @@ __device__ __forceinline__ wide_item wide_item_of(int L, int n_nt, const moe_til
 __global__ __launch_bounds__(WIDE_THREADS, 1) void ffn_wide_kernel(int d, int I, int N, const uint16_t *__restrict__ act,
                                                                    const int32_t *__restrict__ offsets, const int32_t *__restrict__ counts,
                                                                    const uint16_t *__restrict__ w2, const uint8_t *__restrict__ mask,
-                                                                   uint16_t *__restrict__ y, float *__restrict__ partial, int tiled_cols)
+                                                                   uint16_t *__restrict__ y, float *__restrict__ partial, const int32_t *__restrict__ works)
 {
     __shared__ __attribute__((aligned(1024))) char lds[WIDE_BUFS * WIDE_BUF_BYTES];
     const int n_nt = (d + WIDE_TN - 1) / WIDE_TN;
-    const moe_rows rows = moe_masked_rows(N, counts, mask);
-    const wide_plan plan = wide_plan_of(rows, n_nt, I / 32);
-    if (!wide_works(rows, plan, d, I / 32, tiled_cols)) return;
+    if (*works == 0) return;
+    const wide_plan plan = wide_plan_of(moe_masked_rows(N, counts, mask), n_nt, I / 32);
     const int items = plan.items, whole = plan.whole, S = plan.pieces;
     const int pid = blockIdx.x;
     int total = whole, base = 0, r = 1;
@@ -379,12 +374,11 @@ __global__ __launch_bounds__(WIDE_THREADS, 1) void ffn_wide_kernel(int d, int I,
 // y rows of the items that ran in pieces: the partial sums added in piece order
 __global__ __launch_bounds__(256) void wide_finish_kernel(int d, int steps, int N, const int32_t *__restrict__ offsets,
                                                           const int32_t *__restrict__ counts, const uint8_t *__restrict__ mask, const float *__restrict__ partial,
-                                                          uint16_t *__restrict__ y, int tiled_cols)
+                                                          uint16_t *__restrict__ y, const int32_t *__restrict__ works)
 {
     const int n_nt = (d + WIDE_TN - 1) / WIDE_TN;
-    const moe_rows rows = moe_masked_rows(N, counts, mask);
-    const wide_plan plan = wide_plan_of(rows, n_nt, steps);
-    if (!wide_works(rows, plan, d, steps, tiled_cols)) return;
+    if (*works == 0) return;
+    const wide_plan plan = wide_plan_of(moe_masked_rows(N, counts, mask), n_nt, steps);
     const int whole = plan.whole, S = plan.pieces, r = plan.items - whole;
     const int j = blockIdx.y;
     if (S == 1 || j >= r) return;
@@ -404,17 +398,18 @@ __global__ __launch_bounds__(256) void wide_finish_kernel(int d, int steps, int 
     }
 }
 
+// works: whether this kernel or the tiled one, launched before it, takes the projection; written there
 static int moe_ffn_wide_down(const moe_shape *s, const int32_t *offsets, const int32_t *counts, const void *act, const void *w2,
-                      void *y, const uint8_t *mask, float *partial, int tiled_cols, hipStream_t st)
+                      void *y, const uint8_t *mask, float *partial, const int32_t *works, hipStream_t st)
 {
     const int d = s->d, I = s->I, N = s->N;
     const long max_items = (long)moe_wide_max_items(s);
     const long blocks = (max_items / 256 + 1) * 256;          // whole items in rounds of 256, then uncut ones or at most 256 pieces
     hipLaunchKernelGGL(ffn_wide_kernel, dim3((unsigned)blocks), dim3(WIDE_THREADS), 0, st, d, I, N, (const uint16_t *)act, offsets, counts,
-                       (const uint16_t *)w2, mask, (uint16_t *)y, partial, tiled_cols);
+                       (const uint16_t *)w2, mask, (uint16_t *)y, partial, works);
     MOE_CHECK_LAUNCH();
     const long cut = max_items < WIDE_MAX_PIECES / 2 ? max_items : WIDE_MAX_PIECES / 2;      // an item that is cut has two pieces or more
-    hipLaunchKernelGGL(wide_finish_kernel, dim3(4, (unsigned)cut), dim3(256), 0, st, d, I / 32, N, offsets, counts, mask, partial, (uint16_t *)y, tiled_cols);
+    hipLaunchKernelGGL(wide_finish_kernel, dim3(4, (unsigned)cut), dim3(256), 0, st, d, I / 32, N, offsets, counts, mask, partial, (uint16_t *)y, works);
     MOE_CHECK_LAUNCH();
     return MOE_OK;
 }

@@ -232,6 +232,7 @@ static inline size_t moe_align256(size_t x) { return (x + 255) & ~(size_t)255; }
 struct moe_ws_layout {
     size_t act;        // [T*k, I] bf16 inner activations
     size_t partial;    // [nsplit, T*k, d] fp32 split-K partial sums of the down projection (skinny path, or the tiled path's K splits)
+    size_t choice;     // whether the long-K kernel takes the down projection (one word)
     size_t route;      // routing scratch: folded bias [N], idx [T*k], w [T*k] (prediction), 2 x logits [max(T,16), N] (gate product and selection in separate launches)
     size_t total;
 };
@@ -269,9 +270,9 @@ static inline int moe_tiled_down_max_splits(const moe_shape *s)
 }
 
 // Whether the kernel for long inner sizes (ffn_wide.h) is launched beside the tiled down projection; which of the two then
-// works is decided on the device from the rows of the experts at work (wide_faster).  A launch whose blocks all return takes
-// 5 to 8 us (the tiled one 6.4, this kernel 8.2, its finishing pass 5.2), so both are launched only where the projection
-// takes 100 us and more: 2^36 multiplications, 48 MB of activations, and too many rows for the tiled kernel to split K
+// works is decided on the device from the rows of the experts at work (wide_faster).  The launches that only return cost 8 us
+// where this kernel works and 3 to 7 where the tiled one does, so both are launched only where the projection takes 100 us
+// and more: 2^36 multiplications, 48 MB of activations, and too many rows for the tiled kernel to split K
 // (moe_tiled_down_max_splits), which up to there fills the chip by itself (Mixtral shape, up to 1024 tokens).  Shorter inner
 // sizes have items too short to be worth cutting (I = 5632: 97 us on the tiled kernel, 101 on this one).
 static inline bool moe_wide_down(const moe_shape *s)
@@ -315,6 +316,8 @@ static inline moe_ws_layout moe_ws(const moe_shape *s)
     const size_t pieces = moe_wide_down(s) ? moe_wide_max_pieces(s) * WIDE_TM * WIDE_TN * 4 : 0;
     if (pieces > part) part = pieces;
     off += moe_align256(part);
+    L.choice = off;
+    off += 256;
     L.route = off;
     off += moe_align256(MOE_MAX_EXPERTS * 4) + 2 * moe_align256(R * 4) + 2 * moe_logits_scratch_bytes(s);
     L.total = off;

@@ -74,6 +74,7 @@ def down(B, d, I, k, rows, off=(), seed=0):
 # d, I, k, rows, experts off, whether the long-K kernel works; beside each the down projection on the tiled and on that kernel
 CHOICE = [
     (4096, 14336, 2, [1441, 190, 398, 889, 618, 286, 140, 134], [6, 7], True),                   # 617 and 423 us
+    (4096, 14336, 2, [1540, 379, 283, 550, 165, 954, 126, 99], [5, 7], True),                    # 375 and 331
     (4096, 14336, 2, [436, 451, 436, 436, 436, 445, 436, 436], [0, 2, 3, 4, 6, 7], True),        # 196 and 114
     (1024, 11008, 1, [5193, 2428], [], True),                                                    # 227 and 156
     (4096, 14336, 2, [280, 249, 274, 266, 248, 262, 255, 254], [1, 4], False),                   # 230 and 354
