@@ -113,3 +113,54 @@ def test_row_edges_in_whole_and_in_cut_items(binding, d, I, rows, off, whole, cu
     want = [(e, min(256, n - m), c) for e, n in enumerate(rows) if e not in off for c in range((d + 255) // 256) for m in range(0, n, 256)]
     got = sorted(map(tuple, rec.tolist()))
     assert got == sorted(want[:whole] + want[whole:] * pieces)
+
+
+def test_a_replayed_graph_takes_the_kernel_that_its_mask_asks_for(binding):
+    # one captured down stage, replayed with a mask that leaves six experts (the tiled kernel) and one that leaves two (the long-K
+    # kernel): nothing of the choice stays from one replay to the next
+    B = binding
+    d, I, k, rows = 4096, 14336, 2, [280, 249, 274, 266, 248, 262, 255, 254]
+    N, R = len(rows), sum(rows)
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    s = B.shape(R // k, d, N, k, I)
+    ws = B.alloc_workspace(s)
+    first = (-ws.data_ptr()) % 256
+    ws[first:first + 2 * R * I].view(torch.bfloat16).normal_(0.0, 1.0, generator=gen)
+    w2 = torch.empty((N, d, I), dtype=torch.bfloat16, device="cuda")
+    for e in range(N):
+        w2[e].normal_(0.0, I ** -0.5, generator=gen)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    offsets = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+    mask = torch.zeros(N, dtype=torch.uint8, device="cuda")
+    y = torch.empty((R, d), dtype=torch.bfloat16, device="cuda")
+    args = (s, torch.zeros((R // k, d), dtype=torch.bfloat16, device="cuda"), dev(np.arange(R, dtype=np.int32)), dev(offsets),
+            dev(np.array(rows, np.int32)), w2, w2, w2, mask, y, ws, B.STAGE_DOWN)
+    masks = {off: dev(np.array([e not in off for e in range(N)], np.uint8)) for off in ((1, 4), (1, 3, 4, 5, 6, 7), tuple(range(N)))}
+    records = torch.zeros(2 * B.TRACE_MAX_BLOCKS * 8, dtype=torch.int64, device="cuda")
+    want, most_rows = {}, {}
+    for off, m in masks.items():
+        mask.copy_(m)
+        y.view(torch.int16).fill_(SENTINEL)
+        records.zero_()
+        B.moe_debug_set_trace(records)
+        B.moe_expert_ffn_stage(*args)
+        torch.cuda.synchronize()
+        B.moe_debug_set_trace(None)
+        want[off] = y.clone()
+        t = records.view(2, B.TRACE_MAX_BLOCKS, 8)[1]
+        most_rows[off] = int(t[:, 5].max())
+    assert [most_rows[off] > 128 for off in masks] == [False, True, False] and most_rows[tuple(range(N))] == 0
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        B.moe_expert_ffn_stage(*args)
+    torch.cuda.current_stream().wait_stream(side)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        B.moe_expert_ffn_stage(*args)
+    for off in list(masks) * 3 + [(1, 4), (1, 4)]:
+        mask.copy_(masks[off])
+        y.view(torch.int16).fill_(SENTINEL)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y.view(torch.int16), want[off].view(torch.int16)), off
