@@ -324,7 +324,9 @@ __device__ __forceinline__ void tile_body(uint16_t (*Xs)[2][TM * 32], int d, int
 
 // Whether the up projection runs its items at half width: twice as many items, each about 0.6 of the time (measured),
 // so it pays when the rounds the launch needs on 256 compute units do not double: up to 128 items (one round either
-// way), or just above a whole number of rounds (280 items: 2 rounds of wide items against 3 of narrow ones).
+// way), or just above a whole number of rounds (280 items: 2 rounds of wide items against 3 of narrow ones; from 3 rounds
+// on, 5 or 6 of narrow ones are never fewer than 5 thirds of that).
+#define UP_NARROW_MAX_ITEMS (3 * 256)
 __device__ __forceinline__ bool up_items_narrow(int items)
 {
     const int wide = (items + 255) / 256, narrow = (2 * items + 255) / 256;
@@ -501,10 +503,17 @@ static void launch_tiled(const moe_shape *s, long max_mt, const uint16_t *x, con
     const int R = s->T * s->k;
     // blocks for the most items the device-side choice of K splits can produce: with every tile at work it takes the
     // fewest splits that reach 256 items, with fewer tiles at work there are fewer items, so this bound covers both
-    long n_nt = n_ntc * nsp_max;
-    if (MODE == 0 && NF == 4 && WAVES == 8) n_nt = (s->I + cols / 2 - 1) / (cols / 2);   // ... or the half-width items of the up projection
     const long n_e = s->N < (long)s->T * s->k ? s->N : (long)s->T * s->k;   // DIRECT: experts that can be non-empty
-    const dim3 grid((unsigned)((DIRECT ? n_e : max_mt) * n_nt));
+    const long tiles = DIRECT ? n_e : max_mt;
+    long blocks = tiles * n_ntc * nsp_max;
+    if (MODE == 0 && NF == 4 && WAVES == 8) {
+        // ... or the half-width items of the up projection, which run where that takes at most 3 rounds (up_items_narrow).
+        // With a block for every half-width item, whatever their number, the blocks without an item took longer than those
+        // with one on short items (229 tokens over 100 experts, d = 256, I = 6272: 4949 blocks for 1600 items).
+        const long narrow = tiles * ((s->I + cols / 2 - 1) / (cols / 2));
+        blocks = blocks > UP_NARROW_MAX_ITEMS ? blocks : narrow < UP_NARROW_MAX_ITEMS ? narrow : UP_NARROW_MAX_ITEMS;
+    }
+    const dim3 grid((unsigned)blocks);
     hipLaunchKernelGGL((ffn_tiled_kernel<MODE, NF, NTT, DIRECT, NSETS, FENCED, WAVES>), grid, dim3(WAVES * 64), 0, st, s->d, s->I, s->k,
                        s->N, x, perm, offsets, counts, wa, wb, mask, out, nsp_max, part, R, rival, tiled_item_group(MODE));
 }

@@ -158,11 +158,15 @@ struct moe_tiles {
 
 __device__ __forceinline__ moe_rows moe_masked_rows(int N, const int32_t *__restrict__ counts, const uint8_t *__restrict__ mask)
 {
-    const int l = threadIdx.x & 63;
-    moe_rows c = {0, 0};
-    if (l < N && (mask == nullptr || mask[l] != 0)) c.c0 = max(counts[l], 0);
-    if (l + 64 < N && (mask == nullptr || mask[l + 64] != 0)) c.c1 = max(counts[l + 64], 0);
-    return c;
+    // all reads on their way at once: with the count read only where the mask allows it, up to four reads followed one another
+    const int l = threadIdx.x & 63, l0 = min(l, N - 1), l1 = min(l + 64, N - 1);
+    const int c0 = counts[l0], c1 = counts[l1];
+    int m0 = 1, m1 = 1;
+    if (mask != nullptr) {
+        m0 = mask[l0];
+        m1 = mask[l1];
+    }
+    return moe_rows{l < N && m0 != 0 ? max(c0, 0) : 0, l + 64 < N && m1 != 0 ? max(c1, 0) : 0};
 }
 
 // sum over the wave of v, uniform, and the sum over lanes 0 .. l (inclusive) in v

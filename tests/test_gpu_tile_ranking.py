@@ -151,3 +151,43 @@ def test_every_tile_height_and_split_of_the_down_projection(name):
     got = wl.bf16_bits_to_f32(bits[pick])
     worst = max(rel_err(got[i], ref[i]) for i in range(len(pick)))
     assert worst <= OUT_TOL, worst
+
+
+# rows per expert, inner size, blocks of the up projection that have an item: half-width items up to 3 rounds of 256, for which the
+# launch has just enough blocks, and one tile more
+UP_ITEMS = {"768 half-width items": ([257] * 128, 256, 768), "one tile more": ([257] * 127 + [385], 256, 385),
+            "768 half-width items, one tile per expert": ([1] * 128, 768, 768), "704 half-width items": ([130] * 32 + [0] * 8, 1408, 704)}
+
+
+@pytest.mark.parametrize("name", UP_ITEMS)
+def test_every_item_of_the_up_projection_has_a_block(name):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2602_03495_amd import binding as B, layer as Lm
+    B.load_library()
+    rows, I, items = UP_ITEMS[name]
+    N, T, d = len(rows), sum(rows), 128
+    cfg = wl.scaled(wl.CONFIGS["tiny"], d=d, I=I, N=N, k=1)
+    h, (w1, w3, w2) = wl.hidden_states(cfg, T), wl.expert_weights(cfg)
+    perm = np.random.default_rng(N).permutation(T).astype(np.int32)
+    topk_idx = np.empty((T, 1), np.int32)
+    topk_idx[perm, 0] = np.repeat(np.arange(N), rows)
+    offsets = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+    s = B.shape(T, d, N, 1, I)
+    y = torch.empty((T, d), dtype=torch.bfloat16, device="cuda")
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    packed = [B.moe_pack_weights(Lm.to_device_bf16(w)) for w in (w1, w3, w2)]
+    records = torch.zeros(2 * B.TRACE_MAX_BLOCKS * 8, dtype=torch.int64, device="cuda")
+    print(f"up projection items {name} I={I} T={T}", flush=True)
+    B.moe_debug_set_trace(records)
+    B.moe_expert_ffn(s, Lm.to_device_bf16(h), dev(perm), dev(offsets), dev(np.array(rows, np.int32)), *packed, None, y, B.alloc_workspace(s))
+    torch.cuda.synchronize()
+    B.moe_debug_set_trace(None)
+    t = records.cpu().numpy().reshape(2, B.TRACE_MAX_BLOCKS, 8)[0]
+    assert int((t[:, 7] == 1).sum()) == items
+    last = [o + n - 1 for o, n in zip(offsets, rows) if n]                 # the last row of every expert, and some others
+    pick = np.array(sorted(set(last) | set(range(0, T, max(1, T // 200)))))
+    ref = oracle.expert_rows(h, topk_idx, w1, w3, w2, np.ones(N, np.uint8), tokens=perm[pick].astype(np.int32))[:, 0]
+    got = wl.bf16_bits_to_f32(Lm.from_device_bf16(y)[pick])
+    worst = max(rel_err(got[i], ref[i]) for i in range(len(pick)))
+    assert worst <= OUT_TOL, worst
