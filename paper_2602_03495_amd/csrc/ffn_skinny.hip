@@ -269,8 +269,13 @@ int moe_ffn_skinny_impl(const moe_shape *s, const void *h, const int32_t *perm, 
     // every shape measured (tiled / this path, us): d = 2048, I = 1408, 1 token: 4 experts at work 12.3 / 6.5, 6 13.4 / 8.4, 8 14.4
     // / 10.4; d = 2048, I = 768, 8 experts 9.1 / 7.0; d = 512, I = 2048, 18 experts 16.2 / 11.2.  The line is a safe one, not the
     // crossing: above it this path was level or ahead too (d = 2048, I = 1408, 24 experts 28.5 / 24.8, 31 33.3 / 34.0; d = 2048, I =
-    // 768, 12 experts 10.2 / 10.4, 34 25.3 / 24.0; d = 4096, I = 2048, 8 experts 25.9 / 26.4, 17 59.2 / 47.7).
-    if ((stages & MOE_FFN_STAGE_DOWN) && I <= MOE_SKINNY_DOWN_MIN_I && (long)est_active * ((d + 127) / 128) >= 256)
+    // 768, 12 experts 10.2 / 10.4, 34 25.3 / 24.0; d = 4096, I = 2048, 8 experts 25.9 / 26.4, 17 59.2 / 47.7).  At I = 128 a wave has
+    // one K step and the sum over the waves is most of its work: the line is at 160 items (tiled / this path, us, medians of random
+    // calls: 96 to 159 items 3.54 / 3.69, 160 to 199 3.57 / 3.78, 200 to 255 3.60 / 4.06; with few of the experts at work 3.51 /
+    // 3.19, 3.53 / 3.38 and 3.55 / 3.44).  At I = 256 it stays: 160 to 199 items 3.90 / 3.85, 200 to 255 3.95 / 4.15, and 3.86 /
+    // 3.44 and 3.88 / 3.53 with few at work.
+    const long min_items = I <= 128 ? 160 : 256;
+    if ((stages & MOE_FFN_STAGE_DOWN) && I <= MOE_SKINNY_DOWN_MIN_I && (long)est_active * ((d + 127) / 128) >= min_items)
         return moe_ffn_tiled_impl(s, h, perm, offsets, counts, w1, w3, w2, expert_mask, y, workspace, MOE_FFN_STAGE_DOWN, st);
     if (stages & MOE_FFN_STAGE_DOWN) {
         const int total = I >> 5;

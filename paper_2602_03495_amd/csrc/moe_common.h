@@ -251,7 +251,7 @@ struct moe_ws_layout {
 #define WIDE_TN 256                 // output columns per item
 #define WIDE_MAX_SPLIT 16           // most pieces of one item
 #define WIDE_MAX_PIECES 256         // most pieces of items of a launch: one round of compute units (64 MB of fp32 partial sums)
-#define MOE_SKINNY_DOWN_MIN_I 2048  // decode-sized down projections with I up to this run on the tiled kernel where it has 256 items or more
+#define MOE_SKINNY_DOWN_MIN_I 2048  // decode-sized down projections with I up to this run on the tiled kernel where it has enough items
 
 static inline int moe_skinny_nsplit(int K)
 {
