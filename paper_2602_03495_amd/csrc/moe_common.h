@@ -237,7 +237,7 @@ struct moe_ws_layout {
     size_t act;        // [T*k, I] bf16 inner activations
     size_t partial;    // [nsplit, T*k, d] fp32 split-K partial sums of the down projection (skinny path, or the tiled path's K splits)
     size_t choice;     // whether the long-K kernel takes the down projection (one word)
-    size_t route;      // routing scratch: folded bias [N], idx [T*k], w [T*k] (prediction), 2 x logits [max(T,16), N] (gate product and selection in separate launches)
+    size_t route;      // routing scratch: sigmoid gates of the shared experts [T <= 16], idx [T*k], w [T*k] (prediction), 2 x logits [max(T,16), N] (gate product and selection in separate launches)
     size_t total;
 };
 

@@ -1,8 +1,8 @@
 // Gate, top-k, workload histogram, token permutation and next-layer workload prediction for gfx950.
 //
 // moe_route (Eq. 1 and the expert workload of Section "Greedy Assignment Strategy"):
-//   gate_topk_kernel      16 tokens per block; logits by bf16 MFMA 16x16x32 straight from global memory
-//                         (K split over the 8 waves, reduced through LDS), then softmax and top-k per token
+//   gate_topk_kernel      16 tokens per block, all experts; logits by bf16 MFMA 16x16x32 straight from global memory
+//                         (K split over the 16 waves, reduced through LDS), then softmax and top-k per token
 //                         inside one wavefront: k rounds of a DPP max reduction + ballot.
 //   hist_scan_perm_kernel one block per expert: ballot counts of the selections below / equal to the expert
 //                         (= its offset and workload), then a ballot-based stable compaction of its rows.
@@ -12,38 +12,17 @@
 //   (one wavefront per token) selects from the stored logits.
 // moe_predict_workload (Section "Residual-Based Prefetching"):
 //   the same kernels on the next layer's gate with bias'[e] = bias[e] + res_vec . W[e], so that
-//   (h + res_vec) . W + bias = h . W + bias'.  Decode-sized: the fold happens inside the gate kernel and the
-//   selecting block emits the workloads and their p largest.  Larger: the fold runs in blocks of its own beside the gate
-//   product and the selection adds it (few experts: fold_residual_kernel first); then hist_top_block.
+//   (h + res_vec) . W + bias = h . W + bias'.  res_vec runs through the gate product as three more token rows (its exact split
+//   into three bf16 numbers), so the fold costs no pass over the gate matrix.  Decode-sized: the selecting block emits the
+//   workloads and their p largest.  Larger: hist_top_block.
 // moe_route_predict: both gates as two "jobs" of the same launches (blockIdx.z); beyond decode sizes the histogram of the
 // prediction is one more block of hist_scan_perm_kernel.
 #include "moe_common.h"
 
 #define ROUTE_TOKENS 16      // tokens per block of gate_topk_kernel
-#define ROUTE_THREADS 512
-#define ROUTE_WAVES 8
-
-// res_vec . W[e,:] over one wavefront: lane l takes the 8-element groups at 8l + 512m (d is a multiple of 128, so a
-// group is whole or absent), each group accumulated in element order onto the lane's sum; the 64 partial sums are
-// added by butterfly.  One definition for every caller, so the folded bias does not depend on the batch size.
-__device__ __forceinline__ float residual_dot(int d, const float *__restrict__ res_vec, const uint16_t *__restrict__ w, int lane)
-{
-    float acc = 0.f;
-    for (int j = lane * 8; j < d; j += 512) {
-        const u32x4 pr = *reinterpret_cast<const u32x4 *>(w + j);
-        const float4 r0 = *reinterpret_cast<const float4 *>(res_vec + j);
-        const float4 r1 = *reinterpret_cast<const float4 *>(res_vec + j + 4);
-        acc = fmaf(r0.x, bf16_lo(pr[0]), acc);
-        acc = fmaf(r0.y, bf16_hi(pr[0]), acc);
-        acc = fmaf(r0.z, bf16_lo(pr[1]), acc);
-        acc = fmaf(r0.w, bf16_hi(pr[1]), acc);
-        acc = fmaf(r1.x, bf16_lo(pr[2]), acc);
-        acc = fmaf(r1.y, bf16_hi(pr[2]), acc);
-        acc = fmaf(r1.z, bf16_lo(pr[3]), acc);
-        acc = fmaf(r1.w, bf16_hi(pr[3]), acc);
-    }
-    return wave_sum(acc);
-}
+#define ROUTE_THREADS 1024
+#define ROUTE_SEGS 16
+#define FOLD_ROW 13          // a gate with a residual vector takes 13 tokens per block; rows 13 .. 15 hold the residual
 
 // The p largest workloads by descending value, equal values by ascending index; one wavefront, lane l holding the
 // workloads c0 of expert l and c1 of expert l + 64.  A workload is at most T < 2^24 (T d < 2^31, d >= 128), so workload and
@@ -74,9 +53,7 @@ __device__ __forceinline__ void select_token(float v0, float v1, int N, int k, i
     const float p1 = v1 > NEG ? expf(v1 - m) : 0.f;
     const float den = wave_sum_dpp(p0 + p1);
     my_idx = 0;
-    my_p = 0.f;
-    sel = 0.f;
-    float best = m;
+    float best = m, my_best = m;
     for (int s = 0; s < k; ++s) {
         if (s > 0) best = wave_max_dpp(fmaxf(v0, v1));
         const unsigned long long b0 = __ballot(v0 == best);
@@ -91,10 +68,12 @@ __device__ __forceinline__ void select_token(float v0, float v1, int N, int k, i
         } else {
             bi = N - 1;                                  // only reachable with NaN logits: stay in range
         }
-        const float pb = expf(best - m) / den;           // uniform
-        sel += pb;
-        if (lane == s) { my_idx = bi; my_p = pb; }
+        if (lane == s) { my_idx = bi; my_best = best; }
     }
+    // the k scores at once, one per lane: an exponential and a division in every round were a third of its time
+    my_p = expf(my_best - m) / den;
+    sel = 0.f;
+    for (int s = 0; s < k; ++s) sel += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_p), s));
 }
 
 // Weight of a sigmoid-gated shared expert for one token, by one wavefront: c = 1 / (1 + exp(-(x . w_sg))).  One
@@ -119,6 +98,7 @@ __device__ __forceinline__ float sigmoid_gate_of(const uint16_t *__restrict__ x,
 struct shared_tail {
     int S, d;
     const uint16_t *h, *w_sg;          // w_sg null: weight 1
+    float *gate;                       // [T] the sigmoid gates, by a plane of the gate launch; null: evaluated by the selecting block
     int32_t *x_idx;
     float *x_w;
     int32_t *x_counts, *x_offsets, *x_perm, *x_inv;
@@ -153,12 +133,8 @@ __device__ __forceinline__ void decode_tables(const int *sel_idx, unsigned *tokm
         const int c0 = lane < N ? __popc(tokmask[lane]) : 0;
         const int c1 = lane + 64 < N ? __popc(tokmask[lane + 64]) : 0;
         int s0 = c0, s1 = c1;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int u0 = __shfl_up(s0, o, MOE_WAVE), u1 = __shfl_up(s1, o, MOE_WAVE);
-            if (lane >= o) { s0 += u0; s1 += u1; }
-        }
-        const int tot0 = __shfl(s0, 63, MOE_WAVE);
+        const int tot0 = wave_scan_int_dpp(s0);
+        wave_scan_int_dpp(s1);
         if (lane < N) counts[lane] = c0;
         if (lane + 64 < N) counts[lane + 64] = c1;
         if (perm == nullptr) {
@@ -184,7 +160,7 @@ __device__ __forceinline__ void decode_tables(const int *sel_idx, unsigned *tokm
     // ---- the same layer as N + S experts with k + S slots per token (what append_shared_kernel derives from the tables)
     const int S = X.S, kx = k + S, tid = threadIdx.x, nthreads = blockDim.x;
     for (int t = wave; t < T; t += nthreads >> 6) {
-        const float c = X.w_sg != nullptr ? sigmoid_gate_of(X.h + (size_t)t * X.d, X.w_sg, X.d, lane) : 1.0f;
+        const float c = X.w_sg == nullptr ? 1.0f : X.gate != nullptr ? X.gate[t] : sigmoid_gate_of(X.h + (size_t)t * X.d, X.w_sg, X.d, lane);
         if (lane == 0) cs[t] = c;
     }
     __syncthreads();
@@ -215,15 +191,13 @@ __device__ __forceinline__ void decode_tables(const int *sel_idx, unsigned *tokm
 struct gate_job {
     const uint16_t *gate_w;    // [N,d] bf16
     const float *bias;         // [N] or null
-    const float *res_vec;      // non-null (decode-sized launches only): add res_vec . W[e] to the bias of expert e
+    const float *res_vec;      // non-null: add res_vec . W[e] to the logit of expert e
     int norm_mode;
     int32_t *topk_idx;         // [T,k]
     float *topk_w;             // [T,k]
     int32_t *counts;           // non-null: single-block launch that also does the histogram (and, with perm, scan and permutation)
     int32_t *offsets, *perm, *inv_perm;
-    float *fold_out;           // non-null: bias + res_vec . W[e] [N], by the last blockIdx.z of the gate launch; the selection adds it
-    const float *logits_in;    // select_*_kernel: the [T,N] logits to select from
-    float *logits_out;         // gate_topk_kernel<NT, true>: where the logits go [T,N]
+    float *logits;             // [T,N] between gate_topk_kernel<NT, true> and select_decode_kernel
     int32_t *top;              // with counts and without perm: the p largest workloads
     int p;
     shared_tail x;             // x.S > 0 (with perm, decode-sized launches only): also write the tables with the shared experts appended
@@ -235,151 +209,276 @@ struct gate_jobs {
     gate_job job[2];
 };
 
-// The second half of gate_topk_kernel: selection from the logits lg of the block's 16 tokens and, for a decode-sized batch,
-// the tables.  part: scratch of the product, reused.
-template <int NT>
-__device__ __forceinline__ void gate_select(int T, int N, int k, int t0, float (&lg)[ROUTE_TOKENS][NT * 16 + 4],
-                                            float (&part)[ROUTE_WAVES][ROUTE_TOKENS][NT * 16 + 1], const gate_job &J)
+// Eight elements of row `part` of the residual's exact split x = hi + mid + lo into bf16 numbers (8 bits of its 24 each, cut off,
+// so that both differences are exact).  What is not finite stays in hi.
+__device__ __forceinline__ u32x4 residual_rows(const float *__restrict__ r, int part)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    __syncthreads();
-
-    // ---- softmax + top-k: one wave per token, lane l owns experts l and l+64.  k rounds of: wave-wide max on the
-    // DPP crossbar, then the lowest expert index holding that value (ballot + find-first-set; the lower 64 experts
-    // are asked first), which is the tie rule "equal scores by ascending index".
-    for (int q = 0; q < ROUTE_TOKENS / ROUTE_WAVES; ++q) {
-        const int tt = wave * (ROUTE_TOKENS / ROUTE_WAVES) + q;
-        const int t = t0 + tt;
-        if (t >= T) break;                                   // uniform per wave
-        const float NEG = -__builtin_huge_valf();
-        const float v0 = lane < N ? lg[tt][lane] : NEG;
-        const float v1 = (NT > 4 && lane + 64 < N) ? lg[tt][lane + 64] : NEG;
-        int my_idx;
-        float my_p, sel;
-        select_token(v0, v1, N, k, lane, my_idx, my_p, sel);
-        if (lane < k) {
-            J.topk_idx[(size_t)t * k + lane] = my_idx;
-            J.topk_w[(size_t)t * k + lane] = J.norm_mode == MOE_NORM_RENORM ? my_p / sel : my_p;
-            if (J.counts != nullptr) {                                                                  // keep for the tail below
-                reinterpret_cast<int *>(&part[0][0][0])[tt * k + lane] = my_idx;
-                (&part[1][0][0])[tt * k + lane] = J.norm_mode == MOE_NORM_RENORM ? my_p / sel : my_p;
-            }
+    const float4 r0 = *reinterpret_cast<const float4 *>(r), r1 = *reinterpret_cast<const float4 *>(r + 4);
+    const float x[8] = {r0.x, r0.y, r0.z, r0.w, r1.x, r1.y, r1.z, r1.w};
+    u32x4 o;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        uint32_t w[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const float v = x[2 * j + q];
+            const bool finite = __builtin_fabsf(v) < __builtin_huge_valf();
+            uint32_t hi = __float_as_uint(v) & 0xffff0000u;
+            if (v != v) hi = 0x7fc00000u;
+            const float rem = finite ? v - __uint_as_float(hi) : 0.f;
+            const uint32_t mid = __float_as_uint(rem) & 0xffff0000u;
+            const uint32_t lo = __float_as_uint(rem - __uint_as_float(mid));
+            w[q] = part == 0 ? hi : part == 1 ? mid : lo;
         }
+        o[j] = w[0] >> 16 | (w[1] & 0xffff0000u);
     }
-    if (J.counts == nullptr) return;
-
-    // ---- decode-sized batch (one block, T <= 16): histogram, scan and stable permutation right here ----------
-    __shared__ unsigned tokmask[MOE_MAX_EXPERTS];
-    __shared__ int off_s[MOE_MAX_EXPERTS];
-    decode_tables(reinterpret_cast<const int *>(&part[0][0][0]), tokmask, off_s, T, N, k, J.counts, J.offsets, J.perm, J.inv_perm, J.top, J.p,
-                  &part[1][0][0], &part[2][0][0], J.x);
+    return o;
 }
 
-// NT: 16-expert tiles of a block.  LOGITS: only the logits of the experts 16 NT blockIdx.y .. are computed and stored; else
-// NT = ceil(N / 16) and the block selects too.  (One kernel for both held the fields of every path in scalar registers and
-// spilled them.)
-template <int NT, bool LOGITS>
+// 16 rows x 32 k, lane l holding chunk l % 4 of row l / 4, to an MFMA operand (row l % 16, chunk l / 16); from_lane: four times the
+// lane this one's data comes from
+__device__ __forceinline__ bf16x8 rows_to_frag(u32x4 v, int from_lane)
+{
+    u32x4 o;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) o[j] = (uint32_t)__builtin_amdgcn_ds_bpermute(from_lane, (int)v[j]);
+    return as_frag(o);
+}
+
+// The gate product of one block: 16 token rows (with a residual vector 13 and its three rows) times the 16 NT experts from e_base.
+// Rows are read four lanes to a row, 64 contiguous bytes, and put into fragment order by a lane permutation: read in
+// fragment order (neighbouring lanes in different rows) every lane is an access of its own, 38 GB/s per compute unit against 147
+// from L2 and 30 against 58 from HBM.  K is cut into ROUTE_SEGS runs by d alone and the sums of the runs are added as a tree, so
+// that a logit is the same number whatever the batch size and the number of jobs.
+// (FOLD: the gate may have a residual vector.)
+template <int NT, bool FOLD> struct gate_tile {
+    static constexpr int NP = NT * 16;                       // padded expert count
+    static constexpr int G = NT <= 4 ? NT : 4;               // expert groups of a wave, ...
+    static constexpr int KW = NT <= 4 ? 16 : 8;              // ... waves K is dealt to, ...
+    static constexpr int SEGS = ROUTE_SEGS / KW;             // ... runs of a wave
+    const char *hb, *wb;
+    const float *res_vec;
+    uint32_t wo[G];                                          // byte offsets: T*d < 2^31 elements keeps them in 32 bits
+    int T, d, nsteps, per, kw, g0, row, chunk, frag_lane;
+
+    __device__ __forceinline__ gate_tile(int T_, int d_, int N, const uint16_t *h, const gate_job &J, int e_base)
+    {
+        const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        T = T_;
+        d = d_;
+        hb = reinterpret_cast<const char *>(h);
+        wb = reinterpret_cast<const char *>(J.gate_w);
+        res_vec = FOLD ? J.res_vec : nullptr;
+        kw = wave % KW;
+        g0 = wave / KW * G;
+        row = lane >> 2;
+        chunk = lane & 3;
+        frag_lane = ((lane & 15) * 4 + (lane >> 4)) * 4;
+        nsteps = d >> 5;
+        per = (nsteps + ROUTE_SEGS - 1) / ROUTE_SEGS;
+#pragma unroll
+        for (int j = 0; j < G; ++j) wo[j] = ((uint32_t)min(e_base + (g0 + j) * 16 + row, N - 1) * (uint32_t)d + chunk * 8) * 2u;
+    }
+    __device__ __forceinline__ bool fold_row() const { return FOLD && res_vec != nullptr && row >= FOLD_ROW; }
+    __device__ __forceinline__ uint32_t row_offset(int t0) const { return ((uint32_t)min(t0 + row, T - 1) * (uint32_t)d + chunk * 8) * 2u; }
+    // n steps from s on (a step beyond the last one reads that again); along the rows first: the halves of a line follow each other
+    template <int n> __device__ __forceinline__ void load_tokens(u32x4 (&a)[n], int t0, int s, int last) const
+    {
+        const uint32_t ho = row_offset(t0);
+        if (!fold_row()) {
+#pragma unroll
+            for (int u = 0; u < n; ++u) a[u] = *reinterpret_cast<const u32x4 *>(hb + ho + min(s + u, last) * 64);
+        }
+    }
+    template <int n> __device__ __forceinline__ void load_residual(u32x4 (&a)[n], int s, int last) const
+    {
+        if (fold_row()) {
+#pragma unroll
+            for (int u = 0; u < n; ++u) a[u] = residual_rows(res_vec + min(s + u, last) * 32 + chunk * 8, row - FOLD_ROW);
+        }
+    }
+    template <int n> __device__ __forceinline__ void load_gate(u32x4 (&b)[n][G], int s, int last) const
+    {
+#pragma unroll
+        for (int j = 0; j < G; ++j)
+#pragma unroll
+            for (int u = 0; u < n; ++u) b[u][j] = *reinterpret_cast<const u32x4 *>(wb + wo[j] + min(s + u, last) * 64);
+    }
+    __device__ __forceinline__ bf16x8 gate_frag(bf16x8 b) const { return b; }
+    __device__ __forceinline__ bf16x8 gate_frag(u32x4 b) const { return rows_to_frag(b, frag_lane); }
+    // b: gate rows as loaded, or fragments
+    template <int n, class B> __device__ __forceinline__ void mfmas(f32x4 (&acc)[G], const u32x4 (&a)[n], const B (&b)[n][G], int steps) const
+    {
+#pragma unroll
+        for (int u = 0; u < n; ++u) {
+            if (u >= steps) break;                           // uniform
+            const bf16x8 af = rows_to_frag(a[u], frag_lane);
+#pragma unroll
+            for (int j = 0; j < G; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, gate_frag(b[u][j]), acc[j], 0, 0, 0);
+        }
+    }
+    // the steps [s, s_end) of a run, n on their way at once
+    template <int n> __device__ __forceinline__ void walk(f32x4 (&acc)[G], int t0, int s, int s_end) const
+    {
+        for (; s < s_end; s += n) {
+            u32x4 a[n], b[n][G];
+            load_tokens(a, t0, s, s_end - 1);
+            load_gate(b, s, s_end - 1);
+            load_residual(a, s, s_end - 1);
+            __builtin_amdgcn_sched_barrier(0);               // every load of the batch is on its way
+            mfmas(acc, a, b, s_end - s);
+        }
+    }
+    __device__ __forceinline__ void store(float (&part)[ROUTE_SEGS][ROUTE_TOKENS][NP + 1], int seg, const f32x4 (&acc)[G]) const
+    {
+        const int lane = threadIdx.x & 63;
+#pragma unroll
+        for (int j = 0; j < G; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (g0 + j < NT) part[seg][4 * (lane >> 4) + r][(g0 + j) * 16 + (lane & 15)] = acc[j][r];
+    }
+    // the sums of the runs; ends with a barrier
+    static __device__ __forceinline__ void reduce(const float (&part)[ROUTE_SEGS][ROUTE_TOKENS][NP + 1], float (&lg)[ROUTE_TOKENS][NP + 4])
+    {
+        for (int idx = threadIdx.x; idx < ROUTE_TOKENS * NP; idx += ROUTE_THREADS) {
+            const int tt = idx / NP, e = idx % NP;
+            float v[ROUTE_SEGS];
+#pragma unroll
+            for (int w = 0; w < ROUTE_SEGS; ++w) v[w] = part[w][tt][e];
+#pragma unroll
+            for (int o = 1; o < ROUTE_SEGS; o *= 2)
+#pragma unroll
+                for (int w = 0; w < ROUTE_SEGS; w += 2 * o) v[w] += v[w + o];
+            lg[tt][e] = v[0];
+        }
+        __syncthreads();
+    }
+    // logit of a token's row: the bias with the residual vector folded in is added, (h + res_vec).W + b = h.W + (res_vec.W + b)
+    __device__ __forceinline__ float logit(const float (&lg)[ROUTE_TOKENS][NP + 4], const float (&bias_s)[NP], int tt, int e) const
+    {
+        float b = bias_s[e];
+        if (FOLD && res_vec != nullptr) b = ((lg[FOLD_ROW + 2][e] + lg[FOLD_ROW + 1][e]) + lg[FOLD_ROW][e]) + b;
+        return lg[tt][e] + b;
+    }
+    static __device__ __forceinline__ void load_bias(float (&bias_s)[NP], const float *bias, int e_base, int N)
+    {
+        const int e = threadIdx.x;
+        if (e < NP) bias_s[e] = bias != nullptr && e_base + e < N ? bias[e_base + e] : 0.f;
+    }
+};
+
+// Logits of 16 NT experts per blockIdx.y.  Bound by the latency of its reads at decode sizes and by what one compute unit takes in
+// beyond: a block keeps its gate rows in registers (all of them up to d = 2048) and walks token tiles, so that the gate matrix is
+// read once per block, not once per 16 tokens.  With fragment-order reads by 8 waves (16 x 32 tiles, the residual folded by waves of
+// their own) and now: 16 tokens of 64 experts 5.7 / 4.6 us, 16 of two gates of 128 with a residual 8.2 / 6.3, 77 of 128 8.0 / 5.4,
+// 2048 of 64 10.4 / 7.3, 4096 of 60 17.3 / 9.8, 1531 of two gates of 128 22 / 13.6 (d = 2048).
+template <int NT>
+__global__ __launch_bounds__(ROUTE_THREADS) void gate_logits_kernel(int T, int d, int N, const uint16_t *__restrict__ h, gate_jobs jobs)
+{
+    const gate_job &J = jobs.job[blockIdx.z == 0 ? 0 : 1];
+    if (J.x.gate != nullptr && blockIdx.z == gridDim.z - 1) {
+        // the sigmoid gates of the shared experts, one wave per token
+        const int t = threadIdx.x >> 6, lane = threadIdx.x & 63;
+        if (blockIdx.y == 0 && t < T) {
+            const float c = sigmoid_gate_of(h + (size_t)t * d, J.x.w_sg, d, lane);
+            if (lane == 0) J.x.gate[t] = c;
+        }
+        return;
+    }
+    const int tokens = J.res_vec != nullptr ? FOLD_ROW : ROUTE_TOKENS;
+    int t0 = blockIdx.x * tokens;
+    if (t0 >= T) return;
+    constexpr int NP = NT * 16, KEEP = 4;
+    __shared__ float part[ROUTE_SEGS][ROUTE_TOKENS][NP + 1];    // partial logits
+    __shared__ __attribute__((aligned(16))) float lg[ROUTE_TOKENS][NP + 4];   // reduced logits, rows 16-byte aligned
+    __shared__ float bias_s[NP];
+    const int e_base = blockIdx.y * NP;
+    const gate_tile<NT, true> G(T, d, N, h, J, e_base);
+    static_assert(G.SEGS == 1, "one run per wave");
+    const int s0 = G.kw * G.per, s_end = min(s0 + G.per, G.nsteps), last = max(min(s_end, G.nsteps) - 1, 0);
+    u32x4 a[KEEP], b[KEEP][G.G];
+    G.load_tokens(a, t0, s0, last);
+    G.load_gate(b, s0, last);
+    G.load_residual(a, s0, last);
+    G.load_bias(bias_s, J.bias, e_base, N);
+    bf16x8 bf[KEEP][G.G];
+#pragma unroll
+    for (int u = 0; u < KEEP; ++u)
+#pragma unroll
+        for (int j = 0; j < G.G; ++j) bf[u][j] = rows_to_frag(b[u][j], G.frag_lane);
+    float *__restrict__ out = J.logits;
+    for (; t0 < T; t0 += gridDim.x * tokens) {
+        f32x4 acc[G.G];
+#pragma unroll
+        for (int j = 0; j < G.G; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        G.mfmas(acc, a, bf, s_end - s0);
+        G.template walk<2>(acc, t0, s0 + KEEP, s_end);
+        G.store(part, G.kw, acc);
+        G.load_tokens(a, t0 + gridDim.x * tokens, s0, last);     // of the next tile (of the last token beyond the last tile)
+        __syncthreads();
+        G.reduce(part, lg);
+        const int n = min(tokens, T - t0) * NP;
+        for (int idx = threadIdx.x; idx < n; idx += ROUTE_THREADS) {
+            const int tt = idx / NP, e = idx % NP;
+            if (e_base + e < N) out[(size_t)(t0 + tt) * N + e_base + e] = G.logit(lg, bias_s, tt, e);
+        }
+    }
+}
+
+// Gate and selection of 16 tokens, NT = ceil(N / 16); with TABLES (a decode-sized batch, one block) the tables too.  (One kernel for
+// all held the fields of every path in scalar registers and spilled them.)  Before and now, d = 4096, 8 experts: 200 tokens 10.9 /
+// 7.8 us, 8192 23 / 19.
+template <int NT, bool TABLES>
 __global__ __launch_bounds__(ROUTE_THREADS) void gate_topk_kernel(int T, int d, int N, int k, const uint16_t *__restrict__ h,
                                                                   gate_jobs jobs)
 {
     const gate_job &J = jobs.job[blockIdx.z == 0 ? 0 : 1];
-    const uint16_t *__restrict__ gate_w = J.gate_w;
-    if (LOGITS && J.fold_out != nullptr && blockIdx.z == gridDim.z - 1) {
-        // the residual folded into the bias, one wave per expert
-        const int n_waves = gridDim.x * gridDim.y * ROUTE_WAVES;
-        for (int e = (blockIdx.y * gridDim.x + blockIdx.x) * ROUTE_WAVES + (threadIdx.x >> 6); e < N; e += n_waves) {
-            const float acc = residual_dot(d, J.res_vec, gate_w + (size_t)e * d, threadIdx.x & 63);
-            if ((threadIdx.x & 63) == 0) J.fold_out[e] = acc + (J.bias != nullptr ? J.bias[e] : 0.f);
-        }
-        return;
-    }
-    const float *__restrict__ bias = LOGITS && J.fold_out != nullptr ? nullptr : J.bias;
-    const float *__restrict__ res_vec = LOGITS && J.fold_out != nullptr ? nullptr : J.res_vec;
-    float *__restrict__ logits_out = J.logits_out;
-
-    constexpr int NP = NT * 16;                       // padded expert count
-    __shared__ float part[ROUTE_WAVES][ROUTE_TOKENS][NP + 1];   // per-wave partial logits
-    __shared__ __attribute__((aligned(16))) float lg[ROUTE_TOKENS][NP + 4];   // reduced logits (+bias), rows 16-byte aligned
-
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const int t0 = blockIdx.x * ROUTE_TOKENS;
-    const int i = lane & 15, g = lane >> 4;
-    const int e_base = LOGITS ? blockIdx.y * NP : 0;   // first expert of this block
-
-    // ---- logits: D[token][expert] += A[token][k] * B[k][expert], 32 k per MFMA -------------------
-    int tr = t0 + i;
-    if (tr >= T) tr = T - 1;
-    const uint16_t *hp = h + (size_t)tr * d + g * 8;
-    const uint16_t *wp[NT];
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-        int er = e_base + nt * 16 + i;
-        if (er >= N) er = N - 1;
-        wp[nt] = gate_w + (size_t)er * d + g * 8;
-    }
-    f32x4 acc[NT];
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) acc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-    // K is dealt to the 8 waves in 32-wide steps (step s -> wave s % 8); each wave issues the loads of four of
-    // its steps before the first MFMA so that the block has ~8 x 4 x (1 + NT) loads in flight (eight at a time
-    // measured no faster)
-    constexpr int BATCH = 4;
-    const int nsteps = d >> 5;
-    int s = wave;
-    for (; s + (BATCH - 1) * ROUTE_WAVES < nsteps; s += BATCH * ROUTE_WAVES) {
-        u32x4 a[BATCH], b[BATCH][NT];
-#pragma unroll
-        for (int u = 0; u < BATCH; ++u) {
-            a[u] = *reinterpret_cast<const u32x4 *>(hp + (s + u * ROUTE_WAVES) * 32);
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) b[u][nt] = *reinterpret_cast<const u32x4 *>(wp[nt] + (s + u * ROUTE_WAVES) * 32);
-        }
-        __builtin_amdgcn_sched_barrier(0);      // keep every load of the batch ahead of the first MFMA
-#pragma unroll
-        for (int u = 0; u < BATCH; ++u)
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt)
-                acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_frag(a[u]), as_frag(b[u][nt]), acc[nt], 0, 0, 0);
-    }
-    for (; s < nsteps; s += ROUTE_WAVES) {
-        bf16x8 a = as_frag(*reinterpret_cast<const u32x4 *>(hp + s * 32));
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-            bf16x8 b = as_frag(*reinterpret_cast<const u32x4 *>(wp[nt] + s * 32));
-            acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc[nt], 0, 0, 0);
-        }
-    }
-    // bias of the block's experts, with the residual vector folded in: (h + res_vec).W + b = h.W + (res_vec.W + b)
+    const int tokens = !TABLES && J.res_vec != nullptr ? FOLD_ROW : ROUTE_TOKENS;
+    const int t0 = blockIdx.x * tokens;
+    if (t0 >= T) return;
+    constexpr int NP = NT * 16;
+    __shared__ float part[ROUTE_SEGS][ROUTE_TOKENS][NP + 1];
+    __shared__ __attribute__((aligned(16))) float lg[ROUTE_TOKENS][NP + 4];
     __shared__ float bias_s[NP];
-    for (int el = wave; el < NP; el += ROUTE_WAVES) {
-        const int e = e_base + el;
-        float b = 0.f;
-        if (e < N) {
-            b = bias != nullptr ? bias[e] : 0.f;
-            if (res_vec != nullptr) b = residual_dot(d, res_vec, gate_w + (size_t)e * d, lane) + b;
-        }
-        if (lane == 0) bias_s[el] = b;
+    const gate_tile<NT, !TABLES> G(T, d, N, h, J, 0);
+    G.load_bias(bias_s, J.bias, 0, N);
+    for (int seg = G.kw * G.SEGS; seg < (G.kw + 1) * G.SEGS; ++seg) {
+        f32x4 acc[G.G];
+#pragma unroll
+        for (int j = 0; j < G.G; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        G.template walk<TABLES && NT == 1 ? 8 : NT <= 3 ? 4 : 2>(acc, t0, seg * G.per, min((seg + 1) * G.per, G.nsteps));
+        G.store(part, seg, acc);
     }
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-            part[wave][4 * g + r][nt * 16 + i] = acc[nt][r];
     __syncthreads();
-    for (int idx = threadIdx.x; idx < ROUTE_TOKENS * NP; idx += ROUTE_THREADS) {
-        int tt = idx / NP, e = idx % NP;
-        float v = ((part[0][tt][e] + part[1][tt][e]) + (part[2][tt][e] + part[3][tt][e])) +
-                  ((part[4][tt][e] + part[5][tt][e]) + (part[6][tt][e] + part[7][tt][e]));
-        if (e_base + e < N) v += bias_s[e];
-        if constexpr (LOGITS) {
-            if (t0 + tt < T && e_base + e < N) logits_out[(size_t)(t0 + tt) * N + e_base + e] = v;
-        } else {
-            lg[tt][e] = v;
+    G.reduce(part, lg);
+
+    // softmax + top-k: one wave per token, lane l owns experts l and l + 64
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (wave < min(tokens, T - t0)) {
+        const int t = t0 + wave;
+        const float NEG = -__builtin_huge_valf();
+        const float v0 = lane < N ? G.logit(lg, bias_s, wave, lane) : NEG;
+        const float v1 = NT > 4 && lane + 64 < N ? G.logit(lg, bias_s, wave, lane + 64) : NEG;
+        int my_idx;
+        float my_p, sel;
+        select_token(v0, v1, N, k, lane, my_idx, my_p, sel);
+        if (lane < k) {
+            const float wgt = J.norm_mode == MOE_NORM_RENORM ? my_p / sel : my_p;
+            J.topk_idx[(size_t)t * k + lane] = my_idx;
+            J.topk_w[(size_t)t * k + lane] = wgt;
+            if (TABLES) {
+                reinterpret_cast<int *>(&part[0][0][0])[wave * k + lane] = my_idx;
+                (&part[1][0][0])[wave * k + lane] = wgt;
+            }
         }
     }
-    if constexpr (!LOGITS) gate_select<NT>(T, N, k, t0, lg, part, J);
+    if constexpr (!TABLES) return;
+    __syncthreads();
+    __shared__ unsigned tokmask[MOE_MAX_EXPERTS];
+    __shared__ int off_s[MOE_MAX_EXPERTS];
+    decode_tables(reinterpret_cast<const int *>(&part[0][0][0]), tokmask, off_s, T, N, k, J.counts, J.offsets, J.perm, J.inv_perm, J.top, J.p,
+                  &part[1][0][0], &part[2][0][0], J.x);
 }
 
 // Selection for a decode-sized batch from stored logits [T, N] (bias already added): one wavefront per token, then
@@ -393,9 +492,12 @@ __global__ __launch_bounds__(SELECT_THREADS) void select_decode_kernel(int T, in
     __shared__ unsigned tokmask[MOE_MAX_EXPERTS];
     __shared__ int off_s[MOE_MAX_EXPERTS];
     const int lane = threadIdx.x & 63, t = threadIdx.x >> 6;
+    // all arguments at once: read where they are used, each line of them is a round trip of its own (0.4 us)
+    asm volatile("" ::"s"(J.topk_idx), "s"(J.topk_w), "s"(J.counts), "s"(J.offsets), "s"(J.perm), "s"(J.inv_perm), "s"(J.norm_mode), "s"(J.x.S),
+                 "s"(J.x.gate), "s"(J.x.x_idx), "s"(J.x.x_w), "s"(J.x.x_counts), "s"(J.x.x_offsets), "s"(J.x.x_perm), "s"(J.x.x_inv));
     if (t < T) {
         const float NEG = -__builtin_huge_valf();
-        const float *row = J.logits_in + (size_t)t * N;
+        const float *row = J.logits + (size_t)t * N;
         const float v0 = lane < N ? row[lane] : NEG;
         const float v1 = lane + 64 < N ? row[lane + 64] : NEG;
         int my_idx;
@@ -421,13 +523,9 @@ __global__ __launch_bounds__(SELECT_THREADS) void select_rows_kernel(int T, int 
     const int t = blockIdx.x * (SELECT_THREADS / 64) + (threadIdx.x >> 6);
     if (t >= T) return;
     const float NEG = -__builtin_huge_valf();
-    const float *row = J.logits_in + (size_t)t * N;
-    float v0 = lane < N ? row[lane] : NEG;
-    float v1 = lane + 64 < N ? row[lane + 64] : NEG;
-    if (J.fold_out != nullptr) {
-        if (lane < N) v0 += J.fold_out[lane];
-        if (lane + 64 < N) v1 += J.fold_out[lane + 64];
-    }
+    const float *row = J.logits + (size_t)t * N;
+    const float v0 = lane < N ? row[lane] : NEG;
+    const float v1 = lane + 64 < N ? row[lane + 64] : NEG;
     int my_idx;
     float my_p, sel;
     select_token(v0, v1, N, k, lane, my_idx, my_p, sel);
@@ -589,16 +687,6 @@ static int launch_hist_scan_perm(int R, int N, const int32_t *topk_idx, int32_t 
 }
 
 // ---------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(64) void fold_residual_kernel(int d, const float *__restrict__ res_vec,
-                                                           const uint16_t *__restrict__ gate_w,
-                                                           const float *__restrict__ bias, float *__restrict__ bias_out)
-{
-    const int e = blockIdx.x, lane = threadIdx.x;
-    const float acc = residual_dot(d, res_vec, gate_w + (size_t)e * d, lane);
-    if (lane == 0) bias_out[e] = acc + (bias != nullptr ? bias[e] : 0.f);
-}
-
-// ---------------------------------------------------------------------------------------------------
 __global__ void dense_route_kernel(int T, int S, int32_t *__restrict__ counts, int32_t *__restrict__ offsets,
                                    int32_t *__restrict__ perm)
 {
@@ -679,68 +767,58 @@ static gate_job make_job(const void *gate_w, const float *bias, int norm_mode, i
     return j;
 }
 
+// Token tiles are dealt to as many blocks as make one round of compute units
+static unsigned gate_streams(unsigned tiles, unsigned slices)
+{
+    const unsigned n = slices >= 256 ? 1 : 256 / slices;
+    return tiles < n ? tiles : n;
+}
+
 // Launches the gate kernels for one job, or for two jobs side by side (both of the same size, so they take the same
-// path).  ws_logits[i]: [max(T,16), N] scratch of job i for the paths that store logits, or null.  Beyond decode sizes a
-// job with a residual has fold_out set.
+// path).  ws_logits[i]: [16, N] scratch of job i for decode-sized batches, or null (a job with a residual always has one).
 static int launch_gate_topk(const moe_shape *s, const void *h, hipStream_t st, int n_jobs, gate_job *jobs, float *const *ws_logits)
 {
     const int NT = (s->N + 15) / 16;
-    dim3 grid((s->T + ROUTE_TOKENS - 1) / ROUTE_TOKENS, 1, n_jobs), block(ROUTE_THREADS);
+    gate_jobs two = {{jobs[0], jobs[n_jobs - 1]}};
+    const bool fold = jobs[n_jobs - 1].res_vec != nullptr;
+    const int tokens = fold ? FOLD_ROW : ROUTE_TOKENS;
+    dim3 grid((s->T + tokens - 1) / tokens, 1, n_jobs), block(ROUTE_THREADS);
     const uint16_t *hp = (const uint16_t *)h;
-    gate_jobs sel = {{jobs[0], jobs[n_jobs - 1]}};
-    if (s->T <= ROUTE_TOKENS && NT >= 2 && ws_logits[0] != nullptr) {
-        // decode-sized batch with many experts: one block would stream the whole gate matrix alone, so the gate
-        // product is spread over one block per 16 experts and the selection runs from the stored logits
-        gate_jobs lg;
-        for (int i = 0; i < 2; ++i) {
-            const int ji = i < n_jobs ? i : n_jobs - 1;
-            lg.job[i] = make_job(jobs[ji].gate_w, jobs[ji].bias, jobs[ji].norm_mode, nullptr, nullptr);
-            lg.job[i].res_vec = jobs[ji].res_vec;
-            lg.job[i].logits_out = ws_logits[ji];
-            sel.job[i].logits_in = ws_logits[ji];
-        }
-        hipLaunchKernelGGL((gate_topk_kernel<1, true>), dim3(1, NT, n_jobs), block, 0, st, s->T, s->d, s->N, s->k, hp, lg);
+    if (s->T <= ROUTE_TOKENS && (NT >= 2 || fold) && ws_logits[0] != nullptr) {
+        // decode-sized batch: one block would stream the whole gate matrix of many experts alone, so the gate product is spread
+        // over one block per 16 experts and the selection runs from the stored logits (with a residual also because its
+        // rows and 16 tokens are two blocks)
+        for (int i = 0; i < 2; ++i) two.job[i].logits = ws_logits[i < n_jobs ? i : n_jobs - 1];
+        grid.y = NT;
+        if (two.job[0].x.gate != nullptr) grid.z += 1;
+        hipLaunchKernelGGL(gate_logits_kernel<1>, grid, block, 0, st, s->T, s->d, s->N, hp, two);
         MOE_CHECK_LAUNCH();
         // T <= 16 and k <= 8: at most 128 selections, so the selecting block also builds the tables
-        hipLaunchKernelGGL(select_decode_kernel, dim3(1, 1, n_jobs), dim3(SELECT_THREADS), 0, st, s->T, s->N, s->k, sel);
+        hipLaunchKernelGGL(select_decode_kernel, dim3(1, 1, n_jobs), dim3(SELECT_THREADS), 0, st, s->T, s->N, s->k, two);
         MOE_CHECK_LAUNCH();
         return MOE_OK;
     }
     if (s->T > ROUTE_TOKENS && NT >= 4 && ws_logits[0] != nullptr) {
-        // many experts: a block that evaluated all of them for its 16 tokens would leave half the chip idle and spend
-        // its time on the gate rows, so the gate product runs as (token blocks x 32-expert slices) and the selection,
-        // one wavefront per token, reads the stored logits
-        gate_jobs lg;
-        for (int i = 0; i < 2; ++i) {
-            const int ji = i < n_jobs ? i : n_jobs - 1;
-            lg.job[i] = make_job(jobs[ji].gate_w, jobs[ji].bias, jobs[ji].norm_mode, nullptr, nullptr);
-            lg.job[i].res_vec = jobs[ji].res_vec;
-            lg.job[i].fold_out = jobs[ji].fold_out;
-            lg.job[i].logits_out = ws_logits[ji];
-            sel.job[i].logits_in = ws_logits[ji];
-        }
-        const int planes = n_jobs + (lg.job[1].fold_out != nullptr ? 1 : 0);
-        hipLaunchKernelGGL((gate_topk_kernel<2, true>), dim3(grid.x, (s->N + 31) / 32, planes), block, 0, st, s->T, s->d, s->N, s->k, hp,
-                           lg);
+        // many experts: a block that evaluated all of them for its tokens would leave half the chip idle and spend its time on the
+        // gate rows, so the gate product runs as (token blocks x 32-expert slices) and the selection, one wavefront per token,
+        // reads the stored logits
+        for (int i = 0; i < 2; ++i) two.job[i].logits = ws_logits[i < n_jobs ? i : n_jobs - 1];
+        grid.y = (s->N + 31) / 32;
+        grid.x = gate_streams(grid.x, grid.y * n_jobs);
+        hipLaunchKernelGGL(gate_logits_kernel<2>, grid, block, 0, st, s->T, s->d, s->N, hp, two);
         MOE_CHECK_LAUNCH();
         hipLaunchKernelGGL(select_rows_kernel, dim3((s->T + SELECT_THREADS / 64 - 1) / (SELECT_THREADS / 64), 1, n_jobs),
-                           dim3(SELECT_THREADS), 0, st, s->T, s->N, s->k, sel);
+                           dim3(SELECT_THREADS), 0, st, s->T, s->N, s->k, two);
         MOE_CHECK_LAUNCH();
         return MOE_OK;
     }
-    for (int i = 0; i < 2; ++i) {
-        if (sel.job[i].fold_out == nullptr) continue;
-        // few experts: the gate kernel selects too and needs the folded bias at its start
-        if (i == 1)
-            hipLaunchKernelGGL(fold_residual_kernel, dim3(s->N), dim3(64), 0, st, s->d, sel.job[i].res_vec, sel.job[i].gate_w, sel.job[i].bias,
-                               sel.job[i].fold_out);
-        sel.job[i].bias = sel.job[i].fold_out;
-        sel.job[i].res_vec = nullptr;
-        sel.job[i].fold_out = nullptr;
-    }
+    two.job[0].x.gate = nullptr;      // the block that selects evaluates the shared experts' gates too
 #define GT(n)                                                                                                  \
     case n:                                                                                                    \
-        hipLaunchKernelGGL((gate_topk_kernel<n, false>), grid, block, 0, st, s->T, s->d, s->N, s->k, hp, sel); \
+        if (two.job[0].counts != nullptr)                                                                      \
+            hipLaunchKernelGGL((gate_topk_kernel<n, true>), grid, block, 0, st, s->T, s->d, s->N, s->k, hp, two); \
+        else                                                                                                   \
+            hipLaunchKernelGGL((gate_topk_kernel<n, false>), grid, block, 0, st, s->T, s->d, s->N, s->k, hp, two); \
         break;
     switch (NT) {
         GT(1) GT(2) GT(3) GT(4) GT(5) GT(6) GT(7) GT(8)
@@ -776,8 +854,7 @@ static gate_job route_job(const moe_shape *s, const void *gate_w, const float *g
     return j;
 }
 
-// prediction job: at decode sizes the residual is folded inside the gate kernel and the selecting block does histogram and
-// top-p; beyond, the folded bias goes through fold_out and predict_top names what the histogram reads and writes
+// prediction job: at decode sizes the selecting block does histogram and top-p; beyond, they follow in a launch of their own
 static gate_job predict_job(const moe_shape *s, const float *res_vec, const void *next_gate_w, const float *next_gate_bias, int p,
                             int32_t *pred_counts, int32_t *top_experts, void *workspace)
 {
@@ -792,8 +869,6 @@ static gate_job predict_job(const moe_shape *s, const float *res_vec, const void
         j.counts = pred_counts;
         j.top = top_experts;
         j.p = p;
-    } else {
-        j.fold_out = (float *)ws;
     }
     return j;
 }
@@ -824,7 +899,7 @@ int moe_predict_impl(const moe_shape *s, const void *h, const float *res_vec, co
 }
 
 // Routing of this layer and workload prediction of the next in one pass: the two gates are evaluated by the same launches
-// (blockIdx.z = 0 routes, 1 predicts).  Beyond decode sizes that is three launches instead of eight: 1531 tokens, 128 experts 69 -> 32 us.
+// (blockIdx.z = 0 routes, 1 predicts).  Beyond decode sizes that is three launches: 1531 tokens, 128 experts 25 us.
 int moe_route_predict_impl(const moe_shape *s, const void *h, const void *gate_w, const float *gate_bias, int norm_mode,
                            int32_t *topk_idx, float *topk_w, int32_t *counts, int32_t *offsets, int32_t *perm,
                            int32_t *inv_perm, const float *res_vec, const void *next_gate_w, const float *next_gate_bias,
@@ -868,6 +943,7 @@ int moe_route_shared_impl(const moe_shape *s, int n_shared, const void *h, const
     j.x.d = s->d;
     j.x.h = (const uint16_t *)h;
     j.x.w_sg = (const uint16_t *)w_sg;
+    if (w_sg != nullptr && workspace != nullptr) j.x.gate = (float *)((char *)workspace + moe_ws(s).route);
     j.x.x_idx = x_topk_idx;
     j.x.x_w = x_topk_w;
     j.x.x_counts = x_counts;

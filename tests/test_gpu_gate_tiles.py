@@ -1,0 +1,73 @@
+"""The gate product at the edges of its tiles: blocks that walk several token tiles (with a residual vector 13 tokens each), runs of
+K shorter than, equal to and longer than the steps a wave keeps in registers, expert slices that are not full.  Routing is compared
+with the oracle under the rules of helpers.py and the prediction through its counts; a logit is a function of its token and
+expert alone, so a token routed by itself gets the same bits as inside the batch."""
+import numpy as np
+import pytest
+
+import oracle
+from helpers import check_routing, exempt_tokens
+from paper_2602_03495_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2602_03495_amd import binding, layer
+    binding.load_library()
+    return binding, layer
+
+
+@pytest.mark.parametrize("d,N,k,T", [(128, 128, 8, 1000), (640, 60, 4, 417), (2048, 49, 4, 833), (2176, 64, 6, 53), (4096, 8, 2, 300),
+                                     (4096, 70, 8, 27), (8192, 128, 8, 40), (8192, 17, 2, 14), (2048, 128, 8, 16), (4096, 8, 2, 13)])
+def test_route_and_predict_at_the_edges_of_the_gate_tiles(gpu, d, N, k, T):
+    B, Lm = gpu
+    print(f"gate tiles d={d} N={N} k={k} T={T}", flush=True)
+    cfg = wl.scaled(wl.CONFIGS["qwen3"], d=d, N=N, k=k, I=128)
+    h = wl.hidden_states(cfg, T)
+    W0, b0, W1, b1 = wl.gate_weights(cfg, 0), wl.gate_bias(cfg, 0), wl.gate_weights(cfg, 1), wl.gate_bias(cfg, 1)
+    rv = wl.layer_drift(cfg)
+    assert np.any(rv.view(np.uint32) & 0xFFFF)           # not bf16 numbers: all three parts of the split count
+    up = lambda a: Lm.to_device_bf16(a)
+    hd, W0d, W1d, b0d, b1d, rvd = up(h), up(W0), up(W1), *(torch.from_numpy(a).cuda() for a in (b0, b1, rv))
+    s, p = B.shape(T, d, N, k, cfg.I), min(N, 5)
+    ws, r = B.alloc_workspace(s), B.alloc_routing(s)
+    pc, top = torch.empty(N, dtype=torch.int32, device="cuda"), torch.empty(p, dtype=torch.int32, device="cuda")
+    B.moe_route_predict(s, hd, W0d, b0d, cfg.norm_mode, r, rvd, W1d, b1d, p, pc, top, ws)
+    torch.cuda.synchronize()
+    host = lambda t: t.cpu().numpy()
+    lg, o_idx, o_w, o_counts = oracle.route(h, W0, b0, k, cfg.norm_mode)
+    idx, w = host(r.topk_idx), host(r.topk_w)
+    check_routing(lg, o_idx, o_w, o_counts, idx, w, host(r.counts), host(r.offsets), host(r.perm), host(r.inv_perm), N, k)
+    plg, _, p_counts, _ = oracle.predict_workload(h, rv, W1, b1, k, p)
+    got = host(pc)
+    assert got.sum() == T * k
+    assert int(np.abs(got.astype(np.int64) - p_counts).sum()) <= 2 * int(exempt_tokens(plg, k).sum())
+    assert np.array_equal(host(top), oracle.top_p(got, p))
+
+    s1 = B.shape(1, d, N, k, cfg.I)
+    for workspace in (B.alloc_workspace(s1), None):      # the product spread over blocks, and one block for all of it
+        r1 = B.alloc_routing(s1)
+        for t in sorted({0, 12, 13, T // 2, T - 1} & set(range(T))):
+            B.moe_route(s1, hd[t:t + 1], W0d, b0d, cfg.norm_mode, r1, workspace)
+            torch.cuda.synchronize()
+            assert np.array_equal(host(r1.topk_idx)[0], idx[t]) and np.array_equal(host(r1.topk_w)[0], w[t]), t
+
+
+def test_an_infinite_residual_element_makes_infinite_logits_not_nan(gpu):
+    # its lower parts are zero: an infinity less itself would make every logit NaN
+    B, _ = gpu
+    d, N, k, T = 256, 8, 2, 21
+    W = torch.zeros(N, d, device="cuda")
+    W[0::2, 7], W[1::2, 7] = 1.0, -1.0
+    rv = torch.zeros(d, device="cuda")
+    rv[7], rv[8] = float("inf"), 3.4e38                 # rv[8]: beyond the largest bf16 number, times zero
+    s = B.shape(T, d, N, k, 128)
+    pc, top = torch.empty(N, dtype=torch.int32, device="cuda"), torch.empty(2, dtype=torch.int32, device="cuda")
+    B.moe_predict_workload(s, torch.ones(T, d, device="cuda").bfloat16(), rv, W.bfloat16(), None, 2, pc, top, B.alloc_workspace(s))
+    torch.cuda.synchronize()
+    assert pc.tolist() == [T, 0, T, 0, 0, 0, 0, 0] and top.tolist() == [0, 2]
