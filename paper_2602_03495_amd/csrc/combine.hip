@@ -32,7 +32,7 @@ __device__ __forceinline__ void add_rows(float (&acc)[8], unsigned long long &on
 // Bound by latency at decode sizes, by the reads beyond.  Every wave holds the slots of its token in its first lanes, finds
 // those placed on this GPU by a ballot and reads all their rows at once: with a loop over the slots that skipped the others,
 // the reads of up to 8 rows followed one another (16 tokens, 8 slots, d = 2048: 3.7 us, now 2.5).
-__global__ __launch_bounds__(256) void combine_kernel(int T, int d, int k, const uint16_t *__restrict__ y,
+__global__ __launch_bounds__(256) void combine_kernel(int T, int d, int N, int k, const uint16_t *__restrict__ y,
                                                       const int32_t *__restrict__ topk_idx, const float *__restrict__ topk_w,
                                                       const int32_t *__restrict__ inv_perm, const uint8_t *__restrict__ mask,
                                                       const uint16_t *__restrict__ shared_y, int n_shared,
@@ -42,12 +42,18 @@ __global__ __launch_bounds__(256) void combine_kernel(int T, int d, int k, const
     int p = 0;
     float w = 0.f;
     bool mine = lane < k;
+    unsigned long long on_lo = ~0ull, on_hi = ~0ull;
+    if (mask != nullptr) {              // the whole of it, beside the slots: looked up by expert it was a round trip after them
+        const int m0 = mask[min(lane, N - 1)], m1 = mask[min(lane + 64, N - 1)];
+        on_lo = __ballot(m0 != 0);
+        on_hi = __ballot(m1 != 0);
+    }
     if (mine) {
         const size_t r = (size_t)t * k + lane;
         const int e = topk_idx[r];
         w = topk_w[r];
         p = inv_perm[r];
-        mine = mask == nullptr || mask[e] != 0;
+        mine = ((e < 64 ? on_lo : on_hi) >> (e & 63) & 1ull) != 0;
     }
     unsigned long long on = __ballot(mine);
     const float sc = (n_shared > 0 && shared_scale != nullptr) ? shared_scale[t] : 1.0f;
@@ -87,7 +93,7 @@ __global__ __launch_bounds__(256) void combine_kernel(int T, int d, int k, const
 
 // The same sums for many tokens with few slots: a block walks the columns of its token, whose tables it reads once, and holds
 // few rows at a time, so that 8 waves run on a SIMD (combine_kernel, with room for 8 rows per lane, has 5).
-__global__ __launch_bounds__(256) void combine_walk_kernel(int T, int d, int k, const uint16_t *__restrict__ y,
+__global__ __launch_bounds__(256) void combine_walk_kernel(int T, int d, int N, int k, const uint16_t *__restrict__ y,
                                                            const int32_t *__restrict__ topk_idx, const float *__restrict__ topk_w,
                                                            const int32_t *__restrict__ inv_perm, const uint8_t *__restrict__ mask,
                                                            const uint16_t *__restrict__ shared_y, int n_shared,
@@ -135,7 +141,7 @@ int moe_combine_impl(const moe_shape *s, const void *y, const int32_t *topk_idx,
     // experts: 13.2 us with all four, 7.3 with one)
     const unsigned threads = s->d >= 2048 ? 256 : (unsigned)(s->d + 511) / 512 * 64;
 #define COMBINE(kernel, grid)                                                                                                   \
-    hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, st, s->T, s->d, s->k, (const uint16_t *)y, topk_idx, topk_w, inv_perm, expert_mask, \
+    hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, st, s->T, s->d, s->N, s->k, (const uint16_t *)y, topk_idx, topk_w, inv_perm, expert_mask, \
                        (const uint16_t *)shared_y, shared_y ? n_shared : 0, shared_scale, (uint16_t *)out)
     if (combine_walks(s)) COMBINE(combine_walk_kernel, dim3(s->T));
     else COMBINE(combine_kernel, dim3(s->T, (s->d + 2047) / 2048));

@@ -35,13 +35,13 @@ __global__ __launch_bounds__(SK_THREADS) void skinny_up_kernel(
     const uint16_t *__restrict__ w3, const uint8_t *__restrict__ mask, uint16_t *__restrict__ act)
 {
     int e, bx;
-    if (!moe_working_item(N, counts, mask, blocks_per_expert, blockIdx.x, e, bx)) return;
-    const int c = counts[e];
+    const moe_work work = moe_working_experts(N, counts, offsets, mask);
+    if (!moe_item_of(work, blocks_per_expert, blockIdx.x, e, bx)) return;
+    const int c = work.rows_of(e), off = work.first_row_of(e);
     __shared__ float red[SK_WAVES][RT][2][256];
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int i = lane & 15, g = lane >> 4;
-    const int off = offsets[e];
     const int total = d >> 5;
     const int per = (total + SK_WAVES - 1) / SK_WAVES;
     const int s0 = wave * per;
@@ -112,14 +112,14 @@ __global__ __launch_bounds__(SK_THREADS) void skinny_down_kernel(
     const uint8_t *__restrict__ mask, uint16_t *__restrict__ y, float *__restrict__ partial)
 {
     int e, local;
-    if (!moe_working_item(N, counts, mask, row_blocks * nsplit, blockIdx.x, e, local)) return;
+    const moe_work work = moe_working_experts(N, counts, offsets, mask);
+    if (!moe_item_of(work, row_blocks * nsplit, blockIdx.x, e, local)) return;
     const int bx = local % row_blocks, by = local / row_blocks;    // row block, K split
-    const int c = counts[e];
+    const int c = work.rows_of(e), off = work.first_row_of(e);
     __shared__ float red[SK_WAVES][RT][256];
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int i = lane & 15, g = lane >> 4;
-    const int off = offsets[e];
     const int total = I >> 5;
     const int per = (steps_per_block + SK_WAVES - 1) / SK_WAVES;
     const bool valid = i < c;

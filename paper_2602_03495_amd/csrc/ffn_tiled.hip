@@ -358,17 +358,20 @@ __global__ __launch_bounds__(WAVES * 64, 2) void ffn_tiled_kernel(
     // tiles that have work, which only the device knows (counts and mask live there)
     MOE_TRACE_BEGIN();
     int e, mt, nt, nsp = 1, tmk = TM;      // tmk: token rows per tile of this launch
+    int row0, nrows;
     if (DIRECT) {
         // at most one token tile per expert (T <= 128)
-        unsigned long long act_lo, act_hi;
-        const int n_work = moe_working_experts(N, counts, mask, act_lo, act_hi);
+        const moe_work work = moe_working_experts(N, counts, offsets, mask);
+        const int n_work = work.experts();
         if (MODE == 1) nsp = moe_dev_splits(n_work * n_ntc, nsp_max);
         if (CAN_NARROW && up_items_narrow(n_work * n_ntc)) {
             narrow = true;
             n_ntc = (I + NT_COLS / 2 - 1) / (NT_COLS / 2);
         }
-        if (!moe_item_of(act_lo, act_hi, n_ntc * nsp, blockIdx.x, e, nt)) return;
+        if (!moe_item_of(work, n_ntc * nsp, blockIdx.x, e, nt)) return;
         mt = 0;
+        row0 = work.first_row_of(e);
+        nrows = work.rows_of(e);
     } else {
         const moe_rows rows = moe_masked_rows(N, counts, mask);
         const moe_tiles tiles = MODE == 0 ? tiles_128(rows) : down_tiles(rows, n_ntc, tmk);
@@ -400,11 +403,11 @@ __global__ __launch_bounds__(WAVES * 64, 2) void ffn_tiled_kernel(
         const int gsz = min(group, n_nt - g0 * group);         // the last group may hold fewer column tiles
         mt = within / gsz;
         nt = g0 * group + within % gsz;
+        row0 = offsets[e] + mt * tmk;
+        nrows = counts[e] - mt * tmk;
     }
     const int sp = nt % nsp;      // column tile nt / nsp, K split nt % nsp
     nt /= nsp;
-    const int row0 = offsets[e] + mt * tmk;
-    int nrows = counts[e] - mt * tmk;
     nrows = nrows > tmk ? tmk : nrows;
 #define BODY_NS(nf_, n, ns_) tile_body<MODE, nf_, n, ns_, FENCED, WAVES>(Xs, d, I, k, xsrc, perm, wa, wb, out, e, nt, row0, nrows, sp, nsp, part, R)
 #define BODY_NF(nf_, n) BODY_NS(nf_, n, NSETS)
@@ -462,8 +465,7 @@ __global__ __launch_bounds__(256) void tiled_finish_kernel(int d, int R, int N, 
     if (j >= counts[e] || (mask != nullptr && mask[e] == 0)) return;
     int tiles;
     if (direct) {
-        unsigned long long act_lo, act_hi;
-        tiles = moe_working_experts(N, counts, mask, act_lo, act_hi);
+        tiles = moe_working_experts(N, counts, offsets, mask).experts();
     } else {
         int tm;
         tiles = down_tiles(moe_masked_rows(N, counts, mask), n_ntc, tm).total;

@@ -99,49 +99,57 @@ __device__ __forceinline__ float silu_mul(float g, float u) { return g * __built
 // contiguous run of the compacted item list (expert-major), and the item's expert is found by rank among the set
 // bits.  Returns false for a block beyond the list.  All 64 lanes of the wave must call it.
 #define MOE_NUM_XCD 8
-__device__ __forceinline__ int moe_working_experts(int N, const int32_t *__restrict__ counts, const uint8_t *__restrict__ mask,
-                                                   unsigned long long &act_lo, unsigned long long &act_hi)
+// Lane l holds rows and first row of experts l and l + 64.  All reads are on their way at once: counts, then the mask where a
+// count allowed it, then rows and first row of the expert found were four round trips (0.5 to 1 us each at the start of a launch).
+struct moe_work {
+    unsigned long long lo, hi;      // the working experts
+    int c0, c1, o0, o1;
+    __device__ __forceinline__ int experts() const { return __popcll(lo) + __popcll(hi); }
+    __device__ __forceinline__ int rows_of(int e) const { return e < 64 ? __builtin_amdgcn_readlane(c0, e) : __builtin_amdgcn_readlane(c1, e - 64); }
+    __device__ __forceinline__ int first_row_of(int e) const { return e < 64 ? __builtin_amdgcn_readlane(o0, e) : __builtin_amdgcn_readlane(o1, e - 64); }
+};
+__device__ __forceinline__ moe_work moe_working_experts(int N, const int32_t *__restrict__ counts, const int32_t *__restrict__ offsets,
+                                                        const uint8_t *__restrict__ mask)
 {
-    const int l = threadIdx.x & 63;
-    const bool on_lo = l < N && counts[l] > 0 && (mask == nullptr || mask[l] != 0);
-    const bool on_hi = l + 64 < N && counts[l + 64] > 0 && (mask == nullptr || mask[l + 64] != 0);
-    act_lo = __ballot(on_lo);
-    act_hi = __ballot(on_hi);
-    return __popcll(act_lo) + __popcll(act_hi);
+    const int l = threadIdx.x & 63, l0 = min(l, N - 1), l1 = min(l + 64, N - 1);
+    moe_work w;
+    w.c0 = counts[l0];
+    w.c1 = counts[l1];
+    w.o0 = offsets[l0];
+    w.o1 = offsets[l1];
+    int m0 = 1, m1 = 1;
+    if (mask != nullptr) {
+        m0 = mask[l0];
+        m1 = mask[l1];
+    }
+    w.lo = __ballot(l < N && w.c0 > 0 && m0 != 0);
+    w.hi = __ballot(l + 64 < N && w.c1 > 0 && m1 != 0);
+    return w;
 }
 
 // the item of block pid among (working experts) x per_expert items, or false beyond the list
-__device__ __forceinline__ bool moe_item_of(unsigned long long act_lo, unsigned long long act_hi, int per_expert, int pid, int &e,
-                                            int &local)
+__device__ __forceinline__ bool moe_item_of(const moe_work &w, int per_expert, int pid, int &e, int &local)
 {
     const int l = threadIdx.x & 63;
-    const int n_lo = __popcll(act_lo);
-    const int total = (n_lo + __popcll(act_hi)) * per_expert;
+    const int n_lo = __popcll(w.lo);
+    const int total = w.experts() * per_expert;
     if (pid >= total) return false;
     const int q = total / MOE_NUM_XCD, rem = total % MOE_NUM_XCD;
     const int xcd = pid % MOE_NUM_XCD, loc = pid / MOE_NUM_XCD;
     const int L = xcd < rem ? xcd * (q + 1) + loc : rem * (q + 1) + (xcd - rem) * q + loc;
     int a = L / per_expert;
     local = L - a * per_expert;
-    unsigned long long m = act_lo;
+    unsigned long long m = w.lo;
     int base = 0;
     if (a >= n_lo) {
         a -= n_lo;
-        m = act_hi;
+        m = w.hi;
         base = 64;
     }
     const unsigned long long below = l == 0 ? 0ull : (m << (64 - l));     // the bits of m under position l
     const bool mine = ((m >> l) & 1ull) != 0 && __popcll(below) == a;
     e = base + __ffsll((unsigned long long)__ballot(mine)) - 1;
     return true;
-}
-
-__device__ __forceinline__ bool moe_working_item(int N, const int32_t *__restrict__ counts, const uint8_t *__restrict__ mask,
-                                                 int per_expert, int pid, int &e, int &local)
-{
-    unsigned long long act_lo, act_hi;
-    moe_working_experts(N, counts, mask, act_lo, act_hi);
-    return moe_item_of(act_lo, act_hi, per_expert, pid, e, local);
 }
 
 // ---- token tiles of the experts that have rows and are masked on, derived by every wave ---------------------
