@@ -54,19 +54,7 @@ __device__ __forceinline__ float wave_sum(float v)
 #define MOE_DPP_SHR(ident, v, n) \
     __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(ident), __float_as_int(v), 0x110 + (n), 0xF, 0xF, false))
 
-__device__ __forceinline__ float wave_max_dpp(float v)
-{
-    const float ninf = -__builtin_huge_valf();
-    v = fmaxf(v, MOE_DPP_SHR(ninf, v, 1));
-    v = fmaxf(v, MOE_DPP_SHR(ninf, v, 2));
-    v = fmaxf(v, MOE_DPP_SHR(ninf, v, 4));
-    v = fmaxf(v, MOE_DPP_SHR(ninf, v, 8));
-    const int b = __float_as_int(v);
-    const float r0 = __int_as_float(__builtin_amdgcn_readlane(b, 15)), r1 = __int_as_float(__builtin_amdgcn_readlane(b, 31));
-    const float r2 = __int_as_float(__builtin_amdgcn_readlane(b, 47)), r3 = __int_as_float(__builtin_amdgcn_readlane(b, 63));
-    return fmaxf(fmaxf(r0, r1), fmaxf(r2, r3));
-}
-
+// six steps on the crossbar (the rows' results broadcast to the next rows) and one read of lane 63
 __device__ __forceinline__ int wave_max_int_dpp(int v)
 {
     const int lowest = (int)0x80000000u;
@@ -74,8 +62,9 @@ __device__ __forceinline__ int wave_max_int_dpp(int v)
     v = max(v, __builtin_amdgcn_update_dpp(lowest, v, 0x112, 0xF, 0xF, false));
     v = max(v, __builtin_amdgcn_update_dpp(lowest, v, 0x114, 0xF, 0xF, false));
     v = max(v, __builtin_amdgcn_update_dpp(lowest, v, 0x118, 0xF, 0xF, false));
-    return max(max(__builtin_amdgcn_readlane(v, 15), __builtin_amdgcn_readlane(v, 31)),
-               max(__builtin_amdgcn_readlane(v, 47), __builtin_amdgcn_readlane(v, 63)));
+    v = max(v, __builtin_amdgcn_update_dpp(lowest, v, 0x142, 0xA, 0xF, false));      // lane 15 of rows 0 and 2 -> rows 1 and 3
+    v = max(v, __builtin_amdgcn_update_dpp(lowest, v, 0x143, 0xC, 0xF, false));      // lane 31 -> rows 2 and 3
+    return __builtin_amdgcn_readlane(v, 63);
 }
 
 __device__ __forceinline__ float wave_sum_dpp(float v)

@@ -41,37 +41,52 @@ __device__ __forceinline__ void top_p_of(int c0, int c1, int N, int p, int32_t *
 }
 
 // ---------------------------------------------------------------------------------------------------
-// Softmax + top-k of one token inside a wavefront: lane l holds the logits v0 of expert l and v1 of expert l + 64
-// (-inf where there is no expert).  k rounds of: wave-wide max on the DPP crossbar, then the lowest expert index
-// holding that value (ballot + find-first-set; the lower 64 experts are asked first), which is the tie rule "equal
-// scores by ascending index".  Lane s < k returns the s-th selection and its softmax score; sel = sum of the k scores.
+// Softmax + top-k of one token inside a wavefront: lane l holds the logits v0 of expert l and v1 of expert l + 64.  k rounds of:
+// wave-wide max on the DPP crossbar, then the lowest expert index holding that value (ballot + find-first-set; the lower 64
+// experts are asked first), which is the tie rule "equal scores by ascending index".  Lane s < k returns the s-th selection and its
+// softmax score; sel = sum of the k scores.
+// The rounds compare integers that order as the logits do: floats cost a canonicalisation per maximum, and four waves of a
+// SIMD share its issue slots (16 tokens of 64 experts, 6 slots: 2.3 us of a 5.6 us launch).  A logit that is no number comes
+// after every other one.
+#define NO_EXPERT ((int)0x80000000u)
+__device__ __forceinline__ int logit_key(float v)
+{
+    const int b = __float_as_int(v + 0.f);                                    // -0 and 0 are equal
+    return v != v ? NO_EXPERT + 1 : b ^ (b >> 31 & 0x7fffffff);
+}
+__device__ __forceinline__ float key_logit(int key)
+{
+    return key == NO_EXPERT + 1 ? __int_as_float(0x7fc00000) : __int_as_float(key ^ (key >> 31 & 0x7fffffff));
+}
 __device__ __forceinline__ void select_token(float v0, float v1, int N, int k, int lane, int &my_idx, float &my_p, float &sel)
 {
+    int k0 = lane < N ? logit_key(v0) : NO_EXPERT, k1 = lane + 64 < N ? logit_key(v1) : NO_EXPERT;
+    int best = wave_max_int_dpp(N > 64 ? max(k0, k1) : k0), my_best = best;
+    const float m = key_logit(best);
     const float NEG = -__builtin_huge_valf();
-    const float m = wave_max_dpp(fmaxf(v0, v1));
-    const float p0 = v0 > NEG ? expf(v0 - m) : 0.f;
-    const float p1 = v1 > NEG ? expf(v1 - m) : 0.f;
+    const float p0 = lane < N && v0 > NEG ? expf(v0 - m) : 0.f;
+    const float p1 = lane + 64 < N && v1 > NEG ? expf(v1 - m) : 0.f;
     const float den = wave_sum_dpp(p0 + p1);
     my_idx = 0;
-    float best = m, my_best = m;
-    for (int s = 0; s < k; ++s) {
-        if (s > 0) best = wave_max_dpp(fmaxf(v0, v1));
-        const unsigned long long b0 = __ballot(v0 == best);
-        const unsigned long long b1 = __ballot(v1 == best);
-        int bi;
-        if (b0 != 0ull) {
-            bi = __ffsll((long long)b0) - 1;
-            if (lane == bi) v0 = NEG;
-        } else if (b1 != 0ull) {
-            bi = __ffsll((long long)b1) - 1 + 64;
-            if (lane + 64 == bi) v1 = NEG;
-        } else {
-            bi = N - 1;                                  // only reachable with NaN logits: stay in range
+    if (N > 64) {
+        for (int s = 0; s < k; ++s) {
+            if (s > 0) best = wave_max_int_dpp(max(k0, k1));
+            const unsigned long long b0 = __ballot(k0 == best), b1 = __ballot(k1 == best);
+            const int bi = b0 != 0ull ? __ffsll((long long)b0) - 1 : 63 + __ffsll((long long)b1);
+            if (lane == bi) k0 = NO_EXPERT;
+            if (lane + 64 == bi) k1 = NO_EXPERT;
+            if (lane == s) { my_idx = bi; my_best = best; }
         }
-        if (lane == s) { my_idx = bi; my_best = best; }
+    } else {
+        for (int s = 0; s < k; ++s) {
+            if (s > 0) best = wave_max_int_dpp(k0);
+            const int bi = __ffsll((long long)__ballot(k0 == best)) - 1;
+            if (lane == bi) k0 = NO_EXPERT;
+            if (lane == s) { my_idx = bi; my_best = best; }
+        }
     }
-    // the k scores at once, one per lane: an exponential and a division in every round were a third of its time
-    my_p = expf(my_best - m) / den;
+    // the k scores at once, one per lane
+    my_p = expf(key_logit(my_best) - m) / den;
     sel = 0.f;
     for (int s = 0; s < k; ++s) sel += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_p), s));
 }
@@ -110,12 +125,28 @@ struct shared_tail {
 // expert (the popcount below the token's bit) without any serial pass.  With perm == nullptr (a prediction) the
 // workloads and the p largest of them are written instead.  Every thread of the block must call it.
 // With X.S > 0 (routing only) the tables of the layer with its shared experts appended follow from the same LDS state:
-// sel_w holds the combine weights of the R selections, cs is room for T floats.
+// sel_w holds the combine weights of the R selections, cs is room for T floats.  What depends on the thread alone is worked
+// out beforehand (decode_prep), while the logits are on their way.
+struct decode_prep {
+    int t, s;             // token and slot of selection threadIdx.x
+    int xj, xt;           // shared expert and token of the appended slot threadIdx.x
+    float xc;             // its weight, where that is known beforehand
+};
+__device__ __forceinline__ decode_prep decode_prepare(int T, int k, const shared_tail &X)
+{
+    decode_prep p;
+    p.t = threadIdx.x / k;
+    p.s = threadIdx.x - p.t * k;
+    p.xj = threadIdx.x / T;
+    p.xt = threadIdx.x - p.xj * T;
+    p.xc = X.S > 0 && X.w_sg != nullptr && X.gate != nullptr ? X.gate[p.xt] : 1.0f;
+    return p;
+}
 __device__ __forceinline__ void decode_tables(const int *sel_idx, unsigned *tokmask, int *off_s, int T, int N, int k,
                                               int32_t *__restrict__ counts, int32_t *__restrict__ offsets,
                                               int32_t *__restrict__ perm, int32_t *__restrict__ inv_perm,
                                               int32_t *__restrict__ top, int p, const float *sel_w, float *cs,
-                                              const shared_tail &X)
+                                              const shared_tail &X, const decode_prep &D)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int R = T * k;
@@ -124,7 +155,7 @@ __device__ __forceinline__ void decode_tables(const int *sel_idx, unsigned *tokm
     int my_e = -1, my_t = 0;
     if ((int)threadIdx.x < R) {
         my_e = sel_idx[threadIdx.x];
-        my_t = threadIdx.x / k;
+        my_t = D.t;
         atomicOr(&tokmask[my_e], 1u << my_t);
     }
     __syncthreads();
@@ -134,7 +165,7 @@ __device__ __forceinline__ void decode_tables(const int *sel_idx, unsigned *tokm
         const int c1 = lane + 64 < N ? __popc(tokmask[lane + 64]) : 0;
         int s0 = c0, s1 = c1;
         const int tot0 = wave_scan_int_dpp(s0);
-        wave_scan_int_dpp(s1);
+        if (N > 64) wave_scan_int_dpp(s1);
         if (lane < N) counts[lane] = c0;
         if (lane + 64 < N) counts[lane + 64] = c1;
         if (perm == nullptr) {
@@ -159,23 +190,25 @@ __device__ __forceinline__ void decode_tables(const int *sel_idx, unsigned *tokm
     if (X.S <= 0) return;
     // ---- the same layer as N + S experts with k + S slots per token (what append_shared_kernel derives from the tables)
     const int S = X.S, kx = k + S, tid = threadIdx.x, nthreads = blockDim.x;
-    for (int t = wave; t < T; t += nthreads >> 6) {
-        const float c = X.w_sg == nullptr ? 1.0f : X.gate != nullptr ? X.gate[t] : sigmoid_gate_of(X.h + (size_t)t * X.d, X.w_sg, X.d, lane);
-        if (lane == 0) cs[t] = c;
+    const bool gates_here = X.w_sg != nullptr && X.gate == nullptr;
+    if (gates_here) {
+        for (int t = wave; t < T; t += nthreads >> 6) {
+            const float c = sigmoid_gate_of(X.h + (size_t)t * X.d, X.w_sg, X.d, lane);
+            if (lane == 0) cs[t] = c;
+        }
+        __syncthreads();
     }
-    __syncthreads();
     if (tid < R) {                                             // routed slots keep their order; slot ids move to the wider stride
-        const int o = my_t * kx + (tid - my_t * k);
+        const int o = my_t * kx + D.s;
         X.x_idx[o] = my_e;
         X.x_w[o] = sel_w[tid];
         X.x_inv[o] = pos;
         X.x_perm[pos] = tid + my_t * S;
     }
-    for (int i = tid; i < T * S; i += nthreads) {              // shared expert j takes slot k + j of every token
-        const int j = i / T, t = i - j * T;
-        const int o = t * kx + k + j, row = R + j * T + t;
-        X.x_idx[o] = N + j;
-        X.x_w[o] = cs[t];
+    if (tid < T * S) {                                         // shared expert j takes slot k + j of every token
+        const int o = D.xt * kx + k + D.xj, row = R + tid;
+        X.x_idx[o] = N + D.xj;
+        X.x_w[o] = gates_here ? cs[D.xt] : D.xc;
         X.x_inv[o] = row;
         X.x_perm[row] = o;
     }
@@ -457,9 +490,8 @@ __global__ __launch_bounds__(ROUTE_THREADS) void gate_topk_kernel(int T, int d, 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if (wave < min(tokens, T - t0)) {
         const int t = t0 + wave;
-        const float NEG = -__builtin_huge_valf();
-        const float v0 = lane < N ? G.logit(lg, bias_s, wave, lane) : NEG;
-        const float v1 = NT > 4 && lane + 64 < N ? G.logit(lg, bias_s, wave, lane + 64) : NEG;
+        const float v0 = G.logit(lg, bias_s, wave, min(lane, N - 1));
+        const float v1 = NT > 4 ? G.logit(lg, bias_s, wave, min(lane + 64, N - 1)) : v0;
         int my_idx;
         float my_p, sel;
         select_token(v0, v1, N, k, lane, my_idx, my_p, sel);
@@ -478,7 +510,7 @@ __global__ __launch_bounds__(ROUTE_THREADS) void gate_topk_kernel(int T, int d, 
     __shared__ unsigned tokmask[MOE_MAX_EXPERTS];
     __shared__ int off_s[MOE_MAX_EXPERTS];
     decode_tables(reinterpret_cast<const int *>(&part[0][0][0]), tokmask, off_s, T, N, k, J.counts, J.offsets, J.perm, J.inv_perm, J.top, J.p,
-                  &part[1][0][0], &part[2][0][0], J.x);
+                  &part[1][0][0], &part[2][0][0], J.x, decode_prepare(T, k, J.x));
 }
 
 // Selection for a decode-sized batch from stored logits [T, N] (bias already added): one wavefront per token, then
@@ -495,11 +527,10 @@ __global__ __launch_bounds__(SELECT_THREADS) void select_decode_kernel(int T, in
     // all arguments at once: read where they are used, each line of them is a round trip of its own (0.4 us)
     asm volatile("" ::"s"(J.topk_idx), "s"(J.topk_w), "s"(J.counts), "s"(J.offsets), "s"(J.perm), "s"(J.inv_perm), "s"(J.norm_mode), "s"(J.x.S),
                  "s"(J.x.gate), "s"(J.x.x_idx), "s"(J.x.x_w), "s"(J.x.x_counts), "s"(J.x.x_offsets), "s"(J.x.x_perm), "s"(J.x.x_inv));
+    const float *row = J.logits + (size_t)min(t, T - 1) * N;
+    const float v0 = row[min(lane, N - 1)], v1 = row[min(lane + 64, N - 1)];
+    const decode_prep prep = decode_prepare(T, k, J.x);
     if (t < T) {
-        const float NEG = -__builtin_huge_valf();
-        const float *row = J.logits + (size_t)t * N;
-        const float v0 = lane < N ? row[lane] : NEG;
-        const float v1 = lane + 64 < N ? row[lane + 64] : NEG;
         int my_idx;
         float my_p, sel;
         select_token(v0, v1, N, k, lane, my_idx, my_p, sel);
@@ -512,7 +543,7 @@ __global__ __launch_bounds__(SELECT_THREADS) void select_decode_kernel(int T, in
         }
     }
     __syncthreads();
-    decode_tables(sel_idx, tokmask, off_s, T, N, k, J.counts, J.offsets, J.perm, J.inv_perm, J.top, J.p, sel_w, cs, J.x);
+    decode_tables(sel_idx, tokmask, off_s, T, N, k, J.counts, J.offsets, J.perm, J.inv_perm, J.top, J.p, sel_w, cs, J.x, prep);
 }
 
 // Selection from stored logits [T, N] for any batch size: one wavefront per token, 16 tokens per block.
@@ -522,10 +553,8 @@ __global__ __launch_bounds__(SELECT_THREADS) void select_rows_kernel(int T, int 
     const int lane = threadIdx.x & 63;
     const int t = blockIdx.x * (SELECT_THREADS / 64) + (threadIdx.x >> 6);
     if (t >= T) return;
-    const float NEG = -__builtin_huge_valf();
     const float *row = J.logits + (size_t)t * N;
-    const float v0 = lane < N ? row[lane] : NEG;
-    const float v1 = lane + 64 < N ? row[lane + 64] : NEG;
+    const float v0 = row[min(lane, N - 1)], v1 = row[min(lane + 64, N - 1)];
     int my_idx;
     float my_p, sel;
     select_token(v0, v1, N, k, lane, my_idx, my_p, sel);
