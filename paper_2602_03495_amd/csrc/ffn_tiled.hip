@@ -17,7 +17,7 @@
 //   * 8 waves per block (2 per SIMD, 128 fp32 accumulator registers each): one wave's barrier or load wait is
 //     covered by the other's MFMAs, and the accumulators stay in place (no AGPR shuffling).
 //   * The MFMA takes weight rows as A and token rows as B, so a lane ends up with 4 consecutive output columns
-//     of one token: SwiGLU is applied in registers and the result leaves as one 8-byte store.
+//     of one token: SwiGLU is applied in registers; the result leaves through LDS in whole runs of a row.
 // A work item is (expert, 128-row token tile, weight tile); every wave derives the item list from counts and mask
 // (moe_rank_tiles; up to 128 tokens an expert has at most one token tile and two ballots do), so empty and masked-off
 // experts cost nothing, there is no host round trip and no schedule pass ahead of the launch.  Block ids are remapped so that every XCD (own
@@ -100,7 +100,7 @@ __device__ __forceinline__ moe_tiles down_tiles(const moe_rows &c, int n_ntc, in
 // Weight tile of a block: 8 waves x NF fragments x 16 rows.  NTT = 16-row token subtiles computed (rows past
 // nrows are clamped copies whose results are dropped).
 template <int MODE, int NF, int NTT, int NSETS, bool FENCED, int WAVES>
-__device__ __forceinline__ void tile_body(uint16_t (*Xs)[2][TM * 32], int d, int I, int k, const uint16_t *__restrict__ xsrc,
+__device__ __forceinline__ void tile_body(uint16_t (*Xs)[2][TM * 32], char *ys, int d, int I, int k, const uint16_t *__restrict__ xsrc,
                                           const int32_t *__restrict__ perm, const uint16_t *__restrict__ wa,
                                           const uint16_t *__restrict__ wb, uint16_t *__restrict__ out, int e, int nt,
                                           int row0, int nrows, int sp, int nsp, float *__restrict__ part, int R)
@@ -301,11 +301,18 @@ __device__ __forceinline__ void tile_body(uint16_t (*Xs)[2][TM * 32], int d, int
         }
         return;
     }
+    // The results leave through LDS (2 KB of the wave's own), so that the lanes of a store cover whole runs of a row: stored from the
+    // accumulators, neighbouring lanes in different rows, each of the 64 lanes is an access of its own, and the next block waits
+    // for all of them (12089 rows of 64 experts, d = 2048, I = 768: up 119 us level, down 87 -> 77; 12047 rows of 32, I = 1408:
+    // down 95 -> 92; the passes 1.104 / 1.037 and 1.056 / 1.010 of the start's speed with and without).  Chunk c (16 bytes) of
+    // row i sits in slot c ^ (i & (C - 1)).
+    constexpr int C = WAVE_COLS / 8;                       // 16-byte chunks of a row
+    constexpr int TS = NTT < 8 / C ? NTT : C == 2 ? 2 : 1; // subtiles per store: all 64 lanes, where there are that many rows
+    const int yr = lane / C, yc = lane % C;
 #pragma unroll
-    for (int t = 0; t < NTT; ++t) {
-        const int tr = t * 16 + li;
-        if (tr < nrows) {
-            uint16_t *orow = out + (size_t)(row0 + tr) * NOUT + colw + 4 * lg;
+    for (int t0 = 0; t0 < NTT; t0 += TS) {
+#pragma unroll
+        for (int t = t0; t < t0 + TS && t < NTT; ++t) {
 #pragma unroll
             for (int f = 0; f < HF; ++f) {
                 u32x2 o;
@@ -316,9 +323,20 @@ __device__ __forceinline__ void tile_body(uint16_t (*Xs)[2][TM * 32], int d, int
                     o.x = pack_bf16x2(acc[f][t][0], acc[f][t][1]);
                     o.y = pack_bf16x2(acc[f][t][2], acc[f][t][3]);
                 }
-                *reinterpret_cast<u32x2 *>(orow + f * 16) = o;
+                *reinterpret_cast<u32x2 *>(ys + ((t - t0) * 16 + li) * (C * 16) + (((f * 2 + (lg >> 1)) ^ (li & (C - 1))) * 16) + (lg & 1) * 8) = o;
             }
         }
+        // the lanes of a wave exchange data: LDS serves a wave's accesses in order, the compiler keeps theirs
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+        for (int q = 0; q < TS * 16; q += 64 / C) {
+            const int i = q + yr;                          // row of the TS subtiles
+            if (i < TS * 16) {
+                const u32x4 v = *reinterpret_cast<const u32x4 *>(ys + i * (C * 16) + ((yc ^ (i & (C - 1))) * 16));
+                if (t0 * 16 + i < nrows) *reinterpret_cast<u32x4 *>(out + (size_t)(row0 + t0 * 16 + i) * NOUT + colw + yc * 8) = v;
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
 }
 
@@ -347,6 +365,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void ffn_tiled_kernel(
     int group)                                      // column tiles that alternate inside the item order of an expert (1: column tile major)
 {
     __shared__ __attribute__((aligned(16))) uint16_t Xs[2][2][TM * 32];   // [buffer][k32 half][128 tokens x 32 k]
+    __shared__ __attribute__((aligned(16))) char Ys[WAVES][2048];          // results on their way out
     // The up projection with its widest tile (NF = 4: 256 inner columns) can run its items with half that width instead:
     // also decided on the device (up_items_narrow).
     constexpr bool CAN_NARROW = MODE == 0 && NF == 4 && WAVES == 8;
@@ -409,7 +428,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void ffn_tiled_kernel(
     const int sp = nt % nsp;      // column tile nt / nsp, K split nt % nsp
     nt /= nsp;
     nrows = nrows > tmk ? tmk : nrows;
-#define BODY_NS(nf_, n, ns_) tile_body<MODE, nf_, n, ns_, FENCED, WAVES>(Xs, d, I, k, xsrc, perm, wa, wb, out, e, nt, row0, nrows, sp, nsp, part, R)
+#define BODY_NS(nf_, n, ns_) tile_body<MODE, nf_, n, ns_, FENCED, WAVES>(Xs, Ys[__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)], d, I, k, xsrc, perm, wa, wb, out, e, nt, row0, nrows, sp, nsp, part, R)
 #define BODY_NF(nf_, n) BODY_NS(nf_, n, NSETS)
     // tiles with few token rows do little arithmetic per weight byte: their speed is the speed of the weight stream, so
     // they prefetch further ahead (8 register sets instead of 4; the accumulators of a short tile leave the room)
