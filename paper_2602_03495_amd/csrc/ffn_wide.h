@@ -8,7 +8,7 @@
 //     from counts and mask on the device (wide_plan_of).
 //   * 4 waves per block, one per SIMD, 256 accumulator registers per lane: the largest tile the register file holds
 //     asks L2 for 32 KB per k32 step and 4.2 MFLOP (a little more than it holds: the epilogue of the 256-row body, with
-//     the bf16 and the fp32 stores both live, parks 13 accumulators per lane in scratch).  A wave owns 64 output columns,
+//     the bf16 and the fp32 stores both live, parks 17 registers per lane in scratch).  A wave owns 64 output columns,
 //     i.e. 4 weight fragments per step in the packed order of moe_pack_weights, loaded global -> VGPR seven steps ahead.
 //   * Activation rows go straight from global memory to LDS (buffer_load ... lds, no VGPR, no LDS store): four buffers
 //     of k64 stages, issued two and a half stages ahead.  The barrier that hands a stage over sits in the middle of the
@@ -30,7 +30,8 @@
 // few rows is shorter (measured at K = 14336: 166 us with up to 32 rows, 186, 215 and 288 with up to 64, 128 and 192, 360
 // with more), so the whole rounds have room for some of the pieces: rest16 is what exceeds them, in sixteenths of a full
 // item.  In k32 steps (0.7 us) an item takes `steps`, a piece steps / S plus about 14 for filling and draining its
-// pipeline and writing its partial sums, the finishing pass about 25 plus what it reads (256 KB per piece).
+// pipeline and writing its partial sums, the finishing pass about 25 plus what it reads (256 KB per piece; with the partial sums
+// in register order it takes half of that, 35 -> 19 us for 256 pieces, and the estimate errs to the side of fewer pieces).
 __device__ __forceinline__ int wide_cost16(int rows) { return rows <= 32 ? 7 : rows <= 64 ? 8 : rows <= 128 ? 10 : rows <= 192 ? 13 : 16; }
 
 // Lane s weighs up s pieces; the cheapest, of equals the fewest, is taken.  All 64 lanes must call it.
@@ -295,21 +296,36 @@ __device__ __forceinline__ void wide_body(char *lds, int d, int I, const uint16_
 
     // ---- epilogue: a lane holds output columns 4 lg + 0..3 of row li of every 16x16 tile
     if (n0 >= d) return;
+    if (part != nullptr) {
+        // the sums of a piece as they lie in the registers, 1 KB per tile (wide_finish_kernel knows the order): stored by rows,
+        // neighbouring lanes in different rows, each of the 64 lanes is an access of its own
+#pragma unroll
+        for (int t = 0; t < NTT; ++t)
+#pragma unroll
+            for (int f = 0; f < NF; ++f)
+                *reinterpret_cast<f32x4 *>(part + ((size_t)((wave * NF + f) * (WIDE_TM / 16) + t) * 64 + lane) * 4) = acc[f][t];
+        return;
+    }
+    // rows of y go through LDS (2 KB of this wave's own), so that eight lanes store 128 bytes of a row; chunk c (16 bytes) of row i in
+    // slot c ^ (i & 7)
+    __syncthreads();                                   // every wave is done with the stages
+    char *ys = lds + wave * 2048;
+    const int yr = lane >> 3, yc = lane & 7;
 #pragma unroll
     for (int t = 0; t < NTT; ++t) {
-        const int tr = t * 16 + li;
-        if (tr < nrows) {
-            if (part != nullptr) {
 #pragma unroll
-                for (int f = 0; f < NF; ++f)
-                    *reinterpret_cast<f32x4 *>(part + (size_t)tr * WIDE_TN + wave * (WIDE_TN / WIDE_WAVES) + f * 16 + 4 * lg) = acc[f][t];
-            } else {
+        for (int f = 0; f < NF; ++f)
+            *reinterpret_cast<u32x2 *>(ys + li * 128 + (((f * 2 + (lg >> 1)) ^ (li & 7)) * 16) + (lg & 1) * 8) =
+                u32x2{pack_bf16x2(acc[f][t][0], acc[f][t][1]), pack_bf16x2(acc[f][t][2], acc[f][t][3])};
+        // the lanes of a wave exchange data: LDS serves a wave's accesses in order, the compiler keeps theirs
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 #pragma unroll
-                for (int f = 0; f < NF; ++f)
-                    *reinterpret_cast<u32x2 *>(y + (size_t)(row0 + tr) * d + n0 + f * 16 + 4 * lg) =
-                        u32x2{pack_bf16x2(acc[f][t][0], acc[f][t][1]), pack_bf16x2(acc[f][t][2], acc[f][t][3])};
-            }
+        for (int q = 0; q < 16; q += 8) {
+            const int i = q + yr;
+            const u32x4 v = *reinterpret_cast<const u32x4 *>(ys + i * 128 + ((yc ^ (i & 7)) * 16));
+            if (t * 16 + i < nrows) *reinterpret_cast<u32x4 *>(y + (size_t)(row0 + t * 16 + i) * d + n0 + yc * 8) = v;
         }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
 }
 
@@ -371,30 +387,37 @@ __global__ __launch_bounds__(WIDE_THREADS, 1) void ffn_wide_kernel(int d, int I,
     MOE_TRACE_END(1, it.e, it.nrows, it.nt);
 }
 
-// y rows of the items that ran in pieces: the partial sums added in piece order
+// y rows of the items that ran in pieces: the partial sums added in piece order.  A block takes 64 columns (a wave's share of the
+// item) of 16 rows at a time, each wave one fragment of them; the rows are put together in LDS.
 __global__ __launch_bounds__(256) void wide_finish_kernel(int d, int steps, int N, const int32_t *__restrict__ offsets,
                                                           const int32_t *__restrict__ counts, const uint8_t *__restrict__ mask, const float *__restrict__ partial,
                                                           uint16_t *__restrict__ y, const int32_t *__restrict__ works)
 {
+    __shared__ __attribute__((aligned(16))) char ys[2][2048];
     const int n_nt = (d + WIDE_TN - 1) / WIDE_TN;
     if (*works == 0) return;
     const wide_plan plan = wide_plan_of(moe_masked_rows(N, counts, mask), n_nt, steps);
     const int whole = plan.whole, S = plan.pieces, r = plan.items - whole;
-    const int j = blockIdx.y;
+    const int j = blockIdx.y, w = blockIdx.x % 4;
     if (S == 1 || j >= r) return;
     const wide_item it = wide_item_of(whole + j, n_nt, plan.tiles, offsets, counts);
-    const int c = (threadIdx.x & 31) * 8;
-    if (it.nt * WIDE_TN + c >= d) return;
-    for (int row = blockIdx.x * 8 + (threadIdx.x >> 5); row < it.nrows; row += 8 * gridDim.x) {
-        const float *p = partial + ((size_t)j * WIDE_TM + row) * WIDE_TN + c;
-        f32x4 a = *reinterpret_cast<const f32x4 *>(p), b = *reinterpret_cast<const f32x4 *>(p + 4);
+    const int col = it.nt * WIDE_TN + w * 64;
+    if (col >= d) return;
+    const int lane = threadIdx.x & 63, f = threadIdx.x >> 6, li = lane & 15, lg = lane >> 4;
+    const int nt16 = (it.nrows + 15) / 16;
+    int b = 0;
+    for (int t = blockIdx.x / 4; t < nt16; t += gridDim.x / 4, b ^= 1) {
+        const float *p = partial + ((((size_t)j * 16 + w * 4 + f) * (WIDE_TM / 16) + t) * 64 + lane) * 4;
+        f32x4 a = *reinterpret_cast<const f32x4 *>(p);
         for (int s = 1; s < S; ++s) {
             p += (size_t)r * WIDE_TM * WIDE_TN;
             a += *reinterpret_cast<const f32x4 *>(p);
-            b += *reinterpret_cast<const f32x4 *>(p + 4);
         }
-        *reinterpret_cast<u32x4 *>(y + (size_t)(it.row0 + row) * d + it.nt * WIDE_TN + c) =
-            u32x4{pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3]), pack_bf16x2(b[0], b[1]), pack_bf16x2(b[2], b[3])};
+        *reinterpret_cast<u32x2 *>(ys[b] + li * 128 + (((f * 2 + (lg >> 1)) ^ (li & 7)) * 16) + (lg & 1) * 8) = u32x2{pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3])};
+        __syncthreads();
+        const int i = threadIdx.x >> 3, c = threadIdx.x & 7;
+        if (i < 16 && t * 16 + i < it.nrows)
+            *reinterpret_cast<u32x4 *>(y + (size_t)(it.row0 + t * 16 + i) * d + col + c * 8) = *reinterpret_cast<const u32x4 *>(ys[b] + i * 128 + ((c ^ (i & 7)) * 16));
     }
 }
 
@@ -409,7 +432,7 @@ static int moe_ffn_wide_down(const moe_shape *s, const int32_t *offsets, const i
                        (const uint16_t *)w2, mask, (uint16_t *)y, partial, works);
     MOE_CHECK_LAUNCH();
     const long cut = max_items < WIDE_MAX_PIECES / 2 ? max_items : WIDE_MAX_PIECES / 2;      // an item that is cut has two pieces or more
-    hipLaunchKernelGGL(wide_finish_kernel, dim3(4, (unsigned)cut), dim3(256), 0, st, d, I / 32, N, offsets, counts, mask, partial, (uint16_t *)y, works);
+    hipLaunchKernelGGL(wide_finish_kernel, dim3(16, (unsigned)cut), dim3(256), 0, st, d, I / 32, N, offsets, counts, mask, partial, (uint16_t *)y, works);
     MOE_CHECK_LAUNCH();
     return MOE_OK;
 }
