@@ -289,14 +289,19 @@ __device__ __forceinline__ void tile_body(uint16_t (*Xs)[2][TM * 32], char *ys, 
     const int colw = n0 + wave * WAVE_COLS;
     if (colw >= NOUT) return;                               // wave past the ragged edge: its columns were recomputed only
     if (MODE == 1 && nsp > 1) {
-        // one of nsp partial sums over K: fp32, summed in split order by the finishing pass
+        // one of nsp partial sums over K: fp32, summed in split order by the finishing pass; four lanes to the 64 bytes of a row, as
+        // below, chunk c of row i in slot c ^ (i >> 2 & 3)
+        const int pr = lane >> 2, pc = lane & 3;
 #pragma unroll
         for (int t = 0; t < NTT; ++t) {
-            const int tr = t * 16 + li;
-            if (tr < nrows) {
-                float *prow = part + ((size_t)sp * R + row0 + tr) * NOUT + colw + 4 * lg;
 #pragma unroll
-                for (int f = 0; f < HF; ++f) *reinterpret_cast<f32x4 *>(prow + f * 16) = acc[f][t];
+            for (int f = 0; f < HF; ++f) {
+                char *b = ys + (f & 1) * 1024;
+                *reinterpret_cast<f32x4 *>(b + li * 64 + (lg ^ (li >> 2 & 3)) * 16) = acc[f][t];
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                const f32x4 v = *reinterpret_cast<const f32x4 *>(b + pr * 64 + (pc ^ (pr >> 2 & 3)) * 16);
+                if (t * 16 + pr < nrows) *reinterpret_cast<f32x4 *>(part + ((size_t)sp * R + row0 + t * 16 + pr) * NOUT + colw + f * 16 + pc * 4) = v;
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             }
         }
         return;
