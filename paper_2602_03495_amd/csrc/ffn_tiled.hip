@@ -476,6 +476,19 @@ __global__ __launch_bounds__(WAVES * 64, 2) void ffn_tiled_kernel(
 #undef BODY_NS
 }
 
+// four columns of a row, the partial sums of all S splits on their way at once
+template <int S>
+__device__ __forceinline__ void add_splits(const float *__restrict__ partial, size_t p, int R, int d, int f, uint16_t *__restrict__ y)
+{
+    f32x4 v[S];
+#pragma unroll
+    for (int ks = 0; ks < S; ++ks) v[ks] = *reinterpret_cast<const f32x4 *>(partial + ((size_t)ks * R + p) * d + f);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int ks = 1; ks < S; ++ks) v[0] += v[ks];
+    *reinterpret_cast<u32x2 *>(y + p * d + f) = u32x2{pack_bf16x2(v[0][0], v[0][1]), pack_bf16x2(v[0][2], v[0][3])};
+}
+
 // y[p,:] = bf16( sum over the K splits, in split order ), when the down projection of this launch split K (the same
 // device-side decision as in ffn_tiled_kernel; nothing to do otherwise: the tiles wrote y themselves)
 __global__ __launch_bounds__(256) void tiled_finish_kernel(int d, int R, int N, int n_ntc, int nsp_max, int direct,
@@ -483,10 +496,10 @@ __global__ __launch_bounds__(256) void tiled_finish_kernel(int d, int R, int N, 
                                                            const int32_t *__restrict__ offsets, const int32_t *__restrict__ counts,
                                                            const uint8_t *__restrict__ mask, uint16_t *__restrict__ y)
 {
-    // first, because most blocks have no row (there is one for every token and expert): ranking the tiles in all 48000 of
-    // 3000 tokens and 16 experts took 25 of 99 us (d = 1024, I = 4096)
-    const int e = blockIdx.y, j = blockIdx.x;
-    if (j >= counts[e] || (mask != nullptr && mask[e] == 0)) return;
+    // Blocks walk the rows of their expert: with one for every token and expert, most had no row (3000 tokens, 16 experts: ranking
+    // the tiles in all 48000 of them took 25 of 99 us), and where the launch did not split all of them ranked for nothing.
+    const int e = blockIdx.y, c = counts[e];
+    if ((int)blockIdx.x >= c || (mask != nullptr && mask[e] == 0)) return;
     int tiles;
     if (direct) {
         tiles = moe_working_experts(N, counts, offsets, mask).experts();
@@ -496,17 +509,13 @@ __global__ __launch_bounds__(256) void tiled_finish_kernel(int d, int R, int N, 
     }
     const int nsp = moe_dev_splits(tiles * n_ntc, nsp_max);
     if (nsp == 1) return;
-    const size_t p = (size_t)offsets[e] + j;
-    for (int f = threadIdx.x * 4; f < d; f += 1024) {
-        float4 a = *reinterpret_cast<const float4 *>(partial + p * d + f);
-        for (int ks = 1; ks < nsp; ++ks) {
-            const float4 b = *reinterpret_cast<const float4 *>(partial + ((size_t)ks * R + p) * d + f);
-            a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w;
-        }
-        uint2 o;
-        o.x = pack_bf16x2(a.x, a.y);
-        o.y = pack_bf16x2(a.z, a.w);
-        *reinterpret_cast<uint2 *>(y + p * d + f) = o;
+    const int f = (blockIdx.z * 256 + threadIdx.x) * 4;
+    if (f >= d) return;
+    const size_t row0 = offsets[e];
+    for (int j = blockIdx.x; j < c; j += gridDim.x) {
+        if (nsp == 2) add_splits<2>(partial, row0 + j, R, d, f, y);
+        else if (nsp == 4) add_splits<4>(partial, row0 + j, R, d, f, y);
+        else add_splits<8>(partial, row0 + j, R, d, f, y);
     }
 }
 
@@ -632,8 +641,9 @@ int moe_ffn_tiled_impl(const moe_shape *s, const void *h, const int32_t *perm, c
         MOE_CHECK_LAUNCH();
         const int cols = 16 * waves_down * nf;      // of an item
         if (nsp_max > 1) {
-            const int max_rows = s->T < (int)R ? s->T : (int)R;
-            hipLaunchKernelGGL(tiled_finish_kernel, dim3(max_rows, N), dim3(256), 0, st, d, (int)R, N, (d + cols - 1) / cols, nsp_max,
+            const int slices = (d + 1023) / 1024, blocks = 2048 / (N * slices);
+            const int max_rows = s->T < (blocks > 64 ? blocks : 64) ? s->T : blocks > 64 ? blocks : 64;
+            hipLaunchKernelGGL(tiled_finish_kernel, dim3(max_rows, N, slices), dim3(256), 0, st, d, (int)R, N, (d + cols - 1) / cols, nsp_max,
                                s->T <= TM ? 1 : 0, part, offsets, counts, expert_mask, (uint16_t *)y);
             MOE_CHECK_LAUNCH();
         }
