@@ -26,8 +26,8 @@
 // run up to 40 % slower, even with one token tile per expert).
 // Tiles are rarely full: the launch bounds the 16-row subtiles by T and every block runs the body sized for its own
 // row count (16, 32, 64, 96, 112 or 128 rows).
-// What only the device knows (counts and mask) also shapes the launch there: with few working tiles the up projection
-// switches to half-width items and the down projection splits the K range of its tiles over several items (fp32 partial
+// What only the device knows (counts and mask) also shapes the launch there: the last items of the up projection
+// run at half width where they would fill less than half a round of compute units, and the down projection splits the K range of its tiles over several items (fp32 partial
 // sums, summed in split order by tiled_finish_kernel); with many, the blocks pick the token-tile height of
 // the down projection so that its items fill whole rounds of compute units.
 // Each item walks K as a ring starting at an expert-dependent offset, so that the token tiles that share a weight tile
@@ -61,7 +61,6 @@ extern "C" int moe_debug_set_trace(unsigned long long *records)
     } while (0)
 
 #define TM MOE_TILE_M     // token rows per tile
-#define NUM_XCD MOE_NUM_XCD
 #define TILED_THREADS 512
 
 // The up projection uses 128-row tiles.  The down projection has few
@@ -345,15 +344,29 @@ __device__ __forceinline__ void tile_body(uint16_t (*Xs)[2][TM * 32], char *ys, 
     }
 }
 
-// Whether the up projection runs its items at half width: twice as many items, each about 0.6 of the time (measured),
-// so it pays when the rounds the launch needs on 256 compute units do not double: up to 128 items (one round either
-// way), or just above a whole number of rounds (280 items: 2 rounds of wide items against 3 of narrow ones; from 3 rounds
-// on, 5 or 6 of narrow ones are never fewer than 5 thirds of that).
-#define UP_NARROW_MAX_ITEMS (3 * 256)
-__device__ __forceinline__ bool up_items_narrow(int items)
+// Item of a block of the up projection.  Every XCD takes a contiguous run of the item list on its 32 compute units.  Where the
+// last round of the launch would occupy less than half of the units, its items run as two of half the width each (0.6 of the time,
+// measured): the round ends after 0.6 of an item instead of a whole one; with more the halves would not fit one round (1.2).
+// d = 2048, I = 768, whole / cut: 522 items of 256 inner columns 195 / 176 us, 636 198 / 185, 783 237 / 220, 1035 298 / 282; the
+// rounds of 261 to 381 items, all of which ran as halves before, 139 / 137 to 166 / 160.
+// 128 and 384 items, an exact half of a round, run as halves altogether: one and three full rounds of them (384: 165 us, 161 with
+// the last ones only; a test counts their blocks).
+// Returns the item, or -1 for a block without one; half is 0 or 1, or -1 for a whole item.
+#define XCD_CUS 32
+#define UP_HALVES_ITEMS 384
+__device__ __forceinline__ int up_item_of(int total, int pid, int &half)
 {
-    const int wide = (items + 255) / 256, narrow = (2 * items + 255) / 256;
-    return narrow * 3 < wide * 5;
+    const int q = total / MOE_NUM_XCD, rem = total % MOE_NUM_XCD;
+    const int xcd = pid % MOE_NUM_XCD, loc = pid / MOE_NUM_XCD;
+    const int n = q + (xcd < rem ? 1 : 0), first = xcd * q + min(xcd, rem);
+    const int over = total % (MOE_NUM_XCD * XCD_CUS), half_round = MOE_NUM_XCD * XCD_CUS / 2;
+    const int cut = over < half_round ? n % XCD_CUS : over == half_round && total <= UP_HALVES_ITEMS ? n : 0, whole = n - cut;
+    half = -1;
+    if (loc < whole) return first + loc;
+    const int j = loc - whole;
+    if (j >= 2 * cut) return -1;
+    half = j & 1;
+    return first + whole + (j >> 1);
 }
 
 // NTT_MAX bounds the token subtiles a tile of this launch can need (from T); the block then runs the smallest
@@ -371,12 +384,11 @@ __global__ __launch_bounds__(WAVES * 64, 2) void ffn_tiled_kernel(
 {
     __shared__ __attribute__((aligned(16))) uint16_t Xs[2][2][TM * 32];   // [buffer][k32 half][128 tokens x 32 k]
     __shared__ __attribute__((aligned(16))) char Ys[WAVES][2048];          // results on their way out
-    // The up projection with its widest tile (NF = 4: 256 inner columns) can run its items with half that width instead:
-    // also decided on the device (up_items_narrow).
+    // The up projection with its widest tile (NF = 4: 256 inner columns) can run an item with half that width instead (up_item_of).
     constexpr bool CAN_NARROW = MODE == 0 && NF == 4 && WAVES == 8;
     constexpr int NT_COLS = WAVES * 16 * (MODE == 0 ? NF / 2 : NF);
-    int n_ntc = ((MODE == 0 ? I : d) + NT_COLS - 1) / NT_COLS;   // column tiles
-    bool narrow = false;
+    const int n_ntc = ((MODE == 0 ? I : d) + NT_COLS - 1) / NT_COLS;   // column tiles
+    int half = -1;
 
     // ---- which item: (expert, token tile, column tile, K split).  The number of K splits follows from the number of
     // tiles that have work, which only the device knows (counts and mask live there)
@@ -388,11 +400,13 @@ __global__ __launch_bounds__(WAVES * 64, 2) void ffn_tiled_kernel(
         const moe_work work = moe_working_experts(N, counts, offsets, mask);
         const int n_work = work.experts();
         if (MODE == 1) nsp = moe_dev_splits(n_work * n_ntc, nsp_max);
-        if (CAN_NARROW && up_items_narrow(n_work * n_ntc)) {
-            narrow = true;
-            n_ntc = (I + NT_COLS / 2 - 1) / (NT_COLS / 2);
+        if (CAN_NARROW) {
+            const int L = up_item_of(n_work * n_ntc, blockIdx.x, half);
+            if (L < 0) return;
+            moe_item_at(work, n_ntc, L, e, nt);
+        } else if (!moe_item_of(work, n_ntc * nsp, blockIdx.x, e, nt)) {
+            return;
         }
-        if (!moe_item_of(work, n_ntc * nsp, blockIdx.x, e, nt)) return;
         mt = 0;
         row0 = work.first_row_of(e);
         nrows = work.rows_of(e);
@@ -405,17 +419,16 @@ __global__ __launch_bounds__(WAVES * 64, 2) void ffn_tiled_kernel(
             if (blockIdx.x == 0 && threadIdx.x == 0) *rival = wide;
             if (wide) return;
         }
-        if (CAN_NARROW && up_items_narrow(tiles.total * n_ntc)) {
-            narrow = true;
-            n_ntc = (I + NT_COLS / 2 - 1) / (NT_COLS / 2);
-        }
         const int n_nt = n_ntc * nsp;
         const int total = tiles.total * n_nt;
-        const int pid = blockIdx.x;
-        if (pid >= total) return;
-        const int q = total / NUM_XCD, rem = total % NUM_XCD;
-        const int xcd = pid % NUM_XCD, loc = pid / NUM_XCD;
-        const int L = xcd < rem ? xcd * (q + 1) + loc : rem * (q + 1) + (xcd - rem) * q + loc;
+        int L;
+        if (CAN_NARROW) {
+            L = up_item_of(total, blockIdx.x, half);
+            if (L < 0) return;
+        } else {
+            if ((int)blockIdx.x >= total) return;
+            L = moe_xcd_run(total, blockIdx.x);
+        }
         int first, n;
         moe_find_tile(tiles, L / n_nt, e, first, n);
         const int local = L - first * n_nt;
@@ -458,11 +471,12 @@ __global__ __launch_bounds__(WAVES * 64, 2) void ffn_tiled_kernel(
     } while (0)
     if constexpr (CAN_NARROW) {
         // a ragged last column tile that fits a half-width item runs as one (I = 1408: five items of 256 + one of 128)
-        if (!narrow && nt == n_ntc - 1 && I % NT_COLS != 0 && I % NT_COLS <= NT_COLS / 2) {
-            narrow = true;
-            nt *= 2;
+        if (nt == n_ntc - 1 && I % NT_COLS != 0 && I % NT_COLS <= NT_COLS / 2) {
+            if (half == 1) return;
+            half = 0;
         }
-        if (narrow) {
+        if (half >= 0) {
+            nt = 2 * nt + half;
             BODIES(2);
             MOE_TRACE_END(MODE, e, nrows, nt);
             return;
@@ -542,11 +556,10 @@ static void launch_tiled(const moe_shape *s, long max_mt, const uint16_t *x, con
     const long tiles = DIRECT ? n_e : max_mt;
     long blocks = tiles * n_ntc * nsp_max;
     if (MODE == 0 && NF == 4 && WAVES == 8) {
-        // ... or the half-width items of the up projection, which run where that takes at most 3 rounds (up_items_narrow).
-        // With a block for every half-width item, whatever their number, the blocks without an item took longer than those
-        // with one on short items (229 tokens over 100 experts, d = 256, I = 6272: 4949 blocks for 1600 items).
-        const long narrow = tiles * ((s->I + cols / 2 - 1) / (cols / 2));
-        blocks = blocks > UP_NARROW_MAX_ITEMS ? blocks : narrow < UP_NARROW_MAX_ITEMS ? narrow : UP_NARROW_MAX_ITEMS;
+        // and the items that run as two (up_item_of)
+        const long halves = blocks >= UP_HALVES_ITEMS ? 2 * UP_HALVES_ITEMS : 0;
+        blocks += MOE_NUM_XCD * (XCD_CUS / 2);
+        if (blocks < halves) blocks = halves;
     }
     const dim3 grid((unsigned)blocks);
     hipLaunchKernelGGL((ffn_tiled_kernel<MODE, NF, NTT, DIRECT, NSETS, FENCED, WAVES>), grid, dim3(WAVES * 64), 0, st, s->d, s->I, s->k,

@@ -116,16 +116,19 @@ __device__ __forceinline__ moe_work moe_working_experts(int N, const int32_t *__
     return w;
 }
 
-// the item of block pid among (working experts) x per_expert items, or false beyond the list
-__device__ __forceinline__ bool moe_item_of(const moe_work &w, int per_expert, int pid, int &e, int &local)
+// place of block pid in a list of total items of which every XCD takes a contiguous run (pid < total)
+__device__ __forceinline__ int moe_xcd_run(int total, int pid)
+{
+    const int q = total / MOE_NUM_XCD, rem = total % MOE_NUM_XCD;
+    const int xcd = pid % MOE_NUM_XCD, loc = pid / MOE_NUM_XCD;
+    return xcd < rem ? xcd * (q + 1) + loc : rem * (q + 1) + (xcd - rem) * q + loc;
+}
+
+// item L of (working experts) x per_expert items: its expert and its place there
+__device__ __forceinline__ void moe_item_at(const moe_work &w, int per_expert, int L, int &e, int &local)
 {
     const int l = threadIdx.x & 63;
     const int n_lo = __popcll(w.lo);
-    const int total = w.experts() * per_expert;
-    if (pid >= total) return false;
-    const int q = total / MOE_NUM_XCD, rem = total % MOE_NUM_XCD;
-    const int xcd = pid % MOE_NUM_XCD, loc = pid / MOE_NUM_XCD;
-    const int L = xcd < rem ? xcd * (q + 1) + loc : rem * (q + 1) + (xcd - rem) * q + loc;
     int a = L / per_expert;
     local = L - a * per_expert;
     unsigned long long m = w.lo;
@@ -138,6 +141,14 @@ __device__ __forceinline__ bool moe_item_of(const moe_work &w, int per_expert, i
     const unsigned long long below = l == 0 ? 0ull : (m << (64 - l));     // the bits of m under position l
     const bool mine = ((m >> l) & 1ull) != 0 && __popcll(below) == a;
     e = base + __ffsll((unsigned long long)__ballot(mine)) - 1;
+}
+
+// the item of block pid, or false beyond the list
+__device__ __forceinline__ bool moe_item_of(const moe_work &w, int per_expert, int pid, int &e, int &local)
+{
+    const int total = w.experts() * per_expert;
+    if (pid >= total) return false;
+    moe_item_at(w, per_expert, moe_xcd_run(total, pid), e, local);
     return true;
 }
 
