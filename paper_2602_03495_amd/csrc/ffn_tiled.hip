@@ -26,7 +26,7 @@
 // run up to 40 % slower, even with one token tile per expert).
 // Tiles are rarely full: the launch bounds the 16-row subtiles by T and every block runs the body sized for its own
 // row count (16, 32, 64, 96, 112 or 128 rows).
-// What only the device knows (counts and mask) also shapes the launch there: the last items of the up projection
+// What only the device knows (counts and mask) also shapes the launch there: the last items of a launch
 // run at half width where they would fill less than half a round of compute units, and the down projection splits the K range of its tiles over several items (fp32 partial
 // sums, summed in split order by tiled_finish_kernel); with many, the blocks pick the token-tile height of
 // the down projection so that its items fill whole rounds of compute units.
@@ -344,23 +344,26 @@ __device__ __forceinline__ void tile_body(uint16_t (*Xs)[2][TM * 32], char *ys, 
     }
 }
 
-// Item of a block of the up projection.  Every XCD takes a contiguous run of the item list on its 32 compute units.  Where the
+// Item of a block of a launch that can cut.  Every XCD takes a contiguous run of the item list on its 32 compute units.  Where the
 // last round of the launch would occupy less than half of the units, its items run as two of half the width each (0.6 of the time,
 // measured): the round ends after 0.6 of an item instead of a whole one; with more the halves would not fit one round (1.2).
-// d = 2048, I = 768, whole / cut: 522 items of 256 inner columns 195 / 176 us, 636 198 / 185, 783 237 / 220, 1035 298 / 282; the
-// rounds of 261 to 381 items, all of which ran as halves before, 139 / 137 to 166 / 160.
-// 128 and 384 items, an exact half of a round, run as halves altogether: one and three full rounds of them (384: 165 us, 161 with
-// the last ones only; a test counts their blocks).
+// Up, d = 2048, I = 768, whole / cut: 522 items of 256 inner columns 195 / 176 us, 636 198 / 185, 783 237 / 220, 1035 298 / 282; the
+// rounds of 261 to 381 items, all of which ran as halves before, 139 / 137 to 166 / 160.  Down, same layer: 40 items of 512 columns
+// 28 / 21 us, 124 32 / 28, 260 69 / 62, 376 73 / 72, 528 86 / 79, 800 118 / 111, launches that are not cut 0 to 1 % slower.
+// 128 and 384 items, an exact half of a round, run as halves altogether: one and three full rounds of them (384 of the up
+// projection: 165 us, 161 with the last ones only; a test counts their blocks).
 // Returns the item, or -1 for a block without one; half is 0 or 1, or -1 for a whole item.
 #define XCD_CUS 32
-#define UP_HALVES_ITEMS 384
-__device__ __forceinline__ int up_item_of(int total, int pid, int &half)
+#define HALVES_ITEMS 384
+// Not cut: the narrowest tiles, and the down projection over a K of 8192 and more, whose time wide_faster weighs against the long-K kernel.
+constexpr bool tiled_can_cut(int mode, int nf, bool fenced, int waves) { return waves == 8 && nf > 1 && (mode == 0 || !fenced); }
+__device__ __forceinline__ int cut_item_of(int total, int pid, int &half)
 {
     const int q = total / MOE_NUM_XCD, rem = total % MOE_NUM_XCD;
     const int xcd = pid % MOE_NUM_XCD, loc = pid / MOE_NUM_XCD;
     const int n = q + (xcd < rem ? 1 : 0), first = xcd * q + min(xcd, rem);
     const int over = total % (MOE_NUM_XCD * XCD_CUS), half_round = MOE_NUM_XCD * XCD_CUS / 2;
-    const int cut = over < half_round ? n % XCD_CUS : over == half_round && total <= UP_HALVES_ITEMS ? n : 0, whole = n - cut;
+    const int cut = over < half_round ? n % XCD_CUS : over == half_round && total <= HALVES_ITEMS ? n : 0, whole = n - cut;
     half = -1;
     if (loc < whole) return first + loc;
     const int j = loc - whole;
@@ -384,8 +387,8 @@ __global__ __launch_bounds__(WAVES * 64, 2) void ffn_tiled_kernel(
 {
     __shared__ __attribute__((aligned(16))) uint16_t Xs[2][2][TM * 32];   // [buffer][k32 half][128 tokens x 32 k]
     __shared__ __attribute__((aligned(16))) char Ys[WAVES][2048];          // results on their way out
-    // The up projection with its widest tile (NF = 4: 256 inner columns) can run an item with half that width instead (up_item_of).
-    constexpr bool CAN_NARROW = MODE == 0 && NF == 4 && WAVES == 8;
+    // a launch that can run an item as two of half its width (cut_item_of)
+    constexpr bool CAN_CUT = tiled_can_cut(MODE, NF, FENCED, WAVES);
     constexpr int NT_COLS = WAVES * 16 * (MODE == 0 ? NF / 2 : NF);
     const int n_ntc = ((MODE == 0 ? I : d) + NT_COLS - 1) / NT_COLS;   // column tiles
     int half = -1;
@@ -400,8 +403,8 @@ __global__ __launch_bounds__(WAVES * 64, 2) void ffn_tiled_kernel(
         const moe_work work = moe_working_experts(N, counts, offsets, mask);
         const int n_work = work.experts();
         if (MODE == 1) nsp = moe_dev_splits(n_work * n_ntc, nsp_max);
-        if (CAN_NARROW) {
-            const int L = up_item_of(n_work * n_ntc, blockIdx.x, half);
+        if (CAN_CUT && nsp == 1) {
+            const int L = cut_item_of(n_work * n_ntc, blockIdx.x, half);
             if (L < 0) return;
             moe_item_at(work, n_ntc, L, e, nt);
         } else if (!moe_item_of(work, n_ntc * nsp, blockIdx.x, e, nt)) {
@@ -422,8 +425,8 @@ __global__ __launch_bounds__(WAVES * 64, 2) void ffn_tiled_kernel(
         const int n_nt = n_ntc * nsp;
         const int total = tiles.total * n_nt;
         int L;
-        if (CAN_NARROW) {
-            L = up_item_of(total, blockIdx.x, half);
+        if (CAN_CUT && nsp == 1) {
+            L = cut_item_of(total, blockIdx.x, half);
             if (L < 0) return;
         } else {
             if ((int)blockIdx.x >= total) return;
@@ -469,18 +472,21 @@ __global__ __launch_bounds__(WAVES * 64, 2) void ffn_tiled_kernel(
         else if (MODE == 1 && nrows <= 112) BODY_NF(nf_, 7);       \
         else BODY_NF(nf_, 8);                                      \
     } while (0)
-    if constexpr (CAN_NARROW) {
+    if constexpr (CAN_CUT) {
         // a ragged last column tile that fits a half-width item runs as one (I = 1408: five items of 256 + one of 128)
-        if (nt == n_ntc - 1 && I % NT_COLS != 0 && I % NT_COLS <= NT_COLS / 2) {
+        if (MODE == 0 && nt == n_ntc - 1 && I % NT_COLS != 0 && I % NT_COLS <= NT_COLS / 2) {
             if (half == 1) return;
             half = 0;
         }
-        if (half >= 0) {
-            nt = 2 * nt + half;
-            BODIES(2);
+        if (__builtin_expect(half < 0, 1)) {
+            BODIES(NF);
             MOE_TRACE_END(MODE, e, nrows, nt);
             return;
         }
+        nt = 2 * nt + half;
+        BODIES(NF / 2);
+        MOE_TRACE_END(MODE, e, nrows, nt);
+        return;
     }
     BODIES(NF);
     MOE_TRACE_END(MODE, e, nrows, nt);
@@ -555,9 +561,9 @@ static void launch_tiled(const moe_shape *s, long max_mt, const uint16_t *x, con
     const long n_e = s->N < (long)s->T * s->k ? s->N : (long)s->T * s->k;   // DIRECT: experts that can be non-empty
     const long tiles = DIRECT ? n_e : max_mt;
     long blocks = tiles * n_ntc * nsp_max;
-    if (MODE == 0 && NF == 4 && WAVES == 8) {
-        // and the items that run as two (up_item_of)
-        const long halves = blocks >= UP_HALVES_ITEMS ? 2 * UP_HALVES_ITEMS : 0;
+    if (tiled_can_cut(MODE, NF, FENCED, WAVES)) {
+        // and the items that run as two (cut_item_of)
+        const long halves = blocks >= HALVES_ITEMS ? 2 * HALVES_ITEMS : 0;
         blocks += MOE_NUM_XCD * (XCD_CUS / 2);
         if (blocks < halves) blocks = halves;
     }
