@@ -295,6 +295,7 @@ __device__ __forceinline__ void wide_body(char *lds, int d, int I, const uint16_
     wait_vmem<0>();                                    // no load may write LDS after the block has gone
 
     // ---- epilogue: a lane holds output columns 4 lg + 0..3 of row li of every 16x16 tile
+    if (part == nullptr) __syncthreads();              // every wave is done with the stages, the ones past the edge of y among them
     if (n0 >= d) return;
     if (part != nullptr) {
         // the sums of a piece as they lie in the registers, 1 KB per tile (wide_finish_kernel knows the order): stored by rows,
@@ -308,7 +309,6 @@ __device__ __forceinline__ void wide_body(char *lds, int d, int I, const uint16_
     }
     // rows of y go through LDS (2 KB of this wave's own), so that eight lanes store 128 bytes of a row; chunk c (16 bytes) of row i in
     // slot c ^ (i & 7)
-    __syncthreads();                                   // every wave is done with the stages
     char *ys = lds + wave * 2048;
     const int yr = lane >> 3, yc = lane & 7;
 #pragma unroll
