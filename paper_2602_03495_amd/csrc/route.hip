@@ -268,6 +268,14 @@ __device__ __forceinline__ u32x4 residual_rows(const float *__restrict__ r, int 
     return o;
 }
 
+// res_vec . W from the products of its three parts.  Where the first is not finite it is the whole result: hi is zero only where the
+// residual is (or is below the smallest bf16 number), the lower parts are zero wherever hi is exact, and zero times an infinite
+// weight would turn the infinity into NaN.
+__device__ __forceinline__ float residual_sum(float hi, float mid, float lo)
+{
+    return __builtin_fabsf(hi) < __builtin_huge_valf() ? (lo + mid) + hi : hi;
+}
+
 // 16 rows x 32 k, lane l holding chunk l % 4 of row l / 4, to an MFMA operand (row l % 16, chunk l / 16); from_lane: four times the
 // lane this one's data comes from
 __device__ __forceinline__ bf16x8 rows_to_frag(u32x4 v, int from_lane)
@@ -391,7 +399,7 @@ template <int NT, bool FOLD> struct gate_tile {
     __device__ __forceinline__ float logit(const float (&lg)[ROUTE_TOKENS][NP + 4], const float (&bias_s)[NP], int tt, int e) const
     {
         float b = bias_s[e];
-        if (FOLD && res_vec != nullptr) b = ((lg[FOLD_ROW + 2][e] + lg[FOLD_ROW + 1][e]) + lg[FOLD_ROW][e]) + b;
+        if (FOLD && res_vec != nullptr) b = residual_sum(lg[FOLD_ROW][e], lg[FOLD_ROW + 1][e], lg[FOLD_ROW + 2][e]) + b;
         return lg[tt][e] + b;
     }
     static __device__ __forceinline__ void load_bias(float (&bias_s)[NP], const float *bias, int e_base, int N)

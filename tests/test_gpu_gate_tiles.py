@@ -71,3 +71,21 @@ def test_an_infinite_residual_element_makes_infinite_logits_not_nan(gpu):
     B.moe_predict_workload(s, torch.ones(T, d, device="cuda").bfloat16(), rv, W.bfloat16(), None, 2, pc, top, B.alloc_workspace(s))
     torch.cuda.synchronize()
     assert pc.tolist() == [T, 0, T, 0, 0, 0, 0, 0] and top.tolist() == [0, 2]
+
+
+@pytest.mark.parametrize("T,N", [(1, 8), (13, 16), (16, 8), (16, 40), (21, 8), (21, 64)])
+def test_an_infinite_gate_weight_makes_an_infinite_logit_not_nan(gpu, T, N):
+    # the residual's lower parts are zero where it is a bf16 number: times an infinity they are NaN, and such a logit comes last
+    B, _ = gpu
+    d, k = 256, 2
+    W = torch.zeros(N, d, device="cuda")
+    W[3, 7], W[5, 7] = float("inf"), float("-inf")
+    rv = torch.zeros(d, device="cuda")
+    rv[7] = 1.0
+    s = B.shape(T, d, N, k, 128)
+    pc, top = torch.empty(N, dtype=torch.int32, device="cuda"), torch.empty(2, dtype=torch.int32, device="cuda")
+    h = torch.zeros(T, d, device="cuda")
+    h[:, 7] = 1.0                                        # zero times infinity in the token's own product is NaN in any order
+    B.moe_predict_workload(s, h.bfloat16(), rv, W.bfloat16(), None, 2, pc, top, B.alloc_workspace(s))
+    torch.cuda.synchronize()
+    assert pc.tolist() == [T, 0, 0, T] + [0] * (N - 4) and top.tolist() == [0, 3]
