@@ -22,7 +22,12 @@
 #define ROUTE_TOKENS 16      // tokens per block of gate_topk_kernel
 #define ROUTE_THREADS 1024
 #define ROUTE_SEGS 16
-#define FOLD_ROW 13          // a gate with a residual vector takes 13 tokens per block; rows 13 .. 15 hold the residual
+// The residual vector of a gate is three more rows of the product.  RES_IN_TILE: rows 13 .. 15 of a block's 16, which takes 13 tokens.
+// RES_BESIDE: an operand of their own, so that 16 tokens stay one block.
+#define RES_NONE 0
+#define RES_IN_TILE 1
+#define RES_BESIDE 2
+#define FOLD_ROW 13
 
 // The p largest workloads by descending value, equal values by ascending index; one wavefront, lane l holding the
 // workloads c0 of expert l and c1 of expert l + 64.  A workload is at most T < 2^24 (T d < 2^31, d >= 128), so workload and
@@ -244,9 +249,8 @@ struct gate_jobs {
 
 // Eight elements of row `part` of the residual's exact split x = hi + mid + lo into bf16 numbers (8 bits of its 24 each, cut off,
 // so that both differences are exact).  What is not finite stays in hi.
-__device__ __forceinline__ u32x4 residual_rows(const float *__restrict__ r, int part)
+__device__ __forceinline__ u32x4 residual_rows(float4 r0, float4 r1, int part)
 {
-    const float4 r0 = *reinterpret_cast<const float4 *>(r), r1 = *reinterpret_cast<const float4 *>(r + 4);
     const float x[8] = {r0.x, r0.y, r0.z, r0.w, r1.x, r1.y, r1.z, r1.w};
     u32x4 o;
 #pragma unroll
@@ -291,12 +295,14 @@ __device__ __forceinline__ bf16x8 rows_to_frag(u32x4 v, int from_lane)
 // fragment order (neighbouring lanes in different rows) every lane is an access of its own, 38 GB/s per compute unit against 147
 // from L2 and 30 against 58 from HBM.  K is cut into ROUTE_SEGS runs by d alone and the sums of the runs are added as a tree, so
 // that a logit is the same number whatever the batch size and the number of jobs.
-// (FOLD: the gate may have a residual vector.)
-template <int NT, bool FOLD> struct gate_tile {
+// RES: how the rows of a residual vector are held, if the gate has one.
+template <int NT, int RES> struct gate_tile {
     static constexpr int NP = NT * 16;                       // padded expert count
     static constexpr int G = NT <= 4 ? NT : 4;               // expert groups of a wave, ...
     static constexpr int KW = NT <= 4 ? 16 : 8;              // ... waves K is dealt to, ...
     static constexpr int SEGS = ROUTE_SEGS / KW;             // ... runs of a wave
+    static constexpr int ROWS = RES == RES_BESIDE ? ROUTE_TOKENS + 3 : ROUTE_TOKENS;
+    static constexpr int RES_ROW = RES == RES_BESIDE ? ROUTE_TOKENS : FOLD_ROW;
     const char *hb, *wb;
     const float *res_vec;
     uint32_t wo[G];                                          // byte offsets: T*d < 2^31 elements keeps them in 32 bits
@@ -309,7 +315,7 @@ template <int NT, bool FOLD> struct gate_tile {
         d = d_;
         hb = reinterpret_cast<const char *>(h);
         wb = reinterpret_cast<const char *>(J.gate_w);
-        res_vec = FOLD ? J.res_vec : nullptr;
+        res_vec = RES != RES_NONE ? J.res_vec : nullptr;
         kw = wave % KW;
         g0 = wave / KW * G;
         row = lane >> 2;
@@ -320,7 +326,7 @@ template <int NT, bool FOLD> struct gate_tile {
 #pragma unroll
         for (int j = 0; j < G; ++j) wo[j] = ((uint32_t)min(e_base + (g0 + j) * 16 + row, N - 1) * (uint32_t)d + chunk * 8) * 2u;
     }
-    __device__ __forceinline__ bool fold_row() const { return FOLD && res_vec != nullptr && row >= FOLD_ROW; }
+    __device__ __forceinline__ bool fold_row() const { return RES == RES_IN_TILE && res_vec != nullptr && row >= FOLD_ROW; }
     __device__ __forceinline__ uint32_t row_offset(int t0) const { return ((uint32_t)min(t0 + row, T - 1) * (uint32_t)d + chunk * 8) * 2u; }
     // n steps from s on (a step beyond the last one reads that again); along the rows first: the halves of a line follow each other
     template <int n> __device__ __forceinline__ void load_tokens(u32x4 (&a)[n], int t0, int s, int last) const
@@ -335,7 +341,10 @@ template <int NT, bool FOLD> struct gate_tile {
     {
         if (fold_row()) {
 #pragma unroll
-            for (int u = 0; u < n; ++u) a[u] = residual_rows(res_vec + min(s + u, last) * 32 + chunk * 8, row - FOLD_ROW);
+            for (int u = 0; u < n; ++u) {
+                const float4 *r = reinterpret_cast<const float4 *>(res_vec + min(s + u, last) * 32 + chunk * 8);
+                a[u] = residual_rows(r[0], r[1], row - FOLD_ROW);
+            }
         }
     }
     template <int n> __device__ __forceinline__ void load_gate(u32x4 (&b)[n][G], int s, int last) const
@@ -370,7 +379,44 @@ template <int NT, bool FOLD> struct gate_tile {
             mfmas(acc, a, b, s_end - s);
         }
     }
-    __device__ __forceinline__ void store(float (&part)[ROUTE_SEGS][ROUTE_TOKENS][NP + 1], int seg, const f32x4 (&acc)[G]) const
+    // the same for the only run of a wave, with the residual's rows beside the tokens: lane l converts elements 8l .. 8l + 7 of the run
+    // (512 at most) while the tokens and gate rows are on their way; rr, of this wave's own, holds them as chunks of the three parts
+    template <int n> __device__ __forceinline__ void walk_beside(f32x4 (&acc)[G], f32x4 (&res)[G], u32x4 (&rr)[3][64], int s0, int s_end) const
+    {
+        const int lane = threadIdx.x & 63, r = lane & 15, c = lane >> 4;
+        const bool mine = res_vec != nullptr && lane < (s_end - s0) * 4;
+        float4 r0, r1;
+        if (mine) {
+            r0 = *reinterpret_cast<const float4 *>(res_vec + s0 * 32 + lane * 8);
+            r1 = *reinterpret_cast<const float4 *>(res_vec + s0 * 32 + lane * 8 + 4);
+        }
+        for (int s = s0; s < s_end; s += n) {
+            u32x4 a[n], b[n][G];
+            load_tokens(a, 0, s, s_end - 1);
+            load_gate(b, s, s_end - 1);
+            __builtin_amdgcn_sched_barrier(0);
+            if (mine && s == s0) {
+#pragma unroll
+                for (int p = 0; p < 3; ++p) rr[p][lane] = residual_rows(r0, r1, p);
+            }
+            // the lanes of a wave exchange data: LDS serves a wave's accesses in order, the compiler keeps theirs
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+            for (int u = 0; u < n; ++u) {
+                if (s + u >= s_end) break;                   // uniform
+                const bf16x8 af = rows_to_frag(a[u], frag_lane);
+                u32x4 rf = u32x4{0, 0, 0, 0};
+                if (res_vec != nullptr && r < 3) rf = rr[r][(s + u - s0) * 4 + c];
+#pragma unroll
+                for (int j = 0; j < G; ++j) {
+                    const bf16x8 bf = gate_frag(b[u][j]);
+                    acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bf, acc[j], 0, 0, 0);
+                    res[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_frag(rf), bf, res[j], 0, 0, 0);
+                }
+            }
+        }
+    }
+    __device__ __forceinline__ void store(float (&part)[ROUTE_SEGS][ROWS][NP + 1], int seg, const f32x4 (&acc)[G]) const
     {
         const int lane = threadIdx.x & 63;
 #pragma unroll
@@ -379,10 +425,19 @@ template <int NT, bool FOLD> struct gate_tile {
             for (int r = 0; r < 4; ++r)
                 if (g0 + j < NT) part[seg][4 * (lane >> 4) + r][(g0 + j) * 16 + (lane & 15)] = acc[j][r];
     }
-    // the sums of the runs; ends with a barrier
-    static __device__ __forceinline__ void reduce(const float (&part)[ROUTE_SEGS][ROUTE_TOKENS][NP + 1], float (&lg)[ROUTE_TOKENS][NP + 4])
+    __device__ __forceinline__ void store_res(float (&part)[ROUTE_SEGS][ROWS][NP + 1], int seg, const f32x4 (&res)[G]) const
     {
-        for (int idx = threadIdx.x; idx < ROUTE_TOKENS * NP; idx += ROUTE_THREADS) {
+        const int lane = threadIdx.x & 63;
+        if (lane >= 16) return;                              // rows 0 .. 3 of the result
+#pragma unroll
+        for (int j = 0; j < G; ++j)
+#pragma unroll
+            for (int r = 0; r < 3; ++r) part[seg][RES_ROW + r][(g0 + j) * 16 + lane] = res[j][r];
+    }
+    // the sums of the runs; ends with a barrier
+    static __device__ __forceinline__ void reduce(const float (&part)[ROUTE_SEGS][ROWS][NP + 1], float (&lg)[ROWS][NP + 4])
+    {
+        for (int idx = threadIdx.x; idx < ROWS * NP; idx += ROUTE_THREADS) {
             const int tt = idx / NP, e = idx % NP;
             float v[ROUTE_SEGS];
 #pragma unroll
@@ -396,10 +451,10 @@ template <int NT, bool FOLD> struct gate_tile {
         __syncthreads();
     }
     // logit of a token's row: the bias with the residual vector folded in is added, (h + res_vec).W + b = h.W + (res_vec.W + b)
-    __device__ __forceinline__ float logit(const float (&lg)[ROUTE_TOKENS][NP + 4], const float (&bias_s)[NP], int tt, int e) const
+    __device__ __forceinline__ float logit(const float (&lg)[ROWS][NP + 4], const float (&bias_s)[NP], int tt, int e) const
     {
         float b = bias_s[e];
-        if (FOLD && res_vec != nullptr) b = residual_sum(lg[FOLD_ROW][e], lg[FOLD_ROW + 1][e], lg[FOLD_ROW + 2][e]) + b;
+        if (RES != RES_NONE && res_vec != nullptr) b = residual_sum(lg[RES_ROW][e], lg[RES_ROW + 1][e], lg[RES_ROW + 2][e]) + b;
         return lg[tt][e] + b;
     }
     static __device__ __forceinline__ void load_bias(float (&bias_s)[NP], const float *bias, int e_base, int N)
@@ -435,7 +490,7 @@ __global__ __launch_bounds__(ROUTE_THREADS) void gate_logits_kernel(int T, int d
     __shared__ __attribute__((aligned(16))) float lg[ROUTE_TOKENS][NP + 4];   // reduced logits, rows 16-byte aligned
     __shared__ float bias_s[NP];
     const int e_base = blockIdx.y * NP;
-    const gate_tile<NT, true> G(T, d, N, h, J, e_base);
+    const gate_tile<NT, RES_IN_TILE> G(T, d, N, h, J, e_base);
     static_assert(G.SEGS == 1, "one run per wave");
     const int s0 = G.kw * G.per, s_end = min(s0 + G.per, G.nsteps), last = max(min(s_end, G.nsteps) - 1, 0);
     u32x4 a[KEEP], b[KEEP][G.G];
@@ -470,25 +525,35 @@ __global__ __launch_bounds__(ROUTE_THREADS) void gate_logits_kernel(int T, int d
 // Gate and selection of 16 tokens, NT = ceil(N / 16); with TABLES (a decode-sized batch, one block) the tables too.  (One kernel for
 // all held the fields of every path in scalar registers and spilled them.)  Before and now, d = 4096, 8 experts: 200 tokens 10.9 /
 // 7.8 us, 8192 23 / 19.
-template <int NT, bool TABLES>
+template <int NT, bool TABLES, int RES>
 __global__ __launch_bounds__(ROUTE_THREADS) void gate_topk_kernel(int T, int d, int N, int k, const uint16_t *__restrict__ h,
                                                                   gate_jobs jobs)
 {
     const gate_job &J = jobs.job[blockIdx.z == 0 ? 0 : 1];
-    const int tokens = !TABLES && J.res_vec != nullptr ? FOLD_ROW : ROUTE_TOKENS;
+    const int tokens = RES == RES_IN_TILE && J.res_vec != nullptr ? FOLD_ROW : ROUTE_TOKENS;
     const int t0 = blockIdx.x * tokens;
     if (t0 >= T) return;
     constexpr int NP = NT * 16;
-    __shared__ float part[ROUTE_SEGS][ROUTE_TOKENS][NP + 1];
-    __shared__ __attribute__((aligned(16))) float lg[ROUTE_TOKENS][NP + 4];
+    typedef gate_tile<NT, RES> tile;
+    __shared__ float part[ROUTE_SEGS][tile::ROWS][NP + 1];
+    __shared__ __attribute__((aligned(16))) float lg[tile::ROWS][NP + 4];
     __shared__ float bias_s[NP];
-    const gate_tile<NT, !TABLES> G(T, d, N, h, J, 0);
+    const tile G(T, d, N, h, J, 0);
     G.load_bias(bias_s, J.bias, 0, N);
     for (int seg = G.kw * G.SEGS; seg < (G.kw + 1) * G.SEGS; ++seg) {
         f32x4 acc[G.G];
 #pragma unroll
         for (int j = 0; j < G.G; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-        G.template walk<TABLES && NT == 1 ? 8 : NT <= 3 ? 4 : 2>(acc, t0, seg * G.per, min((seg + 1) * G.per, G.nsteps));
+        const int s0 = seg * G.per, s_end = min((seg + 1) * G.per, G.nsteps);
+        if constexpr (RES == RES_BESIDE) {
+            static_assert(NT == 1 && TABLES && G.SEGS == 1, "one block, one run per wave");
+            __shared__ u32x4 rr[ROUTE_SEGS][3][64];
+            f32x4 res[1] = {f32x4{0.f, 0.f, 0.f, 0.f}};
+            G.template walk_beside<8>(acc, res, rr[seg], s0, s_end);
+            G.store_res(part, seg, res);
+        } else {
+            G.template walk<TABLES && NT == 1 ? 8 : NT <= 3 ? 4 : 2>(acc, t0, s0, s_end);
+        }
         G.store(part, seg, acc);
     }
     __syncthreads();
@@ -821,10 +886,10 @@ static int launch_gate_topk(const moe_shape *s, const void *h, hipStream_t st, i
     const int tokens = fold ? FOLD_ROW : ROUTE_TOKENS;
     dim3 grid((s->T + tokens - 1) / tokens, 1, n_jobs), block(ROUTE_THREADS);
     const uint16_t *hp = (const uint16_t *)h;
-    if (s->T <= ROUTE_TOKENS && (NT >= 2 || fold) && ws_logits[0] != nullptr) {
-        // decode-sized batch: one block would stream the whole gate matrix of many experts alone, so the gate product is spread
-        // over one block per 16 experts and the selection runs from the stored logits (with a residual also because its
-        // rows and 16 tokens are two blocks)
+    if (s->T <= ROUTE_TOKENS && NT >= 2 && ws_logits[0] != nullptr) {
+        // decode-sized batch with many experts: one block would stream the whole gate matrix alone, so the gate product is spread
+        // over one block per 16 experts and the selection runs from the stored logits.  (Up to 16 experts one block is faster, with a
+        // residual too: prediction at d = 4096, 8 experts, 1 token 7.8 us against 10.8 as two launches, 13 tokens 8.4 / 11.5, 16 8.7 / 12.3)
         for (int i = 0; i < 2; ++i) two.job[i].logits = ws_logits[i < n_jobs ? i : n_jobs - 1];
         grid.y = NT;
         if (two.job[0].x.gate != nullptr) grid.z += 1;
@@ -850,12 +915,19 @@ static int launch_gate_topk(const moe_shape *s, const void *h, hipStream_t st, i
         return MOE_OK;
     }
     two.job[0].x.gate = nullptr;      // the block that selects evaluates the shared experts' gates too
+    const bool tables = two.job[0].counts != nullptr;
+    if (tables) grid.x = 1;
+    if (tables && fold) {             // a residual comes with a workspace: 16 experts at most
+        hipLaunchKernelGGL((gate_topk_kernel<1, true, RES_BESIDE>), grid, block, 0, st, s->T, s->d, s->N, s->k, hp, two);
+        MOE_CHECK_LAUNCH();
+        return MOE_OK;
+    }
 #define GT(n)                                                                                                  \
     case n:                                                                                                    \
-        if (two.job[0].counts != nullptr)                                                                      \
-            hipLaunchKernelGGL((gate_topk_kernel<n, true>), grid, block, 0, st, s->T, s->d, s->N, s->k, hp, two); \
+        if (tables)                                                                                            \
+            hipLaunchKernelGGL((gate_topk_kernel<n, true, RES_NONE>), grid, block, 0, st, s->T, s->d, s->N, s->k, hp, two); \
         else                                                                                                   \
-            hipLaunchKernelGGL((gate_topk_kernel<n, false>), grid, block, 0, st, s->T, s->d, s->N, s->k, hp, two); \
+            hipLaunchKernelGGL((gate_topk_kernel<n, false, RES_IN_TILE>), grid, block, 0, st, s->T, s->d, s->N, s->k, hp, two); \
         break;
     switch (NT) {
         GT(1) GT(2) GT(3) GT(4) GT(5) GT(6) GT(7) GT(8)

@@ -2,6 +2,8 @@
 K shorter than, equal to and longer than the steps a wave keeps in registers, expert slices that are not full.  Routing is compared
 with the oracle under the rules of helpers.py and the prediction through its counts; a logit is a function of its token and
 expert alone, so a token routed by itself gets the same bits as inside the batch."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -89,3 +91,48 @@ def test_an_infinite_gate_weight_makes_an_infinite_logit_not_nan(gpu, T, N):
     B.moe_predict_workload(s, h.bfloat16(), rv, W.bfloat16(), None, 2, pc, top, B.alloc_workspace(s))
     torch.cuda.synchronize()
     assert pc.tolist() == [T, 0, 0, T] + [0] * (N - 4) and top.tolist() == [0, 3]
+
+
+def _kernels(call):
+    """Kernel launches of a call: the nodes of a graph it is captured into."""
+    call()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        call()
+    with open("/proc/self/maps") as maps:
+        hip = ctypes.CDLL(next(line.split()[-1] for line in maps if "libamdhip64" in line))
+    n = ctypes.c_size_t(0)
+    assert hip.hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(n)) == 0
+    return n.value
+
+
+@pytest.mark.parametrize("d,N,k", [(128, 8, 2), (4096, 8, 2), (8192, 16, 8), (2176, 3, 3)])
+def test_decode_prediction_of_few_experts(gpu, d, N, k):
+    """Up to 16 experts and 16 tokens: one launch, also where tokens and the residual's rows are more than the 16 of a tile, and with
+    every token's prediction as it is alone and in a batch of several tiles."""
+    B, Lm = gpu
+    cfg = wl.scaled(wl.CONFIGS["qwen3"], d=d, N=N, k=k, I=128)
+    dev = lambda a: torch.from_numpy(a).cuda()
+    h, W0, W1 = (Lm.to_device_bf16(a) for a in (wl.hidden_states(cfg, 45), wl.gate_weights(cfg, 0), wl.gate_weights(cfg, 1)))
+    b0, b1, rv = dev(wl.gate_bias(cfg, 0)), dev(wl.gate_bias(cfg, 1)), dev(wl.layer_drift(cfg))
+
+    def predict(T, first, fused):
+        s, x = B.shape(T, d, N, k, 128), h[first:first + T].contiguous()
+        ws, r, pc, top = B.alloc_workspace(s), B.alloc_routing(s), torch.full((N,), -1, dtype=torch.int32, device="cuda"), \
+            torch.full((N,), -1, dtype=torch.int32, device="cuda")
+        call = (lambda: B.moe_route_predict(s, x, W0, b0, 1, r, rv, W1, b1, N, pc, top, ws)) if fused else \
+            (lambda: B.moe_predict_workload(s, x, rv, W1, b1, N, pc, top, ws))
+        n = _kernels(call)
+        counts = pc.cpu().numpy()
+        assert np.array_equal(top.cpu().numpy(), oracle.top_p(counts, N))
+        return counts, n
+
+    alone = [predict(1, t, t % 2 == 0)[0] for t in range(45)]
+    for T in (1, 12, 13, 14, 16):
+        for fused in (False, True):
+            print(f"few experts d={d} N={N} T={T} fused={fused}", flush=True)
+            counts, n = predict(T, 0, fused)
+            assert n == 1, n
+            assert np.array_equal(counts, sum(alone[:T]))
+    assert np.array_equal(predict(45, 0, False)[0], sum(alone))
