@@ -22,8 +22,8 @@
 #define ROUTE_TOKENS 16      // tokens per block of gate_topk_kernel
 #define ROUTE_THREADS 1024
 #define ROUTE_SEGS 16
-// The residual vector of a gate is three more rows of the product.  RES_IN_TILE: rows 13 .. 15 of a block's 16, which takes 13 tokens.
-// RES_BESIDE: an operand of their own, so that 16 tokens stay one block.
+// The residual vector of a gate is three more rows of the product.  RES_IN_TILE: rows 13 .. 15 of a block's 16, which takes 13 tokens
+// (blocks that walk token tiles convert them once).  RES_BESIDE: an operand of their own, so that a block still takes 16 tokens.
 #define RES_NONE 0
 #define RES_IN_TILE 1
 #define RES_BESIDE 2
@@ -381,7 +381,7 @@ template <int NT, int RES> struct gate_tile {
     }
     // the same for the only run of a wave, with the residual's rows beside the tokens: lane l converts elements 8l .. 8l + 7 of the run
     // (512 at most) while the tokens and gate rows are on their way; rr, of this wave's own, holds them as chunks of the three parts
-    template <int n> __device__ __forceinline__ void walk_beside(f32x4 (&acc)[G], f32x4 (&res)[G], u32x4 (&rr)[3][64], int s0, int s_end) const
+    template <int n> __device__ __forceinline__ void walk_beside(f32x4 (&acc)[G], f32x4 (&res)[G], u32x4 (&rr)[3][64], int t0, int s0, int s_end) const
     {
         const int lane = threadIdx.x & 63, r = lane & 15, c = lane >> 4;
         const bool mine = res_vec != nullptr && lane < (s_end - s0) * 4;
@@ -392,7 +392,7 @@ template <int NT, int RES> struct gate_tile {
         }
         for (int s = s0; s < s_end; s += n) {
             u32x4 a[n], b[n][G];
-            load_tokens(a, 0, s, s_end - 1);
+            load_tokens(a, t0, s, s_end - 1);
             load_gate(b, s, s_end - 1);
             __builtin_amdgcn_sched_barrier(0);
             if (mine && s == s0) {
@@ -525,13 +525,15 @@ __global__ __launch_bounds__(ROUTE_THREADS) void gate_logits_kernel(int T, int d
 // Gate and selection of 16 tokens, NT = ceil(N / 16); with TABLES (a decode-sized batch, one block) the tables too.  (One kernel for
 // all held the fields of every path in scalar registers and spilled them.)  Before and now, d = 4096, 8 experts: 200 tokens 10.9 /
 // 7.8 us, 8192 23 / 19.
+// RES_BESIDE where the gate may have a residual: with 13 tokens to a block, 4096 of them are 316 blocks for 256 compute units.  Prediction,
+// RES_IN_TILE / RES_BESIDE, d = 4096, 8 experts: 17 tokens 10.8 / 9.5 us, 4096 21 / 14.5, 16384 50 / 41; d = 2048, 48 experts: 4096 21 / 14.4.
+// With up to 16 experts two blocks of 64 registers per lane share a compute unit (20 bytes spill; one of 66: 16384 tokens 45 us).
 template <int NT, bool TABLES, int RES>
-__global__ __launch_bounds__(ROUTE_THREADS) void gate_topk_kernel(int T, int d, int N, int k, const uint16_t *__restrict__ h,
-                                                                  gate_jobs jobs)
+__global__ __launch_bounds__(ROUTE_THREADS, !TABLES && RES == RES_BESIDE && NT == 1 ? 8 : 4) void gate_topk_kernel(
+    int T, int d, int N, int k, const uint16_t *__restrict__ h, gate_jobs jobs)
 {
     const gate_job &J = jobs.job[blockIdx.z == 0 ? 0 : 1];
-    const int tokens = RES == RES_IN_TILE && J.res_vec != nullptr ? FOLD_ROW : ROUTE_TOKENS;
-    const int t0 = blockIdx.x * tokens;
+    const int t0 = blockIdx.x * ROUTE_TOKENS;
     if (t0 >= T) return;
     constexpr int NP = NT * 16;
     typedef gate_tile<NT, RES> tile;
@@ -546,10 +548,13 @@ __global__ __launch_bounds__(ROUTE_THREADS) void gate_topk_kernel(int T, int d, 
         for (int j = 0; j < G.G; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
         const int s0 = seg * G.per, s_end = min((seg + 1) * G.per, G.nsteps);
         if constexpr (RES == RES_BESIDE) {
-            static_assert(NT == 1 && TABLES && G.SEGS == 1, "one block, one run per wave");
+            static_assert(G.SEGS == 1, "one run per wave");
             __shared__ u32x4 rr[ROUTE_SEGS][3][64];
-            f32x4 res[1] = {f32x4{0.f, 0.f, 0.f, 0.f}};
-            G.template walk_beside<8>(acc, res, rr[seg], s0, s_end);
+            f32x4 res[G.G];
+#pragma unroll
+            for (int j = 0; j < G.G; ++j) res[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (TABLES && G.per > 2) G.template walk_beside<8>(acc, res, rr[seg], t0, s0, s_end);
+            else G.template walk_beside<TABLES ? 2 : 4>(acc, res, rr[seg], t0, s0, s_end);
             G.store_res(part, seg, res);
         } else {
             G.template walk<TABLES && NT == 1 ? 8 : NT <= 3 ? 4 : 2>(acc, t0, s0, s_end);
@@ -561,7 +566,7 @@ __global__ __launch_bounds__(ROUTE_THREADS) void gate_topk_kernel(int T, int d, 
 
     // softmax + top-k: one wave per token, lane l owns experts l and l + 64
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (wave < min(tokens, T - t0)) {
+    if (wave < min(ROUTE_TOKENS, T - t0)) {
         const int t = t0 + wave;
         const float v0 = G.logit(lg, bias_s, wave, min(lane, N - 1));
         const float v1 = NT > 4 ? G.logit(lg, bias_s, wave, min(lane + 64, N - 1)) : v0;
@@ -900,10 +905,13 @@ static int launch_gate_topk(const moe_shape *s, const void *h, hipStream_t st, i
         MOE_CHECK_LAUNCH();
         return MOE_OK;
     }
-    if (s->T > ROUTE_TOKENS && NT >= 4 && ws_logits[0] != nullptr) {
+    const int blocks = (s->T + ROUTE_TOKENS - 1) / ROUTE_TOKENS * n_jobs;
+    if (s->T > ROUTE_TOKENS && (NT >= 4 || (fold && NT >= 2 && s->d <= 4096 && blocks > 512)) && ws_logits[0] != nullptr) {
         // many experts: a block that evaluated all of them for its tokens would leave half the chip idle and spend its time on the
         // gate rows, so the gate product runs as (token blocks x 32-expert slices) and the selection, one wavefront per token,
-        // reads the stored logits
+        // reads the stored logits.  With 17 to 48 experts and a residual also where the blocks that select would be more than two rounds
+        // (prediction, those / stored: d = 2048, 32 experts, 8192 tokens 22.9 / 24.1 us, 16384 44 / 37; d = 1024, 20 experts 17.5 / 18.2,
+        // 31 / 27), but not for gate rows that do not stay in registers (d = 8192, 48 experts, 16384 tokens 98 / 153).
         for (int i = 0; i < 2; ++i) two.job[i].logits = ws_logits[i < n_jobs ? i : n_jobs - 1];
         grid.y = (s->N + 31) / 32;
         grid.x = gate_streams(grid.x, grid.y * n_jobs);
@@ -915,25 +923,28 @@ static int launch_gate_topk(const moe_shape *s, const void *h, hipStream_t st, i
         return MOE_OK;
     }
     two.job[0].x.gate = nullptr;      // the block that selects evaluates the shared experts' gates too
+    grid.x = (s->T + ROUTE_TOKENS - 1) / ROUTE_TOKENS;
     const bool tables = two.job[0].counts != nullptr;
-    if (tables) grid.x = 1;
-    if (tables && fold) {             // a residual comes with a workspace: 16 experts at most
-        hipLaunchKernelGGL((gate_topk_kernel<1, true, RES_BESIDE>), grid, block, 0, st, s->T, s->d, s->N, s->k, hp, two);
+#define GT(n, tables_, res) hipLaunchKernelGGL((gate_topk_kernel<n, tables_, res>), grid, block, 0, st, s->T, s->d, s->N, s->k, hp, two)
+    if (fold) {                        // a residual comes with a workspace: 48 experts at most, and 16 in a decode-sized batch
+        if (tables) GT(1, true, RES_BESIDE);
+        else if (NT == 1) GT(1, false, RES_BESIDE);
+        else if (NT == 2) GT(2, false, RES_BESIDE);
+        else GT(3, false, RES_BESIDE);
         MOE_CHECK_LAUNCH();
         return MOE_OK;
     }
-#define GT(n)                                                                                                  \
-    case n:                                                                                                    \
-        if (tables)                                                                                            \
-            hipLaunchKernelGGL((gate_topk_kernel<n, true, RES_NONE>), grid, block, 0, st, s->T, s->d, s->N, s->k, hp, two); \
-        else                                                                                                   \
-            hipLaunchKernelGGL((gate_topk_kernel<n, false, RES_IN_TILE>), grid, block, 0, st, s->T, s->d, s->N, s->k, hp, two); \
+#define GTN(n)                              \
+    case n:                                 \
+        if (tables) GT(n, true, RES_NONE);  \
+        else GT(n, false, RES_IN_TILE);     \
         break;
     switch (NT) {
-        GT(1) GT(2) GT(3) GT(4) GT(5) GT(6) GT(7) GT(8)
+        GTN(1) GTN(2) GTN(3) GTN(4) GTN(5) GTN(6) GTN(7) GTN(8)
     default:
         return MOE_EUNSUPPORTED;
     }
+#undef GTN
 #undef GT
     MOE_CHECK_LAUNCH();
     return MOE_OK;

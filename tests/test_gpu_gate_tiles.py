@@ -136,3 +136,35 @@ def test_decode_prediction_of_few_experts(gpu, d, N, k):
             assert n == 1, n
             assert np.array_equal(counts, sum(alone[:T]))
     assert np.array_equal(predict(45, 0, False)[0], sum(alone))
+
+
+@pytest.mark.parametrize("d,N,k,T", [(128, 16, 8, 53), (4096, 8, 2, 4100), (128, 17, 8, 53), (8192, 33, 4, 300), (1024, 20, 2, 8300),
+                                     (2048, 48, 4, 4200), (4224, 48, 4, 4200)])
+def test_a_large_batch_is_predicted_as_its_decode_batches(gpu, d, N, k, T):
+    """Few experts beyond decode sizes: blocks that hold tokens and residual side by side, and (17 to 48 experts, many blocks) the
+    stored logits; alone and with the routing, which has to be what it is alone."""
+    B, Lm = gpu
+    print(f"large prediction d={d} N={N} k={k} T={T}", flush=True)
+    cfg = wl.scaled(wl.CONFIGS["qwen3"], d=d, N=N, k=k, I=128)
+    dev = lambda a: torch.from_numpy(a).cuda()
+    h, W0, W1 = (Lm.to_device_bf16(a) for a in (wl.hidden_states(cfg, T), wl.gate_weights(cfg, 0), wl.gate_weights(cfg, 1)))
+    b0, b1, rv = dev(wl.gate_bias(cfg, 0)), dev(wl.gate_bias(cfg, 1)), dev(wl.layer_drift(cfg))
+    i32 = dict(dtype=torch.int32, device="cuda")
+    top, expect = torch.empty(N, **i32), torch.zeros(N, dtype=torch.int64, device="cuda")
+    ws16 = B.alloc_workspace(B.shape(16, d, N, k, 128))
+    for t in range(0, T, 16):
+        pc = torch.empty(N, **i32)
+        B.moe_predict_workload(B.shape(min(16, T - t), d, N, k, 128), h[t:t + 16], rv, W1, b1, N, pc, top, ws16)
+        expect += pc
+    s = B.shape(T, d, N, k, 128)
+    ws, alone, both = B.alloc_workspace(s), B.alloc_routing(s), B.alloc_routing(s)
+    B.moe_route(s, h, W0, b0, 1, alone, ws)
+    counts = [torch.empty(N, **i32) for _ in range(2)]
+    B.moe_predict_workload(s, h, rv, W1, b1, N, counts[0], top, ws)
+    B.moe_route_predict(s, h, W0, b0, 1, both, rv, W1, b1, N, counts[1], top, ws)
+    torch.cuda.synchronize()
+    for c in counts:
+        assert torch.equal(c.long(), expect)
+    assert np.array_equal(top.cpu().numpy(), oracle.top_p(counts[1].cpu().numpy(), N))
+    for name in ("topk_idx", "topk_w", "counts", "offsets", "perm", "inv_perm"):
+        assert torch.equal(getattr(alone, name), getattr(both, name)), name
