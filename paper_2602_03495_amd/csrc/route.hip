@@ -466,10 +466,11 @@ template <int NT, int RES> struct gate_tile {
 
 // Logits of 16 NT experts per blockIdx.y.  Bound by the latency of its reads at decode sizes and by what one compute unit takes in
 // beyond: a block keeps its gate rows in registers (all of them up to d = 2048) and walks token tiles, so that the gate matrix is
-// read once per block, not once per 16 tokens.  With fragment-order reads by 8 waves (16 x 32 tiles, the residual folded by waves of
+// read once per block, not once per 16 tokens.  KEEP: how many of its run's steps a wave keeps, no more than a run has: with four of
+// a run of one, each with the residual's conversion, a decode prediction took 8.7 us, now 6.6 (d = 256, 64 experts; 4096 tokens 17.3 / 14.3).  With fragment-order reads by 8 waves (16 x 32 tiles, the residual folded by waves of
 // their own) and now: 16 tokens of 64 experts 5.7 / 4.6 us, 16 of two gates of 128 with a residual 8.2 / 6.3, 77 of 128 8.0 / 5.4,
 // 2048 of 64 10.4 / 7.3, 4096 of 60 17.3 / 9.8, 1531 of two gates of 128 22 / 13.6 (d = 2048).
-template <int NT>
+template <int NT, int KEEP>
 __global__ __launch_bounds__(ROUTE_THREADS) void gate_logits_kernel(int T, int d, int N, const uint16_t *__restrict__ h, gate_jobs jobs)
 {
     const gate_job &J = jobs.job[blockIdx.z == 0 ? 0 : 1];
@@ -485,7 +486,7 @@ __global__ __launch_bounds__(ROUTE_THREADS) void gate_logits_kernel(int T, int d
     const int tokens = J.res_vec != nullptr ? FOLD_ROW : ROUTE_TOKENS;
     int t0 = blockIdx.x * tokens;
     if (t0 >= T) return;
-    constexpr int NP = NT * 16, KEEP = 4;
+    constexpr int NP = NT * 16;
     __shared__ float part[ROUTE_SEGS][ROUTE_TOKENS][NP + 1];    // partial logits
     __shared__ __attribute__((aligned(16))) float lg[ROUTE_TOKENS][NP + 4];   // reduced logits, rows 16-byte aligned
     __shared__ float bias_s[NP];
@@ -881,6 +882,16 @@ static unsigned gate_streams(unsigned tiles, unsigned slices)
     return tiles < n ? tiles : n;
 }
 
+template <int NT>
+static void launch_gate_logits(const moe_shape *s, const uint16_t *h, dim3 grid, hipStream_t st, const gate_jobs &jobs)
+{
+    const int run = (s->d / 32 + ROUTE_SEGS - 1) / ROUTE_SEGS;        // steps of a wave
+    const dim3 block(ROUTE_THREADS);
+    if (run == 1) hipLaunchKernelGGL((gate_logits_kernel<NT, 1>), grid, block, 0, st, s->T, s->d, s->N, h, jobs);
+    else if (run == 2) hipLaunchKernelGGL((gate_logits_kernel<NT, 2>), grid, block, 0, st, s->T, s->d, s->N, h, jobs);
+    else hipLaunchKernelGGL((gate_logits_kernel<NT, 4>), grid, block, 0, st, s->T, s->d, s->N, h, jobs);
+}
+
 // Launches the gate kernels for one job, or for two jobs side by side (both of the same size, so they take the same
 // path).  ws_logits[i]: [16, N] scratch of job i for decode-sized batches, or null (a job with a residual always has one).
 static int launch_gate_topk(const moe_shape *s, const void *h, hipStream_t st, int n_jobs, gate_job *jobs, float *const *ws_logits)
@@ -898,7 +909,7 @@ static int launch_gate_topk(const moe_shape *s, const void *h, hipStream_t st, i
         for (int i = 0; i < 2; ++i) two.job[i].logits = ws_logits[i < n_jobs ? i : n_jobs - 1];
         grid.y = NT;
         if (two.job[0].x.gate != nullptr) grid.z += 1;
-        hipLaunchKernelGGL(gate_logits_kernel<1>, grid, block, 0, st, s->T, s->d, s->N, hp, two);
+        launch_gate_logits<1>(s, hp, grid, st, two);
         MOE_CHECK_LAUNCH();
         // T <= 16 and k <= 8: at most 128 selections, so the selecting block also builds the tables
         hipLaunchKernelGGL(select_decode_kernel, dim3(1, 1, n_jobs), dim3(SELECT_THREADS), 0, st, s->T, s->N, s->k, two);
@@ -915,7 +926,7 @@ static int launch_gate_topk(const moe_shape *s, const void *h, hipStream_t st, i
         for (int i = 0; i < 2; ++i) two.job[i].logits = ws_logits[i < n_jobs ? i : n_jobs - 1];
         grid.y = (s->N + 31) / 32;
         grid.x = gate_streams(grid.x, grid.y * n_jobs);
-        hipLaunchKernelGGL(gate_logits_kernel<2>, grid, block, 0, st, s->T, s->d, s->N, hp, two);
+        launch_gate_logits<2>(s, hp, grid, st, two);
         MOE_CHECK_LAUNCH();
         hipLaunchKernelGGL(select_rows_kernel, dim3((s->T + SELECT_THREADS / 64 - 1) / (SELECT_THREADS / 64), 1, n_jobs),
                            dim3(SELECT_THREADS), 0, st, s->T, s->N, s->k, two);

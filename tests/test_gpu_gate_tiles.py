@@ -25,7 +25,7 @@ def gpu():
 
 
 @pytest.mark.parametrize("d,N,k,T", [(128, 128, 8, 1000), (640, 60, 4, 417), (2048, 49, 4, 833), (2176, 64, 6, 53), (4096, 8, 2, 300),
-                                     (4096, 70, 8, 27), (8192, 128, 8, 40), (8192, 17, 2, 14), (2048, 128, 8, 16), (4096, 8, 2, 13)])
+                                     (4096, 70, 8, 27), (512, 33, 3, 530), (1024, 65, 5, 16), (1152, 64, 6, 29), (8192, 128, 8, 40), (8192, 17, 2, 14), (2048, 128, 8, 16), (4096, 8, 2, 13)])
 def test_route_and_predict_at_the_edges_of_the_gate_tiles(gpu, d, N, k, T):
     B, Lm = gpu
     print(f"gate tiles d={d} N={N} k={k} T={T}", flush=True)
