@@ -32,6 +32,9 @@ __device__ __forceinline__ void add_rows(float (&acc)[8], unsigned long long &on
 // Bound by latency at decode sizes, by the reads beyond.  Every wave holds the slots of its token in its first lanes, finds
 // those placed on this GPU by a ballot and reads all their rows at once: with a loop over the slots that skipped the others,
 // the reads of up to 8 rows followed one another (16 tokens, 8 slots, d = 2048: 3.7 us, now 2.5).
+// MASKED: two kernels, because without a mask the rows need not wait for the experts of the slots (2.42 us, and 2.55 where they do; 1100
+// tokens of 6 slots 4.36 / 4.76) and a branch on it inside costs either (2.54 and 2.65 with a mask).
+template <bool MASKED>
 __global__ __launch_bounds__(256) void combine_kernel(int T, int d, int N, int k, const uint16_t *__restrict__ y,
                                                       const int32_t *__restrict__ topk_idx, const float *__restrict__ topk_w,
                                                       const int32_t *__restrict__ inv_perm, const uint8_t *__restrict__ mask,
@@ -42,18 +45,18 @@ __global__ __launch_bounds__(256) void combine_kernel(int T, int d, int N, int k
     int p = 0;
     float w = 0.f;
     bool mine = lane < k;
-    unsigned long long on_lo = ~0ull, on_hi = ~0ull;
-    if (mask != nullptr) {              // the whole of it, beside the slots: looked up by expert it was a round trip after them
+    unsigned long long on_lo = 0, on_hi = 0;
+    if (MASKED) {                       // the whole of it, beside the slots: looked up by expert it was a round trip after them
         const int m0 = mask[min(lane, N - 1)], m1 = mask[min(lane + 64, N - 1)];
         on_lo = __ballot(m0 != 0);
         on_hi = __ballot(m1 != 0);
     }
     if (mine) {
         const size_t r = (size_t)t * k + lane;
-        const int e = topk_idx[r];
+        const int e = MASKED ? topk_idx[r] : 0;
         w = topk_w[r];
         p = inv_perm[r];
-        mine = ((e < 64 ? on_lo : on_hi) >> (e & 63) & 1ull) != 0;
+        if (MASKED) mine = ((e < 64 ? on_lo : on_hi) >> (e & 63) & 1ull) != 0;
     }
     unsigned long long on = __ballot(mine);
     const float sc = (n_shared > 0 && shared_scale != nullptr) ? shared_scale[t] : 1.0f;
@@ -144,7 +147,8 @@ int moe_combine_impl(const moe_shape *s, const void *y, const int32_t *topk_idx,
     hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, st, s->T, s->d, s->N, s->k, (const uint16_t *)y, topk_idx, topk_w, inv_perm, expert_mask, \
                        (const uint16_t *)shared_y, shared_y ? n_shared : 0, shared_scale, (uint16_t *)out)
     if (combine_walks(s)) COMBINE(combine_walk_kernel, dim3(s->T));
-    else COMBINE(combine_kernel, dim3(s->T, (s->d + 2047) / 2048));
+    else if (expert_mask != nullptr) COMBINE(combine_kernel<true>, dim3(s->T, (s->d + 2047) / 2048));
+    else COMBINE(combine_kernel<false>, dim3(s->T, (s->d + 2047) / 2048));
 #undef COMBINE
     MOE_CHECK_LAUNCH();
     return MOE_OK;
