@@ -94,9 +94,8 @@ __global__ __launch_bounds__(256) void combine_kernel(int T, int d, int N, int k
     }
 }
 
-// The same sums for many tokens with few slots: a block walks the columns of its token, whose tables it reads once, and holds
-// few rows at a time, so that 8 waves run on a SIMD (combine_kernel, with room for 8 rows per lane, has 5).
-__global__ __launch_bounds__(256) void combine_walk_kernel(int T, int d, int N, int k, const uint16_t *__restrict__ y,
+// The same sums for many tokens with few slots: a block walks the columns of its token, whose tables it reads once for all of them.
+__global__ __launch_bounds__(256) void combine_walk_kernel(int T, int d, int k, const uint16_t *__restrict__ y,
                                                            const int32_t *__restrict__ topk_idx, const float *__restrict__ topk_w,
                                                            const int32_t *__restrict__ inv_perm, const uint8_t *__restrict__ mask,
                                                            const uint16_t *__restrict__ shared_y, int n_shared,
@@ -131,9 +130,12 @@ __global__ __launch_bounds__(256) void combine_walk_kernel(int T, int d, int N, 
     }
 }
 
-// combine_kernel's speed over combine_walk_kernel's, no mask / half of the experts on (d = 4096): 2 slots and 200 tokens 1.33 /
-// 1.30, 800 tokens 1.05 / 0.99, 1500 0.95 / 0.88, 12000 0.89 / 0.85; 1 slot and 12000 tokens 1.00 / 0.72.  With 5 slots or
-// more, and up to 1024 columns, it is level or ahead at every size (0.94 to 2.4, and 1.0 to 1.5); with 4, 0.88 to 1.65.
+// combine_kernel's speed over combine_walk_kernel's, no mask / a quarter to half of the experts on.  d = 8192, 2 slots: 1030 tokens 1.03 /
+// 1.03 to 1.08, 12000 1.02 / 0.72, 40000 0.99 / 0.93 to 1.05; 3 slots, 12000 tokens 1.00 / 0.74 to 1.00; 1 slot 0.98 / 0.83.  d = 4096: 2
+// slots, 1030 tokens 1.11 / 1.04, 12000 1.09 / 0.99; 1 slot 1.03 / 0.86, 40000 0.97 / 0.80.  d = 1152: 1.06 to 1.28 / 1.0 to 1.18.
+// With 5 slots or more, and up to 1024 columns, it was level or ahead with 5 waves on a SIMD already (0.94 to 2.4); with 4, 0.88 to 1.65.
+// The line was drawn where combine_kernel ran 5 waves on a SIMD (d = 4096, 2 slots, 1500 tokens 0.95 / 0.88); with the 8 it has
+// now it gains where rows are many, up to a few microseconds, and loses up to a quarter where few are on.
 static bool combine_walks(const moe_shape *s) { return s->k <= 3 && s->d > 1024 && s->T > 1024; }
 
 int moe_combine_impl(const moe_shape *s, const void *y, const int32_t *topk_idx, const float *topk_w,
@@ -143,12 +145,13 @@ int moe_combine_impl(const moe_shape *s, const void *y, const int32_t *topk_idx,
     // rows shorter than a block's 2048 columns: only the waves that have some (20000 tokens of 128 columns, 1 slot, 2 shared
     // experts: 13.2 us with all four, 7.3 with one)
     const unsigned threads = s->d >= 2048 ? 256 : (unsigned)(s->d + 511) / 512 * 64;
-#define COMBINE(kernel, grid)                                                                                                   \
-    hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, st, s->T, s->d, s->N, s->k, (const uint16_t *)y, topk_idx, topk_w, inv_perm, expert_mask, \
-                       (const uint16_t *)shared_y, shared_y ? n_shared : 0, shared_scale, (uint16_t *)out)
-    if (combine_walks(s)) COMBINE(combine_walk_kernel, dim3(s->T));
-    else if (expert_mask != nullptr) COMBINE(combine_kernel<true>, dim3(s->T, (s->d + 2047) / 2048));
-    else COMBINE(combine_kernel<false>, dim3(s->T, (s->d + 2047) / 2048));
+#define COMBINE(kernel, grid, ...)                                                                                              \
+    hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, st, s->T, s->d, __VA_ARGS__, (const uint16_t *)y, topk_idx, topk_w, inv_perm, \
+                       expert_mask, (const uint16_t *)shared_y, shared_y ? n_shared : 0, shared_scale, (uint16_t *)out)
+    const dim3 tiles(s->T, (s->d + 2047) / 2048);
+    if (combine_walks(s)) COMBINE(combine_walk_kernel, dim3(s->T), s->k);
+    else if (expert_mask != nullptr) COMBINE(combine_kernel<true>, tiles, s->N, s->k);
+    else COMBINE(combine_kernel<false>, tiles, s->N, s->k);
 #undef COMBINE
     MOE_CHECK_LAUNCH();
     return MOE_OK;
