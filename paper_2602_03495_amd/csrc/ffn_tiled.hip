@@ -345,11 +345,11 @@ __device__ __forceinline__ void tile_body(uint16_t (*Xs)[2][TM * 32], char *ys, 
 }
 
 // Item of a block of a launch that can cut.  Every XCD takes a contiguous run of the item list on its 32 compute units.  Where the
-// last round of the launch would occupy less than half of the units, its items run as two of half the width each (0.6 of the time,
-// measured): the round ends after 0.6 of an item instead of a whole one; with more the halves would not fit one round (1.2).
-// Up, d = 2048, I = 768, whole / cut: 522 items of 256 inner columns 195 / 176 us, 636 198 / 185, 783 237 / 220, 1035 298 / 282; the
-// rounds of 261 to 381 items, all of which ran as halves before, 139 / 137 to 166 / 160.  Down, same layer: 40 items of 512 columns
-// 28 / 21 us, 124 32 / 28, 260 69 / 62, 376 73 / 72, 528 86 / 79, 800 118 / 111, launches that are not cut 0 to 1 % slower.
+// last round of the launch would occupy less than half of the units, its items run as two of half the width each (0.5 to 0.6 of
+// the time, measured): the round ends after as much of an item instead of a whole one; with more the halves would not fit one round.
+// Up, d = 2048, I = 768, whole / cut: 522 items of 256 inner columns 195 / 176 us, 636 198 / 185, 783 237 / 220, 1035 298 / 282.
+// Down, same layer: 40 items of 512 columns 28 / 21 us, 124 32 / 28, 260 69 / 62, 376 73 / 72, 528 86 / 79, 800 118 / 111, launches that
+// are not cut 0 to 1 % slower.
 // 128 and 384 items, an exact half of a round, run as halves altogether: one and three full rounds of them (384 of the up
 // projection: 165 us, 161 with the last ones only; a test counts their blocks).
 // Returns the item, or -1 for a block without one; half is 0 or 1, or -1 for a whole item.
@@ -372,6 +372,24 @@ __device__ __forceinline__ int cut_item_of(int total, int pid, int &half)
     return first + whole + (j >> 1);
 }
 
+// Whether the up projection, whose whole items would be one round and less than half of another, runs all of them as halves (n_half
+// to a token tile): two to three rounds.
+// Two, where the last column tile is ragged and a half by itself: a cut list leaves its units idle after half of a round, and the
+// halves of the last items wait for others (d = 2048, I = 1408, 258 items = 473 halves, cut / halves: 1 row to a tile 105 / 87 us, 16
+// 106 / 86, 60 112 / 91, 128 127 / 101; 276 = 506: 107 / 90 to 130 / 105; with a third round, 294 = 539: 109 / 110 to 131 / 135; three column
+// tiles, I = 640, tables of routed rows: 73 to 89 / 72 to 80, d = 1152 44 to 55 / 46 to 48).
+// Three, where no tile is ragged and the tiles are short, so that a half takes half the time (d = 2048, I = 768 and 2048, 260 to 380
+// items: 1 to 32 rows to a tile 1 to 3 % faster, 40 rows 0 to 2 % slower, 128 rows 1 to 4 %).
+#define HALVES_SHORT_ROWS 32
+__device__ __forceinline__ bool up_runs_halves(int tiles, int n_ntc, int n_half, const moe_rows &r)
+{
+    const int items = tiles * n_ntc;
+    if (items <= 256 || items > HALVES_ITEMS) return false;
+    if (items == HALVES_ITEMS) return true;
+    if (n_half == 2 * n_ntc) return wave_sum_int_dpp(r.c0 + r.c1) <= HALVES_SHORT_ROWS * tiles;
+    return tiles * n_half <= 512;
+}
+
 // NTT_MAX bounds the token subtiles a tile of this launch can need (from T); the block then runs the smallest
 // body that covers its own rows, so a sparsely filled tile costs MFMA work for the rows it has.
 template <int MODE, int NF, int NTT_MAX, bool DIRECT, int NSETS, bool FENCED, int WAVES>
@@ -391,7 +409,9 @@ __global__ __launch_bounds__(WAVES * 64, 2) void ffn_tiled_kernel(
     constexpr bool CAN_CUT = tiled_can_cut(MODE, NF, FENCED, WAVES);
     constexpr int NT_COLS = WAVES * 16 * (MODE == 0 ? NF / 2 : NF);
     const int n_ntc = ((MODE == 0 ? I : d) + NT_COLS - 1) / NT_COLS;   // column tiles
+    const int n_half = ((MODE == 0 ? I : d) + NT_COLS / 2 - 1) / (NT_COLS / 2);
     int half = -1;
+    bool halves = false;               // every item runs at half width
 
     // ---- which item: (expert, token tile, column tile, K split).  The number of K splits follows from the number of
     // tiles that have work, which only the device knows (counts and mask live there)
@@ -403,7 +423,10 @@ __global__ __launch_bounds__(WAVES * 64, 2) void ffn_tiled_kernel(
         const moe_work work = moe_working_experts(N, counts, offsets, mask);
         const int n_work = work.experts();
         if (MODE == 1) nsp = moe_dev_splits(n_work * n_ntc, nsp_max);
-        if (CAN_CUT && nsp == 1) {
+        halves = MODE == 0 && CAN_CUT && up_runs_halves(n_work, n_ntc, n_half, work.rows());
+        if (halves) {
+            if (!moe_item_of(work, n_half, blockIdx.x, e, nt)) return;
+        } else if (CAN_CUT && nsp == 1) {
             const int L = cut_item_of(n_work * n_ntc, blockIdx.x, half);
             if (L < 0) return;
             moe_item_at(work, n_ntc, L, e, nt);
@@ -422,10 +445,11 @@ __global__ __launch_bounds__(WAVES * 64, 2) void ffn_tiled_kernel(
             if (blockIdx.x == 0 && threadIdx.x == 0) *rival = wide;
             if (wide) return;
         }
-        const int n_nt = n_ntc * nsp;
+        halves = MODE == 0 && CAN_CUT && up_runs_halves(tiles.total, n_ntc, n_half, rows);
+        const int n_nt = halves ? n_half : n_ntc * nsp;
         const int total = tiles.total * n_nt;
         int L;
-        if (CAN_CUT && nsp == 1) {
+        if (CAN_CUT && nsp == 1 && !halves) {
             L = cut_item_of(total, blockIdx.x, half);
             if (L < 0) return;
         } else {
@@ -445,6 +469,10 @@ __global__ __launch_bounds__(WAVES * 64, 2) void ffn_tiled_kernel(
         nt = g0 * group + within % gsz;
         row0 = offsets[e] + mt * tmk;
         nrows = counts[e] - mt * tmk;
+    }
+    if (halves) {
+        half = nt & 1;
+        nt >>= 1;
     }
     const int sp = nt % nsp;      // column tile nt / nsp, K split nt % nsp
     nt /= nsp;
@@ -562,8 +590,8 @@ static void launch_tiled(const moe_shape *s, long max_mt, const uint16_t *x, con
     const long tiles = DIRECT ? n_e : max_mt;
     long blocks = tiles * n_ntc * nsp_max;
     if (tiled_can_cut(MODE, NF, FENCED, WAVES)) {
-        // and the items that run as two (cut_item_of)
-        const long halves = blocks >= HALVES_ITEMS ? 2 * HALVES_ITEMS : 0;
+        // and the items that run as two: those of a last round (cut_item_of), or all of them (up_runs_halves)
+        const long halves = 2 * (blocks < HALVES_ITEMS ? blocks : HALVES_ITEMS);
         blocks += MOE_NUM_XCD * (XCD_CUS / 2);
         if (blocks < halves) blocks = halves;
     }

@@ -88,12 +88,21 @@ __device__ __forceinline__ float silu_mul(float g, float u) { return g * __built
 // contiguous run of the compacted item list (expert-major), and the item's expert is found by rank among the set
 // bits.  Returns false for a block beyond the list.  All 64 lanes of the wave must call it.
 #define MOE_NUM_XCD 8
+// rows of experts l and l + 64 in lane l, 0 where the expert does not work
+struct moe_rows {
+    int c0, c1;
+};
 // Lane l holds rows and first row of experts l and l + 64.  All reads are on their way at once: counts, then the mask where a
 // count allowed it, then rows and first row of the expert found were four round trips (0.5 to 1 us each at the start of a launch).
 struct moe_work {
     unsigned long long lo, hi;      // the working experts
     int c0, c1, o0, o1;
     __device__ __forceinline__ int experts() const { return __popcll(lo) + __popcll(hi); }
+    __device__ __forceinline__ moe_rows rows() const
+    {
+        const int l = threadIdx.x & 63;
+        return moe_rows{(lo >> l & 1ull) != 0 ? c0 : 0, (hi >> l & 1ull) != 0 ? c1 : 0};
+    }
     __device__ __forceinline__ int rows_of(int e) const { return e < 64 ? __builtin_amdgcn_readlane(c0, e) : __builtin_amdgcn_readlane(c1, e - 64); }
     __device__ __forceinline__ int first_row_of(int e) const { return e < 64 ? __builtin_amdgcn_readlane(o0, e) : __builtin_amdgcn_readlane(o1, e - 64); }
 };
@@ -157,9 +166,6 @@ __device__ __forceinline__ bool moe_item_of(const moe_work &w, int per_expert, i
 // places in the expert-major tile list (a prefix sum on the DPP crossbar).  A table written by a kernel ahead of the
 // launch cost that kernel (4.7-6.5 us per FFN call, T > 128) and two dependent reads per block; this costs a block one read
 // and about 60 instructions.  All 64 lanes must call these.
-struct moe_rows {
-    int c0, c1;
-};
 struct moe_tiles {
     int n0, n1, first0, first1, total;
 };

@@ -1,7 +1,8 @@
-"""Tiled expert FFN: the items of a last round that would fill less than half of the compute units run as two of half the width.
+"""Tiled expert FFN: the items of a last round that would fill less than half of the compute units run as two of half the width, and
+those of an up projection of 257 to 384 all of them, where that is two rounds or their token tiles are short.
 
-Row tables whose launches end in such a round, just beside it and in an exact half of one: the blocks that had an item, and
-the results against the oracle."""
+Row tables whose launches end in such a round, just beside it and in an exact half of one, on both sides of the rule of the up
+projection: the blocks that had an item, and the results against the oracle."""
 import numpy as np
 import pytest
 
@@ -15,7 +16,18 @@ torch = pytest.importorskip("torch")
 # rows per expert, d, I, blocks with an item of the up and of the down projection
 LAUNCHES = {
     "24 of 280 cut": ([130] * 70 + [0] * 58, 1024, 512, 304, 304),
-    "at most one tile per expert": ([1] * 90 + [0] * 38, 1024, 768, 284, 464),
+    # short tiles: all 270 of the up projection as halves
+    "at most one tile per expert": ([1] * 90 + [0] * 38, 1024, 768, 540, 464),
+    "32 rows to a tile": ([32] * 90, 128, 768, 540, 90),
+    "33 rows to a tile": ([33] * 90, 128, 768, 284, 90),
+    # 258 items with a ragged last column tile are 473 halves: two rounds of them
+    "two rounds of halves": ([2] * 43 + [0] * 20, 256, 1408, 473, 86),
+    "two rounds of halves, full tiles": ([128] * 43, 256, 1408, 473, 86),
+    "a half less than a third round": ([64] * 46 + [0], 256, 1408, 506, 92),
+    "halves would need a third round": ([64] * 47, 256, 1408, 303, 94),
+    "three column tiles": ([9] * 90, 128, 640, 450, 90),
+    "a whole round of items": ([3] * 64, 256, 1024, 256, 128),
+    "beyond 384": ([3] * 97, 128, 1024, 388, 97),
     "half a round": ([5] * 64 + [0] * 64, 1024, 512, 256, 256),
     "more than half a round": ([4] * 43, 2048, 768, 129, 432),
     "full tiles, deep prefetch": ([1030] * 8, 1024, 2048, 640, 448),
