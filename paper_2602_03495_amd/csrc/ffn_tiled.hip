@@ -345,16 +345,14 @@ __device__ __forceinline__ void tile_body(uint16_t (*Xs)[2][TM * 32], char *ys, 
 }
 
 // Item of a block of a launch that can cut.  Every XCD takes a contiguous run of the item list on its 32 compute units.  Where the
-// last round of the launch would occupy less than half of the units, its items run as two of half the width each (0.5 to 0.6 of
+// last round of the launch would occupy half of the units or less, its items run as two of half the width each (0.5 to 0.6 of
 // the time, measured): the round ends after as much of an item instead of a whole one; with more the halves would not fit one round.
 // Up, d = 2048, I = 768, whole / cut: 522 items of 256 inner columns 195 / 176 us, 636 198 / 185, 783 237 / 220, 1035 298 / 282.
 // Down, same layer: 40 items of 512 columns 28 / 21 us, 124 32 / 28, 260 69 / 62, 376 73 / 72, 528 86 / 79, 800 118 / 111, launches that
-// are not cut 0 to 1 % slower.
-// 128 and 384 items, an exact half of a round, run as halves altogether: one and three full rounds of them (384 of the up
-// projection: 165 us, 161 with the last ones only; a test counts their blocks).
+// are not cut 0 to 1 % slower.  An exact half of a round, up, I = 2048: 640 items 230 / 226 us with one row to a tile, 270 / 259 with 128;
+// down, 384 items, all of them as halves / the last ones: 17 rows 62 / 62, 128 rows 83 / 80.
 // Returns the item, or -1 for a block without one; half is 0 or 1, or -1 for a whole item.
 #define XCD_CUS 32
-#define HALVES_ITEMS 384
 // Not cut: the narrowest tiles, and the down projection over a K of 8192 and more, whose time wide_faster weighs against the long-K kernel.
 constexpr bool tiled_can_cut(int mode, int nf, bool fenced, int waves) { return waves == 8 && nf > 1 && (mode == 0 || !fenced); }
 __device__ __forceinline__ int cut_item_of(int total, int pid, int &half)
@@ -363,7 +361,7 @@ __device__ __forceinline__ int cut_item_of(int total, int pid, int &half)
     const int xcd = pid % MOE_NUM_XCD, loc = pid / MOE_NUM_XCD;
     const int n = q + (xcd < rem ? 1 : 0), first = xcd * q + min(xcd, rem);
     const int over = total % (MOE_NUM_XCD * XCD_CUS), half_round = MOE_NUM_XCD * XCD_CUS / 2;
-    const int cut = over < half_round ? n % XCD_CUS : over == half_round && total <= HALVES_ITEMS ? n : 0, whole = n - cut;
+    const int cut = over <= half_round ? n % XCD_CUS : 0, whole = n - cut;
     half = -1;
     if (loc < whole) return first + loc;
     const int j = loc - whole;
@@ -379,15 +377,16 @@ __device__ __forceinline__ int cut_item_of(int total, int pid, int &half)
 // 106 / 86, 60 112 / 91, 128 127 / 101; 276 = 506: 107 / 90 to 130 / 105; with a third round, 294 = 539: 109 / 110 to 131 / 135; three column
 // tiles, I = 640, tables of routed rows: 73 to 89 / 72 to 80, d = 1152 44 to 55 / 46 to 48).
 // Three, where no tile is ragged and the tiles are short, so that a half takes half the time (d = 2048, I = 768 and 2048, 260 to 380
-// items: 1 to 32 rows to a tile 1 to 3 % faster, 40 rows 0 to 2 % slower, 128 rows 1 to 4 %).
+// items: 1 to 32 rows to a tile 1 to 3 % faster, 40 rows 0 to 2 % slower, 128 rows 1 to 4 %); with ragged ones only where the third
+// round is more than half full (I = 1408, 1 to 16 rows: 294 to 342 items 0 to 1 % slower, 372 2 % faster, 384 3 %).
+#define HALVES_ITEMS 384
 #define HALVES_SHORT_ROWS 32
 __device__ __forceinline__ bool up_runs_halves(int tiles, int n_ntc, int n_half, const moe_rows &r)
 {
-    const int items = tiles * n_ntc;
+    const int items = tiles * n_ntc, halves = tiles * n_half;
     if (items <= 256 || items > HALVES_ITEMS) return false;
-    if (items == HALVES_ITEMS) return true;
-    if (n_half == 2 * n_ntc) return wave_sum_int_dpp(r.c0 + r.c1) <= HALVES_SHORT_ROWS * tiles;
-    return tiles * n_half <= 512;
+    if (halves <= 512) return true;
+    return (halves == 2 * items || halves > 640) && wave_sum_int_dpp(r.c0 + r.c1) <= HALVES_SHORT_ROWS * tiles;
 }
 
 // NTT_MAX bounds the token subtiles a tile of this launch can need (from T); the block then runs the smallest

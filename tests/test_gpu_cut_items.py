@@ -1,4 +1,4 @@
-"""Tiled expert FFN: the items of a last round that would fill less than half of the compute units run as two of half the width, and
+"""Tiled expert FFN: the items of a last round that would fill half of the compute units or less run as two of half the width, and
 those of an up projection of 257 to 384 all of them, where that is two rounds or their token tiles are short.
 
 Row tables whose launches end in such a round, just beside it and in an exact half of one, on both sides of the rule of the up
@@ -27,6 +27,11 @@ LAUNCHES = {
     "halves would need a third round": ([64] * 47, 256, 1408, 303, 94),
     "three column tiles": ([9] * 90, 128, 640, 450, 90),
     "a whole round of items": ([3] * 64, 256, 1024, 256, 128),
+    "384, long tiles": ([40] * 128, 128, 768, 512, 128),
+    "384, short tiles": ([32] * 128, 128, 768, 768, 128),
+    "384, ragged and short": ([3] * 64, 256, 1408, 704, 128),
+    "384 of the down projection": ([20] * 96, 2048, 128, 96, 512),
+    "half a round beyond two": ([3] * 128, 128, 1280, 768, 128),
     "beyond 384": ([3] * 97, 128, 1024, 388, 97),
     "half a round": ([5] * 64 + [0] * 64, 1024, 512, 256, 256),
     "more than half a round": ([4] * 43, 2048, 768, 129, 432),

@@ -153,10 +153,12 @@ def test_every_tile_height_and_split_of_the_down_projection(name):
     assert worst <= OUT_TOL, worst
 
 
-# rows per expert, inner size, blocks of the up projection that have an item: half-width items up to 3 rounds of 256, for which the
-# launch has just enough blocks, and one tile more
-UP_ITEMS = {"768 half-width items": ([257] * 128, 256, 768), "one tile more": ([257] * 127 + [385], 256, 385),
-            "768 half-width items, one tile per expert": ([1] * 128, 768, 768), "704 half-width items": ([130] * 32 + [0] * 8, 1408, 704)}
+# rows per expert, inner size, blocks of the up projection that have an item.  384 items, a round and a half: with a mean of 86 and 65 rows
+# to a tile the last 128 run as two blocks each (those of a ragged column tile, 4 of the 16 of every XCD, as one), with one row
+# all of them, three rounds; one tile more: none
+UP_ITEMS = {"a round and 256 half-width items": ([257] * 128, 256, 512), "one tile more": ([257] * 127 + [385], 256, 385),
+            "768 half-width items, one tile per expert": ([1] * 128, 768, 768),
+            "a round and 224 half-width items": ([130] * 32 + [0] * 8, 1408, 480)}
 
 
 @pytest.mark.parametrize("name", UP_ITEMS)
