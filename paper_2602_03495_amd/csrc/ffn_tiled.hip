@@ -500,10 +500,11 @@ __global__ __launch_bounds__(WAVES * 64, 2) void ffn_tiled_kernel(
         else BODY_NF(nf_, 8);                                      \
     } while (0)
     if constexpr (CAN_CUT) {
-        // a ragged last column tile that fits a half-width item runs as one (I = 1408: five items of 256 + one of 128)
-        if (MODE == 0 && nt == n_ntc - 1 && I % NT_COLS != 0 && I % NT_COLS <= NT_COLS / 2) {
+        // a ragged last column tile that fits a half-width item has no second half; that of the up projection always runs as a
+        // half-width item (I = 1408: five items of 256 + one of 128)
+        if (nt == n_ntc - 1 && n_half < 2 * n_ntc) {
             if (half == 1) return;
-            half = 0;
+            if (MODE == 0) half = 0;
         }
         if (__builtin_expect(half < 0, 1)) {
             BODIES(NF);

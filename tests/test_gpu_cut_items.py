@@ -32,6 +32,9 @@ LAUNCHES = {
     "384, ragged and short": ([3] * 64, 256, 1408, 704, 128),
     "384 of the down projection": ([20] * 96, 2048, 128, 96, 512),
     "half a round beyond two": ([3] * 128, 128, 1280, 768, 128),
+    # half of the last column tile of 512 and of 256 columns: 8 of the 44 items that are cut have no second half
+    "ragged down projection": ([20] * 60, 2304, 128, 60, 336),
+    "ragged down projection, narrow tiles": ([20] * 60, 1152, 128, 60, 336),
     "beyond 384": ([3] * 97, 128, 1024, 388, 97),
     "half a round": ([5] * 64 + [0] * 64, 1024, 512, 256, 256),
     "more than half a round": ([4] * 43, 2048, 768, 129, 432),
