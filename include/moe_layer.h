@@ -115,7 +115,8 @@ int moe_route(const moe_shape *s, const void *h, const void *gate_w, const float
  *   top_experts[0..p) = experts by descending pred_counts, equal counts by ascending index.
  *
  * The logits are evaluated as h.W + (res_vec.W + bias), which equals (h + res_vec).W + bias up to
- * fp32 rounding; h + res_vec is never rounded to bf16.
+ * fp32 rounding; h + res_vec is never rounded to bf16.  Infinite elements of res_vec and of the gate give
+ * infinite logits as that sum does.
  * h [T,d] bf16, res_vec [d] fp32 (16-byte aligned), next_gate_w [N,d] bf16, next_gate_bias [N] fp32 or NULL,
  * pred_counts [N] int32 out, top_experts [p] int32 out (1 <= p <= N): all [device].
  */
@@ -126,9 +127,8 @@ int moe_predict_workload(const moe_shape *s, const void *h, const float *res_vec
 /*
  * moe_route of this layer and moe_predict_workload for the next one in a single call, with the results of the two
  * calls made one after the other (same arguments, same outputs, bit for bit).  The features h are the input of
- * both gates (Section "Residual-Based Prefetching": the prediction uses the current layer's features), so at decode
- * sizes (T <= 16 and T*k <= 128) the two gates are evaluated side by side by the same pair of launches; larger
- * batches run the two calls in sequence.  workspace is required (not NULL).
+ * both gates (Section "Residual-Based Prefetching": the prediction uses the current layer's features), so the two
+ * gates are evaluated side by side by the same launches.  workspace is required (not NULL).
  */
 int moe_route_predict(const moe_shape *s, const void *h, const void *gate_w, const float *gate_bias, int norm_mode,
                       int32_t *topk_idx, float *topk_w, int32_t *counts, int32_t *offsets, int32_t *perm,

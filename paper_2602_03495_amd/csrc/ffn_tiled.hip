@@ -26,10 +26,11 @@
 // run up to 40 % slower, even with one token tile per expert).
 // Tiles are rarely full: the launch bounds the 16-row subtiles by T and every block runs the body sized for its own
 // row count (16, 32, 64, 96, 112 or 128 rows).
-// What only the device knows (counts and mask) also shapes the launch there: the last items of a launch
-// run at half width where they would fill less than half a round of compute units, and the down projection splits the K range of its tiles over several items (fp32 partial
-// sums, summed in split order by tiled_finish_kernel); with many, the blocks pick the token-tile height of
-// the down projection so that its items fill whole rounds of compute units.
+// What only the device knows (counts and mask) also shapes the launch there: the last items of a launch run at half width where
+// they would fill half a round of compute units or less, in some launches of the up projection all of them (up_runs_halves); with
+// few items the down projection splits the K range of its tiles over several (fp32 partial sums, summed in split order by
+// tiled_finish_kernel); with many, the blocks pick the token-tile height of the down projection so that its items fill whole rounds
+// of compute units.
 // Each item walks K as a ring starting at an expert-dependent offset, so that the token tiles that share a weight tile
 // stay in step (started at different points they run 18 % slower); the summation order is a function of the expert
 // and of the number of K splits only, so results are reproducible for given inputs.
@@ -68,7 +69,8 @@ extern "C" int moe_debug_set_trace(unsigned long long *records)
 // units moves its duration in steps: 27 token tiles are 216 items, one round with 40 units idle, and 30 tiles of 112
 // rows are 240 items, still one round of shorter items.  The tile height of the down projection is therefore chosen
 // here, on the device, from the workloads: 128, 112 or 96 rows, whichever gives the smallest (rounds x item time),
-// with an item's time taken as proportional to (height + 64): its weight loads do not shrink with the tile.
+// with an item's time taken as proportional to (height + 64): its weight loads do not shrink with the tile.  (A last round of
+// items that run as halves, cut_item_of, counts as a whole one here and in moe_dev_splits.)
 __device__ __forceinline__ int sched_cost(int tiles, int n_ntc, int tm)
 {
     const int items = tiles * n_ntc;
@@ -305,11 +307,10 @@ __device__ __forceinline__ void tile_body(uint16_t (*Xs)[2][TM * 32], char *ys, 
         }
         return;
     }
-    // The results leave through LDS (2 KB of the wave's own), so that the lanes of a store cover whole runs of a row: stored from the
+    // The results leave through LDS (up to 2 KB of the wave's own), so that the lanes of a store cover whole runs of a row: stored from the
     // accumulators, neighbouring lanes in different rows, each of the 64 lanes is an access of its own, and the next block waits
     // for all of them (12089 rows of 64 experts, d = 2048, I = 768: up 119 us level, down 87 -> 77; 12047 rows of 32, I = 1408:
-    // down 95 -> 92; the passes 1.104 / 1.037 and 1.056 / 1.010 of the start's speed with and without).  Chunk c (16 bytes) of
-    // row i sits in slot c ^ (i & (C - 1)).
+    // down 95 -> 92; the whole layer's pass 6 and 4.5 % faster).  Chunk c (16 bytes) of row i sits in slot c ^ (i & (C - 1)).
     constexpr int C = WAVE_COLS / 8;                       // 16-byte chunks of a row
     constexpr int TS = NTT < 8 / C ? NTT : C == 2 ? 2 : 1; // subtiles per store: all 64 lanes, where there are that many rows
     const int yr = lane / C, yc = lane % C;
@@ -353,7 +354,7 @@ __device__ __forceinline__ void tile_body(uint16_t (*Xs)[2][TM * 32], char *ys, 
 // down, 384 items, all of them as halves / the last ones: 17 rows 62 / 62, 128 rows 83 / 80.
 // Returns the item, or -1 for a block without one; half is 0 or 1, or -1 for a whole item.
 #define XCD_CUS 32
-// Not cut: the narrowest tiles, and the down projection over a K of 8192 and more, whose time wide_faster weighs against the long-K kernel.
+// Not cut: the narrowest tiles, and tiles of 512 columns over a K of 8192 and more (FENCED).
 constexpr bool tiled_can_cut(int mode, int nf, bool fenced, int waves) { return waves == 8 && nf > 1 && (mode == 0 || !fenced); }
 __device__ __forceinline__ int cut_item_of(int total, int pid, int &half)
 {

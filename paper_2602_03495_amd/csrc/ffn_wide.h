@@ -78,6 +78,10 @@ __device__ __forceinline__ wide_plan wide_plan_of(const moe_rows &c, int n_nt, i
 //   tiled kernel  a a round + b a round's worth of items, a and b by the shape of its items (tiled_step_cost)
 // This one has to come out 1 % ahead: 5380 of the calls go to it, median 1.17 times as fast as the tiled one, 4 of them below 0.96.
 // With a line on the size of the activations alone, 1 call in 15 that it sent here was below 0.96, at worst 0.48.
+// Those tiles were whole; items of 256 columns in a last round of half the units or less run as two of half the width now (cut_item_of),
+// 0.80 of the time of such a launch, and are still charged as a whole round: 900 calls that take that width (d = 1024 .. 4096, I =
+// 8192 .. 16384, 6 to 16 experts, skewed rows, masks) take 1.007 of the faster kernel's time in the mean, at worst 1.14, with 0.7 of a round
+// 1.005 and 1.14, with 0.6 1.008 and 1.25; on 400 others 0.7 was level with a whole one (0.94 to 1.09).
 // Down projection, tiled against this kernel, d = 4096, I = 14336: 1441 .. 190 rows of six experts 617 and 423 us, 1540 .. 126 rows of
 // six (256 items of 256 x 256) 375 and 331, 8192 tokens through eight 1790 and 1570, but 280 .. 254 rows of six (256 items of 128 x
 // 256, one exact round) 230 and 354 and 665 .. 596 rows of six (288 items of 256 x 256, 32 beyond one round) 374 and 442.

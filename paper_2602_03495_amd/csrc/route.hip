@@ -235,7 +235,7 @@ struct gate_job {
     float *topk_w;             // [T,k]
     int32_t *counts;           // non-null: single-block launch that also does the histogram (and, with perm, scan and permutation)
     int32_t *offsets, *perm, *inv_perm;
-    float *logits;             // [T,N] between gate_topk_kernel<NT, true> and select_decode_kernel
+    float *logits;             // [T,N] between gate_logits_kernel and the kernel that selects
     int32_t *top;              // with counts and without perm: the p largest workloads
     int p;
     shared_tail x;             // x.S > 0 (with perm, decode-sized launches only): also write the tables with the shared experts appended
@@ -893,7 +893,7 @@ static void launch_gate_logits(const moe_shape *s, const uint16_t *h, dim3 grid,
 }
 
 // Launches the gate kernels for one job, or for two jobs side by side (both of the same size, so they take the same
-// path).  ws_logits[i]: [16, N] scratch of job i for decode-sized batches, or null (a job with a residual always has one).
+// path).  ws_logits[i]: [max(T, 16), N] scratch of job i for the paths that store logits, or null (a job with a residual always has one).
 static int launch_gate_topk(const moe_shape *s, const void *h, hipStream_t st, int n_jobs, gate_job *jobs, float *const *ws_logits)
 {
     const int NT = (s->N + 15) / 16;
@@ -965,7 +965,7 @@ static int launch_gate_topk(const moe_shape *s, const void *h, hipStream_t st, i
     return MOE_OK;
 }
 
-// [16, N] fp32 logits scratch number `which` (0: routing, 1: prediction) inside the routing workspace
+// [max(T, 16), N] fp32 logits scratch number `which` (0: routing, 1: prediction) inside the routing workspace
 static float *route_logits_scratch(const moe_shape *s, void *workspace, int which)
 {
     if (workspace == nullptr) return nullptr;
