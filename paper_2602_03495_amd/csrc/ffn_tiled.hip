@@ -371,7 +371,7 @@ __device__ __forceinline__ int cut_item_of(int total, int pid, int &half)
     return first + whole + (j >> 1);
 }
 
-// Whether the up projection, whose whole items would be one round and less than half of another, runs all of them as halves (n_half
+// Whether the up projection, whose whole items would be one round and up to half of another, runs all of them as halves (n_half
 // to a token tile): two to three rounds.
 // Two, where the last column tile is ragged and a half by itself: a cut list leaves its units idle after half of a round, and the
 // halves of the last items wait for others (d = 2048, I = 1408, 258 items = 473 halves, cut / halves: 1 row to a tile 105 / 87 us, 16
