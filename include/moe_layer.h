@@ -187,6 +187,20 @@ int moe_expert_ffn_stage(const moe_shape *s, const void *h, const int32_t *perm,
                          const uint8_t *expert_mask, void *y, void *workspace, int stages, void *stream);
 
 /*
+ * The expert FFNs of one layer: moe_expert_ffn of the routed experts and, with ss != NULL, of the shared ones (ss: the shape given to
+ * moe_dense_route, same T and d; every token through every shared expert, no mask).  Both write what moe_expert_ffn writes (the fp32
+ * sums of a projection may be added in another order).  Up to an inner size of 8191 and with enough routed rows all projections run as one
+ * launch, in which the down projection of a token tile starts when its activations are there (not in the records of
+ * moe_debug_set_trace); otherwise the calls are made one after the other.
+ * The two workspaces are different ones.  ss == NULL: the arguments behind it are not looked at.
+ * Errors: those of moe_expert_ffn, for either set of experts, before anything is launched.
+ */
+int moe_layer_ffn(const moe_shape *s, const void *h, const int32_t *perm, const int32_t *offsets, const int32_t *counts,
+                  const void *w1, const void *w3, const void *w2, const uint8_t *expert_mask, void *y, void *workspace,
+                  const moe_shape *ss, const int32_t *s_perm, const int32_t *s_offsets, const int32_t *s_counts,
+                  const void *sw1, const void *sw3, const void *sw2, void *shared_y, void *s_workspace, void *stream);
+
+/*
  * moe_expert_ffn for callers that cannot allocate device memory or carry a workspace: code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same kernels and bit-identical results, but
  * the scratch (inner activations, split-K partial sums) lives in an array that is part of the library's

@@ -20,7 +20,7 @@ EXPORTS = ["moe_strerror", "moe_workspace_bytes", "moe_route", "moe_predict_work
            "moe_expert_ffn_stage", "moe_combine", "moe_dense_route", "moe_shared_gate", "moe_pack_weights",
            "moe_expert_times", "moe_greedy_assign", "moe_cache_step", "moe_res_vec_workspace_bytes",
            "moe_res_vec_accumulate", "moe_res_vec_finish", "moe_route_predict", "moe_append_shared",
-           "moe_expert_ffn_static", "moe_static_scratch_bytes", "moe_debug_set_trace", "moe_route_shared"]
+           "moe_expert_ffn_static", "moe_static_scratch_bytes", "moe_debug_set_trace", "moe_route_shared", "moe_layer_ffn"]
 
 
 class MoeShape(C.Structure):
@@ -178,6 +178,23 @@ def moe_expert_ffn(s: MoeShape, h, perm, offsets, counts, w1, w3, w2, expert_mas
                                        _ptr(w3, torch.bfloat16), _ptr(w2, torch.bfloat16), _ptr(expert_mask, torch.uint8),
                                        _ptr(y, torch.bfloat16), _ws_ptr(ws), _stream())
     _check(rc, "moe_expert_ffn")
+    return y
+
+
+def moe_layer_ffn(s: MoeShape, h, perm, offsets, counts, w1, w3, w2, expert_mask, y, ws: torch.Tensor, shared=None):
+    """moe_expert_ffn of the routed experts and, with shared = (shape, perm, offsets, counts, w1, w3, w2, y, workspace), of the shared
+    ones, in one launch where the library can."""
+    def side(perm, offsets, counts, w1, w3, w2):
+        return (_ptr(perm, torch.int32), _ptr(offsets, torch.int32), _ptr(counts, torch.int32), _ptr(w1, torch.bfloat16),
+                _ptr(w3, torch.bfloat16), _ptr(w2, torch.bfloat16))
+
+    if shared is None:
+        tail = (C.c_void_p(0),) * 9
+    else:
+        tail = (C.byref(shared[0]), *side(*shared[1:7]), _ptr(shared[7], torch.bfloat16), _ws_ptr(shared[8]))
+    rc = load_library().moe_layer_ffn(C.byref(s), _ptr(h, torch.bfloat16), *side(perm, offsets, counts, w1, w3, w2),
+                                      _ptr(expert_mask, torch.uint8), _ptr(y, torch.bfloat16), _ws_ptr(ws), *tail, _stream())
+    _check(rc, "moe_layer_ffn")
     return y
 
 

@@ -100,11 +100,15 @@ __device__ __forceinline__ moe_tiles down_tiles(const moe_rows &c, int n_ntc, in
 // MODE 1: down (W2 -> y); a wave owns NF consecutive fragments of W2.
 // Weight tile of a block: 8 waves x NF fragments x 16 rows.  NTT = 16-row token subtiles computed (rows past
 // nrows are clamped copies whose results are dropped).
-template <int MODE, int NF, int NTT, int NSETS, bool FENCED, int WAVES>
+// ahead_of_stores: called by every wave between its last product and its epilogue.
+struct nothing_ahead {
+    __device__ __forceinline__ void operator()() const {}
+};
+template <int MODE, int NF, int NTT, int NSETS, bool FENCED, int WAVES, bool THROUGH = false, class Ahead = nothing_ahead>
 __device__ __forceinline__ void tile_body(uint16_t (*Xs)[2][TM * 32], char *ys, int d, int I, int k, const uint16_t *__restrict__ xsrc,
                                           const int32_t *__restrict__ perm, const uint16_t *__restrict__ wa,
                                           const uint16_t *__restrict__ wb, uint16_t *__restrict__ out, int e, int nt,
-                                          int row0, int nrows, int sp, int nsp, float *__restrict__ part, int R)
+                                          int row0, int nrows, int sp, int nsp, float *__restrict__ part, int R, const int tid, Ahead ahead_of_stores = {})
 {
     constexpr int HF = MODE == 0 ? NF / 2 : NF;           // fragments per matrix per wave
     constexpr int WAVE_COLS = HF * 16;                     // output columns a wave produces
@@ -114,7 +118,7 @@ __device__ __forceinline__ void tile_body(uint16_t (*Xs)[2][TM * 32], char *ys, 
     const int NOUT = MODE == 0 ? I : d;
     const int n0 = nt * NT_COLS;
 
-    const int tid = threadIdx.x, lane = tid & 63;
+    const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: lets the weight addresses live in SGPRs
     const int li = lane & 15, lg = lane >> 4;
     const int kb_n = K / 32;                               // k32 blocks per weight row block
@@ -286,6 +290,7 @@ __device__ __forceinline__ void tile_body(uint16_t (*Xs)[2][TM * 32], char *ys, 
 #undef WLOAD
 #undef MOE_WLD
 
+    ahead_of_stores();
     // ---- epilogue: in every 16x16 tile a lane holds weight rows 4*lg + 0..3 (= output columns) of token li
     const int colw = n0 + wave * WAVE_COLS;
     if (colw >= NOUT) return;                               // wave past the ragged edge: its columns were recomputed only
@@ -338,7 +343,14 @@ __device__ __forceinline__ void tile_body(uint16_t (*Xs)[2][TM * 32], char *ys, 
             const int i = q + yr;                          // row of the TS subtiles
             if (i < TS * 16) {
                 const u32x4 v = *reinterpret_cast<const u32x4 *>(ys + i * (C * 16) + ((yc ^ (i & (C - 1))) * 16));
-                if (t0 * 16 + i < nrows) *reinterpret_cast<u32x4 *>(out + (size_t)(row0 + t0 * 16 + i) * NOUT + colw + yc * 8) = v;
+                if (t0 * 16 + i < nrows) {
+                    u32x4 *const q = reinterpret_cast<u32x4 *>(out + (size_t)(row0 + t0 * 16 + i) * NOUT + colw + yc * 8);
+                    if (THROUGH)      // sc1: past the caches of this XCD
+                        __builtin_amdgcn_raw_buffer_store_b128(v, __builtin_amdgcn_make_buffer_rsrc(out + (size_t)row0 * NOUT, 0, nrows * NOUT * 2, 0x00027000),
+                                                               ((t0 * 16 + i) * NOUT + colw + yc * 8) * 2, 0, 0x10);
+                    else
+                        *q = v;
+                }
             }
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -477,7 +489,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void ffn_tiled_kernel(
     const int sp = nt % nsp;      // column tile nt / nsp, K split nt % nsp
     nt /= nsp;
     nrows = nrows > tmk ? tmk : nrows;
-#define BODY_NS(nf_, n, ns_) tile_body<MODE, nf_, n, ns_, FENCED, WAVES>(Xs, Ys[__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)], d, I, k, xsrc, perm, wa, wb, out, e, nt, row0, nrows, sp, nsp, part, R)
+#define BODY_NS(nf_, n, ns_) tile_body<MODE, nf_, n, ns_, FENCED, WAVES>(Xs, Ys[__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)], d, I, k, xsrc, perm, wa, wb, out, e, nt, row0, nrows, sp, nsp, part, R, threadIdx.x)
 #define BODY_NF(nf_, n) BODY_NS(nf_, n, NSETS)
     // tiles with few token rows do little arithmetic per weight byte: their speed is the speed of the weight stream, so
     // they prefetch further ahead (8 register sets instead of 4; the accumulators of a short tile leave the room)
@@ -567,6 +579,8 @@ __global__ __launch_bounds__(256) void tiled_finish_kernel(int d, int R, int N, 
         else add_splits<8>(partial, row0 + j, R, d, f, y);
     }
 }
+
+#include "ffn_joint.h"
 
 // measurement switch: how many column tiles alternate in the item order (see the kernel); 1 = column tile major
 static int tiled_item_group(int mode)
@@ -697,5 +711,62 @@ int moe_ffn_tiled_impl(const moe_shape *s, const void *h, const int32_t *perm, c
         }
         if (wide != nullptr) return moe_ffn_wide_down(s, offsets, counts, act, w2, y, expert_mask, part, wide, st);
     }
+    return MOE_OK;
+}
+
+// Whether the FFNs of a layer run as a joint launch: K not split (it has no partial sums), inner sizes the long-K kernel does not take,
+// and enough work that filled last rounds pay for the clearing launch, the tickets and the activations' way past the caches.
+// Routed experts alone, two launches / joint, d = 2048, all and half of the experts on: 64 experts, I = 1408, 300 tokens of 6 slots 180 /
+// 183 and 125 / 130 us, 900 tokens 250 / 232 and 156 / 153, 2048 336 / 304 and 250 / 227; 128 experts, I = 768, 150 tokens of 8 slots 113 / 116
+// and 99 / 103, 300 150 / 146 and 113 / 116, 900 212 / 197 and 161 / 155, 4096 436 / 402 and 365 / 327.
+// Together with shared experts there are four launches to join: two of I = 1408, 70 tokens 157 / 134 us, 300 227 / 190, 2048 424 / 362; one of
+// I = 5632, 150 tokens 200 / 171, 2048 425 / 360, 4096 627 / 587, but 70 tokens 127 / 129, where its own down projection splits K.
+#define JOINT_MIN_ROWS 3072
+bool moe_ffn_joint_ok(const moe_shape *s, const moe_shape *ss)
+{
+    if (s->I >= 8192 || moe_tiled_down_max_splits(s) != 1) return false;
+    if (ss == nullptr) return s->T > TM && (long)s->T * s->k >= JOINT_MIN_ROWS;
+    return ss->I < 8192 && s->T > (ss->I > 2 * s->I ? TM : MOE_SKINNY_MAX_T);
+}
+
+static joint_experts joint_side(const moe_shape *s, const int32_t *perm, const int32_t *offsets, const int32_t *counts, const void *w1,
+                                const void *w3, const void *w2, const uint8_t *mask, void *y, void *workspace)
+{
+    const moe_ws_layout L = moe_ws(s);
+    // the counters lie in the routing scratch, which holds 8 bytes per routed row and is idle during the FFN
+    return {perm, offsets, counts, (const uint16_t *)w1, (const uint16_t *)w3, (const uint16_t *)w2, mask,
+            (uint16_t *)((char *)workspace + L.act), (uint16_t *)y, (int32_t *)((char *)workspace + L.route), s->I, s->N, s->k};
+}
+
+int moe_ffn_joint_impl(const moe_shape *s, const void *h, const int32_t *perm, const int32_t *offsets, const int32_t *counts, const void *w1,
+                       const void *w3, const void *w2, const uint8_t *expert_mask, void *y, void *workspace, const moe_shape *ss,
+                       const int32_t *s_perm, const int32_t *s_offsets, const int32_t *s_counts, const void *sw1, const void *sw3,
+                       const void *sw2, void *shared_y, void *s_workspace, hipStream_t st)
+{
+    const auto max_tiles = [](const moe_shape *p) {
+        const long R = (long)p->T * p->k;
+        return R / TM + (p->N < R ? p->N : R);
+    };
+    const auto est_tiles = [](const moe_shape *p) {
+        const long R = (long)p->T * p->k, one = p->N < R ? p->N : R;
+        return (R + TM - 1) / TM > one ? (R + TM - 1) / TM : one;
+    };
+    const int d = s->d;
+    const joint_experts a = joint_side(s, perm, offsets, counts, w1, w3, w2, expert_mask, y, workspace);
+    joint_experts b = {};
+    if (ss != nullptr) b = joint_side(ss, s_perm, s_offsets, s_counts, sw1, sw3, sw2, nullptr, shared_y, s_workspace);
+    // the tickets (2 KB) lie in the room of the split-K partial sums, which this launch has none of (at least 4 d bytes for each of 17 rows)
+    int32_t *const tickets = (int32_t *)((char *)workspace + moe_ws(s).partial);
+    const long na = max_tiles(s), nb = ss != nullptr ? max_tiles(ss) : 0, est = est_tiles(s) + (ss != nullptr ? est_tiles(ss) : 0);
+    hipLaunchKernelGGL(joint_clear_kernel, dim3(1), dim3(256), 0, st, tickets, a.arrived, (int)na, b.arrived, (int)nb);
+    MOE_CHECK_LAUNCH();
+    // the widest weight tile of the down projection that leaves every compute unit a block
+    const int nf = est * ((d + 511) / 512) >= 256 ? 4 : est * ((d + 255) / 256) >= 256 ? 2 : 1;
+    const joint_args args = {{a, b}, (const uint16_t *)h, tickets, d};
+    const dim3 grid(MOE_NUM_XCD * JOINT_BLOCKS_PER_XCD);
+    if (nf == 4) hipLaunchKernelGGL(ffn_joint_kernel<4>, grid, dim3(TILED_THREADS), 0, st, args);
+    else if (nf == 2) hipLaunchKernelGGL(ffn_joint_kernel<2>, grid, dim3(TILED_THREADS), 0, st, args);
+    else hipLaunchKernelGGL(ffn_joint_kernel<1>, grid, dim3(TILED_THREADS), 0, st, args);
+    MOE_CHECK_LAUNCH();
     return MOE_OK;
 }

@@ -19,6 +19,10 @@ int moe_ffn_tiled_impl(const moe_shape *, const void *, const int32_t *, const i
                        const void *, const void *, const uint8_t *, void *, void *, int, hipStream_t);
 int moe_ffn_skinny_impl(const moe_shape *, const void *, const int32_t *, const int32_t *, const int32_t *, const void *,
                         const void *, const void *, const uint8_t *, void *, void *, int, hipStream_t);
+bool moe_ffn_joint_ok(const moe_shape *, const moe_shape *);
+int moe_ffn_joint_impl(const moe_shape *, const void *, const int32_t *, const int32_t *, const int32_t *, const void *, const void *,
+                       const void *, const uint8_t *, void *, void *, const moe_shape *, const int32_t *, const int32_t *,
+                       const int32_t *, const void *, const void *, const void *, void *, void *, hipStream_t);
 int moe_combine_impl(const moe_shape *, const void *, const int32_t *, const float *, const int32_t *, const uint8_t *,
                      const void *, int, const float *, void *, hipStream_t);
 
@@ -66,6 +70,26 @@ static int check_shape(const moe_shape *s, bool need_I)
     if (need_I && (s->I < 128 || s->I % 128 != 0)) return MOE_EINVAL;
     if ((long long)s->T * s->d >= (1ll << 31)) return MOE_EINVAL;
     return MOE_OK;
+}
+
+static int check_ffn(const moe_shape *s, const void *h, const int32_t *perm, const int32_t *offsets, const int32_t *counts,
+                     const void *w1, const void *w3, const void *w2, const void *y, const void *workspace)
+{
+    int rc = check_shape(s, true);
+    if (rc != MOE_OK) return rc;
+    if (!h || !perm || !offsets || !counts || !w1 || !w3 || !w2 || !y || !workspace) return MOE_EINVAL;
+    if (!aligned16(h) || !aligned16(w1) || !aligned16(w3) || !aligned16(w2) || !aligned16(y)) return MOE_EINVAL;
+    if (((uintptr_t)workspace & 255u) != 0) return MOE_EWORKSPACE;
+    // every kernel reads the weights in the packed fragment order; row-major arrays would be multiplied as garbage
+    if (s->weight_layout != MOE_WEIGHTS_PACKED) return MOE_EUNSUPPORTED;
+    return MOE_OK;
+}
+
+// the decode path keeps a wave's share of the hidden dimension in registers: at most 4096 wide
+static int ffn_path_of(const moe_shape *s)
+{
+    if (s->ffn_path != MOE_FFN_AUTO) return s->ffn_path;
+    return s->T <= MOE_SKINNY_MAX_T && s->d <= MOE_SKINNY_WAVES * MOE_SKINNY_MAX_STEPS * 32 ? MOE_FFN_SKINNY : MOE_FFN_TILED;
 }
 
 extern "C" {
@@ -127,17 +151,9 @@ int moe_expert_ffn_stage(const moe_shape *s, const void *h, const int32_t *perm,
                          void *y, void *workspace, int stages, void *stream)
 {
     if (stages < 1 || stages > MOE_FFN_STAGE_ALL) return MOE_EINVAL;
-    int rc = check_shape(s, true);
+    const int rc = check_ffn(s, h, perm, offsets, counts, w1, w3, w2, y, workspace);
     if (rc != MOE_OK) return rc;
-    if (!h || !perm || !offsets || !counts || !w1 || !w3 || !w2 || !y || !workspace) return MOE_EINVAL;
-    if (!aligned16(h) || !aligned16(w1) || !aligned16(w3) || !aligned16(w2) || !aligned16(y)) return MOE_EINVAL;
-    if (((uintptr_t)workspace & 255u) != 0) return MOE_EWORKSPACE;
-    // every kernel reads the weights in the packed fragment order; row-major arrays would be multiplied as garbage
-    if (s->weight_layout != MOE_WEIGHTS_PACKED) return MOE_EUNSUPPORTED;
-    int path = s->ffn_path;
-    // the decode path keeps a wave's share of the hidden dimension in registers: at most 4096 wide
-    if (path == MOE_FFN_AUTO)
-        path = s->T <= MOE_SKINNY_MAX_T && s->d <= MOE_SKINNY_WAVES * MOE_SKINNY_MAX_STEPS * 32 ? MOE_FFN_SKINNY : MOE_FFN_TILED;
+    const int path = ffn_path_of(s);
     if (path == MOE_FFN_SKINNY)
         return moe_ffn_skinny_impl(s, h, perm, offsets, counts, w1, w3, w2, expert_mask, y, workspace, stages, (hipStream_t)stream);
     if (path == MOE_FFN_TILED)
@@ -150,6 +166,26 @@ int moe_expert_ffn(const moe_shape *s, const void *h, const int32_t *perm, const
                    void *stream)
 {
     return moe_expert_ffn_stage(s, h, perm, offsets, counts, w1, w3, w2, expert_mask, y, workspace, MOE_FFN_STAGE_ALL, stream);
+}
+
+int moe_layer_ffn(const moe_shape *s, const void *h, const int32_t *perm, const int32_t *offsets, const int32_t *counts, const void *w1,
+                  const void *w3, const void *w2, const uint8_t *expert_mask, void *y, void *workspace, const moe_shape *ss,
+                  const int32_t *s_perm, const int32_t *s_offsets, const int32_t *s_counts, const void *sw1, const void *sw3,
+                  const void *sw2, void *shared_y, void *s_workspace, void *stream)
+{
+    int rc = check_ffn(s, h, perm, offsets, counts, w1, w3, w2, y, workspace);
+    if (rc != MOE_OK) return rc;
+    if (ss != nullptr) {
+        rc = check_ffn(ss, h, s_perm, s_offsets, s_counts, sw1, sw3, sw2, shared_y, s_workspace);
+        if (rc != MOE_OK) return rc;
+        if (ss->T != s->T || ss->d != s->d || workspace == s_workspace) return MOE_EINVAL;
+    }
+    if (ffn_path_of(s) == MOE_FFN_TILED && (ss == nullptr || ffn_path_of(ss) == MOE_FFN_TILED) && moe_ffn_joint_ok(s, ss))
+        return moe_ffn_joint_impl(s, h, perm, offsets, counts, w1, w3, w2, expert_mask, y, workspace, ss, s_perm, s_offsets, s_counts,
+                                  sw1, sw3, sw2, shared_y, s_workspace, (hipStream_t)stream);
+    rc = moe_expert_ffn(s, h, perm, offsets, counts, w1, w3, w2, expert_mask, y, workspace, stream);
+    if (rc != MOE_OK || ss == nullptr) return rc;
+    return moe_expert_ffn(ss, h, s_perm, s_offsets, s_counts, sw1, sw3, sw2, nullptr, shared_y, s_workspace, stream);
 }
 
 size_t moe_static_scratch_bytes(void) { return MOE_STATIC_SCRATCH_BYTES; }

@@ -110,11 +110,21 @@ class MoeLayer:
 
     def expert_ffn(self, h, w: LayerWeights, mask):
         r = self.routing
-        return B.moe_expert_ffn(self.shape, h, r.perm, r.offsets, r.counts, w.w1, w.w3, w.w2, mask, self.y, self.ws)
+        return B.moe_layer_ffn(self.shape, h, r.perm, r.offsets, r.counts, w.w1, w.w3, w.w2, mask, self.y, self.ws)
 
-    def shared_ffn(self, h, w: LayerWeights):
+    def _shared_gate(self, h, w: LayerWeights):
         if self.shared_scale is not None:
             B.moe_shared_gate(self.sshape, h, w.w_sg, self.shared_scale)
+
+    def all_ffn(self, h, w: LayerWeights, mask):
+        """expert_ffn and shared_ffn in one call."""
+        self._shared_gate(h, w)
+        r = self.routing
+        return B.moe_layer_ffn(self.shape, h, r.perm, r.offsets, r.counts, w.w1, w.w3, w.w2, mask, self.y, self.ws,
+                               (self.sshape, self.s_perm, self.s_offsets, self.s_counts, w.sw1, w.sw3, w.sw2, self.shared_y, self.sws))
+
+    def shared_ffn(self, h, w: LayerWeights):
+        self._shared_gate(h, w)
         return B.moe_expert_ffn(self.sshape, h, self.s_perm, self.s_offsets, self.s_counts, w.sw1, w.sw3, w.sw2, None,
                                 self.shared_y, self.sws)
 
@@ -128,9 +138,10 @@ class MoeLayer:
     def forward(self, h, w: LayerWeights, mask, bias=None, with_shared=True):
         """route -> expert FFN (masked) -> [shared experts] -> combine; returns out [T,d] bf16."""
         self.route(h, w, bias)
-        self.expert_ffn(h, w, mask)
         if self.n_shared and with_shared:
-            self.shared_ffn(h, w)
+            self.all_ffn(h, w, mask)
+        else:
+            self.expert_ffn(h, w, mask)
         return self.combine(mask, with_shared)
 
     def merged_mask(self, mask) -> torch.Tensor:
@@ -148,7 +159,7 @@ class MoeLayer:
         b = w.gate_bias if bias is None else bias
         x = B.moe_route_shared(self.shape, self.n_merged, h, w.gate_w, b, self.cfg.norm_mode,
                                w.w_sg if self.shared_scale is not None else None, self.routing, self.xrouting, self.ws)
-        B.moe_expert_ffn(self.xshape, h, x.perm, x.offsets, x.counts, w.xw1, w.xw3, w.xw2, xmask, self.xy, self.xws)
+        B.moe_layer_ffn(self.xshape, h, x.perm, x.offsets, x.counts, w.xw1, w.xw3, w.xw2, xmask, self.xy, self.xws)
         return B.moe_combine(self.xshape, self.xy, x.topk_idx, x.topk_w, x.inv_perm, xmask, None, 0, None, self.out)
 
     def predict(self, h, res_vec, next_w: LayerWeights, p: int, top_experts, next_bias=None, ws=None):

@@ -1,0 +1,125 @@
+"""moe_layer_ffn: both projections of the routed and the shared experts as one launch, against moe_expert_ffn on either set of experts.
+A projection whose K is not split adds its products in the same order in both, so the rows are the same bits; where the separate
+down projection splits K (fp32 sums of 2 or more parts) the rows differ by one bf16 rounding of y at most, 2^-8 of the value, and
+of sums of that size where terms cancel (2^-8 of the largest value)."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2602_03495_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+SENTINEL = 0x7B7B
+
+# rows of the experts (k = 1: as many tokens), d, I, masked-off experts, shared experts, their inner size
+CASES = {
+    "as few rows as are joined": ([3072 // 8] * 8, 256, 128, (), 0, 0),
+    "fewer are not": ([3072 // 8] * 7 + [383], 256, 128, (), 0, 0),
+    "ragged tiles of every height": ([1, 16, 17, 32, 33, 64, 65, 96, 97, 127, 128, 129, 0, 255, 257, 5000], 640, 384, (), 0, 0),
+    "wide, ragged inner columns": ([700, 1, 2500, 0, 130, 3000], 2048, 1408, (4,), 0, 0),
+    "every expert masked off": ([3100, 3100], 256, 256, (0, 1), 0, 0),
+    "one expert on": ([3100, 3100], 1152, 640, (0,), 0, 0),
+    "128 experts": ([60] * 64 + [1] * 63 + [2500], 384, 256, tuple(range(0, 128, 3)), 0, 0),
+    "shared, few tokens": ([3, 0, 14], 256, 256, (), 2, 256),
+    "shared, long inner size": ([300, 2, 40], 1152, 384, (1,), 1, 1408),
+    "shared, long inner size, wide tiles": ([90] * 60, 2176, 128, (5,), 1, 640),
+    "shared, all routed experts masked off": ([200, 200], 512, 256, (0, 1), 2, 256),
+    "shared, separate projection splits K": ([140, 30], 512, 1408, (), 1, 4096),
+}
+
+
+@pytest.mark.parametrize("name", CASES)
+def test_joint_launch_writes_what_the_separate_launches_write(name):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2602_03495_amd import binding as B, layer as Lm
+    B.load_library()
+    rows, d, I, off, S, Is = CASES[name]
+    N, T = len(rows), sum(rows)
+    gen = torch.Generator(device="cuda").manual_seed(N + T)
+
+    def weights(n, r, K):
+        return B.moe_pack_weights((torch.randn(n, r, K, generator=gen, device="cuda") * K ** -0.5).bfloat16())
+
+    perm = torch.randperm(T, generator=gen, device="cuda").int()
+    offsets = torch.from_numpy(np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)).cuda()
+    counts = torch.tensor(rows, dtype=torch.int32, device="cuda")
+    mask = torch.ones(N, dtype=torch.uint8, device="cuda")
+    mask[list(off)] = 0
+    s, ss = B.shape(T, d, N, 1, I), B.shape(T, d, S, S, Is) if S else None
+    w = [weights(N, I, d), weights(N, I, d), weights(N, d, I)]
+    ws = B.alloc_workspace(s)
+    shared = None
+    if S:
+        sw = [weights(S, Is, d), weights(S, Is, d), weights(S, d, Is)]
+        i32 = dict(dtype=torch.int32, device="cuda")
+        s_counts, s_offsets, s_perm = torch.empty(S, **i32), torch.empty(S + 1, **i32), torch.empty(T * S, **i32)
+        B.moe_dense_route(ss, s_counts, s_offsets, s_perm)
+        sws = B.alloc_workspace(ss)
+
+    def fresh(n):
+        y = torch.empty((n, d), dtype=torch.bfloat16, device="cuda")
+        y.view(torch.int16).fill_(SENTINEL)
+        return y
+
+    exact = name != "shared, separate projection splits K"
+    got, sgot = fresh(T), fresh(T * S) if S else None
+    if S:
+        shared = (ss, s_perm, s_offsets, s_counts, *sw, sgot, sws)
+    h = torch.empty((T, d), dtype=torch.bfloat16, device="cuda")
+
+    def joint():
+        B.moe_layer_ffn(s, h, perm, offsets, counts, *w, mask, got, ws, shared)
+
+    def check(what):
+        for a, b in [(got, ref)] + ([(sgot, sref)] if S else []):
+            if exact or b is ref:
+                assert torch.equal(a.view(torch.int16), b.view(torch.int16)), (name, what)
+            else:
+                x, r = a.float(), b.float()
+                assert (x - r).abs().max() <= 2 ** -8 * r.abs().max(), (name, what)
+
+    print(f"joint launch {name} d={d} I={I} T={T} shared {S} of {Is}", flush=True)
+    graph = None
+    for turn in range(4):
+        # other hidden states every time over the workspace of the time before: activations of an earlier pass must not be read
+        h.normal_(generator=gen)
+        ref, sref = fresh(T), fresh(T * S) if S else None
+        B.moe_expert_ffn(s, h, perm, offsets, counts, *w, mask, ref, B.alloc_workspace(s))
+        if S:
+            B.moe_expert_ffn(ss, h, s_perm, s_offsets, s_counts, *sw, None, sref, B.alloc_workspace(ss))
+        if turn == 0:
+            ws.fill_(0xFF)                    # arbitrary contents: counters and activations alike
+            if S:
+                sws.fill_(0xFF)
+        if graph is not None:
+            graph.replay()
+        else:
+            joint()
+        check(f"turn {turn}")
+        if turn == 1:
+            side = torch.cuda.Stream()
+            side.wait_stream(torch.cuda.current_stream())
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=side):
+                joint()
+    rows_off = np.repeat(np.isin(np.arange(N), list(off)), rows)
+    bits = got.view(torch.int16).cpu().numpy()
+    assert (bits[rows_off] == SENTINEL).all()
+
+
+def test_two_workspaces_and_one_batch_are_required():
+    import ctypes as C
+    from paper_2602_03495_amd import binding as B
+    lib = B.load_library()
+    p, q, z = C.c_void_p(0x1000), C.c_void_p(0x2000), C.c_void_p(0)
+    s, ss = B.shape(16, 256, 8, 2, 512), B.shape(16, 256, 1, 1, 512)
+    call = lambda ss, a=p, w=q: lib.moe_layer_ffn(C.byref(s), p, p, p, p, p, p, p, z, p, p, C.byref(ss), p, p, p, p, p, a, p, w, z)
+    assert call(ss, w=p) == -1                              # the same workspace twice
+    assert call(ss, a=z) == -1                              # no w2 of the shared experts
+    assert call(B.shape(17, 256, 1, 1, 512)) == -1          # another batch
+    assert call(B.shape(16, 128, 1, 1, 512)) == -1          # another hidden size
+    assert call(ss, w=C.c_void_p(0x1010)) == -4             # misaligned workspace
+    ss.weight_layout = 0
+    assert call(ss) == -2                                   # row-major weights
