@@ -95,10 +95,31 @@ __device__ __forceinline__ joint_args_ptr joint_arguments()
     return p;
 }
 
-__device__ __forceinline__ moe_tiles joint_tiles(joint_args_ptr a, int shared)
+// What a block keeps of one set of experts: the places of their token tiles (moe_tiles of every lane), rows and first rows.  Read
+// from memory by every item, counts and offsets were two trips ahead of its first load.
+struct joint_table {
+    int n[2][64], first[2][64], rows[128], row0[128], total;
+};
+// Filled by one wave.
+__device__ __forceinline__ void joint_fill(joint_table &t, joint_args_ptr a, int shared)
 {
-    if (a->x[shared].N == 0) return moe_tiles{0, 0, 0, 0, 0};
-    return tiles_128(moe_masked_rows(a->x[shared].N, a->x[shared].counts, a->x[shared].mask));
+    const int lane = threadIdx.x & 63, N = a->x[shared].N;
+    moe_tiles m = {0, 0, 0, 0, 0};
+    if (N > 0) {
+        const int32_t *const offsets = a->x[shared].offsets;
+        const int o0 = offsets[min(lane, N - 1)], o1 = offsets[min(lane + 64, N - 1)];
+        const moe_rows r = moe_masked_rows(N, a->x[shared].counts, a->x[shared].mask);
+        m = tiles_128(r);
+        t.rows[lane] = r.c0;
+        t.rows[lane + 64] = r.c1;
+        t.row0[lane] = o0;
+        t.row0[lane + 64] = o1;
+    }
+    t.n[0][lane] = m.n0;
+    t.n[1][lane] = m.n1;
+    t.first[0][lane] = m.first0;
+    t.first[1][lane] = m.first1;
+    if (lane == 0) t.total = m.total;
 }
 
 struct joint_item {
@@ -110,19 +131,19 @@ struct joint_item {
 
 // The item of the place that was asked for, or of the next queue (see the kernel).  The first wave of a block calls it.
 template <int NFD>
-__device__ __forceinline__ joint_item joint_next(int asked, int own, bool &asks_down)
+__device__ __forceinline__ joint_item joint_next(const joint_table *tables, int asked, int own, bool &asks_down)
 {
     constexpr int DOWN_COLS = 128 * NFD;
     constexpr bool CUT = NFD > 1;
     const joint_args_ptr a = joint_arguments();
-    const moe_tiles ta = joint_tiles(a, 0), tb = joint_tiles(a, 1);
+    const int tiles_a = __builtin_amdgcn_readfirstlane(tables[0].total), tiles_b = __builtin_amdgcn_readfirstlane(tables[1].total);
     const int Ia = a->x[0].I, Ib = a->x[1].I, d = a->d;
     const int up_a = (Ia + JOINT_UP_COLS - 1) / JOINT_UP_COLS, up_b = (Ib + JOINT_UP_COLS - 1) / JOINT_UP_COLS, down_a = (d + DOWN_COLS - 1) / DOWN_COLS;
     // shared experts of a long inner size: their down items at half width, or one of them outlasts two rounds of the others
     const bool b_half = CUT && Ib > 2 * Ia;
     const int down_b = b_half ? (d + DOWN_COLS / 2 - 1) / (DOWN_COLS / 2) : down_a;
-    const int ups_b = tb.total * up_b, ups_a = ta.total * up_a, downs_b = tb.total * down_b, downs_a = ta.total * down_a;
-    const int qx = (threadIdx.x & 63) % MOE_NUM_XCD;
+    const int ups_b = tiles_b * up_b, ups_a = tiles_a * up_a, downs_b = tiles_b * down_b, downs_a = tiles_a * down_a;
+    const int lane = threadIdx.x & 63, qx = lane % MOE_NUM_XCD;
     int q = 0, place = -1;
     if (!asks_down) {
         place = joint_get(a->tickets, asked, own, joint_share(ups_b, qx) + joint_share(ups_a, qx), q);
@@ -152,10 +173,10 @@ __device__ __forceinline__ joint_item joint_next(int asked, int own, bool &asks_
     const int n_q = sb ? n_b : n_a;
     const int L = joint_first(sb ? list_b : list_a, q) + ((q & 1) != 0 ? n_q - 1 - place : place);
     const int n_nt = asks_down ? (sb ? down_b : down_a) : sb ? up_b : up_a;
+    const joint_table &t = tables[sb];
     joint_item it;
     int first, n;
-    if (sb) moe_find_tile(tb, L / n_nt, it.e, first, n);
-    else moe_find_tile(ta, L / n_nt, it.e, first, n);
+    moe_find_tile(moe_tiles{t.n[0][lane], t.n[1][lane], t.first[0][lane], t.first[1][lane], 0}, L / n_nt, it.e, first, n);
     const int local = L - first * n_nt;
     it.nt = local / n;                         // the token tiles that share a weight tile follow each other
     const int mt = local - it.nt * n;
@@ -164,8 +185,8 @@ __device__ __forceinline__ joint_item joint_next(int asked, int own, bool &asks_
         it.nt >>= 1;
     }
     it.kind = (asks_down ? 1 : 0) | (sb ? 2 : 0) | half << 2;
-    it.row0 = a->x[sb].offsets[it.e] + mt * TM;
-    it.nrows = min(a->x[sb].counts[it.e] - mt * TM, TM);
+    it.row0 = t.row0[it.e] + mt * TM;
+    it.nrows = min(t.rows[it.e] - mt * TM, TM);
     it.tile = first + mt;
     return it;
 }
@@ -175,6 +196,7 @@ template <int NFD>
 __global__ __launch_bounds__(TILED_THREADS, 2) void ffn_joint_kernel(joint_args)
 {
     __shared__ joint_item next;
+    __shared__ joint_table tables[2];
     __shared__ __attribute__((aligned(16))) uint16_t Xs[2][2][TM * 32];
     __shared__ __attribute__((aligned(16))) char Ys[8][2048];
     constexpr int DOWN_COLS = 128 * NFD;
@@ -186,13 +208,15 @@ __global__ __launch_bounds__(TILED_THREADS, 2) void ffn_joint_kernel(joint_args)
     };
     const auto get = [&]() {
         if (wave == 0) {
-            const joint_item it = joint_next<NFD>(asked, own, asks_down);
+            const joint_item it = joint_next<NFD>(tables, asked, own, asks_down);
             if (threadIdx.x == 0) next = it;
         }
         __syncthreads();
     };
     // the first tickets are taken like the others: dealt by the block id, they would belong to blocks that may not have started
     ask();
+    if (wave < 2) joint_fill(tables[wave], joint_arguments(), wave);
+    __syncthreads();
     get();
     while (true) {
         const int kind = __builtin_amdgcn_readfirstlane(next.kind);
