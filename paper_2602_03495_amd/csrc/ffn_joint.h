@@ -230,7 +230,7 @@ __global__ __launch_bounds__(TILED_THREADS, 2) void ffn_joint_kernel(joint_args)
         const int d = args->d, I = x->I, k = x->k, half = kind >> 2;
         uint16_t *const act = x->act;
         char *const ys = Ys[wave];
-#define BODY(mode_, nf_, n_, x_, perm_, wa_, wb_, out_)     tile_body<mode_, nf_, n_, 4, false, 8, mode_ == 0>(Xs, ys, d, I, k, x_, perm_, wa_, wb_, out_, e, nt, row0, nrows, 0, 1, nullptr, 0, tid, ask)
+#define BODY(mode_, nf_, n_, x_, perm_, wa_, wb_, out_)     tile_body<mode_, nf_, n_, 4, false, 8, mode_ == 0>(&Xs[0][0][0], ys, d, I, k, x_, perm_, wa_, wb_, out_, e, nt, row0, nrows, 0, 1, nullptr, 0, tid, ask)
 #define BODIES(mode_, nf_, ...)                                  \
     do {                                                         \
         if (nrows <= 16) BODY(mode_, nf_, 1, __VA_ARGS__);       \

@@ -105,7 +105,7 @@ struct nothing_ahead {
     __device__ __forceinline__ void operator()() const {}
 };
 template <int MODE, int NF, int NTT, int NSETS, bool FENCED, int WAVES, bool THROUGH = false, class Ahead = nothing_ahead>
-__device__ __forceinline__ void tile_body(uint16_t (*Xs)[2][TM * 32], char *ys, int d, int I, int k, const uint16_t *__restrict__ xsrc,
+__device__ __forceinline__ void tile_body(uint16_t *Xs, char *ys, int d, int I, int k, const uint16_t *__restrict__ xsrc,
                                           const int32_t *__restrict__ perm, const uint16_t *__restrict__ wa,
                                           const uint16_t *__restrict__ wb, uint16_t *__restrict__ out, int e, int nt,
                                           int row0, int nrows, int sp, int nsp, float *__restrict__ part, int R, const int tid, Ahead ahead_of_stores = {})
@@ -114,6 +114,7 @@ __device__ __forceinline__ void tile_body(uint16_t (*Xs)[2][TM * 32], char *ys, 
     constexpr int WAVE_COLS = HF * 16;                     // output columns a wave produces
     constexpr int NT_COLS = WAVES * WAVE_COLS;             // output columns per block
     constexpr int RPP = WAVES * 8;                         // token rows one pass of the loader covers (8 threads per row)
+    constexpr int HALF = (NTT > 8 ? 2 * TM : TM) * 32;     // elements of a k32 half of a stage in LDS; a stage is two, there are two stages
     const int K = MODE == 0 ? d : I;
     const int NOUT = MODE == 0 ? I : d;
     const int n0 = nt * NT_COLS;
@@ -156,9 +157,9 @@ __device__ __forceinline__ void tile_body(uint16_t (*Xs)[2][TM * 32], char *ys, 
     // must hit 16 different 16-byte bank groups: i ^ g keeps that (4 clocks per read instead of 8 for plain rows), while
     // the 8 chunks of one row, which one store instruction of the loader carries in 8 adjacent lanes, land in 8
     // different bank groups (16 clocks per store instead of 64 for the unswizzled fragment order).
-    uint16_t *xw = &Xs[0][xc >> 2][(tid >> 7) * 512 + ((xc & 3) * 16 + (((tid >> 3) & 15) ^ (xc & 3) ^ (xc >> 2) * 8)) * 8];   // + buffer * 2*TM*32 + j * RPP rows
-    const uint16_t *xrd0 = &Xs[0][0][(lg * 16 + (li ^ lg)) * 8];       // + buffer * 2*TM*32 + t * 16 rows
-    const uint16_t *xrd1 = &Xs[0][1][(lg * 16 + (li ^ lg ^ 8)) * 8];
+    uint16_t *xw = Xs + (xc >> 2) * HALF + (tid >> 7) * 512 + ((xc & 3) * 16 + (((tid >> 3) & 15) ^ (xc & 3) ^ (xc >> 2) * 8)) * 8;   // + stage * 2 * HALF + j * RPP rows
+    const uint16_t *xrd0 = Xs + (lg * 16 + (li ^ lg)) * 8;       // + stage * 2 * HALF + t * 16 rows
+    const uint16_t *xrd1 = Xs + HALF + (lg * 16 + (li ^ lg ^ 8)) * 8;
 
     f32x4 acc[NF][NTT];
 #pragma unroll
@@ -201,12 +202,12 @@ __device__ __forceinline__ void tile_body(uint16_t (*Xs)[2][TM * 32], char *ys, 
 #define XSTORE(buf)                                                                              \
     do {                                                                                         \
         _Pragma("unroll") for (int j = 0; j < XJ; ++j)                                           \
-            *reinterpret_cast<u32x4 *>(xw + (buf) * (2 * TM * 32) + j * (RPP * 32)) = xg[buf][j]; \
+            *reinterpret_cast<u32x4 *>(xw + (buf) * (2 * HALF) + j * (RPP * 32)) = xg[buf][j]; \
     } while (0)
 #define XREAD(buf, half)                                                                         \
     do {                                                                                         \
         _Pragma("unroll") for (int t = 0; t < NTT; ++t)                                          \
-            xf[t] = as_frag(*reinterpret_cast<const u32x4 *>(((half) ? xrd1 : xrd0) + (buf) * (2 * TM * 32) + t * (16 * 32))); \
+            xf[t] = as_frag(*reinterpret_cast<const u32x4 *>(((half) ? xrd1 : xrd0) + (buf) * (2 * HALF) + t * (16 * 32))); \
     } while (0)
     /* token subtile outermost: the first NF MFMAs need only the first LDS read, so the later reads land behind them */ \
 #define MFMAS(set)                                                                               \
@@ -402,6 +403,22 @@ __device__ __forceinline__ bool up_runs_halves(int tiles, int n_ntc, int n_half,
     return (halves == 2 * items || halves > 640) && wave_sum_int_dpp(r.c0 + r.c1) <= HALVES_SHORT_ROWS * tiles;
 }
 
+// Whether the up projection runs every expert's rows, 256 at most, as one tile of half the width: an expert has more than 128, and such
+// items fill one round of the compute units, three quarters of it or more.  A few last rows as a tile of their own take the whole time
+// of its weights, and two tiles ask for them twice; but an item is 128 rows x 256 columns of LDS traffic more for half the products.
+// d = 4096, I = 14336, whole pass of 200 tokens, two experts of 139 and 95 rows (168 items -> 224) 215 -> 192 us; the launch
+// alone, from cold caches: those 161 / 144, 160 and 60 155 / 147, two of 256 159 / 150, 129 and 1 147 / 147.  d = 2048: 20 of 200 rows, I =
+// 1408 (220) 100 / 99, 40 of 256, I = 768 (240) 114 / 113.  With fewer such items it is the slower one: one expert of 250 (112) 105 / 129, 16
+// with 129 and fewer, I = 1408 (176) 77 / 78, 20 of 200, I = 768 (120) 59 / 69.
+#define TALL_MIN_ITEMS 192
+__device__ __forceinline__ bool up_runs_tall(const moe_rows &r, int n_half, int &experts)
+{
+    const int most = wave_max_int_dpp(max(r.c0, r.c1));
+    experts = __popcll(__ballot(r.c0 > 0)) + __popcll(__ballot(r.c1 > 0));
+    const int items = experts * n_half;
+    return most > TM && most <= 2 * TM && items >= TALL_MIN_ITEMS && items <= MOE_NUM_XCD * XCD_CUS;
+}
+
 // NTT_MAX bounds the token subtiles a tile of this launch can need (from T); the block then runs the smallest
 // body that covers its own rows, so a sparsely filled tile costs MFMA work for the rows it has.
 template <int MODE, int NF, int NTT_MAX, bool DIRECT, int NSETS, bool FENCED, int WAVES>
@@ -415,7 +432,9 @@ __global__ __launch_bounds__(WAVES * 64, 2) void ffn_tiled_kernel(
     int32_t *__restrict__ rival,                    // MODE 1, non-null: the long-K kernel follows; whether it is the one that works (wide_faster)
     int group)                                      // column tiles that alternate inside the item order of an expert (1: column tile major)
 {
-    __shared__ __attribute__((aligned(16))) uint16_t Xs[2][2][TM * 32];   // [buffer][k32 half][128 tokens x 32 k]
+    // a launch that can run tiles of up to 256 rows at half width (up_runs_tall)
+    constexpr bool CAN_TALL = MODE == 0 && !DIRECT && WAVES == 8;
+    __shared__ __attribute__((aligned(16))) uint16_t Xs[2][2][(CAN_TALL ? 2 : 1) * TM * 32];   // [buffer][k32 half][tokens x 32 k]
     __shared__ __attribute__((aligned(16))) char Ys[WAVES][2048];          // results on their way out
     // a launch that can run an item as two of half its width (cut_item_of)
     constexpr bool CAN_CUT = tiled_can_cut(MODE, NF, FENCED, WAVES);
@@ -450,6 +469,30 @@ __global__ __launch_bounds__(WAVES * 64, 2) void ffn_tiled_kernel(
         nrows = work.rows_of(e);
     } else {
         const moe_rows rows = moe_masked_rows(N, counts, mask);
+        if constexpr (CAN_TALL) {
+            int experts;
+            if (up_runs_tall(rows, n_half, experts)) {
+                const int items = experts * n_half;
+                if ((int)blockIdx.x >= items) return;
+                const int L = moe_xcd_run(items, blockIdx.x);
+                int first, n;
+                moe_find_tile(moe_rank_tiles(rows.c0 > 0, rows.c1 > 0), L / n_half, e, first, n);
+                nt = L % n_half;
+                row0 = offsets[e];
+                nrows = counts[e];
+#define TALL_BODY(n_) tile_body<MODE, NF / 2, n_, NSETS, FENCED, WAVES>(&Xs[0][0][0], Ys[__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)], d, I, k, xsrc, perm, wa, wb, out, e, nt, row0, nrows, 0, 1, part, R, threadIdx.x)
+                if (nrows <= 32) TALL_BODY(2);
+                else if (nrows <= 64) TALL_BODY(4);
+                else if (nrows <= 96) TALL_BODY(6);
+                else if (nrows <= 128) TALL_BODY(8);
+                else if (nrows <= 160) TALL_BODY(10);
+                else if (nrows <= 192) TALL_BODY(12);
+                else TALL_BODY(16);
+#undef TALL_BODY
+                MOE_TRACE_END(MODE, e, nrows, nt);
+                return;
+            }
+        }
         const moe_tiles tiles = MODE == 0 ? tiles_128(rows) : down_tiles(rows, n_ntc, tmk);
         if (MODE == 1) nsp = moe_dev_splits(tiles.total * n_ntc, nsp_max);
         if (MODE == 1 && rival != nullptr) {
@@ -489,7 +532,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void ffn_tiled_kernel(
     const int sp = nt % nsp;      // column tile nt / nsp, K split nt % nsp
     nt /= nsp;
     nrows = nrows > tmk ? tmk : nrows;
-#define BODY_NS(nf_, n, ns_) tile_body<MODE, nf_, n, ns_, FENCED, WAVES>(Xs, Ys[__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)], d, I, k, xsrc, perm, wa, wb, out, e, nt, row0, nrows, sp, nsp, part, R, threadIdx.x)
+#define BODY_NS(nf_, n, ns_) tile_body<MODE, nf_, n, ns_, FENCED, WAVES>(&Xs[0][0][0], Ys[__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)], d, I, k, xsrc, perm, wa, wb, out, e, nt, row0, nrows, sp, nsp, part, R, threadIdx.x)
 #define BODY_NF(nf_, n) BODY_NS(nf_, n, NSETS)
     // tiles with few token rows do little arithmetic per weight byte: their speed is the speed of the weight stream, so
     // they prefetch further ahead (8 register sets instead of 4; the accumulators of a short tile leave the room)
