@@ -403,7 +403,8 @@ __device__ __forceinline__ bool up_runs_halves(int tiles, int n_ntc, int n_half,
     return (halves == 2 * items || halves > 640) && wave_sum_int_dpp(r.c0 + r.c1) <= HALVES_SHORT_ROWS * tiles;
 }
 
-// Whether the up projection runs every expert's rows, 256 at most, as one tile of half the width: an expert has more than 128, and such
+// Whether the up projection runs every expert's rows, 256 at most, as one tile of half the width (asked in launches of up to 256 rows per
+// expert in the mean, masked-off ones counted: there an expert may be within that): an expert has more than 128, and such
 // items fill one round of the compute units, three quarters of it or more.  A few last rows as a tile of their own take the whole time
 // of its weights, and two tiles ask for them twice; but an item is 128 rows x 256 columns of LDS traffic more for half the products.
 // d = 4096, I = 14336, whole pass of 200 tokens, two experts of 139 and 95 rows (168 items -> 224) 215 -> 192 us; the launch
@@ -421,7 +422,7 @@ __device__ __forceinline__ bool up_runs_tall(const moe_rows &r, int n_half, int 
 
 // NTT_MAX bounds the token subtiles a tile of this launch can need (from T); the block then runs the smallest
 // body that covers its own rows, so a sparsely filled tile costs MFMA work for the rows it has.
-template <int MODE, int NF, int NTT_MAX, bool DIRECT, int NSETS, bool FENCED, int WAVES>
+template <int MODE, int NF, int NTT_MAX, bool DIRECT, int NSETS, bool FENCED, int WAVES, bool CAN_TALL>
 __global__ __launch_bounds__(WAVES * 64, 2) void ffn_tiled_kernel(
     int d, int I, int k, int N, const uint16_t *__restrict__ xsrc,   // MODE 0: h [T,d]; MODE 1: act [R,I]
     const int32_t *__restrict__ perm, const int32_t *__restrict__ offsets, const int32_t *__restrict__ counts,
@@ -432,8 +433,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void ffn_tiled_kernel(
     int32_t *__restrict__ rival,                    // MODE 1, non-null: the long-K kernel follows; whether it is the one that works (wide_faster)
     int group)                                      // column tiles that alternate inside the item order of an expert (1: column tile major)
 {
-    // a launch that can run tiles of up to 256 rows at half width (up_runs_tall)
-    constexpr bool CAN_TALL = MODE == 0 && !DIRECT && WAVES == 8;
+    // CAN_TALL: a launch that can run tiles of up to 256 rows at half width (up_runs_tall)
     __shared__ __attribute__((aligned(16))) uint16_t Xs[2][2][(CAN_TALL ? 2 : 1) * TM * 32];   // [buffer][k32 half][tokens x 32 k]
     __shared__ __attribute__((aligned(16))) char Ys[WAVES][2048];          // results on their way out
     // a launch that can run an item as two of half its width (cut_item_of)
@@ -654,8 +654,18 @@ static void launch_tiled(const moe_shape *s, long max_mt, const uint16_t *x, con
         if (blocks < halves) blocks = halves;
     }
     const dim3 grid((unsigned)blocks);
-    hipLaunchKernelGGL((ffn_tiled_kernel<MODE, NF, NTT, DIRECT, NSETS, FENCED, WAVES>), grid, dim3(WAVES * 64), 0, st, s->d, s->I, s->k,
-                       s->N, x, perm, offsets, counts, wa, wb, mask, out, nsp_max, part, R, rival, tiled_item_group(MODE));
+#define LAUNCH(tall_) \
+    hipLaunchKernelGGL((ffn_tiled_kernel<MODE, NF, NTT, DIRECT, NSETS, FENCED, WAVES, tall_>), grid, dim3(WAVES * 64), 0, st, s->d, s->I, s->k, \
+                       s->N, x, perm, offsets, counts, wa, wb, mask, out, nsp_max, part, R, rival, tiled_item_group(MODE))
+    if constexpr (MODE == 0 && !DIRECT && WAVES == 8) {
+        // an instance of its own: with the tall bodies beside the others, 8192 tokens through 8 experts of I = 14336 took 1.4 % longer
+        if (R <= 2 * TM * s->N) {
+            LAUNCH(true);
+            return;
+        }
+    }
+    LAUNCH(false);
+#undef LAUNCH
 }
 
 // Weight fragments per wave (NF), 16-row token subtiles per tile (NTT) and weight register sets (NSETS).  An expert
