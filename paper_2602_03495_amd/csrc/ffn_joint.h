@@ -17,8 +17,8 @@
 //     With release and acquire fences in place of that (the whole L2 written back by each up item) an up item of 50 us took 56 to 65.
 //   * Counters and tickets are cleared by a launch of one block ahead.
 // Passes of whole layers, two or four launches / this: 2048 tokens of 6 slots, 32 of 64 experts, d = 2048, I = 1408, and two shared
-// ones 348 / 316 us; 1531 tokens of 8 slots, 64 of 128 experts, I = 768 217 / 201; 4096 tokens of 4 slots, 60 experts, I = 1408, and a shared
-// one of 5632 655 / 626.  The compute units are busy for 0.92 of the launch (0.78 to 0.85 of the separate ones); what an item takes is
+// ones 348 / 303 us; 1531 tokens of 8 slots, 64 of 128 experts, I = 768 215 / 195; 4096 tokens of 4 slots, 60 experts, I = 1408, and a shared
+// one of 5632 653 / 604.  The compute units are busy for 0.92 of the launch (0.78 to 0.85 of the separate ones); what an item takes is
 // bound as in ffn_tiled.hip.
 #pragma once
 
@@ -81,8 +81,9 @@ __device__ __forceinline__ int joint_get(int32_t *tickets, int asked, int own, i
     return place;
 }
 
-// The last routed down items of every queue run as two of half the width: with 0 / 16 / 32 of them cut, 2048 tokens of 4 slots, 60
-// experts, I = 1408 267 / 254 / 261 us, 2048 tokens of 6 slots, 64 experts 316 / 318 / 320, 900 of 8, 128 experts, I = 768 199 / 195 / 199.
+// The last routed down items of every queue run as two of half the width.  8 / 16 / 24 of them, two or four separate launches as the
+// yardstick, 48 calls of 300 to 4096 tokens on three layer shapes: 1.122, 1.124 and 1.120 times as fast in the mean; 2048 tokens of 6
+// slots, 32 of 64 experts, I = 1408 220 / 217 / 220 us, 900 tokens of 4 slots, 30 of 60 experts 135 / 143 / 144.
 #define JOINT_CUT 16
 
 // The arguments where the launch put them.  Read anew by every item: kept in registers across the items' loops they are more than
@@ -100,7 +101,7 @@ __device__ __forceinline__ joint_args_ptr joint_arguments()
 struct joint_table {
     int n[2][64], first[2][64], rows[128], row0[128], total;
 };
-// Filled by one wave.
+// Filled by one wave: of an item's 35 to 60 us the two trips were 0.4 to 0.8 (passes 312.8 -> 308.4, 199.5 -> 198.2 and 612.1 -> 605.9 us).
 __device__ __forceinline__ void joint_fill(joint_table &t, joint_args_ptr a, int shared)
 {
     const int lane = threadIdx.x & 63, N = a->x[shared].N;
@@ -230,7 +231,8 @@ __global__ __launch_bounds__(TILED_THREADS, 2) void ffn_joint_kernel(joint_args)
         const int d = args->d, I = x->I, k = x->k, half = kind >> 2;
         uint16_t *const act = x->act;
         char *const ys = Ys[wave];
-#define BODY(mode_, nf_, n_, x_, perm_, wa_, wb_, out_)     tile_body<mode_, nf_, n_, 4, false, 8, mode_ == 0>(&Xs[0][0][0], ys, d, I, k, x_, perm_, wa_, wb_, out_, e, nt, row0, nrows, 0, 1, nullptr, 0, tid, ask)
+#define BODY(mode_, nf_, n_, x_, perm_, wa_, wb_, out_) \
+    tile_body<mode_, nf_, n_, 4, false, 8, mode_ == 0>(&Xs[0][0][0], ys, d, I, k, x_, perm_, wa_, wb_, out_, e, nt, row0, nrows, 0, 1, nullptr, 0, tid, ask)
 #define BODIES(mode_, nf_, ...)                                  \
     do {                                                         \
         if (nrows <= 16) BODY(mode_, nf_, 1, __VA_ARGS__);       \

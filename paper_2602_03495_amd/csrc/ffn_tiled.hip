@@ -31,6 +31,7 @@
 // few items the down projection splits the K range of its tiles over several (fp32 partial sums, summed in split order by
 // tiled_finish_kernel); with many, the blocks pick the token-tile height of the down projection so that its items fill whole rounds
 // of compute units.
+// The two projections of a whole layer run as one launch of this file's items in ffn_joint.h.
 // Each item walks K as a ring starting at an expert-dependent offset, so that the token tiles that share a weight tile
 // stay in step (started at different points they run 18 % slower); the summation order is a function of the expert
 // and of the number of K splits only, so results are reproducible for given inputs.
@@ -770,10 +771,10 @@ int moe_ffn_tiled_impl(const moe_shape *s, const void *h, const int32_t *perm, c
 // Whether the FFNs of a layer run as a joint launch: K not split (it has no partial sums), inner sizes the long-K kernel does not take,
 // and enough work that filled last rounds pay for the clearing launch, the tickets and the activations' way past the caches.
 // Routed experts alone, two launches / joint, d = 2048, all and half of the experts on: 64 experts, I = 1408, 300 tokens of 6 slots 180 /
-// 183 and 125 / 130 us, 900 tokens 250 / 232 and 156 / 153, 2048 336 / 304 and 250 / 227; 128 experts, I = 768, 150 tokens of 8 slots 113 / 116
-// and 99 / 103, 300 150 / 146 and 113 / 116, 900 212 / 197 and 161 / 155, 4096 436 / 402 and 365 / 327.
-// Together with shared experts there are four launches to join: two of I = 1408, 70 tokens 157 / 134 us, 300 227 / 190, 2048 424 / 362; one of
-// I = 5632, 150 tokens 200 / 171, 2048 425 / 360, 4096 627 / 587, but 70 tokens 127 / 129, where its own down projection splits K.
+// 183 and 125 / 130 us, 900 tokens 254 / 230 and 156 / 151, 2048 332 / 295 and 246 / 217; 128 experts, I = 768, 150 tokens of 8 slots 113 / 116
+// and 99 / 103, 300 150 / 146 and 113 / 116, 900 211 / 196 and 160 / 155, 4096 427 / 388 and 352 / 312.
+// Together with shared experts there are four launches to join: two of I = 1408, 70 tokens 157 / 134 us, 300 221 / 185, 2048 415 / 346; one of
+// I = 5632, 150 tokens 200 / 171, 2048 415 / 350, 4096 608 / 553, but 70 tokens 127 / 129, where its own down projection splits K.
 #define JOINT_MIN_ROWS 3072
 bool moe_ffn_joint_ok(const moe_shape *s, const moe_shape *ss)
 {
