@@ -243,8 +243,6 @@ int moe_ffn_skinny_impl(const moe_shape *s, const void *h, const int32_t *perm, 
                         const uint8_t *expert_mask, void *y, void *workspace, int stages, hipStream_t st)
 {
     const int d = s->d, I = s->I, N = s->N, k = s->k, R = s->T * s->k;
-    if (s->T > MOE_SKINNY_MAX_T) return MOE_EUNSUPPORTED;
-    if (d > SK_WAVES * MOE_SKINNY_MAX_STEPS * 32) return MOE_EUNSUPPORTED;
     moe_ws_layout L = moe_ws(s);
     uint16_t *act = (uint16_t *)((char *)workspace + L.act);
     float *partial = (float *)((char *)workspace + L.partial);

@@ -72,6 +72,14 @@ static int check_shape(const moe_shape *s, bool need_I)
     return MOE_OK;
 }
 
+// the decode path keeps a wave's share of the hidden dimension in registers: at most 4096 wide
+static bool skinny_takes(const moe_shape *s) { return s->T <= MOE_SKINNY_MAX_T && s->d <= MOE_SKINNY_WAVES * MOE_SKINNY_MAX_STEPS * 32; }
+static int ffn_path_of(const moe_shape *s)
+{
+    if (s->ffn_path != MOE_FFN_AUTO) return s->ffn_path;
+    return skinny_takes(s) ? MOE_FFN_SKINNY : MOE_FFN_TILED;
+}
+
 static int check_ffn(const moe_shape *s, const void *h, const int32_t *perm, const int32_t *offsets, const int32_t *counts,
                      const void *w1, const void *w3, const void *w2, const void *y, const void *workspace)
 {
@@ -82,14 +90,10 @@ static int check_ffn(const moe_shape *s, const void *h, const int32_t *perm, con
     if (((uintptr_t)workspace & 255u) != 0) return MOE_EWORKSPACE;
     // every kernel reads the weights in the packed fragment order; row-major arrays would be multiplied as garbage
     if (s->weight_layout != MOE_WEIGHTS_PACKED) return MOE_EUNSUPPORTED;
+    const int path = ffn_path_of(s);
+    if (path != MOE_FFN_TILED && path != MOE_FFN_SKINNY) return MOE_EINVAL;
+    if (path == MOE_FFN_SKINNY && !skinny_takes(s)) return MOE_EUNSUPPORTED;
     return MOE_OK;
-}
-
-// the decode path keeps a wave's share of the hidden dimension in registers: at most 4096 wide
-static int ffn_path_of(const moe_shape *s)
-{
-    if (s->ffn_path != MOE_FFN_AUTO) return s->ffn_path;
-    return s->T <= MOE_SKINNY_MAX_T && s->d <= MOE_SKINNY_WAVES * MOE_SKINNY_MAX_STEPS * 32 ? MOE_FFN_SKINNY : MOE_FFN_TILED;
 }
 
 extern "C" {
@@ -153,12 +157,9 @@ int moe_expert_ffn_stage(const moe_shape *s, const void *h, const int32_t *perm,
     if (stages < 1 || stages > MOE_FFN_STAGE_ALL) return MOE_EINVAL;
     const int rc = check_ffn(s, h, perm, offsets, counts, w1, w3, w2, y, workspace);
     if (rc != MOE_OK) return rc;
-    const int path = ffn_path_of(s);
-    if (path == MOE_FFN_SKINNY)
+    if (ffn_path_of(s) == MOE_FFN_SKINNY)
         return moe_ffn_skinny_impl(s, h, perm, offsets, counts, w1, w3, w2, expert_mask, y, workspace, stages, (hipStream_t)stream);
-    if (path == MOE_FFN_TILED)
-        return moe_ffn_tiled_impl(s, h, perm, offsets, counts, w1, w3, w2, expert_mask, y, workspace, stages, (hipStream_t)stream);
-    return MOE_EINVAL;
+    return moe_ffn_tiled_impl(s, h, perm, offsets, counts, w1, w3, w2, expert_mask, y, workspace, stages, (hipStream_t)stream);
 }
 
 int moe_expert_ffn(const moe_shape *s, const void *h, const int32_t *perm, const int32_t *offsets, const int32_t *counts,

@@ -190,3 +190,17 @@ def test_partial_sums_of_a_narrow_layer_are_bounded_by_its_items(lib):
     T, d, I = 1024, 128, (1 << 19) + 128                       # an inner size that the tiled kernel cannot split
     assert lib.moe_workspace_bytes(C.byref(Shape(T, d, 1, 1, I, 0)), C.byref(n)) == MOE_OK
     assert n.value <= T * I * 2 + 16 * 5 * 256 * 256 * 4 + 8 * T * 2 + 4096
+
+
+@pytest.mark.parametrize("T,d,path,code", [(17, 256, 2, MOE_EUNSUPPORTED),      # the skinny path takes at most 16 tokens
+                                           (16, 4224, 2, MOE_EUNSUPPORTED),     # ... of at most 4096
+                                           (16, 256, 3, MOE_EINVAL), (16, 256, -1, MOE_EINVAL)])
+def test_layer_ffn_looks_at_both_paths_before_launching(lib, T, d, path, code):
+    # a launch without a device is MOE_ELAUNCH, so the expected code says that none was tried
+    p, q, z = C.c_void_p(0x1000), C.c_void_p(0x2000), C.c_void_p(0)
+    good = lambda N, k: Shape(T, d, N, k, 512, 1, 1)
+    bad = lambda N, k: Shape(T, d, N, k, 512, path, 1)
+    call = lambda s, ss: lib.moe_layer_ffn(C.byref(s), p, p, p, p, p, p, p, z, p, p, ss, p, p, p, p, p, p, p, q, z)
+    assert call(good(8, 2), C.byref(bad(1, 1))) == code
+    assert call(bad(8, 2), C.byref(good(1, 1))) == code
+    assert call(bad(8, 2), None) == code
