@@ -77,6 +77,8 @@ const char *moe_strerror(int code);
  * Bytes of device workspace that any call with this shape may use.  [host] pointers only.  That is the inner activations
  * (T*k*I*2), the partial sums of a down projection whose K is split (64 MiB at most for I up to 65536) and the routing
  * scratch (8*T*(N+k) and a little).
+ * Expert FFN, routing and prediction each use a part of their own: one call of each kind may run on one workspace at the same
+ * time (on several streams), two of the same kind may not.  moe_route_predict is routing and prediction.
  */
 int moe_workspace_bytes(const moe_shape *s, size_t *bytes);
 

@@ -39,7 +39,6 @@ struct joint_args {
     int d;
 };
 
-#define JOINT_TICKET_STRIDE 32
 #define JOINT_BLOCKS_PER_XCD 32         // a block to a compute unit
 
 // tickets: of eight queues of up items and eight of down items (joint_ask); a, b: counters of the routed and of the shared experts' tiles
@@ -47,7 +46,7 @@ __global__ __launch_bounds__(256) void joint_clear_kernel(int32_t *tickets, int3
 {
     for (int i = threadIdx.x; i < na; i += 256) a[i] = 0;
     for (int i = threadIdx.x; i < nb; i += 256) b[i] = 0;
-    if (threadIdx.x < 2 * MOE_NUM_XCD) tickets[threadIdx.x * JOINT_TICKET_STRIDE] = 0;
+    if (threadIdx.x < 2 * MOE_NUM_XCD) tickets[threadIdx.x * MOE_JOINT_TICKET_STRIDE] = 0;
 }
 
 // items of a list of total that XCD xcd takes, and the first of them
@@ -58,7 +57,7 @@ __device__ __forceinline__ int joint_first(int total, int xcd) { return xcd * (t
 // asked for ahead of its use, by lane 0.
 __device__ __forceinline__ int joint_ask(int32_t *tickets, int q)
 {
-    return (threadIdx.x & 63) == 0 ? __hip_atomic_fetch_add(tickets + q * JOINT_TICKET_STRIDE, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+    return (threadIdx.x & 63) == 0 ? __hip_atomic_fetch_add(tickets + q * MOE_JOINT_TICKET_STRIDE, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
 }
 
 // The place that was asked for in queue `own`, or, where that is beyond its end, one of the next queue with an item left (q); -1 once
@@ -71,7 +70,7 @@ __device__ __forceinline__ int joint_get(int32_t *tickets, int asked, int own, i
     while (place >= __builtin_amdgcn_readlane(length, q)) {
         // all eight counters at once: most blocks that come here find that nothing is left
         int taken = 0x7fffffff;
-        if (lane < MOE_NUM_XCD) taken = __hip_atomic_load(tickets + lane * JOINT_TICKET_STRIDE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (lane < MOE_NUM_XCD) taken = __hip_atomic_load(tickets + lane * MOE_JOINT_TICKET_STRIDE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const unsigned left = (unsigned)__ballot(taken < length);
         if (left == 0) return -1;
         const unsigned after = left >> q << q;
@@ -150,12 +149,12 @@ __device__ __forceinline__ joint_item joint_next(const joint_table *tables, int 
         place = joint_get(a->tickets, asked, own, joint_share(ups_b, qx) + joint_share(ups_a, qx), q);
         if (place < 0) {
             asks_down = true;
-            asked = joint_ask(a->tickets + MOE_NUM_XCD * JOINT_TICKET_STRIDE, own);
+            asked = joint_ask(a->tickets + MOE_NUM_XCD * MOE_JOINT_TICKET_STRIDE, own);
         }
     }
     if (asks_down) {
         const int n = joint_share(downs_a, qx);
-        place = joint_get(a->tickets + MOE_NUM_XCD * JOINT_TICKET_STRIDE, asked, own, joint_share(downs_b, qx) + n + (CUT ? min(n, JOINT_CUT) : 0), q);
+        place = joint_get(a->tickets + MOE_NUM_XCD * MOE_JOINT_TICKET_STRIDE, asked, own, joint_share(downs_b, qx) + n + (CUT ? min(n, JOINT_CUT) : 0), q);
     }
     if (place < 0) return joint_item{-1, 0, 0, 0, 0, 0};
     const int list_b = asks_down ? downs_b : ups_b, list_a = asks_down ? downs_a : ups_a;
@@ -205,7 +204,7 @@ __global__ __launch_bounds__(TILED_THREADS, 2) void ffn_joint_kernel(joint_args)
     bool asks_down = false;
     int asked = 0;
     const auto ask = [&]() {
-        if (wave == 0) asked = joint_ask(joint_arguments()->tickets + (asks_down ? MOE_NUM_XCD * JOINT_TICKET_STRIDE : 0), own);
+        if (wave == 0) asked = joint_ask(joint_arguments()->tickets + (asks_down ? MOE_NUM_XCD * MOE_JOINT_TICKET_STRIDE : 0), own);
     };
     const auto get = [&]() {
         if (wave == 0) {

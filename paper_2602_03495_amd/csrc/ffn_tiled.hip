@@ -787,9 +787,9 @@ static joint_experts joint_side(const moe_shape *s, const int32_t *perm, const i
                                 const void *w3, const void *w2, const uint8_t *mask, void *y, void *workspace)
 {
     const moe_ws_layout L = moe_ws(s);
-    // the counters lie in the routing scratch, which holds 8 bytes per routed row and is idle during the FFN
+    int32_t *const counters = (int32_t *)((char *)workspace + L.partial) + MOE_JOINT_TICKETS;
     return {perm, offsets, counts, (const uint16_t *)w1, (const uint16_t *)w3, (const uint16_t *)w2, mask,
-            (uint16_t *)((char *)workspace + L.act), (uint16_t *)y, (int32_t *)((char *)workspace + L.route), s->I, s->N, s->k};
+            (uint16_t *)((char *)workspace + L.act), (uint16_t *)y, counters, s->I, s->N, s->k};
 }
 
 int moe_ffn_joint_impl(const moe_shape *s, const void *h, const int32_t *perm, const int32_t *offsets, const int32_t *counts, const void *w1,
@@ -797,10 +797,6 @@ int moe_ffn_joint_impl(const moe_shape *s, const void *h, const int32_t *perm, c
                        const int32_t *s_perm, const int32_t *s_offsets, const int32_t *s_counts, const void *sw1, const void *sw3,
                        const void *sw2, void *shared_y, void *s_workspace, hipStream_t st)
 {
-    const auto max_tiles = [](const moe_shape *p) {
-        const long R = (long)p->T * p->k;
-        return R / TM + (p->N < R ? p->N : R);
-    };
     const auto est_tiles = [](const moe_shape *p) {
         const long R = (long)p->T * p->k, one = p->N < R ? p->N : R;
         return (R + TM - 1) / TM > one ? (R + TM - 1) / TM : one;
@@ -809,9 +805,8 @@ int moe_ffn_joint_impl(const moe_shape *s, const void *h, const int32_t *perm, c
     const joint_experts a = joint_side(s, perm, offsets, counts, w1, w3, w2, expert_mask, y, workspace);
     joint_experts b = {};
     if (ss != nullptr) b = joint_side(ss, s_perm, s_offsets, s_counts, sw1, sw3, sw2, nullptr, shared_y, s_workspace);
-    // the tickets (2 KB) lie in the room of the split-K partial sums, which this launch has none of (at least 4 d bytes for each of 17 rows)
     int32_t *const tickets = (int32_t *)((char *)workspace + moe_ws(s).partial);
-    const long na = max_tiles(s), nb = ss != nullptr ? max_tiles(ss) : 0, est = est_tiles(s) + (ss != nullptr ? est_tiles(ss) : 0);
+    const long na = moe_joint_max_tiles(s), nb = ss != nullptr ? moe_joint_max_tiles(ss) : 0, est = est_tiles(s) + (ss != nullptr ? est_tiles(ss) : 0);
     hipLaunchKernelGGL(joint_clear_kernel, dim3(1), dim3(256), 0, st, tickets, a.arrived, (int)na, b.arrived, (int)nb);
     MOE_CHECK_LAUNCH();
     // the widest weight tile of the down projection that leaves every compute unit a block

@@ -247,9 +247,12 @@ __host__ __device__ __forceinline__ int moe_dev_splits(int items, int nsp_max)
 static inline size_t moe_align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // ---- workspace layout (one per shape; every entry point carves what it needs from offset 0) ----
+// The expert FFN uses act, partial and choice, a gate product `route` (routing and prediction different parts of it): calls of different
+// kinds may run side by side on one workspace.
 struct moe_ws_layout {
     size_t act;        // [T*k, I] bf16 inner activations
-    size_t partial;    // [nsplit, T*k, d] fp32 split-K partial sums of the down projection (skinny path, or the tiled path's K splits)
+    size_t partial;    // [nsplit, T*k, d] fp32 split-K partial sums of the down projection (skinny path, or the tiled path's K splits);
+                       // in a joint launch (ffn_joint.h), which splits no K, its tickets and the counters of its token tiles
     size_t choice;     // whether the long-K kernel takes the down projection (one word)
     size_t route;      // routing scratch: sigmoid gates of the shared experts [T <= 16], idx [T*k], w [T*k] (prediction), 2 x logits [max(T,16), N] (gate product and selection in separate launches)
     size_t total;
@@ -312,6 +315,16 @@ static inline size_t moe_wide_max_pieces(const moe_shape *s)
     return n < WIDE_MAX_PIECES ? n : WIDE_MAX_PIECES;
 }
 
+// Joint launch: the tickets of sixteen queues, a line each, then a counter for every token tile.
+#define MOE_JOINT_TICKET_STRIDE 32
+#define MOE_JOINT_TICKETS (2 * MOE_NUM_XCD * MOE_JOINT_TICKET_STRIDE)
+static inline size_t moe_joint_max_tiles(const moe_shape *s)
+{
+    const size_t R = (size_t)s->T * s->k, N = (size_t)s->N;
+    return R / MOE_TILE_M + (N < R ? N : R);
+}
+static inline size_t moe_joint_scratch_bytes(const moe_shape *s) { return (MOE_JOINT_TICKETS + moe_joint_max_tiles(s)) * 4; }
+
 // one [max(T, 16), N] fp32 block of gate logits (the gate product and the selection are separate launches when the
 // gate matrix has many rows)
 static inline size_t moe_logits_scratch_bytes(const moe_shape *s)
@@ -333,6 +346,8 @@ static inline moe_ws_layout moe_ws(const moe_shape *s)
     if (nsp > 1 && (size_t)nsp * R * s->d * 4 > part) part = (size_t)nsp * R * s->d * 4;
     const size_t pieces = moe_wide_down(s) ? moe_wide_max_pieces(s) * WIDE_TM * WIDE_TN * 4 : 0;
     if (pieces > part) part = pieces;
+    // 17 and more rows of d sums hold it but for millions of rows of a narrow layer
+    if (s->T > MOE_SKINNY_MAX_T && moe_joint_scratch_bytes(s) > part) part = moe_joint_scratch_bytes(s);
     off += moe_align256(part);
     L.choice = off;
     off += 256;

@@ -109,6 +109,53 @@ def test_joint_launch_writes_what_the_separate_launches_write(name):
     assert (bits[rows_off] == SENTINEL).all()
 
 
+def launched_jointly(B, call):
+    """Whether call ran as a joint launch: the blocks of separate launches leave records."""
+    records = torch.zeros(2 * B.TRACE_MAX_BLOCKS * 8, dtype=torch.int64, device="cuda")
+    B.moe_debug_set_trace(records)
+    call()
+    torch.cuda.synchronize()
+    B.moe_debug_set_trace(None)
+    return not bool((records.view(-1, 8)[:, 7] == 1).any())
+
+
+def test_ffn_and_gates_use_parts_of_the_workspace_of_their_own():
+    """What lets a prediction on another stream run beside the FFN: neither writes where the other does."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2602_03495_amd import binding as B, layer as Lm
+    cfg = wl.LayerConfig(71, "parts", d=256, N=32, k=3, I=128, norm_mode=wl.NORM_RENORM, bias_law="normal", n_shared=2, I_shared=256,
+                         shared_gate="one")
+    T, fill = 1024, 0x5C
+    w = Lm.LayerWeights.upload(wl.gate_weights(cfg), wl.gate_bias(cfg), *wl.expert_weights(cfg), wl.shared_expert_weights(cfg))
+    L = Lm.MoeLayer(cfg, T)
+    h = Lm.to_device_bf16(wl.hidden_states(cfg, T))
+    top = torch.empty(2, dtype=torch.int32, device="cuda")
+    res_vec = torch.zeros(cfg.d, device="cuda")
+
+    def routing_bytes(s):                 # the tail of the workspace
+        up = lambda n: (n + 255) // 256 * 256
+        return up(128 * 4) + 2 * up(s.T * s.k * 4) + 2 * up(max(s.T, 16) * s.N * 4)
+
+    def parts(ws, s):
+        n = B.workspace_bytes(s)
+        ws = ws[B._ws_ptr(ws).value - ws.data_ptr():][:n]
+        return ws[:n - routing_bytes(s)], ws[n - routing_bytes(s):]
+
+    for gates in (lambda: L.route(h, w), lambda: L.predict(h, res_vec, w, 2, top), lambda: L.route_predict(h, w, res_vec, w, 2, top)):
+        L.ws.fill_(fill)
+        gates()
+        ffn, gate = parts(L.ws, L.shape)
+        assert (ffn == fill).all()
+    assert (gate != fill).any()
+    L.ws.fill_(fill)
+    L.sws.fill_(fill)
+    assert launched_jointly(B, lambda: L.all_ffn(h, w, None))
+    for ws, s in ((L.ws, L.shape), (L.sws, L.sshape)):
+        ffn, gate = parts(ws, s)
+        assert (gate == fill).all() and (ffn != fill).any()
+
+
 def test_two_workspaces_and_one_batch_are_required():
     import ctypes as C
     from paper_2602_03495_amd import binding as B
