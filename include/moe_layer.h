@@ -194,6 +194,8 @@ int moe_expert_ffn_stage(const moe_shape *s, const void *h, const int32_t *perm,
  * sums of a projection may be added in another order).  Up to an inner size of 8191 and with enough routed rows all projections run as one
  * launch, in which the down projection of a token tile starts when its activations are there (not in the records of
  * moe_debug_set_trace); otherwise the calls are made one after the other.
+ * That wait has a bound of seconds, which no launch has been seen to come near (it waits for running blocks only); beyond it the
+ * rows of that tile become NaN in y or shared_y.
  * The two workspaces are different ones.  ss == NULL: the arguments behind it are not looked at.
  * Errors: those of moe_expert_ffn, for either set of experts, before anything is launched.
  */

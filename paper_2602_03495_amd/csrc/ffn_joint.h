@@ -8,7 +8,9 @@
 //     the border of two shares are the first of both or the last of both, and few blocks ever wait.
 //   * A block takes a down item only when all up items have been taken, and has none of them in hand while it waits: they are
 //     being worked on by running blocks that wait for nothing.  That holds in whatever order blocks start, with fewer compute units
-//     than blocks and with another such launch beside this one.  The wait has a bound all the same (JOINT_MAX_POLLS).
+//     than blocks and with another such launch beside this one.  The wait has a bound all the same (MOE_JOINT_MAX_POLLS looks at the
+//     counter, seconds; the waits seen are tens of microseconds).  A wave that reaches it has loaded rows that may be incomplete: the
+//     rows of that item become NaN (joint_void).
 //   * The ticket after an item is asked for between its last product and its stores, which hide the way to the counter and back.
 //   * arrived[t] counts the up items of token tile t whose activations have been stored.  The activations are stored past the caches of
 //     the XCD (sc1, device scope) and every wave waits for its stores before the block counts itself in, so the block that sees the
@@ -22,8 +24,6 @@
 // bound as in ffn_tiled.hip.
 #pragma once
 
-#define JOINT_MAX_POLLS (1 << 21)       // seconds; the waits seen are tens of microseconds
-
 struct joint_experts {
     const int32_t *perm, *offsets, *counts;
     const uint16_t *w1, *w3, *w2;
@@ -36,7 +36,7 @@ struct joint_args {
     joint_experts x[2];                 // routed, shared
     const uint16_t *h;
     int32_t *tickets;                   // of the up items, then of the down items
-    int d;
+    int d, polls;
 };
 
 #define JOINT_BLOCKS_PER_XCD 32         // a block to a compute unit
@@ -191,11 +191,24 @@ __device__ __forceinline__ joint_item joint_next(const joint_table *tables, int 
     return it;
 }
 
+// NaN into the results of a down item.  Called by a wave behind a barrier that follows the stores of all of them.
+template <int NFD>
+__device__ __forceinline__ void joint_void(const joint_item &it)
+{
+    const joint_args_ptr a = joint_arguments();
+    const int half = it.kind >> 2, d = a->d, cols = half == 0 ? 128 * NFD : 64 * NFD;
+    const int col0 = half == 0 ? it.nt * cols : (2 * it.nt + half - 1) * cols, end = min(col0 + cols, d);
+    uint16_t *const y = a->x[it.kind >> 1 & 1].y;
+    for (int r = 0; r < it.nrows; ++r)
+        for (int c = col0 + (threadIdx.x & 63) * 8; c < end; c += 64 * 8)
+            *reinterpret_cast<u32x4 *>(y + (size_t)(it.row0 + r) * d + c) = u32x4{0x7fc07fc0u, 0x7fc07fc0u, 0x7fc07fc0u, 0x7fc07fc0u};
+}
+
 // NFD: weight fragments per wave of the down projection (128 output columns each)
 template <int NFD>
 __global__ __launch_bounds__(TILED_THREADS, 2) void ffn_joint_kernel(joint_args)
 {
-    __shared__ joint_item next;
+    __shared__ joint_item next, given_up[8];       // given_up: of every wave, the item whose activations it did not wait for any longer
     __shared__ joint_table tables[2];
     __shared__ __attribute__((aligned(16))) uint16_t Xs[2][2][TM * 32];
     __shared__ __attribute__((aligned(16))) char Ys[8][2048];
@@ -228,6 +241,7 @@ __global__ __launch_bounds__(TILED_THREADS, 2) void ffn_joint_kernel(joint_args)
         const joint_args_ptr args = joint_arguments();
         const auto x = &args->x[kind >> 1 & 1];
         const int d = args->d, I = x->I, k = x->k, half = kind >> 2;
+        bool gave_up = false;
         uint16_t *const act = x->act;
         char *const ys = Ys[wave];
 #define BODY(mode_, nf_, n_, x_, perm_, wa_, wb_, out_) \
@@ -258,9 +272,14 @@ __global__ __launch_bounds__(TILED_THREADS, 2) void ffn_joint_kernel(joint_args)
             const uint16_t *const w2 = x->w2;
             uint16_t *const y = x->y;
             int32_t *const arrived = x->arrived + tile;
-            const int want = (I + JOINT_UP_COLS - 1) / JOINT_UP_COLS;
-            for (int i = 0; i < JOINT_MAX_POLLS && __hip_atomic_load(arrived, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < want; ++i)
+            const int want = (I + JOINT_UP_COLS - 1) / JOINT_UP_COLS, most = args->polls;
+            int polls = 0;
+            while (polls < most && __builtin_amdgcn_readfirstlane(__hip_atomic_load(arrived, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) < want) {
                 __builtin_amdgcn_s_sleep(8);
+                ++polls;
+            }
+            gave_up = polls == most;
+            if (__builtin_expect(gave_up, 0)) given_up[wave] = next;
             const uint16_t *act_in = act;
             asm volatile("" : "+s"(act_in)::"memory");      // no read of the activations moves ahead of the wait
             if (NFD == 1 || half == 0) {
@@ -276,6 +295,7 @@ __global__ __launch_bounds__(TILED_THREADS, 2) void ffn_joint_kernel(joint_args)
             }
         }
         get();
+        if (__builtin_expect(gave_up, 0)) joint_void<NFD>(given_up[wave]);
     }
 #undef BODIES
 #undef BODY

@@ -792,10 +792,11 @@ static joint_experts joint_side(const moe_shape *s, const int32_t *perm, const i
             (uint16_t *)((char *)workspace + L.act), (uint16_t *)y, counters, s->I, s->N, s->k};
 }
 
-int moe_ffn_joint_impl(const moe_shape *s, const void *h, const int32_t *perm, const int32_t *offsets, const int32_t *counts, const void *w1,
+// polls: the most looks at a counter, see ffn_joint.h (C linkage: with none at all every item takes the way of a wait that ran out)
+extern "C" int moe_ffn_joint_impl(const moe_shape *s, const void *h, const int32_t *perm, const int32_t *offsets, const int32_t *counts, const void *w1,
                        const void *w3, const void *w2, const uint8_t *expert_mask, void *y, void *workspace, const moe_shape *ss,
                        const int32_t *s_perm, const int32_t *s_offsets, const int32_t *s_counts, const void *sw1, const void *sw3,
-                       const void *sw2, void *shared_y, void *s_workspace, hipStream_t st)
+                       const void *sw2, void *shared_y, void *s_workspace, int polls, hipStream_t st)
 {
     const auto est_tiles = [](const moe_shape *p) {
         const long R = (long)p->T * p->k, one = p->N < R ? p->N : R;
@@ -811,7 +812,7 @@ int moe_ffn_joint_impl(const moe_shape *s, const void *h, const int32_t *perm, c
     MOE_CHECK_LAUNCH();
     // the widest weight tile of the down projection that leaves every compute unit a block
     const int nf = est * ((d + 511) / 512) >= 256 ? 4 : est * ((d + 255) / 256) >= 256 ? 2 : 1;
-    const joint_args args = {{a, b}, (const uint16_t *)h, tickets, d};
+    const joint_args args = {{a, b}, (const uint16_t *)h, tickets, d, polls};
     const dim3 grid(MOE_NUM_XCD * JOINT_BLOCKS_PER_XCD);
     if (nf == 4) hipLaunchKernelGGL(ffn_joint_kernel<4>, grid, dim3(TILED_THREADS), 0, st, args);
     else if (nf == 2) hipLaunchKernelGGL(ffn_joint_kernel<2>, grid, dim3(TILED_THREADS), 0, st, args);

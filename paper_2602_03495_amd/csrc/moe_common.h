@@ -318,6 +318,7 @@ static inline size_t moe_wide_max_pieces(const moe_shape *s)
 // Joint launch: the tickets of sixteen queues, a line each, then a counter for every token tile.
 #define MOE_JOINT_TICKET_STRIDE 32
 #define MOE_JOINT_TICKETS (2 * MOE_NUM_XCD * MOE_JOINT_TICKET_STRIDE)
+#define MOE_JOINT_MAX_POLLS (1 << 21)
 static inline size_t moe_joint_max_tiles(const moe_shape *s)
 {
     const size_t R = (size_t)s->T * s->k, N = (size_t)s->N;

@@ -109,6 +109,97 @@ def test_joint_launch_writes_what_the_separate_launches_write(name):
     assert (bits[rows_off] == SENTINEL).all()
 
 
+class Layer:
+    """Tables, weights and buffers of one call: rows of the experts (k slots per token), shared experts S of inner size Is."""
+
+    def __init__(self, B, rows, k, d, I, off=(), S=0, Is=0):
+        self.B, self.rows, self.off, self.d, self.S = B, rows, off, d, S
+        N, R = len(rows), sum(rows)
+        self.T = T = R // k
+        assert T * k == R
+        self.gen = gen = torch.Generator(device="cuda").manual_seed(N + R)
+
+        def weights(n, r, K):
+            return B.moe_pack_weights((torch.randn(n, r, K, generator=gen, device="cuda") * K ** -0.5).bfloat16())
+
+        self.h = torch.randn(T, d, generator=gen, device="cuda").bfloat16()
+        self.mask = torch.ones(N, dtype=torch.uint8, device="cuda")
+        self.mask[list(off)] = 0
+        self.s = B.shape(T, d, N, k, I)
+        self.tables = (torch.randperm(R, generator=gen, device="cuda").int(),
+                       torch.from_numpy(np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)).cuda(),
+                       torch.tensor(rows, dtype=torch.int32, device="cuda"))
+        self.w = weights(N, I, d), weights(N, I, d), weights(N, d, I)
+        self.ws = B.alloc_workspace(self.s)
+        if S:
+            i32 = dict(dtype=torch.int32, device="cuda")
+            self.ss = B.shape(T, d, S, S, Is)
+            counts, offsets, perm = torch.empty(S, **i32), torch.empty(S + 1, **i32), torch.empty(T * S, **i32)
+            B.moe_dense_route(self.ss, counts, offsets, perm)
+            self.stables, self.sw = (perm, offsets, counts), (weights(S, Is, d), weights(S, Is, d), weights(S, d, Is))
+            self.sws = B.alloc_workspace(self.ss)
+        self.row_on = torch.from_numpy(~np.repeat(np.isin(np.arange(N), list(off)), rows)).cuda()
+
+    def fresh(self):
+        """Results of the routed and of the shared experts, filled with the sentinel."""
+        y = [torch.empty((n, self.d), dtype=torch.bfloat16, device="cuda") for n in (sum(self.rows), self.T * self.S) if n]
+        for a in y:
+            a.view(torch.int16).fill_(SENTINEL)
+        return y
+
+    def joint(self, y):
+        shared = (self.ss, *self.stables, *self.sw, y[1], self.sws) if self.S else None
+        self.B.moe_layer_ffn(self.s, self.h, *self.tables, *self.w, self.mask, y[0], self.ws, shared)
+
+    def joint_without_waiting(self, y):
+        """The joint launch as if every wait had run out."""
+        import ctypes as C
+        p = self.B._ptr
+        tail = (C.c_void_p(0),) * 9
+        if self.S:
+            tail = (C.byref(self.ss), *map(p, self.stables), *map(p, self.sw), p(y[1]), self.B._ws_ptr(self.sws))
+        rc = self.B.load_library().moe_ffn_joint_impl(C.byref(self.s), p(self.h), *map(p, self.tables), *map(p, self.w), p(self.mask),
+                                                      p(y[0]), self.B._ws_ptr(self.ws), *tail, C.c_int(0), self.B._stream())
+        assert rc == 0
+
+    def separate(self, y):
+        self.B.moe_expert_ffn(self.s, self.h, *self.tables, *self.w, self.mask, y[0], self.B.alloc_workspace(self.s))
+        if self.S:
+            self.B.moe_expert_ffn(self.ss, self.h, *self.stables, *self.sw, None, y[1], self.B.alloc_workspace(self.ss))
+
+
+def bits(y):
+    return y.view(torch.int16)
+
+
+# rows, k, d, I, masked-off experts, shared experts, their inner size; the down items are 128, 256 and 512 columns wide
+VOIDED = {
+    "128 columns": ([400] * 8, 2, 256, 128, (2,), 0, 0),
+    "256 columns, ragged": ([60] * 90, 1, 640, 128, (0, 89), 0, 0),
+    "512 columns, ragged, shared": ([60] * 100, 1, 1152, 128, (7,), 1, 640),
+}
+
+
+@pytest.mark.parametrize("name", VOIDED)
+def test_rows_whose_activations_were_not_waited_for_are_nan(name):
+    """A wait that runs out leaves NaN in the whole rows of its item and nothing elsewhere; the launch after it is whole again."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2602_03495_amd import binding as B
+    B.load_library()
+    print(f"waits that ran out: {name}", flush=True)
+    L = Layer(B, *VOIDED[name])
+    y = L.fresh()
+    L.joint_without_waiting(y)
+    assert (bits(y[0])[L.row_on] == 0x7FC0).all() and (bits(y[0])[~L.row_on] == SENTINEL).all()
+    assert all((bits(a) == 0x7FC0).all() for a in y[1:])
+    ref = L.fresh()
+    L.separate(ref)
+    L.joint(y)
+    assert (bits(y[0])[L.row_on] == bits(ref[0])[L.row_on]).all()
+    assert all((bits(a) == bits(b)).all() for a, b in zip(y[1:], ref[1:]))
+
+
 def launched_jointly(B, call):
     """Whether call ran as a joint launch: the blocks of separate launches leave records."""
     records = torch.zeros(2 * B.TRACE_MAX_BLOCKS * 8, dtype=torch.int64, device="cuda")
