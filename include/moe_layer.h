@@ -191,9 +191,11 @@ int moe_expert_ffn_stage(const moe_shape *s, const void *h, const int32_t *perm,
 /*
  * The expert FFNs of one layer: moe_expert_ffn of the routed experts and, with ss != NULL, of the shared ones (ss: the shape given to
  * moe_dense_route, same T and d; every token through every shared expert, no mask).  Both write what moe_expert_ffn writes (the fp32
- * sums of a projection may be added in another order).  Up to an inner size of 8191 and with enough routed rows all projections run as one
- * launch, in which the down projection of a token tile starts when its activations are there (not in the records of
- * moe_debug_set_trace); otherwise the calls are made one after the other.
+ * sums of a projection may be added in another order).  Where that was measured to be faster, all projections run as one launch, in
+ * which the down projection of a token tile starts when its activations are there (not in the records of moe_debug_set_trace): with
+ * shared experts in most calls of 17 and more tokens, without them in large batches of layers with many experts, larger ones under a
+ * mask; never with an inner size of 8192 or more, or where the routed down projection splits its K.  Otherwise the calls are made one
+ * after the other.
  * That wait has a bound of seconds, which no launch has been seen to come near (it waits for running blocks only); beyond it the
  * rows of that tile become NaN in y or shared_y.
  * The two workspaces are different ones.  ss == NULL: the arguments behind it are not looked at.

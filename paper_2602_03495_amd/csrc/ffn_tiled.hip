@@ -768,19 +768,40 @@ int moe_ffn_tiled_impl(const moe_shape *s, const void *h, const int32_t *perm, c
     return MOE_OK;
 }
 
-// Whether the FFNs of a layer run as a joint launch: K not split (it has no partial sums), inner sizes the long-K kernel does not take,
-// and enough work that filled last rounds pay for the clearing launch, the tickets and the activations' way past the caches.
-// Routed experts alone, two launches / joint, d = 2048, all and half of the experts on: 64 experts, I = 1408, 300 tokens of 6 slots 180 /
-// 183 and 125 / 130 us, 900 tokens 254 / 230 and 156 / 151, 2048 332 / 295 and 246 / 217; 128 experts, I = 768, 150 tokens of 8 slots 113 / 116
-// and 99 / 103, 300 150 / 146 and 113 / 116, 900 211 / 196 and 160 / 155, 4096 427 / 388 and 352 / 312.
-// Together with shared experts there are four launches to join: two of I = 1408, 70 tokens 157 / 134 us, 300 221 / 185, 2048 415 / 346; one of
-// I = 5632, 150 tokens 200 / 171, 2048 415 / 350, 4096 608 / 553, but 70 tokens 127 / 129, where its own down projection splits K.
+// Whether the FFNs of a layer run as a joint launch: the routed K not split (it has no partial sums), inner sizes the long-K kernel does not
+// take, and enough items that filled last rounds pay for the clearing launch, the tickets and the activations' way past the caches; an
+// up item is never cut there, so with about a round of them or less the separate launches end sooner.  masked: how many experts a mask
+// leaves on is known to the device only; the line is where a quarter of them is not slower.  Separate launches / joint in us:
+// Routed experts alone, d = 2048, all on / half / a quarter.  64 experts, I = 1408, 512 tokens of 6 slots 227 / 224, 127 / 132, 84 / 91, 1400 269 /
+// 262, 184 / 170, 130 / 133, 2048 328 / 299, 230 / 211, 174 / 160; 128 experts, I = 768, 384 tokens of 8 slots 234 / 223, 125 / 122, 70 / 87, 1000
+// 251 / 240, 157 / 150, 92 / 96, 1531 282 / 260, 172 / 162, 114 / 107.  Beyond a quarter it loses still: an eighth of these 121 / 130 and 79 / 81.
+// Other sizes, all on / a quarter, at 9216 to 16384 rows: 64 of 1024, d = 3072 302 / 272 and 141 / 131; 64 of 2048, d = 7168 1338 / 1286 and
+// 718 / 633; 75 of 640 (255 up items) half 116 / 101, a quarter 72 / 77; 46 of 256, d = 7168 (110) 3/4 214 / 254, a quarter 161 / 185.
+// Few experts: 8 of 4096, d = 4096, 4096 rows 426 / 415 and 155 / 159, 3072 rows (24 tiles) 323 / 370 and 132 / 170; 32 of 768, 4096 rows (96 up
+// items) 89 / 93 and 45 / 63; 32 of 1408 with a quarter on, 12288 rows 125 / 137.  d = 1024: 32 of 2816, 8192 rows 203 / 196 and 96 / 115; d = 512:
+// 64 of 512, 8192 rows 39 / 44 and 22 / 31.
+// Together with shared experts there are four launches to join, on layers of d = 512 to 8192 at 17 to 4096 tokens 1.02 to 1.4 times as fast in
+// nearly every call, masked or not; in some of few routed experts and at most 48 tokens not (16 of 3200, d = 4096, and one of 6400, half on, 206 / 210).
+// Where the separate shared down projection would split its K, the joint launch ends with its long items: 60 of 1408 and a shared one
+// of 5632, d = 2048, all on / half / a quarter: 64 tokens 224 / 191, 150 / 151, 103 / 116, 200 248 / 205, 167 / 153, 122 / 121, 512 267 / 220, 188 / 170,
+// 138 / 149 (the one that loses), 1024 316 / 259, 228 / 178, 180 / 156; 10 of 3840 and one of 7680, 64 tokens 157 / 164, 125 / 133, 85 / 90, 512 250 / 222,
+// 177 / 185, 138 / 135; d = 1024, 60 of 1408 and one of 5632: 200 tokens 145 / 129, 103 / 114, 80 / 89, 2048 240 / 217, 196 / 179, 162 / 145; d = 512:
+// 200 99 / 98, 76 / 95, 66 / 82, 2048 150 / 136, 125 / 115, 112 / 107.
 #define JOINT_MIN_ROWS 3072
-bool moe_ffn_joint_ok(const moe_shape *s, const moe_shape *ss)
+#define JOINT_MIN_ROWS_MASKED 9216
+#define JOINT_MIN_TILES 56          // in the mean, or experts: a mask makes tiles of them fewer
+#define JOINT_MIN_UP_ITEMS 256
+extern "C" bool moe_ffn_joint_ok(const moe_shape *s, const moe_shape *ss, bool masked)
 {
     if (s->I >= 8192 || moe_tiled_down_max_splits(s) != 1) return false;
-    if (ss == nullptr) return s->T > TM && (long)s->T * s->k >= JOINT_MIN_ROWS;
-    return ss->I < 8192 && s->T > (ss->I > 2 * s->I ? TM : MOE_SKINNY_MAX_T);
+    if (ss != nullptr) {
+        if (ss->I >= 8192 || s->T <= MOE_SKINNY_MAX_T) return false;
+        if (moe_tiled_down_max_splits(ss) != 1) return s->T > TM && (s->d >= 2048 || s->T >= 2048);
+        return s->T > TM || ss->I <= 2 * s->I;
+    }
+    const long R = (long)s->T * s->k, tiles = R / TM > s->N ? R / TM : s->N;
+    if (s->d < 2048 || tiles * ((s->I + JOINT_UP_COLS - 1) / JOINT_UP_COLS) < JOINT_MIN_UP_ITEMS) return false;
+    return masked ? R >= JOINT_MIN_ROWS_MASKED && s->N >= JOINT_MIN_TILES : R >= JOINT_MIN_ROWS && tiles >= JOINT_MIN_TILES;
 }
 
 static joint_experts joint_side(const moe_shape *s, const int32_t *perm, const int32_t *offsets, const int32_t *counts, const void *w1,

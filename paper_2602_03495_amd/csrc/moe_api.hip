@@ -19,7 +19,7 @@ int moe_ffn_tiled_impl(const moe_shape *, const void *, const int32_t *, const i
                        const void *, const void *, const uint8_t *, void *, void *, int, hipStream_t);
 int moe_ffn_skinny_impl(const moe_shape *, const void *, const int32_t *, const int32_t *, const int32_t *, const void *,
                         const void *, const void *, const uint8_t *, void *, void *, int, hipStream_t);
-bool moe_ffn_joint_ok(const moe_shape *, const moe_shape *);
+extern "C" bool moe_ffn_joint_ok(const moe_shape *, const moe_shape *, bool);
 extern "C" int moe_ffn_joint_impl(const moe_shape *, const void *, const int32_t *, const int32_t *, const int32_t *, const void *, const void *,
                        const void *, const uint8_t *, void *, void *, const moe_shape *, const int32_t *, const int32_t *,
                        const int32_t *, const void *, const void *, const void *, void *, void *, int, hipStream_t);
@@ -181,7 +181,7 @@ int moe_layer_ffn(const moe_shape *s, const void *h, const int32_t *perm, const 
         if (rc != MOE_OK) return rc;
         if (ss->T != s->T || ss->d != s->d || workspace == s_workspace) return MOE_EINVAL;
     }
-    if (ffn_path_of(s) == MOE_FFN_TILED && (ss == nullptr || ffn_path_of(ss) == MOE_FFN_TILED) && moe_ffn_joint_ok(s, ss))
+    if (ffn_path_of(s) == MOE_FFN_TILED && (ss == nullptr || ffn_path_of(ss) == MOE_FFN_TILED) && moe_ffn_joint_ok(s, ss, expert_mask != nullptr))
         return moe_ffn_joint_impl(s, h, perm, offsets, counts, w1, w3, w2, expert_mask, y, workspace, ss, s_perm, s_offsets, s_counts,
                                   sw1, sw3, sw2, shared_y, s_workspace, MOE_JOINT_MAX_POLLS, (hipStream_t)stream);
     rc = moe_expert_ffn(s, h, perm, offsets, counts, w1, w3, w2, expert_mask, y, workspace, stream);

@@ -1,4 +1,5 @@
-"""moe_layer_ffn: both projections of the routed and the shared experts as one launch, against moe_expert_ffn on either set of experts.
+"""Both projections of the routed and the shared experts as one launch (called directly, whatever the rule of moe_layer_ffn says of the
+sizes; the rule: test_joint_rule.py), against moe_expert_ffn on either set of experts.
 A projection whose K is not split adds its products in the same order in both, so the rows are the same bits; where the separate
 down projection splits K (fp32 sums of 2 or more parts) the rows differ by one bf16 rounding of y at most, 2^-8 of the value, and
 of sums of that size where terms cancel (2^-8 of the largest value)."""
@@ -12,101 +13,21 @@ pytestmark = pytest.mark.gpu
 
 SENTINEL = 0x7B7B
 
-# rows of the experts (k = 1: as many tokens), d, I, masked-off experts, shared experts, their inner size
+# rows of the experts, k, d, I, masked-off experts, shared experts, their inner size
 CASES = {
-    "as few rows as are joined": ([3072 // 8] * 8, 256, 128, (), 0, 0),
-    "fewer are not": ([3072 // 8] * 7 + [383], 256, 128, (), 0, 0),
-    "ragged tiles of every height": ([1, 16, 17, 32, 33, 64, 65, 96, 97, 127, 128, 129, 0, 255, 257, 5000], 640, 384, (), 0, 0),
-    "wide, ragged inner columns": ([700, 1, 2500, 0, 130, 3000], 2048, 1408, (4,), 0, 0),
-    "every expert masked off": ([3100, 3100], 256, 256, (0, 1), 0, 0),
-    "one expert on": ([3100, 3100], 1152, 640, (0,), 0, 0),
-    "128 experts": ([60] * 64 + [1] * 63 + [2500], 384, 256, tuple(range(0, 128, 3)), 0, 0),
-    "shared, few tokens": ([3, 0, 14], 256, 256, (), 2, 256),
-    "shared, long inner size": ([300, 2, 40], 1152, 384, (1,), 1, 1408),
-    "shared, long inner size, wide tiles": ([90] * 60, 2176, 128, (5,), 1, 640),
-    "shared, all routed experts masked off": ([200, 200], 512, 256, (0, 1), 2, 256),
-    "shared, separate projection splits K": ([140, 30], 512, 1408, (), 1, 4096),
+    "three tiles to an expert": ([3072 // 8] * 8, 1, 256, 128, (), 0, 0),
+    "one expert with a row less": ([3072 // 8] * 7 + [383], 1, 256, 128, (), 0, 0),
+    "ragged tiles of every height": ([1, 16, 17, 32, 33, 64, 65, 96, 97, 127, 128, 129, 0, 255, 257, 5000], 1, 640, 384, (), 0, 0),
+    "wide, ragged inner columns": ([700, 1, 2500, 0, 130, 3000], 1, 2048, 1408, (4,), 0, 0),
+    "every expert masked off": ([3100, 3100], 1, 256, 256, (0, 1), 0, 0),
+    "one expert on": ([3100, 3100], 1, 1152, 640, (0,), 0, 0),
+    "128 experts": ([60] * 64 + [1] * 63 + [2500], 1, 384, 256, tuple(range(0, 128, 3)), 0, 0),
+    "shared, few tokens": ([3, 0, 14], 1, 256, 256, (), 2, 256),
+    "shared, long inner size": ([300, 2, 40], 1, 1152, 384, (1,), 1, 1408),
+    "shared, long inner size, wide tiles": ([90] * 60, 1, 2176, 128, (5,), 1, 640),
+    "shared, all routed experts masked off": ([200, 200], 1, 512, 256, (0, 1), 2, 256),
+    "shared, separate projection splits K": ([140, 30], 1, 512, 1408, (), 1, 4096),
 }
-
-
-@pytest.mark.parametrize("name", CASES)
-def test_joint_launch_writes_what_the_separate_launches_write(name):
-    if not torch.cuda.is_available():
-        pytest.skip("no GPU")
-    from paper_2602_03495_amd import binding as B, layer as Lm
-    B.load_library()
-    rows, d, I, off, S, Is = CASES[name]
-    N, T = len(rows), sum(rows)
-    gen = torch.Generator(device="cuda").manual_seed(N + T)
-
-    def weights(n, r, K):
-        return B.moe_pack_weights((torch.randn(n, r, K, generator=gen, device="cuda") * K ** -0.5).bfloat16())
-
-    perm = torch.randperm(T, generator=gen, device="cuda").int()
-    offsets = torch.from_numpy(np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)).cuda()
-    counts = torch.tensor(rows, dtype=torch.int32, device="cuda")
-    mask = torch.ones(N, dtype=torch.uint8, device="cuda")
-    mask[list(off)] = 0
-    s, ss = B.shape(T, d, N, 1, I), B.shape(T, d, S, S, Is) if S else None
-    w = [weights(N, I, d), weights(N, I, d), weights(N, d, I)]
-    ws = B.alloc_workspace(s)
-    shared = None
-    if S:
-        sw = [weights(S, Is, d), weights(S, Is, d), weights(S, d, Is)]
-        i32 = dict(dtype=torch.int32, device="cuda")
-        s_counts, s_offsets, s_perm = torch.empty(S, **i32), torch.empty(S + 1, **i32), torch.empty(T * S, **i32)
-        B.moe_dense_route(ss, s_counts, s_offsets, s_perm)
-        sws = B.alloc_workspace(ss)
-
-    def fresh(n):
-        y = torch.empty((n, d), dtype=torch.bfloat16, device="cuda")
-        y.view(torch.int16).fill_(SENTINEL)
-        return y
-
-    exact = name != "shared, separate projection splits K"
-    got, sgot = fresh(T), fresh(T * S) if S else None
-    if S:
-        shared = (ss, s_perm, s_offsets, s_counts, *sw, sgot, sws)
-    h = torch.empty((T, d), dtype=torch.bfloat16, device="cuda")
-
-    def joint():
-        B.moe_layer_ffn(s, h, perm, offsets, counts, *w, mask, got, ws, shared)
-
-    def check(what):
-        for a, b in [(got, ref)] + ([(sgot, sref)] if S else []):
-            if exact or b is ref:
-                assert torch.equal(a.view(torch.int16), b.view(torch.int16)), (name, what)
-            else:
-                x, r = a.float(), b.float()
-                assert (x - r).abs().max() <= 2 ** -8 * r.abs().max(), (name, what)
-
-    print(f"joint launch {name} d={d} I={I} T={T} shared {S} of {Is}", flush=True)
-    graph = None
-    for turn in range(4):
-        # other hidden states every time over the workspace of the time before: activations of an earlier pass must not be read
-        h.normal_(generator=gen)
-        ref, sref = fresh(T), fresh(T * S) if S else None
-        B.moe_expert_ffn(s, h, perm, offsets, counts, *w, mask, ref, B.alloc_workspace(s))
-        if S:
-            B.moe_expert_ffn(ss, h, s_perm, s_offsets, s_counts, *sw, None, sref, B.alloc_workspace(ss))
-        if turn == 0:
-            ws.fill_(0xFF)                    # arbitrary contents: counters and activations alike
-            if S:
-                sws.fill_(0xFF)
-        if graph is not None:
-            graph.replay()
-        else:
-            joint()
-        check(f"turn {turn}")
-        if turn == 1:
-            side = torch.cuda.Stream()
-            side.wait_stream(torch.cuda.current_stream())
-            graph = torch.cuda.CUDAGraph()
-            with torch.cuda.graph(graph, stream=side):
-                joint()
-    rows_off = np.repeat(np.isin(np.arange(N), list(off)), rows)
-    bits = got.view(torch.int16).cpu().numpy()
-    assert (bits[rows_off] == SENTINEL).all()
 
 
 class Layer:
@@ -147,19 +68,19 @@ class Layer:
             a.view(torch.int16).fill_(SENTINEL)
         return y
 
-    def joint(self, y):
+    def call(self, y, masked=True):
         shared = (self.ss, *self.stables, *self.sw, y[1], self.sws) if self.S else None
-        self.B.moe_layer_ffn(self.s, self.h, *self.tables, *self.w, self.mask, y[0], self.ws, shared)
+        self.B.moe_layer_ffn(self.s, self.h, *self.tables, *self.w, self.mask if masked else None, y[0], self.ws, shared)
 
-    def joint_without_waiting(self, y):
-        """The joint launch as if every wait had run out."""
+    def joint(self, y, polls=1 << 21):
+        """The joint launch itself.  polls = 0: as if every wait had run out."""
         import ctypes as C
         p = self.B._ptr
         tail = (C.c_void_p(0),) * 9
         if self.S:
             tail = (C.byref(self.ss), *map(p, self.stables), *map(p, self.sw), p(y[1]), self.B._ws_ptr(self.sws))
         rc = self.B.load_library().moe_ffn_joint_impl(C.byref(self.s), p(self.h), *map(p, self.tables), *map(p, self.w), p(self.mask),
-                                                      p(y[0]), self.B._ws_ptr(self.ws), *tail, C.c_int(0), self.B._stream())
+                                                      p(y[0]), self.B._ws_ptr(self.ws), *tail, C.c_int(polls), self.B._stream())
         assert rc == 0
 
     def separate(self, y):
@@ -170,6 +91,43 @@ class Layer:
 
 def bits(y):
     return y.view(torch.int16)
+
+
+@pytest.mark.parametrize("name", CASES)
+def test_joint_launch_writes_what_the_separate_launches_write(name):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2602_03495_amd import binding as B
+    B.load_library()
+    print(f"joint launch: {name} {CASES[name][1:]}", flush=True)
+    L = Layer(B, *CASES[name])
+    exact = name != "shared, separate projection splits K"
+    got, graph = L.fresh(), None
+    for turn in range(4):
+        # other hidden states every time over the workspace of the time before: activations of an earlier pass must not be read
+        L.h.normal_(generator=L.gen)
+        ref = L.fresh()
+        L.separate(ref)
+        if turn == 0:
+            for ws in [L.ws] + ([L.sws] if L.S else []):
+                ws.fill_(0xFF)                    # arbitrary contents: counters and activations alike
+        if graph is not None:
+            graph.replay()
+        else:
+            L.joint(got)
+        for i, (a, b) in enumerate(zip(got, ref)):
+            if exact or i == 0:
+                assert torch.equal(bits(a), bits(b)), (name, turn)
+            else:
+                x, r = a.float(), b.float()
+                assert (x - r).abs().max() <= 2 ** -8 * r.abs().max(), (name, turn)
+        if turn == 1:
+            side = torch.cuda.Stream()
+            side.wait_stream(torch.cuda.current_stream())
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=side):
+                L.joint(got)
+    assert (bits(got[0])[~L.row_on] == SENTINEL).all()
 
 
 # rows, k, d, I, masked-off experts, shared experts, their inner size; the down items are 128, 256 and 512 columns wide
@@ -190,7 +148,7 @@ def test_rows_whose_activations_were_not_waited_for_are_nan(name):
     print(f"waits that ran out: {name}", flush=True)
     L = Layer(B, *VOIDED[name])
     y = L.fresh()
-    L.joint_without_waiting(y)
+    L.joint(y, polls=0)
     assert (bits(y[0])[L.row_on] == 0x7FC0).all() and (bits(y[0])[~L.row_on] == SENTINEL).all()
     assert all((bits(a) == 0x7FC0).all() for a in y[1:])
     ref = L.fresh()
@@ -201,13 +159,31 @@ def test_rows_whose_activations_were_not_waited_for_are_nan(name):
 
 
 def launched_jointly(B, call):
-    """Whether call ran as a joint launch: the blocks of separate launches leave records."""
+    """Whether call, of more than 16 tokens, ran as a joint launch: the blocks of separate launches leave records."""
     records = torch.zeros(2 * B.TRACE_MAX_BLOCKS * 8, dtype=torch.int64, device="cuda")
     B.moe_debug_set_trace(records)
     call()
     torch.cuda.synchronize()
     B.moe_debug_set_trace(None)
     return not bool((records.view(-1, 8)[:, 7] == 1).any())
+
+
+def test_calls_take_the_launch_that_the_rule_names():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2602_03495_amd import binding as B
+    import test_joint_rule as rule
+    for rows, shape, shared in (([165] * 55 + [141], (2048, 56, 1, 1152), ()), ([165] * 55 + [140], (2048, 56, 1, 1152), ()),
+                                ([65, 64], (256, 2, 1, 256), (1, 640)), ([64, 64], (256, 2, 1, 256), (1, 640))):
+        d, N, k, I = shape
+        L = Layer(B, rows, k, d, I, (), *shared)
+        for masked in (False, True):
+            y, ref = L.fresh(), L.fresh()
+            want = rule.joint(masked, L.T, d, N, k, I, shared)
+            print(f"route: {L.T} tokens {shape} {shared} masked {masked}: joint {want}", flush=True)
+            assert launched_jointly(B, lambda: L.call(y, masked)) == want
+            L.separate(ref)
+            assert all(torch.equal(bits(a), bits(b)) for a, b in zip(y, ref))
 
 
 def test_ffn_and_gates_use_parts_of_the_workspace_of_their_own():
