@@ -405,20 +405,22 @@ __device__ __forceinline__ bool up_runs_halves(int tiles, int n_ntc, int n_half,
 }
 
 // Whether the up projection runs every expert's rows, 256 at most, as one tile of half the width (asked in launches of up to 256 rows per
-// expert in the mean, masked-off ones counted: there an expert may be within that): an expert has more than 128, and such
-// items fill one round of the compute units, three quarters of it or more.  A few last rows as a tile of their own take the whole time
-// of its weights, and two tiles ask for them twice; but an item is 128 rows x 256 columns of LDS traffic more for half the products.
-// d = 4096, I = 14336, whole pass of 200 tokens, two experts of 139 and 95 rows (168 items -> 224) 215 -> 192 us; the launch
-// alone, from cold caches: those 161 / 144, 160 and 60 155 / 147, two of 256 159 / 150, 129 and 1 147 / 147.  d = 2048: 20 of 200 rows, I =
-// 1408 (220) 100 / 99, 40 of 256, I = 768 (240) 114 / 113.  With fewer such items it is the slower one: one expert of 250 (112) 105 / 129, 16
-// with 129 and fewer, I = 1408 (176) 77 / 78, 20 of 200, I = 768 (120) 59 / 69.
+// expert in the mean, masked-off ones counted, where an expert may be within that, and of a hidden size of 2048 or more): an expert has more
+// than 128, such items fill one round of the compute units, three quarters of it or more, and the whole items would not all be cut.  A
+// few last rows as a tile of their own take the whole time of its weights, and two tiles ask for them twice; but an item is 128 rows x
+// 256 columns of LDS traffic more for half the products.  d = 4096, I = 14336, whole pass of 200 tokens, two experts of 139 and 95 rows (168
+// items -> 224) 215 -> 192 us.  The launch alone, from cold caches, 2 to 100 experts of 14336 to 256 in seven mixtures of heights: over 129 to
+// 240 whole items 1.03 times as fast in the mean at d = 2048 (0.93 to 1.16), 1.04 at 4096, 1.08 at 7168 (20 of 139 and 95 rows, I = 1408, 251 / 215,
+// two of 256, I = 14336, d = 4096 164 / 155).  Lines: up to 128 whole items, which run as halves anyway, 0.97, 0.96 and 0.94 (129 rows and 15 times 40,
+// I = 1536, d = 4096, 130 / 140); d = 1024 1.01, 0.92 to 1.07; fewer such items: one expert of 250 (112) 105 / 129, 20 of 200, I = 768 (120) 59 / 69.
 #define TALL_MIN_ITEMS 192
-__device__ __forceinline__ bool up_runs_tall(const moe_rows &r, int n_half, int &experts)
+#define TALL_MIN_D 2048
+__device__ __forceinline__ bool up_runs_tall(const moe_rows &r, int whole, int n_half, int &experts)
 {
     const int most = wave_max_int_dpp(max(r.c0, r.c1));
     experts = __popcll(__ballot(r.c0 > 0)) + __popcll(__ballot(r.c1 > 0));
     const int items = experts * n_half;
-    return most > TM && most <= 2 * TM && items >= TALL_MIN_ITEMS && items <= MOE_NUM_XCD * XCD_CUS;
+    return most > TM && most <= 2 * TM && items >= TALL_MIN_ITEMS && items <= MOE_NUM_XCD * XCD_CUS && whole > MOE_NUM_XCD * XCD_CUS / 2;
 }
 
 // NTT_MAX bounds the token subtiles a tile of this launch can need (from T); the block then runs the smallest
@@ -470,9 +472,10 @@ __global__ __launch_bounds__(WAVES * 64, 2) void ffn_tiled_kernel(
         nrows = work.rows_of(e);
     } else {
         const moe_rows rows = moe_masked_rows(N, counts, mask);
+        const moe_tiles tiles = MODE == 0 ? tiles_128(rows) : down_tiles(rows, n_ntc, tmk);
         if constexpr (CAN_TALL) {
             int experts;
-            if (up_runs_tall(rows, n_half, experts)) {
+            if (up_runs_tall(rows, tiles.total * n_ntc, n_half, experts)) {
                 const int items = experts * n_half;
                 if ((int)blockIdx.x >= items) return;
                 const int L = moe_xcd_run(items, blockIdx.x);
@@ -494,7 +497,6 @@ __global__ __launch_bounds__(WAVES * 64, 2) void ffn_tiled_kernel(
                 return;
             }
         }
-        const moe_tiles tiles = MODE == 0 ? tiles_128(rows) : down_tiles(rows, n_ntc, tmk);
         if (MODE == 1) nsp = moe_dev_splits(tiles.total * n_ntc, nsp_max);
         if (MODE == 1 && rival != nullptr) {
             const bool wide = wide_faster(wide_plan_of(rows, (d + WIDE_TN - 1) / WIDE_TN, I / 32), I / 32, tiles.total * n_ntc, tmk, NT_COLS);
@@ -660,7 +662,7 @@ static void launch_tiled(const moe_shape *s, long max_mt, const uint16_t *x, con
                        s->N, x, perm, offsets, counts, wa, wb, mask, out, nsp_max, part, R, rival, tiled_item_group(MODE))
     if constexpr (MODE == 0 && !DIRECT && WAVES == 8) {
         // an instance of its own: with the tall bodies beside the others, 8192 tokens through 8 experts of I = 14336 took 1.4 % longer
-        if (R <= 2 * TM * s->N) {
+        if (R <= 2 * TM * s->N && s->d >= TALL_MIN_D) {
             LAUNCH(true);
             return;
         }
