@@ -22,6 +22,9 @@ CASES = {
     "every expert masked off": ([3100, 3100], 1, 256, 256, (0, 1), 0, 0),
     "one expert on": ([3100, 3100], 1, 1152, 640, (0,), 0, 0),
     "128 experts": ([60] * 64 + [1] * 63 + [2500], 1, 384, 256, tuple(range(0, 128, 3)), 0, 0),
+    "8 slots, wide tiles": ([100] * 70 + [0, 1, 999], 8, 2048, 128, (3, 72), 0, 0),
+    "6 slots, long inner size": ([200, 129, 200, 5, 200, 66, 0, 200, 200], 6, 1152, 8064, (1,), 0, 0),
+    "6 slots, shared": ([100, 17, 1, 100, 0, 82, 100, 100, 100], 6, 640, 384, (0,), 2, 384),
     "shared, few tokens": ([3, 0, 14], 1, 256, 256, (), 2, 256),
     "shared, long inner size": ([300, 2, 40], 1, 1152, 384, (1,), 1, 1408),
     "shared, long inner size, wide tiles": ([90] * 60, 1, 2176, 128, (5,), 1, 640),
@@ -37,7 +40,7 @@ class Layer:
         self.B, self.rows, self.off, self.d, self.S = B, rows, off, d, S
         N, R = len(rows), sum(rows)
         self.T = T = R // k
-        assert T * k == R
+        assert T * k == R and max(rows) <= T
         self.gen = gen = torch.Generator(device="cuda").manual_seed(N + R)
 
         def weights(n, r, K):
@@ -128,6 +131,28 @@ def test_joint_launch_writes_what_the_separate_launches_write(name):
             with torch.cuda.graph(graph, stream=side):
                 L.joint(got)
     assert (bits(got[0])[~L.row_on] == SENTINEL).all()
+
+
+def test_two_joint_launches_beside_each_other():
+    """On two streams, each with blocks for the whole chip: whichever of them get a place, no block waits for one that has none."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2602_03495_amd import binding as B
+    B.load_library()
+    print("two joint launches on two streams", flush=True)
+    layers = [Layer(B, [150] * 40, 3, 2048, 384, (1,), 2, 768), Layer(B, [90] * 64 + [240], 2, 1024, 640, (2, 9))]
+    got, ref = [L.fresh() for L in layers], [L.fresh() for L in layers]
+    for L, r in zip(layers, ref):
+        L.separate(r)
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    torch.cuda.synchronize()
+    for _ in range(8):
+        for L, g, st in zip(layers, got, streams):
+            with torch.cuda.stream(st):
+                L.joint(g)
+    torch.cuda.synchronize()
+    for r, g in zip(ref, got):
+        assert all(torch.equal(bits(a), bits(b)) for a, b in zip(g, r))
 
 
 # rows, k, d, I, masked-off experts, shared experts, their inner size; the down items are 128, 256 and 512 columns wide
