@@ -223,8 +223,8 @@ def time_graph_replays(torch, L, hd, dw, mask_d, steps, warmup):
 
 
 def survey_config(torch, B, Lm, wl, name, Ts, mask_kind, steps=20, merged=True):
-    """One JSON-able record per batch size: the whole step (route, masked routed FFN, shared experts, combine) with HIP
-    events between the calls, and the FFN's share of the bf16 MFMA / HBM peaks."""
+    """One JSON-able record per batch size: the whole step (route, masked routed FFN, shared experts, combine), its expert FFNs
+    timed on their own with HIP events, and their share of the bf16 MFMA / HBM peaks."""
     cfg = wl.CONFIGS[name]
     w1, w3, w2 = wl.expert_weights(cfg)
     dw = Lm.LayerWeights.upload(wl.gate_weights(cfg), wl.gate_bias(cfg), w1, w3, w2, wl.shared_expert_weights(cfg), merge_shared=True)
@@ -239,43 +239,44 @@ def survey_config(torch, B, Lm, wl, name, Ts, mask_kind, steps=20, merged=True):
                 "rand6": wl.mask_random(cfg, 6)}[mask_kind]
         md, on = torch.from_numpy(mask).cuda(), mask.astype(bool)
 
-        def step(ev=None):
-            L.route(hd, dw)
-            if ev: ev[0].record()
-            L.expert_ffn(hd, dw, md)
-            if ev: ev[1].record()
-            if cfg.n_shared: L.shared_ffn(hd, dw)
-            if ev: ev[2].record()
-            L.combine(md)
-            if ev: ev[3].record()
+        # the step as a caller makes it: routed and shared experts in one call, which may be one launch
+        step = lambda: L.forward(hd, dw, md)
         for _ in range(3):
             step()
-        evs = [[torch.cuda.Event(enable_timing=True) for _ in range(4)] for _ in range(steps)]
         torch.cuda.synchronize()
         t0 = time.perf_counter()
         for i in range(steps):
-            step(evs[i])
+            step()
         torch.cuda.synchronize()
         wall = (time.perf_counter() - t0) / steps
-        med = lambda a, b: sorted(e[a].elapsed_time(e[b]) for e in evs)[steps // 2] * 1e-3
-        ffn, sh = med(0, 1), med(1, 2)
         rows_on, active = int(counts[on].sum()), int(((counts > 0) & on).sum())
         if T <= 16:
             # a decode step touches few hundred MB at most: flush the Infinity Cache between steps so that it is HBM traffic
             if flush is None:
                 flush = torch.zeros(1 << 28, dtype=torch.int32, device="cuda")      # 1 GiB
             wall = median_event_seconds(torch, step, steps, flush)
-            ffn = median_event_seconds(torch, lambda: L.expert_ffn(hd, dw, md), steps, flush)
-            if cfg.n_shared:
-                sh = median_event_seconds(torch, lambda: L.shared_ffn(hd, dw), steps, flush)
+
+        def timed(fn):
+            if T <= 16:
+                return median_event_seconds(torch, fn, steps, flush)
+            evs = [[torch.cuda.Event(enable_timing=True) for _ in range(2)] for _ in range(steps)]
+            for a, b in evs:
+                a.record()
+                fn()
+                b.record()
+            torch.cuda.synchronize()
+            return sorted(a.elapsed_time(b) for a, b in evs)[steps // 2] * 1e-3
+        # the two sets of experts in calls of their own, and both in one
+        ffn = timed(lambda: L.expert_ffn(hd, dw, md))
+        sh = timed(lambda: L.shared_ffn(hd, dw)) if cfg.n_shared else 0.0
+        t_all = timed(lambda: L.all_ffn(hd, dw, md)) if cfg.n_shared else ffn
         # both bounds of the routed FFN (algorithmic flops of the masked-on routed rows; weights of the touched masked-on
         # experts once from HBM) and of the layer's whole expert work, shared experts included (always on: T rows each)
         F_r, B_r = 6.0 * cfg.d * cfg.I * rows_on, 6.0 * cfg.d * cfg.I * active
         F_s, B_s = 6.0 * cfg.d * cfg.I_shared * cfg.n_shared * T, 6.0 * cfg.d * cfg.I_shared * cfg.n_shared
-        t_all = ffn + (sh if cfg.n_shared else 0.0)
         rec = {"workload": name, "tokens": T, "mask": mask_kind, "us_per_step": wall * 1e6, "tokens_per_s": T / wall,
                "ffn_us": ffn * 1e6, "ffn_mfma_frac": F_r / ffn / PEAK_BF16_MFMA,
-               "ffn_hbm_frac": B_r / ffn / PEAK_HBM, "shared_us": sh * 1e6 if cfg.n_shared else 0.0,
+               "ffn_hbm_frac": B_r / ffn / PEAK_HBM, "shared_us": sh * 1e6, "experts_us": t_all * 1e6,
                "experts_mfma_frac": (F_r + F_s) / t_all / PEAK_BF16_MFMA, "experts_hbm_frac": (B_r + B_s) / t_all / PEAK_HBM,
                "active_experts": active, "rows_on": rows_on}
         rec["bound"] = "mfma" if rec["experts_mfma_frac"] >= rec["experts_hbm_frac"] else "hbm"
@@ -290,9 +291,9 @@ def survey_config(torch, B, Lm, wl, name, Ts, mask_kind, steps=20, merged=True):
             ws_ = median_event_seconds(torch, step, steps, flush if T <= 16 else None)
             rec["merged_us_per_step"], rec["merged_tokens_per_s"], rec["separate_us_per_step"] = wm * 1e6, T / wm, ws_ * 1e6
             log(f"[bench] {name:9s} T={T:5d} shared experts inside the grouped launches: step {wm * 1e6:8.1f} us "
-                f"(separate launches, timed the same way: {ws_ * 1e6:8.1f} us)")
+                f"(beside the routed ones, timed the same way: {ws_ * 1e6:8.1f} us)")
         log(f"[bench] {name:9s} T={T:5d} step {wall * 1e6:8.1f} us | ffn {ffn * 1e6:8.1f} us mfma {rec['ffn_mfma_frac']:.3f} "
-            f"hbm {rec['ffn_hbm_frac']:.3f} | shared {rec['shared_us']:7.1f} us | active {active} rows_on {rows_on}")
+            f"hbm {rec['ffn_hbm_frac']:.3f} | shared {rec['shared_us']:7.1f} us, both {rec['experts_us']:7.1f} us | active {active} rows_on {rows_on}")
         out.append(rec)
     del dw, flush
     torch.cuda.empty_cache()
@@ -403,7 +404,8 @@ def survey_rows_per_expert(torch, B, Lm, wl, steps=20):
 
 def timeline(torch, B, Lm, wl, spec):
     """Per-block timeline of the two tiled expert-FFN launches of one shape (moe_debug_set_trace): how long blocks of
-    each tile height take, how evenly the compute units and the XCDs finish.  spec: SHAPE:TOKENS:MASK with MASK = all,
+    each tile height take, how evenly the compute units and the XCDs finish.  The launches are those of moe_expert_ffn; a joint launch
+    (moe_layer_ffn) leaves no records.  spec: SHAPE:TOKENS:MASK with MASK = all,
     half (top half by this batch's workloads), rand6, or onlyE[,E...] (just those experts on)."""
     name, T, mk = spec.split(":")
     T = int(T)
@@ -422,11 +424,13 @@ def timeline(torch, B, Lm, wl, spec):
         mask = {"all": np.ones(cfg.N, np.uint8), "half": wl.mask_top_by_counts(counts, cfg.N // 2), "rand6": wl.mask_random(cfg, 6)}[mk]
     md = torch.from_numpy(mask).cuda()
     records = torch.zeros(2 * B.TRACE_MAX_BLOCKS * 8, dtype=torch.int64, device="cuda")
+    r = L.routing
+    ffn = lambda: B.moe_expert_ffn(L.shape, hd, r.perm, r.offsets, r.counts, dw.w1, dw.w3, dw.w2, md, L.y, L.ws)
     for _ in range(3):
-        L.expert_ffn(hd, dw, md)
+        ffn()
     torch.cuda.synchronize()
     B.moe_debug_set_trace(records)
-    L.expert_ffn(hd, dw, md)
+    ffn()
     torch.cuda.synchronize()
     B.moe_debug_set_trace(None)
     tr = records.cpu().numpy().reshape(2, B.TRACE_MAX_BLOCKS, 8)
@@ -436,7 +440,7 @@ def timeline(torch, B, Lm, wl, spec):
         t = tr[mode]
         t = t[t[:, 7] == 1]
         if len(t) == 0:
-            continue
+            raise RuntimeError(f"the {nm} launch left no record")
         t0 = t[:, 0].min()
         b, e = (t[:, 0] - t0) / 100.0, (t[:, 1] - t0) / 100.0
         dur, rows, xcd = e - b, t[:, 5], t[:, 3] & 0xF
