@@ -19,8 +19,8 @@
 //     With release and acquire fences in place of that (the whole L2 written back by each up item) an up item of 50 us took 56 to 65.
 //   * Counters and tickets are cleared by a launch of one block ahead.
 // Passes of whole layers, two or four launches / this: 2048 tokens of 6 slots, 32 of 64 experts, d = 2048, I = 1408, and two shared
-// ones 348 / 303 us; 1531 tokens of 8 slots, 64 of 128 experts, I = 768 215 / 195; 4096 tokens of 4 slots, 60 experts, I = 1408, and a shared
-// one of 5632 653 / 604.  The compute units are busy for 0.92 of the launch (0.78 to 0.85 of the separate ones); what an item takes is
+// ones 356 / 309 us; 1531 tokens of 8 slots, 64 of 128 experts, I = 768 222 / 201; 4096 tokens of 4 slots, 60 experts, I = 1408, and a shared
+// one of 5632 653 / 609.  The compute units are busy for 0.92 of the launch (0.78 to 0.85 of the separate ones); what an item takes is
 // bound as in ffn_tiled.hip.
 #pragma once
 
