@@ -773,12 +773,14 @@ int moe_ffn_tiled_impl(const moe_shape *s, const void *h, const int32_t *perm, c
 // Whether the FFNs of a layer run as a joint launch: the routed K not split (it has no partial sums), inner sizes the long-K kernel does not
 // take, and enough items that filled last rounds pay for the clearing launch, the tickets and the activations' way past the caches; an
 // up item is never cut there, so with about a round of them or less the separate launches end sooner.  masked: how many experts a mask
-// leaves on is known to the device only; the line is where a quarter of them is not slower.  Separate launches / joint in us:
-// Routed experts alone, d = 2048, all on / half / a quarter.  64 experts, I = 1408, 512 tokens of 6 slots 227 / 224, 127 / 132, 84 / 91, 1400 269 /
-// 262, 184 / 170, 130 / 133, 2048 328 / 299, 230 / 211, 174 / 160; 128 experts, I = 768, 384 tokens of 8 slots 234 / 223, 125 / 122, 70 / 87, 1000
+// leaves on is known to the device only; the lines are where a quarter of them is about level (30 random shapes within them: a quarter on 0.99 to
+// 1.15 times as fast, half 1.00 to 1.23; next to the lines, 64 and 60 experts of 1408, 0.95 to 1.02 and 1.00 to 1.13).  Separate launches / joint in us:
+// Routed experts alone, d = 2048, all on / half / a quarter.  64 experts, I = 1408, 512 tokens of 6 slots 227 / 224, 127 / 132, 84 / 91, 1024 256 /
+// 244, 157 / 154, 119 / 116, 1400 269 / 262, 184 / 170, 130 / 133, 2048 328 / 299, 230 / 211, 174 / 160; 128 experts, I = 768, 384 tokens of 8 slots 234 / 223, 125 / 122, 70 / 87, 1000
 // 251 / 240, 157 / 150, 92 / 96, 1531 282 / 260, 172 / 162, 114 / 107.  Beyond a quarter it loses still: an eighth of these 121 / 130 and 79 / 81.
+// Few rows to an expert make short items: 128 of 384 at 8192 rows, 3/4 127 / 120, a quarter 54 / 64, at 12288 74 / 72.
 // Other sizes, all on / a quarter, at 9216 to 16384 rows: 64 of 1024, d = 3072 302 / 272 and 141 / 131; 64 of 2048, d = 7168 1338 / 1286 and
-// 718 / 633; 75 of 640 (255 up items) half 116 / 101, a quarter 72 / 77; 46 of 256, d = 7168 (110) 3/4 214 / 254, a quarter 161 / 185.
+// 718 / 633; 64 of 1024, d = 3072, 6144 rows (256 up items) a quarter 115 / 120; 75 of 640 (255) half 116 / 101, a quarter 72 / 77; 46 of 256, d = 7168 (110) 3/4 214 / 254, a quarter 161 / 185.
 // Few experts: 8 of 4096, d = 4096, 4096 rows 426 / 415 and 155 / 159, 3072 rows (24 tiles) 323 / 370 and 132 / 170; 32 of 768, 4096 rows (96 up
 // items) 89 / 93 and 45 / 63; 32 of 1408 with a quarter on, 12288 rows 125 / 137.  d = 1024: 32 of 2816, 8192 rows 203 / 196 and 96 / 115; d = 512:
 // 64 of 512, 8192 rows 39 / 44 and 22 / 31.
@@ -790,9 +792,12 @@ int moe_ffn_tiled_impl(const moe_shape *s, const void *h, const int32_t *perm, c
 // 177 / 185, 138 / 135; d = 1024, 60 of 1408 and one of 5632: 200 tokens 145 / 129, 103 / 114, 80 / 89, 2048 240 / 217, 196 / 179, 162 / 145; d = 512:
 // 200 99 / 98, 76 / 95, 66 / 82, 2048 150 / 136, 125 / 115, 112 / 107.
 #define JOINT_MIN_ROWS 3072
-#define JOINT_MIN_ROWS_MASKED 9216
-#define JOINT_MIN_TILES 56          // in the mean, or experts: a mask makes tiles of them fewer
+#define JOINT_MIN_TILES 56
 #define JOINT_MIN_UP_ITEMS 256
+// under a mask, which leaves some of the experts
+#define JOINT_MIN_ROWS_MASKED 6144
+#define JOINT_MIN_EXPERT_ROWS_MASKED 72
+#define JOINT_MIN_UP_ITEMS_MASKED 288
 extern "C" bool moe_ffn_joint_ok(const moe_shape *s, const moe_shape *ss, bool masked)
 {
     if (s->I >= 8192 || moe_tiled_down_max_splits(s) != 1) return false;
@@ -801,9 +806,10 @@ extern "C" bool moe_ffn_joint_ok(const moe_shape *s, const moe_shape *ss, bool m
         if (moe_tiled_down_max_splits(ss) != 1) return s->T > TM && (s->d >= 2048 || s->T >= 2048);
         return s->T > TM || ss->I <= 2 * s->I;
     }
-    const long R = (long)s->T * s->k, tiles = R / TM > s->N ? R / TM : s->N;
-    if (s->d < 2048 || tiles * ((s->I + JOINT_UP_COLS - 1) / JOINT_UP_COLS) < JOINT_MIN_UP_ITEMS) return false;
-    return masked ? R >= JOINT_MIN_ROWS_MASKED && s->N >= JOINT_MIN_TILES : R >= JOINT_MIN_ROWS && tiles >= JOINT_MIN_TILES;
+    const long R = (long)s->T * s->k, tiles = R / TM > s->N ? R / TM : s->N, up = tiles * ((s->I + JOINT_UP_COLS - 1) / JOINT_UP_COLS);
+    if (s->d < 2048) return false;
+    if (!masked) return R >= JOINT_MIN_ROWS && tiles >= JOINT_MIN_TILES && up >= JOINT_MIN_UP_ITEMS;
+    return R >= JOINT_MIN_ROWS_MASKED && R >= JOINT_MIN_EXPERT_ROWS_MASKED * s->N && s->N >= JOINT_MIN_TILES && up >= JOINT_MIN_UP_ITEMS_MASKED;
 }
 
 static joint_experts joint_side(const moe_shape *s, const int32_t *perm, const int32_t *offsets, const int32_t *counts, const void *w1,

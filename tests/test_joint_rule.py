@@ -17,11 +17,12 @@ def joint(masked, T, d, N, k, I, shared=None):
     (False, 384, 2048, 128, 8, 768, True), (False, 383, 2048, 128, 8, 768, False),           # routed rows, all experts on
     (False, 896, 2048, 8, 8, 2944, True), (False, 895, 2048, 8, 8, 2944, False),             # 56 tiles of few experts
     (False, 3072, 2048, 56, 1, 1408, True), (False, 3072, 2048, 55, 1, 1408, False),         # as many experts
-    (True, 1152, 2048, 128, 8, 768, True), (True, 1151, 2048, 128, 8, 768, False),           # routed rows under a mask
+    (True, 1024, 2048, 64, 6, 1408, True), (True, 1023, 2048, 64, 6, 1408, False),           # routed rows under a mask
+    (True, 1152, 2048, 128, 8, 768, True), (True, 1151, 2048, 128, 8, 768, False),           # 72 to an expert
     (True, 9216, 2048, 56, 1, 1408, True), (True, 9216, 2048, 55, 1, 1408, False),           # experts under a mask
     (False, 2048, 2048, 128, 2, 512, True), (False, 2048, 1920, 128, 2, 512, False),         # hidden size
     (False, 4096, 2048, 128, 2, 384, True), (False, 4096, 2048, 127, 2, 384, False),         # up items
-    (True, 4096, 2048, 128, 8, 128, True), (True, 4095, 2048, 128, 8, 128, False),           # ... of half the width
+    (True, 4608, 2048, 128, 8, 128, True), (True, 4607, 2048, 128, 8, 128, False),           # ... under a mask
     (False, 8192, 2048, 64, 8, 8064, True), (False, 8192, 2048, 64, 8, 8192, False),         # inner size of the long-K kernel
     (False, 1024, 2048, 64, 4, 2048, False), (False, 1025, 2048, 64, 4, 2048, True),         # K split: up to 64 MB of partial sums
 ])
