@@ -780,7 +780,8 @@ int moe_ffn_tiled_impl(const moe_shape *s, const void *h, const int32_t *perm, c
 // 251 / 240, 157 / 150, 92 / 96, 1531 282 / 260, 172 / 162, 114 / 107.  Beyond a quarter it loses still: an eighth of these 121 / 130 and 79 / 81.
 // Few rows to an expert make short items: 128 of 384 at 8192 rows, 3/4 127 / 120, a quarter 54 / 64, at 12288 74 / 72.
 // Other sizes, all on / a quarter, at 9216 to 16384 rows: 64 of 1024, d = 3072 302 / 272 and 141 / 131; 64 of 2048, d = 7168 1338 / 1286 and
-// 718 / 633; 64 of 1024, d = 3072, 6144 rows (256 up items) a quarter 115 / 120; 75 of 640 (255) half 116 / 101, a quarter 72 / 77; 46 of 256, d = 7168 (110) 3/4 214 / 254, a quarter 161 / 185.
+// 718 / 633; 64 of 1024, d = 3072, 6144 rows (256 up items) a quarter 115 / 120; 75 of 640 (255) half 116 / 101, a quarter 72 / 77;
+// 46 of 256, d = 7168 (110) 3/4 214 / 254, a quarter 161 / 185.
 // Few experts: 8 of 4096, d = 4096, 4096 rows 426 / 415 and 155 / 159, 3072 rows (24 tiles) 323 / 370 and 132 / 170; 32 of 768, 4096 rows (96 up
 // items) 89 / 93 and 45 / 63; 32 of 1408 with a quarter on, 12288 rows 125 / 137.  d = 1024: 32 of 2816, 8192 rows 203 / 196 and 96 / 115; d = 512:
 // 64 of 512, 8192 rows 39 / 44 and 22 / 31.
